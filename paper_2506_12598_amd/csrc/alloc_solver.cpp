@@ -31,14 +31,69 @@ static const uint64_t INF = std::numeric_limits<uint64_t>::max();
 struct Point { uint64_t s; uint64_t b; };            // (scaled CU sum, latency sum)
 
 // Pareto front: s strictly increasing, b strictly decreasing.
-static std::vector<Point> prune(std::vector<Point> v)
+// Merge of two fronts into the front of their union: linear, no sort.
+static void merge_fronts(const std::vector<Point> &x, const std::vector<Point> &y, std::vector<Point> &out)
 {
-    std::sort(v.begin(), v.end(), [](const Point &x, const Point &y) { return x.s != y.s ? x.s < y.s : x.b < y.b; });
-    std::vector<Point> out;
+    out.clear();
+    out.reserve(x.size() + y.size());
+    size_t i = 0, j = 0;
     uint64_t best = INF;
-    for (const Point &p : v)
+    while (i < x.size() || j < y.size()) {
+        const bool from_x = j == y.size() || (i < x.size() && (x[i].s != y[j].s ? x[i].s < y[j].s : x[i].b <= y[j].b));
+        const Point p = from_x ? x[i++] : y[j++];
         if (p.b < best) { out.push_back(p); best = p.b; }
+    }
+}
+
+// Front of { a + b : a in A, b in B }.  Every a shifts B to another front; the shifted fronts are merged pairwise, so that a
+// point dominated early never takes part again (sorting all sums, 10^5 to 10^6 of them, was half of a solve).
+static std::vector<Point> add_fronts(const std::vector<Point> &A, const std::vector<Point> &B)
+{
+    const std::vector<Point> &few = A.size() < B.size() ? A : B, &many = A.size() < B.size() ? B : A;
+    std::vector<std::vector<Point>> level;               // level[k]: merge of 2^k shifted fronts, empty when there is none
+    std::vector<Point> cur, tmp;
+    for (const Point &a : few) {
+        cur.clear();
+        for (const Point &b : many) cur.push_back(Point{a.s + b.s, a.b + b.b});
+        size_t k = 0;
+        for (; k < level.size() && !level[k].empty(); ++k) {
+            merge_fronts(level[k], cur, tmp);
+            cur.swap(tmp);
+            level[k].clear();
+        }
+        if (k == level.size()) level.emplace_back();
+        level[k].swap(cur);
+    }
+    std::vector<Point> out;
+    for (std::vector<Point> &l : level)
+        if (!l.empty()) {
+            merge_fronts(out, l, tmp);
+            out.swap(tmp);
+        }
     return out;
+}
+
+// Inner loops of the dynamic programme over the CU sum u, for 32- and 64-bit latencies (V's largest value = unreachable;
+// every reachable value plus one more latency and switch stays below it).  Compiled for AVX2 too, picked at load time.
+#ifdef __HIP_DEVICE_COMPILE__                          // host code only; the device pass merely parses it
+#define ECLIP_DP_ROW
+#else
+#define ECLIP_DP_ROW __attribute__((target_clones("avx2", "default")))
+#endif
+// m[u] = min(m[u], src[u] + add)
+ECLIP_DP_ROW static void row_min_add(uint32_t *m, const uint32_t *src, uint32_t add, size_t n)
+{
+    for (size_t u = 0; u < n; ++u) {
+        const uint32_t t = src[u], v = t == UINT32_MAX ? t : t + add;
+        m[u] = v < m[u] ? v : m[u];
+    }
+}
+ECLIP_DP_ROW static void row_min_add(uint64_t *m, const uint64_t *src, uint64_t add, size_t n)
+{
+    for (size_t u = 0; u < n; ++u) {
+        const uint64_t t = src[u], v = t == UINT64_MAX ? t : t + add;
+        m[u] = v < m[u] ? v : m[u];
+    }
 }
 
 struct WorkerDP {
@@ -49,61 +104,87 @@ struct WorkerDP {
     uint64_t switch_cost = 0;                 // added to the latency at every configuration switch
     std::vector<int> allowed;                 // configurations this run may use (all, or a subset)
     uint32_t umax = 0;                        // largest reduced CU sum
-    // h[g][c_prev][s_left][u] = min latency of units g..G-1 given unit g-1 used c_prev, s_left switches
-    // remain and the units g..G-1 must add up to reduced CU sum u.  g = 0 uses c_prev = C ("none").
-    std::vector<uint64_t> h;
+    bool narrow = false;                      // every latency sum fits 32 bits
+    // h[g][i_prev][s_left][u] = min latency of units g..G-1 given unit g-1 used allowed[i_prev], s_left switches
+    // remain and the units g..G-1 must add up to reduced CU sum u.  g = 0 has one row, (i_prev, s_left) = (0, SM).
+    std::vector<uint64_t> h64;
+    std::vector<uint32_t> h32;
     std::vector<uint32_t> rem_max;            // rem_max[g] = max reduced CU sum of units g..G-1
-    size_t idx(int g, int cp, int sl, uint32_t u) const
-    {
-        return (((size_t)g * (C + 1) + cp) * (SM + 1) + sl) * (umax + 1) + u;
-    }
-    bool is_allowed(int c) const { return std::find(allowed.begin(), allowed.end(), c) != allowed.end(); }
+    std::vector<int> have;                    // the subset h belongs to
     size_t states() const { return (size_t)(G + 1) * (C + 1) * (SM + 1) * ((size_t)umax + 1); }
+    size_t row(int g, int i, int sl) const
+    {
+        return (((size_t)g * allowed.size() + i) * (SM + 1) + sl) * ((size_t)umax + 1);
+    }
+    template <typename V> std::vector<V> &store();
 
+    // With t_c = h[g+1][c][.][u - du_c] + beta[g][c], the row of a unit whose predecessor used c is
+    //   min(t_c with the budget kept, min over all c' of t_c' with one switch less + switch cost):
+    // the second term may include c' = c, which never wins (a smaller budget is never better), so it is one row for all
+    // predecessors and a state costs two candidates instead of one per configuration.
+    template <typename V> void fill()
+    {
+        const V none = std::numeric_limits<V>::max();
+        std::vector<V> &h = store<V>();
+        const int A = (int)allowed.size();
+        const size_t U = (size_t)umax + 1;
+        h.assign((size_t)(G + 1) * A * (SM + 1) * U, none);
+        for (int i = 0; i < A; ++i)
+            for (int sl = 0; sl <= SM; ++sl) h[row(G, i, sl)] = 0;
+        std::vector<V> any(U);
+        for (int g = G - 1; g >= 0; --g) {
+            auto take = [&](V *dst, int i, int sl, uint64_t extra) {
+                const size_t du = (size_t)n[g] * cq[allowed[i]];
+                row_min_add(dst + du, &h[row(g + 1, i, sl)], (V)(beta[(size_t)g * C + allowed[i]] + extra), (size_t)rem_max[g + 1] + 1);
+            };
+            if (g == 0) {
+                for (int i = 0; i < A; ++i) take(&h[row(0, 0, SM)], i, SM, 0);
+                break;
+            }
+            for (int sl = 0; sl <= SM; ++sl) {
+                if (sl > 0) {
+                    std::fill(any.begin(), any.begin() + rem_max[g] + 1, none);
+                    for (int i = 0; i < A; ++i) take(any.data(), i, sl - 1, switch_cost);
+                }
+                for (int i = 0; i < A; ++i) {
+                    V *dst = &h[row(g, i, sl)];
+                    if (sl > 0) std::copy(any.begin(), any.begin() + rem_max[g] + 1, dst);
+                    take(dst, i, sl, 0);
+                }
+            }
+        }
+    }
     void run()
     {
-        h.assign(states(), INF);
-        for (int cp = 0; cp <= C; ++cp)
-            for (int sl = 0; sl <= SM; ++sl) h[idx(G, cp, sl, 0)] = 0;
-        for (int g = G - 1; g >= 0; --g)
-            for (int cp = 0; cp <= C; ++cp) {
-                if (g == 0 && cp != C) continue;
-                if (g > 0 && (cp == C || !is_allowed(cp))) continue;
-                for (int sl = 0; sl <= SM; ++sl)
-                    for (uint32_t u = 0; u <= rem_max[g]; ++u) {
-                        uint64_t best = INF;
-                        for (int c : allowed) {
-                            const bool sw = (g > 0 && c != cp);
-                            if (sw && sl == 0) continue;
-                            const uint32_t du = n[g] * cq[c];
-                            if (du > u) continue;
-                            const uint64_t t = h[idx(g + 1, c, sl - (sw ? 1 : 0), u - du)];
-                            if (t == INF) continue;
-                            const uint64_t v = t + beta[(size_t)g * C + c] + (sw ? switch_cost : 0);
-                            if (v < best) best = v;
-                        }
-                        h[idx(g, cp, sl, u)] = best;
-                    }
-            }
+        if (have == allowed) return;
+        if (narrow) fill<uint32_t>(); else fill<uint64_t>();
+        have = allowed;
     }
-    uint64_t f(uint32_t u) const { return h[idx(0, C, SM, u)]; }
+    uint64_t at(int g, int i, int sl, uint32_t u) const
+    {
+        if (!narrow) return h64[row(g, i, sl) + u];
+        const uint32_t v = h32[row(g, i, sl) + u];
+        return v == UINT32_MAX ? INF : v;
+    }
+    uint64_t f(uint32_t u) const { return at(0, 0, SM, u); }
     // lexicographically smallest assignment reaching exactly (u, f(u))
     void rebuild(uint32_t u, uint32_t *out, uint32_t *switches) const
     {
-        int cp = C, sl = SM;
+        int ip = 0, sl = SM;
         uint32_t sw_count = 0;
         for (int g = 0; g < G; ++g) {
-            const uint64_t target = h[idx(g, cp, sl, u)];
-            for (int c : allowed) {                 // ascending: the first match is the lexicographic minimum
-                const bool sw = (g > 0 && c != cp);
+            const uint64_t target = at(g, ip, sl, u);
+            for (int i = 0; i < (int)allowed.size(); ++i) {                 // ascending: the first match is the lexicographic minimum
+                const int c = allowed[i];
+                const bool sw = (g > 0 && i != ip);
                 if (sw && sl == 0) continue;
                 const uint32_t du = n[g] * cq[c];
                 if (du > u) continue;
-                const uint64_t t = h[idx(g + 1, c, sl - (sw ? 1 : 0), u - du)];
+                const uint64_t t = at(g + 1, i, sl - (sw ? 1 : 0), u - du);
                 if (t == INF || t + beta[(size_t)g * C + c] + (sw ? switch_cost : 0) != target) continue;
                 out[g] = (uint32_t)c;
                 if (sw) { --sl; ++sw_count; }
-                cp = c;
+                ip = i;
                 u -= du;
                 break;
             }
@@ -111,6 +192,8 @@ struct WorkerDP {
         *switches = sw_count;
     }
 };
+template <> std::vector<uint32_t> &WorkerDP::store<uint32_t>() { return h32; }
+template <> std::vector<uint64_t> &WorkerDP::store<uint64_t>() { return h64; }
 
 static bool mul_overflows(uint64_t a, uint64_t b) { return b != 0 && a > INF / b; }
 
@@ -192,6 +275,7 @@ std::string solve_alloc(const eclip_alloc_problem *p, uint32_t *cfg_out, eclip_u
         }
         if (beta_total_max > INF - bmax) { *limit = true; return "latency sum overflows 64 bits"; }
         beta_total_max += bmax;
+        d.narrow = bmax + p->switch_cost_ns < UINT32_MAX;        // bmax counts a switch before every unit but the first
         if (nsum * d.cq[C - 1] > (1u << 24)) { *limit = true; return "CU-sum range too large"; }
         d.umax = (uint32_t)(nsum * d.cq[C - 1]);
         d.rem_max.assign(d.G + 1, 0);
@@ -212,30 +296,32 @@ std::string solve_alloc(const eclip_alloc_problem *p, uint32_t *cfg_out, eclip_u
     // per-worker fronts in the common scale: s = U_reduced * cg * (D / N_w); with a subset limit the front is the
     // Pareto union over the subsets
     std::vector<std::vector<Point>> front(W);
+    std::vector<std::vector<std::vector<Point>>> front_of_subset(W);
     std::vector<uint64_t> mult(W);
     for (int w = 0; w < W; ++w) {
         mult[w] = (uint64_t)cg * (D / Nw[w]);
-        std::vector<Point> v;
+        std::vector<Point> tmp;
         for (const std::vector<int> &sub : subsets_w[w]) {
             dp[w].allowed = sub;
             dp[w].run();
+            std::vector<Point> v;
+            uint64_t best = INF;
             for (uint32_t u = 0; u <= dp[w].umax; ++u) {
                 const uint64_t b = dp[w].f(u);
-                if (b != INF) v.push_back(Point{(uint64_t)u * mult[w], b});
+                if (b < best) { v.push_back(Point{(uint64_t)u * mult[w], b}); best = b; }
             }
+            merge_fronts(front[w], v, tmp);
+            front[w].swap(tmp);
+            front_of_subset[w].push_back(std::move(v));
         }
-        front[w] = prune(std::move(v));
     }
-    // suffix fronts R[w] = front[w] (+) front[w+1] (+) ... ; R[W] = {(0,0)}
+    // suffix fronts R[w] = front[w] (+) front[w+1] (+) ... ; R[W] = {(0,0)}.  R[0] itself is not built: only its best point
+    // is wanted.
     std::vector<std::vector<Point>> R(W + 1);
     R[W] = {Point{0, 0}};
     for (int w = W - 1; w >= 0; --w) {
         if (front[w].size() * R[w + 1].size() > ((size_t)1 << 27)) { *limit = true; return "front product exceeds the solver's budget"; }
-        std::vector<Point> v;
-        v.reserve(front[w].size() * R[w + 1].size());
-        for (const Point &a : front[w])
-            for (const Point &b : R[w + 1]) v.push_back(Point{a.s + b.s, a.b + b.b});
-        R[w] = prune(std::move(v));
+        if (w > 0) R[w] = add_fronts(front[w], R[w + 1]);
     }
     // objective over the combined front
     const u128 TD = (u128)p->total_cus * D;
@@ -251,10 +337,20 @@ std::string solve_alloc(const eclip_alloc_problem *p, uint32_t *cfg_out, eclip_u
     u128 best = 0;
     Point bp{0, 0};
     bool have = false;
-    for (const Point &q : R[0]) {           // s ascending: the first minimum has the smallest S_D
-        const u128 j = (u128)q.b * phi(q.s);
-        if (!have || j < best) { best = j; bp = q; have = true; }
-    }
+    // Smallest (objective, S_D) over all sums of a point of front[0] and one of R[1].  Along a block of R[1] s grows and b
+    // falls, so (b of its last point) * phi(s of its first) bounds the block's objectives from below, and nearly every
+    // block is passed over.
+    constexpr size_t BLK = 32;
+    for (const Point &a : front[0])
+        for (size_t i = 0; i < R[1].size(); i += BLK) {
+            const size_t e = std::min(i + BLK, R[1].size());
+            if (have && (u128)(a.b + R[1][e - 1].b) * phi(a.s + R[1][i].s) > best) continue;
+            for (size_t k = i; k < e; ++k) {
+                const Point q{a.s + R[1][k].s, a.b + R[1][k].b};
+                const u128 j = (u128)q.b * phi(q.s);
+                if (!have || j < best || (j == best && q.s < bp.s)) { best = j; bp = q; have = true; }
+            }
+        }
     if (!have) return "no feasible assignment";
     if (obj_out) { obj_out->lo = (uint64_t)best; obj_out->hi = (uint64_t)(best >> 64); }
 
@@ -273,11 +369,14 @@ std::string solve_alloc(const eclip_alloc_problem *p, uint32_t *cfg_out, eclip_u
             auto it = std::lower_bound(R[w + 1].begin(), R[w + 1].end(), need,
                                        [](const Point &x, const Point &y) { return x.s < y.s; });
             if (it == R[w + 1].end() || it->s != need.s || it->b != need.b) continue;
-            for (const std::vector<int> &sub : subsets_w[w]) {
-                dp[w].allowed = sub;
+            for (size_t k = 0; k < subsets_w[w].size(); ++k) {
+                // a is on the front of the union, so a subset that reaches it has it on its own front
+                const std::vector<Point> &own = front_of_subset[w][k];
+                const auto at = std::lower_bound(own.begin(), own.end(), a, [](const Point &x, const Point &y) { return x.s < y.s; });
+                if (at == own.end() || at->s != a.s || at->b != a.b) continue;
+                dp[w].allowed = subsets_w[w][k];
                 dp[w].run();
                 const uint32_t u = (uint32_t)(a.s / mult[w]);
-                if (dp[w].f(u) != a.b) continue;
                 dp[w].rebuild(u, cur.data(), &cur_sw);
                 if (!found || cur < best_assign) { best_assign = cur; best_sw = cur_sw; chosen = a; found = true; }
             }

@@ -65,6 +65,17 @@ def test_solver_extensions_match_exhaustive_oracle_bit_exact(seed, max_configs, 
             assert all(len(set(a)) <= max_configs for a in got[0])
 
 
+@pytest.mark.parametrize("shift", [0, 14, 15, 16, 40])
+@pytest.mark.parametrize("max_configs,mode", [(0, oa.OVERLAP_EXCESS), (2, oa.OVERLAP_LITERAL), (1, oa.OVERLAP_TABLE)])
+def test_solver_is_exact_with_32_and_64_bit_latency_sums(shift, max_configs, mode):
+    # latencies on both sides of the limit below which the dynamic programme keeps them in 32 bits
+    p = wl.random_problem(77, 3, [3, 2, 1], [32, 64, 128, 256], 256, 2, mode, "scaling")
+    for w in p.workers:
+        w.beta = [[v << shift for v in row] for row in w.beta]
+    p.max_configs, p.switch_cost = max_configs, 900 << shift
+    assert tuple(solve_lib(p)) == tuple(oa.solve_exhaustive(p))
+
+
 def test_solver_hand_worked_example():
     a = wl.Worker([1, 1], [[100, 60, 50, 45], [80, 70, 65, 64]])
     b = wl.Worker([1], [[200, 110, 80, 60]])
