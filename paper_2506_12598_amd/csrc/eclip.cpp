@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -66,10 +67,13 @@ static bool trace_on()
 struct PoolStream {
     hipStream_t stream = nullptr;
     uint32_t n_cu = 0;
+    SeDeal deal;                         // of an unevenly spread mask, see se_deal.h
+    std::atomic<uint32_t> deal_turn{0};
     uint32_t pipe = UINT32_MAX;          // creation rank among the pool's masked streams, modulo ECLIP_N_PIPES
     std::vector<uint32_t> words;
     int32_t owner = -1;
 };
+static CuShare share_of(const PoolStream &ps) { return CuShare{(int)ps.n_cu, ps.deal}; }
 struct eclip_pool {
     int device = 0;
     uint32_t device_cus = 0;
@@ -111,6 +115,36 @@ static hipError_t static_scratch_of(int device, void **ptr)
     return hipSuccess;
 }
 
+// Sets up the dealing of workgroups to the shader engines of an unevenly spread mask (se_deal.h).  Mask bit i enables a CU of
+// shader engine (i / 8) % 4 on XCD i % 8.  Evenly spread masks need none; masks that differ from XCD to XCD get none.
+static hipError_t deal_of_mask(PoolStream &s, uint32_t n_xcc)
+{
+    constexpr uint32_t XCC = 8, SE = 4;
+    if (n_xcc != XCC || s.words.empty()) return hipSuccess;
+    uint32_t cap[XCC][SE] = {};
+    for (uint32_t b = 0; b < s.words.size() * 32; ++b)
+        if (s.words[b / 32] >> (b % 32) & 1u) cap[b % XCC][b / XCC % SE]++;
+    SeDeal d;
+    uint32_t cmin = UINT32_MAX, order = 0;
+    for (uint32_t e = 0; e < SE; ++e) {
+        const uint32_t c = cap[0][e];
+        for (uint32_t x = 1; x < XCC; ++x)
+            if (cap[x][e] != c) return hipSuccess;
+        if (c == 0) continue;
+        d.se_caps |= c << (8 * e);
+        order |= c << (8 * d.slots++);
+        d.level = std::max(d.level, c);
+        cmin = std::min(cmin, c);
+    }
+    if (cmin == d.level) return hipSuccess;
+    uint32_t notes[2 * XCC];
+    for (uint32_t &n : notes) n = order;
+    d.turn = &s.deal_turn;
+    s.deal = d;
+    const hipError_t e = hipMalloc(&s.deal.notes, sizeof notes);
+    return e == hipSuccess ? hipMemcpy(s.deal.notes, notes, sizeof notes, hipMemcpyHostToDevice) : e;
+}
+
 extern "C" eclip_status eclip_pool_create(int device, const eclip_mask *masks, uint32_t n_masks, eclip_pool **out)
 {
     if (!out) return fail(ECLIP_EINVAL, "out is null");
@@ -140,6 +174,7 @@ extern "C" eclip_status eclip_pool_create(int device, const eclip_mask *masks, u
     // Consecutive mask bits rotate over the device's XCDs (bit i belongs to XCD i % n_xcc); the runtime does
     // not survive a queue mask that leaves an XCD without any CU, so such masks are refused here.  The XCD count
     // comes from the device; when the runtime cannot tell it, masked streams are refused altogether.
+    uint32_t xccs = 0;
     bool any_masked = false;
     for (uint32_t i = 0; i < n_masks; ++i) any_masked |= masks[i].n_words != 0;
     if (any_masked) {
@@ -148,7 +183,7 @@ extern "C" eclip_status eclip_pool_create(int device, const eclip_mask *masks, u
         if (xe != hipSuccess || xcc < 1 || cus % (uint32_t)xcc)
             return fail(ECLIP_EHIP, "cannot read the XCD count of device %d (%s, value %d): CU-masked streams are refused", device,
                         hipGetErrorString(xe), xcc);
-        const uint32_t n_xcc = (uint32_t)xcc;
+        const uint32_t n_xcc = xccs = (uint32_t)xcc;
         TRACE("device %d: %u XCDs", device, n_xcc);
         for (uint32_t i = 0; i < n_masks; ++i) {
             if (masks[i].n_words == 0) continue;
@@ -170,7 +205,7 @@ extern "C" eclip_status eclip_pool_create(int device, const eclip_mask *masks, u
     p->device = device;
     p->device_cus = cus;
     p->scratch = scratch_ptr;
-    p->streams.resize(n_masks);
+    p->streams = std::vector<PoolStream>(n_masks);
     uint32_t n_masked = 0;
     for (uint32_t i = 0; i < n_masks; ++i) {
         PoolStream &s = p->streams[i];
@@ -184,10 +219,13 @@ extern "C" eclip_status eclip_pool_create(int device, const eclip_mask *masks, u
             s.words.assign(masks[i].words, masks[i].words + masks[i].n_words);
             s.n_cu = popcount_words(s.words.data(), masks[i].n_words);
             e = hipExtStreamCreateWithCUMask(&s.stream, masks[i].n_words, s.words.data());
+            if (e == hipSuccess) e = deal_of_mask(s, xccs);
+            if (e != hipSuccess && s.stream) (void)hipStreamDestroy(s.stream);
         }
         TRACE("stream %u: %u CUs, %s", i, s.n_cu, hipGetErrorString(e));
         if (e != hipSuccess) {
             for (uint32_t j = 0; j < i; ++j) (void)hipStreamDestroy(p->streams[j].stream);
+            for (uint32_t j = 0; j <= i; ++j) (void)hipFree(p->streams[j].deal.notes);
             delete p;
             return fail(ECLIP_EHIP, "creating pool stream %u failed: %s", i, hipGetErrorString(e));
         }
@@ -313,6 +351,7 @@ extern "C" eclip_status eclip_pool_destroy(eclip_pool *pool)
     for (PoolStream &s : pool->streams) {
         (void)hipStreamSynchronize(s.stream);
         (void)hipStreamDestroy(s.stream);
+        (void)hipFree(s.deal.notes);
     }
     delete pool;
     return ECLIP_OK;
@@ -1235,12 +1274,12 @@ static char *out_ptr(const eclip_model *m, const LayerPlan &P)
 static int pitch_of(const eclip_model *m, int idx) { return idx >= 0 ? m->layers[idx].ld : 0; }
 
 // Launches layer i on `s`.  `d_out32` non-null: this is the last layer and its result goes to the caller.
-static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_t s, int n_cu, const void *d_in, float *d_out32,
+static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_t s, const CuShare &cu, const void *d_in, float *d_out32,
                                uint32_t *n_launched)
 {
     LayerPlan &P = m->layers[i];
     const eclip_layer &L = P.L;
-    const int dt = m->dtype;
+    const int dt = m->dtype, n_cu = cu.n_cu;
     auto src = [&](int idx) -> const void * {
         if (idx == -2) return nullptr;
         if (idx == -1) return m->in_kind == ECLIP_IN_IMAGE ? (const void *)m->d_in_stage : d_in;
@@ -1266,7 +1305,7 @@ static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_
             a.ldy = P.ld;
             const GemmPlan pl = plan_of(m, (long)g.B * g.Ho * g.Wo, g.Cout, (long)g.KH * g.KW * g.Cin, n_cu);
             *n_launched -= 1;
-            e = launch_conv_gemm(a, pl, s, n_launched);
+            e = launch_conv_gemm(a, pl, cu.deal, s, n_launched);
         } else if (L.op == ECLIP_OP_CONV && L.groups > 1 && !(L.groups == g.Cin && L.c == L.groups)) {
             GConvArgs a{src(L.in0), wptr(m, P.w_dev), wptr(m, P.b_dev), src(L.in1), y, g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout,
                         g.KH, g.KW, g.stride, g.pad, L.groups, L.act, dt};
@@ -1303,7 +1342,7 @@ static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_
     case ECLIP_OP_ATTENTION: {
         if (d_out32) y32 = d_out32;
         AttnArgs a{src(L.in0), y, y32, batch, P.in.w, L.c, L.heads, dt};
-        e = launch_attention(a, n_cu, s);
+        e = launch_attention(a, cu, s);
         break;
     }
     case ECLIP_OP_EMBED: {
@@ -1337,11 +1376,12 @@ static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_
 }
 
 // Launches layers i and i + 1 (pair_next) in one kernel when the planner finds a common plan; *done tells whether it did.
-static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t s, int n_cu, const void *d_in, uint32_t *n_launched, bool *done)
+static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t s, const CuShare &cu, const void *d_in, uint32_t *n_launched, bool *done)
 {
     *done = false;
     ConvGemmArgs a[2];
     GemmPlan own[2], pl[2];
+    const int n_cu = cu.n_cu;
     long mnk[2][3];
     for (int k = 0; k < 2; ++k) {
         const LayerPlan &P = m->layers[i + k];
@@ -1381,18 +1421,18 @@ static hipError_t launch_gapfc_pair(eclip_model *m, uint32_t i, int batch, hipSt
 
 // First layer straight from the caller's NCHW tensor (stem_direct), when a plan of that form is within the cost of the
 // re-layout kernel it saves; *done tells whether it was launched.
-static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, int n_cu, const void *d_in, uint32_t *n_launched, bool *done)
+static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, const CuShare &cu, const void *d_in, uint32_t *n_launched, bool *done)
 {
     *done = false;
     const LayerPlan &P = m->layers[0];
     const GemmShape g = gemm_shape(P, batch);
     GemmPlan pl;
-    if (!conv_gemm_plan_stem((long)g.B * g.Ho * g.Wo, g.Cout, (long)g.KH * g.KW * g.Cin, n_cu, m->ws_floats, 2.0, &pl)) return hipSuccess;
+    if (!conv_gemm_plan_stem((long)g.B * g.Ho * g.Wo, g.Cout, (long)g.KH * g.KW * g.Cin, cu.n_cu, m->ws_floats, 2.0, &pl)) return hipSuccess;
     ConvGemmArgs a{d_in, wptr(m, P.w_dev), wptr(m, P.b_dev), nullptr, out_ptr(m, P), nullptr, m->ws,
                    g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, P.L.act, m->dtype};
     a.nchw_c = m->in_c;
     *done = true;
-    return launch_conv_gemm(a, pl, s, n_launched);
+    return launch_conv_gemm(a, pl, cu.deal, s, n_launched);
 }
 
 static hipError_t launch_input_stage(eclip_model *m, int batch, const void *d_in, hipStream_t s, uint32_t *n_launched)
@@ -1406,7 +1446,7 @@ static hipError_t launch_input_stage(eclip_model *m, int batch, const void *d_in
 // (or reading the caller's tensor itself), two independent matrix-core layers in one launch, pool + classifier in one
 // launch, or a single layer.  *consumed receives the number of layers the unit covered.  eclip_submit and the profiler
 // both walk a model through this function, so what is profiled is what is served.
-static hipError_t launch_unit(eclip_model *m, uint32_t i, int batch, hipStream_t s, int n_cu, const void *d_in, float *d_out,
+static hipError_t launch_unit(eclip_model *m, uint32_t i, int batch, hipStream_t s, const CuShare &cu, const void *d_in, float *d_out,
                               uint32_t *n_launched, uint32_t *consumed)
 {
     const uint32_t n_layers = (uint32_t)m->layers.size();
@@ -1415,14 +1455,14 @@ static hipError_t launch_unit(eclip_model *m, uint32_t i, int batch, hipStream_t
     if (i == 0) {
         bool stem_done = false;
         if (m->stem_direct) {
-            if ((e = launch_stem_direct(m, batch, s, n_cu, d_in, n_launched, &stem_done)) != hipSuccess) return e;
+            if ((e = launch_stem_direct(m, batch, s, cu, d_in, n_launched, &stem_done)) != hipSuccess) return e;
             if (stem_done) return hipSuccess;
         }
         if ((e = launch_input_stage(m, batch, d_in, s, n_launched)) != hipSuccess) return e;
     }
     if (m->layers[i].pair_next) {
         bool paired = false;
-        if ((e = launch_pair(m, i, batch, s, n_cu, d_in, n_launched, &paired)) != hipSuccess) return e;
+        if ((e = launch_pair(m, i, batch, s, cu, d_in, n_launched, &paired)) != hipSuccess) return e;
         if (paired) { *consumed = 2; return hipSuccess; }
     }
     if (m->layers[i].gapfc_next) {
@@ -1430,7 +1470,7 @@ static hipError_t launch_unit(eclip_model *m, uint32_t i, int batch, hipStream_t
         if ((e = launch_gapfc_pair(m, i, batch, s, d_in, i + 2 == n_layers ? d_out : nullptr, n_launched, &fused)) != hipSuccess) return e;
         if (fused) { *consumed = 2; return hipSuccess; }
     }
-    return launch_layer(m, i, batch, s, n_cu, d_in, i + 1 == n_layers ? d_out : nullptr, n_launched);
+    return launch_layer(m, i, batch, s, cu, d_in, i + 1 == n_layers ? d_out : nullptr, n_launched);
 }
 
 // The captured form of a request on (d_in, d_out, batch) under the current table, plans and workspace: looked up, or
@@ -1475,7 +1515,7 @@ static hipError_t graph_entry(eclip_model *m, const void *d_in, void *d_out, uin
         hipError_t le = hipSuccess;
         while (i < n_layers && le == hipSuccess && m->pool->streams[m->mask_of_group[m->group_of_layer[i]]].stream == ps.stream) {
             uint32_t consumed = 1;
-            le = launch_unit(m, i, (int)batch, m->capture_stream, (int)ps.n_cu, d_in, (float *)d_out, &ge.n_kernels, &consumed);
+            le = launch_unit(m, i, (int)batch, m->capture_stream, share_of(ps), d_in, (float *)d_out, &ge.n_kernels, &consumed);
             i += consumed;
         }
         hipGraph_t graph = nullptr;
@@ -1551,7 +1591,7 @@ static eclip_status submit_locked(eclip_model *model, const void *d_in, void *d_
         }
         prev_group = g;
         uint32_t consumed = 1;
-        SUB_TRY(launch_unit(model, i, (int)batch, cur, (int)ps.n_cu, d_in, (float *)d_out, &r->n_kernels, &consumed));
+        SUB_TRY(launch_unit(model, i, (int)batch, cur, share_of(ps), d_in, (float *)d_out, &r->n_kernels, &consumed));
         i += consumed;
     }
     }
@@ -1676,7 +1716,7 @@ static eclip_status profile_prepare(eclip_model *model, uint32_t group, uint32_t
     uint32_t dummy = 0;
     for (uint32_t i = 0; i < n_layers;) {
         uint32_t consumed = 1;
-        HIP_TRY(launch_unit(model, i, (int)batch, ps.stream, (int)ps.n_cu, model->d_self_in, model->d_self_out, &dummy, &consumed));
+        HIP_TRY(launch_unit(model, i, (int)batch, ps.stream, share_of(ps), model->d_self_in, model->d_self_out, &dummy, &consumed));
         i += consumed;
     }
     HIP_TRY(hipStreamSynchronize(ps.stream));
@@ -1711,7 +1751,7 @@ extern "C" eclip_status eclip_profile_group(eclip_model *model, uint32_t group, 
             const uint32_t i = idx[k];
             e = hipEventRecord(ev[2 * k], ps.stream);
             for (uint32_t r = 0; r < REPS && e == hipSuccess; ++r)
-                e = launch_layer(model, i, (int)batch, ps.stream, (int)ps.n_cu, model->d_self_in, i + 1 == n_layers ? model->d_self_out : nullptr, &dummy);
+                e = launch_layer(model, i, (int)batch, ps.stream, share_of(ps), model->d_self_in, i + 1 == n_layers ? model->d_self_out : nullptr, &dummy);
             if (e == hipSuccess) e = hipEventRecord(ev[2 * k + 1], ps.stream);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(ps.stream);
@@ -1779,7 +1819,7 @@ extern "C" eclip_status eclip_model_tune(eclip_model *model, uint32_t mask_id, u
                 // first, so the bar is set early)
                 const uint32_t reps = it ? REPS : 1;
                 hipError_t e = hipEventRecord(ev[0], ps.stream);
-                for (uint32_t r = 0; r < reps && e == hipSuccess; ++r) e = launch_conv_gemm(a, cand[c], ps.stream, nullptr);
+                for (uint32_t r = 0; r < reps && e == hipSuccess; ++r) e = launch_conv_gemm(a, cand[c], ps.deal, ps.stream, nullptr);
                 if (e == hipSuccess) e = hipEventRecord(ev[1], ps.stream);
                 if (e == hipSuccess) e = hipStreamSynchronize(ps.stream);
                 float ms = 0.0f;
@@ -1829,7 +1869,7 @@ extern "C" eclip_status eclip_profile_group_served(eclip_model *model, uint32_t 
         for (uint32_t r = 0; r < REPS && e == hipSuccess; ++r)
             for (uint32_t i = first; i <= last && e == hipSuccess;) {
                 uint32_t consumed = 1;
-                e = launch_unit(model, i, (int)batch, ps.stream, (int)ps.n_cu, model->d_self_in, model->d_self_out, &launches, &consumed);
+                e = launch_unit(model, i, (int)batch, ps.stream, share_of(ps), model->d_self_in, model->d_self_out, &launches, &consumed);
                 i += consumed;
             }
         if (e == hipSuccess) e = hipEventRecord(ev[1], ps.stream);

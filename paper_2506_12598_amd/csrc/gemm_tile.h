@@ -224,7 +224,7 @@ enum { LOOP_PLAIN = 0, LOOP_PINGPONG = 2, LOOP_PP_BDIRECT = 3 };
 enum { A_GENERAL = 0, A_UNIFORM = 1, A_MATRIX = 2 };
 
 template <typename T, int BM, int BN, int BK, int WM, int WN, int RS, int LOOP = LOOP_PLAIN, int AMODE = A_GENERAL>
-__global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p)
+__global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p, SeDeal deal)
 {
     constexpr int NT = WM * WN * 64;         // threads per workgroup: 4 wavefronts, 8 for the 256x256 tile
     static_assert(RS % 2 == 0, "register stages alternate between the two LDS slots");
@@ -248,27 +248,23 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p)
     // L2, and the 32 CUs of an XCD run 32 consecutive workgroups of that XCD at a time.  With `raster` set
     // (large problems) those 32 workgroups form an 8 x 4 block of tiles, so that one K step pulls 8 + 4
     // operand tiles into the L2 instead of up to 32 + 1; blocks are dealt to the XCDs in row-major order.
+    // Raster 2 (3): an XCD owns a contiguous range of the tiles, counted down the tile columns (along the tile rows).
     int tile_m, tile_n;
-    if (p.raster == 2) {                      // an XCD owns a contiguous range of tile columns (mid-size problems)
-        const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3, per = (p.tiles_n + 7) >> 3, r = q / p.tiles_m;
-        tile_m = q - r * p.tiles_m;
-        tile_n = xcd * per + r;
-        if (r >= per || tile_n >= p.tiles_n) return;
-    } else if (p.raster == 3) {               // ... or of tile rows
-        const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3, per = (p.tiles_m + 7) >> 3, r = q / p.tiles_n;
-        tile_n = q - r * p.tiles_n;
-        tile_m = xcd * per + r;
-        if (r >= per || tile_m >= p.tiles_m) return;
-    } else if (p.raster) {
-        const int b = blockIdx.x, l = b >> 3, w = l & 31;
+    const uint32_t bid = se_dealt_block(deal, blockIdx.x);
+    if (bid == 0xffffffffu) return;
+    if (p.raster == 1) {
+        const int b = (int)bid, l = b >> 3, w = l & 31;
         const int sb = (l >> 5) * 8 + (b & 7);
         const int sbm = (p.tiles_m + 7) >> 3;
         tile_m = (sb % sbm) * 8 + (w & 7);
         tile_n = (sb / sbm) * 4 + (w >> 3);
         if (tile_m >= p.tiles_m || tile_n >= p.tiles_n) return;
     } else {
-        tile_m = blockIdx.x % p.tiles_m;
-        tile_n = blockIdx.x / p.tiles_m;
+        const uint32_t t = p.raster ? xcd_range_item(bid, (uint32_t)(p.tiles_m * p.tiles_n)) : bid;
+        if (t == 0xffffffffu) return;
+        const int fast = p.raster == 3 ? p.tiles_n : p.tiles_m, slow = (int)t / fast, rem = (int)t - slow * fast;
+        tile_m = p.raster == 3 ? slow : rem;
+        tile_n = p.raster == 3 ? rem : slow;
     }
     const int m_base = tile_m * BM, n_base = tile_n * BN;
 
@@ -663,7 +659,7 @@ inline int gemm_amode(const GemmDev &d, int bk)
     return A_GENERAL;
 }
 
-template <int ID> hipError_t launch_pp(const GemmDev &d, int dtype, dim3 grid, hipStream_t s);
+template <int ID> hipError_t launch_pp(const GemmDev &d, const SeDeal &deal, int dtype, dim3 grid, hipStream_t s);
 template <int ID> hipError_t init_pp();
 
 }  // namespace eclip

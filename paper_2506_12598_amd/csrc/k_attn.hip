@@ -45,6 +45,7 @@ struct AttnDev {
     int B, S, Hd, heads, Sp, ldv;   // Sp = S rounded up to 32; ldv = LDS pitch of V^T in elements
     int ck, nchunks;                // chunked kernel: keys per chunk (a multiple of 32) and number of chunks
     float scale;
+    SeDeal deal;
 };
 
 // KB = number of 16-key blocks held in registers (Sp / 16 <= KB <= 16)
@@ -54,8 +55,12 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(AttnDev p)
     extern __shared__ __attribute__((aligned(16))) uint16_t vt[];    // [D][ldv]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int qblocks = (p.S + NW * 16 - 1) / (NW * 16);
-    const int qb = blockIdx.x % qblocks;
-    const int bh = blockIdx.x / qblocks;
+    // an XCD owns a contiguous range of (head, query block) pairs, so that a head's keys and values enter one L2, not eight
+    const uint32_t vb = se_dealt_block(p.deal, blockIdx.x);
+    if (vb == 0xffffffffu) return;
+    const uint32_t item = xcd_range_item(vb, (uint32_t)(p.B * p.heads * qblocks));
+    if (item == 0xffffffffu) return;
+    const int bh = (int)item / qblocks, qb = (int)item - bh * qblocks;
     const int h = bh % p.heads, b = bh / p.heads;
     const long row0 = (long)b * p.S;
     const int ld = 3 * p.Hd;
@@ -219,8 +224,12 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 && KBC <= 12) ? 4 : 2) void atten
     extern __shared__ __attribute__((aligned(16))) uint16_t vt[];    // V^T chunk [D][ldv], then the key chunk [ck][D + 8]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int qblocks = (p.S + NW * 16 - 1) / (NW * 16);
-    const int qb = blockIdx.x % qblocks;
-    const int bh = blockIdx.x / qblocks;
+    // an XCD owns a contiguous range of (head, query block) pairs, so that a head's keys and values enter one L2, not eight
+    const uint32_t vb = se_dealt_block(p.deal, blockIdx.x);
+    if (vb == 0xffffffffu) return;
+    const uint32_t item = xcd_range_item(vb, (uint32_t)(p.B * p.heads * qblocks));
+    if (item == 0xffffffffu) return;
+    const int bh = (int)item / qblocks, qb = (int)item - bh * qblocks;
     const int h = bh % p.heads, b = bh / p.heads;
     const long row0 = (long)b * p.S;
     const int ld = 3 * p.Hd;
@@ -399,10 +408,10 @@ inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 inline int ldv_of(int keys) { return keys + 4; }
 
 template <typename T, int D, int NW>
-hipError_t launch_d(const AttnDev &d, size_t lds, hipStream_t s)
+hipError_t launch_d(AttnDev d, size_t lds, hipStream_t s)
 {
     const int qblocks = (d.S + NW * 16 - 1) / (NW * 16);
-    const dim3 grid((unsigned)(d.B * d.heads * qblocks)), block(NW * 64);
+    const dim3 grid(se_deal_grid(d.deal, xcd_range_blocks((uint32_t)(d.B * d.heads * qblocks)))), block(NW * 64);
     const int nkb = d.Sp / 16;
     if (nkb <= 8) hipLaunchKernelGGL((attention_kernel<T, D, 8, NW>), grid, block, lds, s, d);
     else if (nkb <= 16) hipLaunchKernelGGL((attention_kernel<T, D, 16, NW>), grid, block, lds, s, d);
@@ -411,10 +420,10 @@ hipError_t launch_d(const AttnDev &d, size_t lds, hipStream_t s)
 }
 
 template <typename T, int D, int NW>
-hipError_t launch_chunked(const AttnDev &d, size_t lds, hipStream_t s)
+hipError_t launch_chunked(AttnDev d, size_t lds, hipStream_t s)
 {
     const int qblocks = (d.S + NW * 16 - 1) / (NW * 16);
-    const dim3 grid((unsigned)(d.B * d.heads * qblocks)), block(NW * 64);
+    const dim3 grid(se_deal_grid(d.deal, xcd_range_blocks((uint32_t)(d.B * d.heads * qblocks)))), block(NW * 64);
     if (d.ck % 32 != 0 || d.ck > 256 || d.nchunks * d.ck < d.Sp || (d.nchunks - 1) * d.ck >= d.S) return hipErrorInvalidValue;
     if (d.ck <= 192) hipLaunchKernelGGL((attention_chunk_kernel<T, D, 12, NW>), grid, block, lds, s, d);
     else hipLaunchKernelGGL((attention_chunk_kernel<T, D, 16, NW>), grid, block, lds, s, d);
@@ -466,9 +475,11 @@ hipError_t attention_init()
     return hipSuccess;
 }
 
-hipError_t launch_attention(const AttnArgs &a, int n_cu, hipStream_t s)
+hipError_t launch_attention(const AttnArgs &a, const CuShare &cu, hipStream_t s)
 {
+    const int n_cu = cu.n_cu;
     AttnDev d;
+    d.deal = cu.deal;
     d.qkv = (const uint16_t *)a.qkv; d.y = (uint16_t *)a.y; d.y32 = a.y32;
     d.B = a.B; d.S = a.S; d.Hd = a.Hd; d.heads = a.heads;
     d.Sp = round_up(a.S, 32);

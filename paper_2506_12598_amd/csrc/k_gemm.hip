@@ -75,15 +75,15 @@ template <typename T>
 hipError_t launch_pp_split(const GemmDev &d, const GemmPlan &pl, hipStream_t s, hipError_t e);
 
 template <typename T>
-hipError_t launch_t(const GemmDev &d, const GemmPlan &pl, hipStream_t s)
+hipError_t launch_t(const GemmDev &d, const GemmPlan &pl, SeDeal deal, hipStream_t s)
 {
-    const dim3 grid((unsigned)pl.tiles, (unsigned)pl.splits);
+    const dim3 grid(se_deal_grid(deal, (uint32_t)pl.tiles), (unsigned)pl.splits);
     switch (pl.variant) {
-    case 0: hipLaunchKernelGGL((conv_gemm_kernel<T, 128, 128, 32, 2, 2, 2>), grid, dim3(256), lds_bytes(128, 128, 32), s, d); break;
-    case 1: hipLaunchKernelGGL((conv_gemm_kernel<T, 64, 64, 64, 2, 2, 4>), grid, dim3(256), lds_bytes(64, 64, 64), s, d); break;
-    case 2: hipLaunchKernelGGL((conv_gemm_kernel<T, 32, 64, 64, 1, 4, 4>), grid, dim3(256), lds_bytes(32, 64, 64), s, d); break;
+    case 0: hipLaunchKernelGGL((conv_gemm_kernel<T, 128, 128, 32, 2, 2, 2>), grid, dim3(256), lds_bytes(128, 128, 32), s, d, deal); break;
+    case 1: hipLaunchKernelGGL((conv_gemm_kernel<T, 64, 64, 64, 2, 2, 4>), grid, dim3(256), lds_bytes(64, 64, 64), s, d, deal); break;
+    case 2: hipLaunchKernelGGL((conv_gemm_kernel<T, 32, 64, 64, 1, 4, 4>), grid, dim3(256), lds_bytes(32, 64, 64), s, d, deal); break;
 #define X(ID, BM, BN, BK, RS, LP) \
-    case ID: return launch_pp_split<T>(d, pl, s, launch_pp<ID>(d, std::is_same<T, bf16_t>::value ? DT_BF16 : DT_F16, grid, s));
+    case ID: return launch_pp_split<T>(d, pl, s, launch_pp<ID>(d, deal, std::is_same<T, bf16_t>::value ? DT_BF16 : DT_F16, grid, s));
         ECLIP_PP_TILES(X)
 #undef X
     default: return hipErrorInvalidValue;
@@ -133,9 +133,11 @@ static void set_raster(GemmPlan &pl, long M, long N)
     if (pl.kind != 0) return;
     if (tm * tn < 256 || pl.splits != 1) {
         // fewer tiles than CUs (or K slices in grid.y): deal whole tile columns or rows to the XCDs when they divide
-        // evenly, so that each L2 holds 1/8 of one operand instead of all of both
-        if (tn >= 8 && tn % 8 == 0) { pl.raster = 2; pl.tiles = (int)(tn * tm); }
-        else if (tm >= 8 && tm % 8 == 0) { pl.raster = 3; pl.tiles = (int)(tn * tm); }
+        // evenly, so that each L2 holds 1/8 of one operand instead of all of both.  (Uneven ranges of tiles per XCD were
+        // slower than the plain order: ResNet-50's 64 x 128 tiles at batch 1, 13 tile rows, 2 us per launch in the chain.)
+        if (tn >= 8 && tn % 8 == 0) pl.raster = 2;
+        else if (tm >= 8 && tm % 8 == 0) pl.raster = 3;
+        pl.tiles = (int)(tn * tm);
         return;
     }
     if (tn < 4) {
@@ -143,7 +145,7 @@ static void set_raster(GemmPlan &pl, long M, long N)
         // not free to launch: bands of tile rows per XCD instead, which pads the grid to 8 rows only
         // (VGG-16 conv1_2 at batch 8, one tile column: 12544 workgroups of which 3136 have a tile, 69 -> 63 us)
         pl.raster = 3;
-        pl.tiles = (int)(8 * cdiv(tm, 8) * tn);
+        pl.tiles = (int)xcd_range_blocks((uint32_t)(tm * tn));
         return;
     }
     const long blocks = cdiv(tm, 8) * cdiv(tn, 4);
@@ -408,15 +410,15 @@ static GemmDev make_dev(const ConvGemmArgs &a, const GemmPlan &pl)
     return d;
 }
 
-hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &pl, hipStream_t s, uint32_t *n_launched)
+hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &pl, const SeDeal &deal, hipStream_t s, uint32_t *n_launched)
 {
     if ((a.ldx && (a.ldx % 8 || a.ldx < a.Cin || a.nchw_c)) || (a.ldy && (a.ldy % 8 || a.ldy < a.Cout || a.res || a.y32 || ((uintptr_t)a.y & 15))))
         return hipErrorInvalidValue;
     const GemmDev d = make_dev(a, pl);
     if (n_launched) *n_launched += pl.splits > 1 ? 2 : 1;
     if (pl.kind == 1) return launch_conv_wsk(d, a.dtype, pl.variant, pl.nw, pl.tiles, s);
-    if (a.dtype == DT_BF16) return launch_t<bf16_t>(d, pl, s);
-    return launch_t<f16_t>(d, pl, s);
+    if (a.dtype == DT_BF16) return launch_t<bf16_t>(d, pl, deal, s);
+    return launch_t<f16_t>(d, pl, deal, s);
 }
 
 hipError_t launch_conv_gemm_pair(const ConvGemmArgs &a0, const GemmPlan &p0, const ConvGemmArgs &a1, const GemmPlan &p1, hipStream_t s,

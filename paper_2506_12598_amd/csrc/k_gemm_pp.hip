@@ -15,20 +15,20 @@ constexpr PPTile kTile = pp_tile(ECLIP_PP_ID);
 static_assert(kTile.id == ECLIP_PP_ID, "ECLIP_PP_ID is not in ECLIP_PP_TILES");
 
 template <typename T, int AMODE>
-hipError_t launch_one(const GemmDev &d, dim3 grid, hipStream_t s)
+hipError_t launch_one(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream_t s)
 {
     hipLaunchKernelGGL((conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>), grid, dim3(512),
-                       lds_bytes(kTile.bm, kTile.bn, kTile.bk, 16, kTile.loop != LOOP_PP_BDIRECT), s, d);
+                       lds_bytes(kTile.bm, kTile.bn, kTile.bk, 16, kTile.loop != LOOP_PP_BDIRECT), s, d, deal);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_mode(const GemmDev &d, dim3 grid, hipStream_t s)
+hipError_t launch_mode(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream_t s)
 {
     switch (gemm_amode(d, kTile.bk)) {
-    case A_MATRIX: return launch_one<T, A_MATRIX>(d, grid, s);
-    case A_UNIFORM: return launch_one<T, A_UNIFORM>(d, grid, s);
-    default: return launch_one<T, A_GENERAL>(d, grid, s);
+    case A_MATRIX: return launch_one<T, A_MATRIX>(d, deal, grid, s);
+    case A_UNIFORM: return launch_one<T, A_UNIFORM>(d, deal, grid, s);
+    default: return launch_one<T, A_GENERAL>(d, deal, grid, s);
     }
 }
 
@@ -41,9 +41,9 @@ hipError_t init_one()
 
 }  // namespace
 
-template <> hipError_t launch_pp<ECLIP_PP_ID>(const GemmDev &d, int dtype, dim3 grid, hipStream_t s)
+template <> hipError_t launch_pp<ECLIP_PP_ID>(const GemmDev &d, const SeDeal &deal, int dtype, dim3 grid, hipStream_t s)
 {
-    return dtype == DT_BF16 ? launch_mode<bf16_t>(d, grid, s) : launch_mode<f16_t>(d, grid, s);
+    return dtype == DT_BF16 ? launch_mode<bf16_t>(d, deal, grid, s) : launch_mode<f16_t>(d, deal, grid, s);
 }
 
 template <> hipError_t init_pp<ECLIP_PP_ID>()

@@ -7,6 +7,8 @@
 
 #include <vector>
 
+#include "se_deal.h"
+
 namespace eclip {
 
 enum { DT_F32 = 0, DT_BF16 = 1, DT_F16 = 2 };
@@ -35,7 +37,8 @@ struct GemmPlan {
     int splits;    // kind 0: K is cut into this many slices, summed by a second kernel
     int tiles;     // output tiles = workgroups (per slice)
     int nw;        // kind 1: wavefronts per workgroup, each taking 1/nw of K
-    int raster;    // kind 0: workgroups walk the tiles in 8 x 4 blocks per XCD (tiles then counts whole blocks)
+    int raster;    // how workgroups walk the tiles: 2 (3) = an XCD owns a contiguous range of tiles counted down the tile columns
+                   // (along the tile rows); 1 (kind 0) = 8 x 4 blocks of tiles per XCD.  `tiles` counts the padding of the walk
 };
 bool conv_gemm_plan_stem(long M, long N, long K, int n_cu, size_t ws_floats, double stage_us, GemmPlan *out);   // ConvGemmArgs::nchw_c
 enum { CONV_GEMM_VARIANTS = 17 };        // 0..2: 128x128x32, 64x64x64, 32x64x64 (4 wavefronts); 3, 4: 256x256x32, 128x256x64 (8 wavefronts on the
@@ -54,7 +57,7 @@ GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats);
 std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, size_t ws_floats);
 double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int variant, int nw);   // the planner's estimate, us without the launch
 // *n_launched (optional) is increased by the number of kernels launched (2 when K is split).
-hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &p, hipStream_t s, uint32_t *n_launched);
+hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &p, const SeDeal &deal, hipStream_t s, uint32_t *n_launched);
 // Two layers that do not depend on each other in one launch (wave-split-K kernel only).  conv_gemm_plan_pair takes
 // the layers' own plans and returns true, with a common plan for each, when sharing a launch is modelled to pay.
 bool conv_gemm_plan_pair(const GemmPlan &s0, long M0, long N0, long K0, const GemmPlan &s1, long M1, long N1, long K1, int n_cu,
@@ -146,7 +149,7 @@ struct AttnArgs {
     int B, S, Hd, heads, dtype;
 };
 size_t attention_lds_bytes(int S, int d);
-hipError_t launch_attention(const AttnArgs &a, int n_cu, hipStream_t s);
+hipError_t launch_attention(const AttnArgs &a, const CuShare &cu, hipStream_t s);
 hipError_t attention_init();   // raises the dynamic LDS limit once per process
 
 // ---- layout conversion at the model boundary ------------------------------------------------------

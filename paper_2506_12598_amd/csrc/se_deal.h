@@ -1,0 +1,111 @@
+// Dealing workgroups to the shader engines of a CU mask in proportion to the compute units the mask enables there.
+//
+// Measured on MI355X (hardware ids and start times of every workgroup, masks of 64 to 256 CUs): the workgroups of a dispatch
+// go round-robin over the XCDs, and inside an XCD round-robin over the shader engines that have an enabled CU, strictly
+// and in order: a workgroup whose shader engine is full holds back every later one, whatever room the others have.  A mask
+// with 8 + 8 + 2 + 2 CUs per XCD (160 CUs in granules of 16) therefore runs workgroups that fill a compute unit on 64 of
+// them: 160 workgroups of 30 us took 91 us on it and 31 us on the 160-CU mask with 5 + 5 + 5 + 5.
+//
+// So on such masks a launch that wants V workgroups is given more, and the surplus ends at once (0.4 us): of every `level`
+// consecutive workgroups of a shader engine with c < level enabled CUs the first level - c return (its CUs are free or about
+// to be, so nothing waits behind them), the last c work.  Per round the working ones are one for every enabled CU.
+//
+// Which turn of the rotation falls to which shader engine differs from XCD to XCD and moves when another queue has
+// dispatched in between, so every dealt launch notes what its own first turn saw for the launch after it and deals
+// by what the launch before it noted.  A wrong note costs time, never results: the note is constant while a
+// launch runs, a working workgroup's index is a function of blockIdx and the note alone, every index is handed out once
+// whatever order the note gives the capacities in, and a note whose capacities do not add up is not used.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <atomic>
+
+namespace eclip {
+
+struct SeDeal {
+    uint32_t *notes = nullptr;           // [2][8] on the device: per XCD of the rotation one byte per turn, enabled CUs of the shader
+                                         // engine that had it; dealt launches take turns reading one half and writing the other
+    std::atomic<uint32_t> *turn = nullptr;   // host
+    uint32_t half = 0;                   // the half this launch reads
+    uint32_t se_caps = 0;                // one byte per shader engine: its enabled CUs (the same on every XCD)
+    uint32_t slots = 0;                  // shader engines in the rotation
+    uint32_t level = 0;                  // workgroups per turn and round; 0: not dealt
+    uint32_t any_order = 0, sum = 0;     // capacities clipped to `level`, in some order; their sum
+    uint32_t blocks = 0;                 // workgroups wanted
+};
+
+// The compute units a launch may count on: how many, and whether it needs dealing (deal.level: largest capacity, or 0).
+struct CuShare {
+    int n_cu = 0;
+    SeDeal deal;
+};
+
+__host__ __device__ inline uint32_t se_cap_sum(uint32_t caps) { return (caps & 255u) + (caps >> 8 & 255u) + (caps >> 16 & 255u) + (caps >> 24); }
+__host__ __device__ inline uint32_t se_cap_clip(uint32_t caps, uint32_t level)
+{
+    uint32_t r = 0;
+    for (uint32_t q = 0; q < 4; ++q) {
+        const uint32_t c = caps >> (8 * q) & 255u;
+        r |= (c < level ? c : level) << (8 * q);
+    }
+    return r;
+}
+
+// Prepares `d` for a launch of `blocks` workgroups and returns the grid.  The level is the lowest that gives every wanted
+// workgroup a compute unit of its own in one round, and the largest capacity when one round cannot hold them; when the
+// smallest capacity already suffices the plain rotation is the balanced one.
+inline uint32_t se_deal_grid(SeDeal &d, uint32_t blocks)
+{
+    d.blocks = blocks;
+    if (d.level == 0) return blocks;
+    const uint32_t per = (blocks + 7) / 8;               // of the XCD with the most
+    uint32_t caps = 0, cmin = d.level;                   // enabled shader engines only, packed
+    for (uint32_t q = 0, n = 0; q < 4; ++q) {
+        const uint32_t c = d.se_caps >> (8 * q) & 255u;
+        if (c == 0) continue;
+        caps |= c << (8 * n++);
+        cmin = c < cmin ? c : cmin;
+    }
+    if (per <= cmin * d.slots) { d.level = 0; return blocks; }
+    uint32_t level = cmin + 1;
+    while (level < d.level && se_cap_sum(se_cap_clip(caps, level)) < per) ++level;
+    d.level = level;
+    d.any_order = se_cap_clip(caps, level);
+    d.sum = se_cap_sum(d.any_order);
+    d.half = d.turn->fetch_add(1, std::memory_order_relaxed) & 1u;
+    return 8 * d.slots * level * ((per + d.sum - 1) / d.sum);
+}
+
+// Index of this workgroup among the wanted ones, or 0xffffffff when it has nothing to do.  `b` is the workgroup's number along
+// x, `caps` the noted order of its XCD (b & 7), clipped.
+__host__ __device__ __forceinline__ uint32_t se_deal_index(const SeDeal &d, uint32_t b, uint32_t caps)
+{
+    const uint32_t x = b & 7u, j = b >> 3, t = j / d.slots, q = j - t * d.slots, round = t / d.level, r = t - round * d.level;
+    const uint32_t c = caps >> (8u * q) & 255u, below = caps & ((1u << (8u * q)) - 1u), skip = d.level - c;
+    if (r < skip) return 0xffffffffu;
+    const uint32_t v = (round * d.sum + se_cap_sum(below) + (r - skip)) * 8u + x;
+    return v < d.blocks ? v : 0xffffffffu;
+}
+__device__ __forceinline__ uint32_t se_dealt_block(const SeDeal &d, uint32_t b)
+{
+    if (d.level == 0) return b;
+    uint32_t caps = se_cap_clip((uint32_t)__builtin_amdgcn_readfirstlane((int)d.notes[8u * d.half + (b & 7u)]), d.level);
+    if (se_cap_sum(caps) != d.sum) caps = d.any_order;
+    if ((b >> 3) < d.slots && threadIdx.x == 0) {
+        const uint32_t se = __builtin_amdgcn_s_getreg(4 | (13 << 6) | (2 << 11));       // HW_ID: se_id, bits 13..15
+        reinterpret_cast<uint8_t *>(d.notes + 8u * (d.half ^ 1u))[(b & 7u) * 4u + (b >> 3)] = (uint8_t)(se < 4u ? d.se_caps >> (8u * se) : 0u);
+    }
+    return se_deal_index(d, b, caps);
+}
+
+// The v-th of n work items when every XCD is to own a contiguous range of them: item numbers grow along the XCD's own
+// workgroups (v = 8 * rank + XCD, see above).  0xffffffff when the XCD's range is used up; v runs to 8 * ceil(n / 8); n < 2^29.
+__host__ __device__ __forceinline__ uint32_t xcd_range_item(uint32_t v, uint32_t n)
+{
+    const uint32_t x = v & 7u, lo = n * x >> 3, hi = n * (x + 1u) >> 3, i = lo + (v >> 3);
+    return i < hi ? i : 0xffffffffu;
+}
+inline uint32_t xcd_range_blocks(uint32_t n) { return (n + 7u) & ~7u; }
+
+}  // namespace eclip
