@@ -1,0 +1,370 @@
+// The LDS-tiled matrix-core kernel whose operand tiles are copied straight from memory into LDS (implicit-GEMM convolution /
+// linear layer; same contraction, weights layout and epilogue as conv_gemm_kernel in gemm_tile.h).
+//
+// What bounds this class of kernel is the path into a compute unit, not its matrix pipes: conv_gemm_kernel brings the weights
+// of a tile column in once per wavefront that needs them and moves the activations through registers, and its 128 x 128 tile
+// takes 0.47-0.67 us per K step of 64 where the matrix instructions need 0.21.  Here both operands cross that path once,
+// land in LDS without passing registers (buffer_load_dwordx4 ... lds), several K steps ahead, and four wavefronts with
+// square sub-tiles read every LDS byte as rarely as a workgroup tile allows:
+//   - a ring of ST stages of BK = 64 or 32; the loads of K step t + ST go out as soon as every wavefront has read step t;
+//   - fragments are read half a step ahead of the matrix instructions that use them, and loads, LDS reads and matrix
+//     instructions are interleaved one by one: a SIMD has one wavefront, so nothing else would fill its gaps;
+//   - LDS positions: the weights in the order of their 1 KB blocks (a fragment is 1 KB in a row); a row of the activation
+//     tile is 128 (64) bytes, its 16-byte chunk c at position c ^ (row / 2 % 8) (c ^ (row / 4 % 4)), so that 16 lanes reading
+//     one chunk of 16 consecutive rows touch all banks once, while the lanes that load a row still read it in one piece.
+#pragma once
+#include "gemm_tile.h"
+
+namespace eclip {
+
+// Copies 16 bytes per lane from `rsrc` (byte offset voff + soff; zeros beyond its end) to LDS byte lds + 16 * lane.  Written out
+// because the compiler would otherwise wait for every such load before any later LDS read; the waits are explicit.
+__device__ __forceinline__ void dma_lds16(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+
+// Accumulators that leave no room for the rest in the 256 vector registers go to the accumulation registers (one wavefront
+// per SIMD has both files).  The matrix instruction is then written out: left to itself the compiler copies accumulators
+// between registers around every instruction.
+constexpr bool dma_acc_in_agprs(int bm, int bn, int waves) { return bm * bn / waves > 128 * 64; }
+template <typename T> __device__ __forceinline__ void mma_agpr(uint4 a, uint4 b, f32x4 &c)
+{
+    const u32x4 va = {a.x, a.y, a.z, a.w}, vb = {b.x, b.y, b.z, b.w};
+    if constexpr (std::is_same<T, bf16_t>::value) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(va), "v"(vb));
+    else asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(va), "v"(vb));
+}
+
+// Epilogue for outputs of the storage type with N a multiple of 8 (the rest goes through tile_epilogue).  One wavefront per SIMD
+// has nobody to hide behind, so this one is kept short and straight: buffer stores that drop what lies beyond M or N instead
+// of a branch per store, accumulators taken block row by block row.
+// (256 x 192 tile: 5.5 us with
+// the general epilogue, 5.0 with this one.  Passing the accumulators through LDS to a short rolled loop was slower, 7 us.)
+template <typename T, int BM, int BN, int WM, int WN, int TM, int TN, int ACT, bool RES>
+__device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][TN], int m_base, int n_base, int wm, int wn)
+{
+    static_assert(TN % 2 == 0, "pairs of blocks");
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    const int lane = threadIdx.x & 63, q = lane >> 4;
+    const int m0 = m_base + wm * (BM / WM) + (lane & 15), n0 = n_base + wn * (BN / WN) + 16 * (q & 1) + 8 * (q >> 1);   // see tile_epilogue_impl
+    constexpr unsigned OOB = 0xffffffffu;
+    const unsigned bytes = (unsigned)(((size_t)(p.M - 1) * p.ldy + p.N) * 2);
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void *)p.y, 0, (int)bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void *)(RES ? p.res : p.y), 0, (int)bytes, 0x00020000);
+    unsigned off[TN / 2];
+    float bv[TN / 2][8];
+    static_for<TN / 2>([&](auto jc) {
+        constexpr int jp = decltype(jc)::value;
+        off[jp] = n0 + 32 * jp < p.N ? ((unsigned)m0 * (unsigned)p.ldy + (unsigned)(n0 + 32 * jp)) * 2u : OOB;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bv[jp][e] = 0.f;
+        if (p.bias && n0 + 32 * jp < p.N) Pack<T, 8>::load(reinterpret_cast<const T *>(p.bias) + n0 + 32 * jp, bv[jp]);
+    });
+    const unsigned row16 = 32u * (unsigned)p.ldy;
+    u32x4 rq[2][TN / 2];
+    auto load_res = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (RES && i < TM)
+            static_for<TN / 2>([&](auto jc) {
+                constexpr int jp = decltype(jc)::value;
+                rq[i & 1][jp] = __builtin_amdgcn_raw_buffer_load_b128(rr, m0 + 16 * i < p.M ? off[jp] : OOB, (int)(row16 * i), 0);
+            });
+    };
+    load_res(std::integral_constant<int, 0>{});
+    static_for<TM>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        load_res(std::integral_constant<int, i + 1>{});
+        static_for<TN / 2>([&](auto jc) {
+            constexpr int jp = decltype(jc)::value;
+            float o[8];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const u32x2 sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][2 * jp][c]), __float_as_uint(acc[i][2 * jp + 1][c]), false, false);
+                o[c] = __uint_as_float(sw[0]);
+                o[4 + c] = __uint_as_float(sw[1]);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] += bv[jp][e];
+            if constexpr (RES) {
+                const u32x4 w = rq[i & 1][jp];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    o[2 * e] += Cvt<T>::from_bits(w[e] & 0xffffu);
+                    o[2 * e + 1] += Cvt<T>::from_bits(w[e] >> 16);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = apply_act_c<ACT>(o[e]);
+            u32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = Cvt<T>::pack2(o[2 * e], o[2 * e + 1]);
+            // The row's offset goes into the vector offset here, not into the scalar one: with a scalar-register offset the compiler
+            // leaves no gap between a 16-byte store and the next write of its data registers, and on this GPU the store then
+            // now and then takes the new values (only with several workgroups on the CU).
+            const bool ok = m0 + 16 * i < p.M && n0 + 32 * jp < p.N;
+            __builtin_amdgcn_raw_buffer_store_b128(v, ry, ok ? off[jp] + row16 * i : OOB, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    });
+}
+
+// Touches one 128-byte line per lane (4 bytes each go to LDS bytes lds .. lds + 255, which nobody reads).
+__device__ __forceinline__ void dma_touch(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+
+template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE>
+__global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1 : 2) void conv_gemm_dma_kernel(GemmDev p, SeDeal deal)
+{
+    constexpr int NW = WM * WN, KS = BK / 32;                           // KS: matrix instructions along K per step and block
+    static_assert(KS == 1 || KS == 2, "K step of 32 or 64");
+    constexpr int TM = BM / WM / 16, TN = BN / WN / 16, NM = TM * TN;
+    constexpr int RPC = 16 / KS, CPR = 4 * KS;                          // rows per 1 KB copy of the activations, 16-byte chunks per row
+    constexpr int AI = BM / RPC / NW, BI = BN / 16 * KS / NW;           // 1 KB copies per wavefront and step
+    static_assert(AI * RPC * NW == BM && BI * 16 * NW == BN * KS && TM * 16 * WM == BM && TN * 16 * WN == BN, "whole copies and blocks per wavefront");
+    constexpr int TOUCH = AMODE == A_MATRIX && dma_touches(BM, BN, BK, ST) ? 1 : 0;
+    constexpr unsigned STAGE = (BM + BN) * BK * 2u;                        // bytes: activations, then weights
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    int tile_m, tile_n;
+    const uint32_t bid = se_dealt_block(deal, blockIdx.x);
+    if (bid == 0xffffffffu || !gemm_tile_of(p, bid, tile_m, tile_n)) return;
+    const int m_base = tile_m * BM, n_base = tile_n * BN;
+    constexpr unsigned OOB = 0xffffffffu;
+    u32x4 rx, rw;
+    rx.x = (unsigned)(uintptr_t)p.x; rx.y = (unsigned)((uintptr_t)p.x >> 32) & 0xffffu; rx.z = p.x_bytes; rx.w = 0x00020000u;
+    rw.x = (unsigned)(uintptr_t)p.w; rw.y = (unsigned)((uintptr_t)p.w >> 32) & 0xffffu; rw.z = p.w_bytes; rw.w = 0x00020000u;
+
+    // ---- per-lane addressing that does not change along K: copy i of this wavefront is rows RPC (AI * wave + i) .. of the tile
+    const int KB = (p.K + 31) >> 5, NB = (p.N + 15) >> 4;
+    const int HoWo = p.Ho * p.Wo;
+    bool a_ok[AI];
+    unsigned a_off[AI];                      // byte offset of this lane's chunk at window tap (0, 0), channel 0 (modulo 2^32 when padded)
+    int a_ih0[AI], a_iw0[AI];
+    // position of chunk c of a row: c ^ swizzle(row).  (A_GENERAL with 128-byte rows: the same chunk in every copy of a lane)
+    auto swizzle = [](int row) { return KS == 1 ? (row >> 2) & 3 : AMODE == A_GENERAL ? row & 7 : (row >> 1) & 7; };
+    int kc = 0;                              // A_GENERAL: first k of this lane's chunk within a step (the same in every copy)
+#pragma unroll
+    for (int i = 0; i < AI; ++i) {
+        const int row = (AI * wave + i) * RPC + lane / CPR, m = m_base + row;
+        const int chunk = lane % CPR ^ swizzle(row);
+        if (AMODE == A_GENERAL) kc = chunk * 8;
+        a_ok[i] = m < p.M;
+        const int mm = a_ok[i] ? m : 0;
+        const int b = mm / HoWo, r = mm - b * HoWo;
+        const int oh = r / p.Wo, ow = r - oh * p.Wo;
+        a_ih0[i] = oh * p.stride - p.pad;
+        a_iw0[i] = ow * p.stride - p.pad;
+        a_off[i] = ((unsigned)b * (unsigned)(p.H * p.W) + (unsigned)(a_ih0[i] * p.W + a_iw0[i])) * (unsigned)p.ldx * 2u;
+        if (AMODE != A_GENERAL) a_off[i] += (unsigned)chunk * 16u;
+        if (AMODE == A_MATRIX && !a_ok[i]) a_off[i] = OOB;
+    }
+    // A_UNIFORM: bit t of a_out says that the row has no pixel under tap t = kh * KW + kw (at most 32 taps, see gemm_amode), so that
+    // a copy's offset costs three vector instructions; tests of the borders go through scalar masks, and a lone wavefront
+    // waits out every hop between its vector and scalar halves (128 x 128 tile, 3 x 3 window, 72 K steps: 36.6 -> 33.0 us).
+    unsigned a_out[AI];
+    if (AMODE == A_UNIFORM) {
+        unsigned cols[AI];                                              // bit kw: the column is outside
+#pragma unroll
+        for (int i = 0; i < AI; ++i) { cols[i] = 0u; a_out[i] = 0u; }
+#pragma unroll 1
+        for (int w = 0; w < p.KW; ++w)
+#pragma unroll
+            for (int i = 0; i < AI; ++i) cols[i] |= ((unsigned)(a_iw0[i] + w) < (unsigned)p.W ? 0u : 1u) << w;
+        const unsigned all = p.KW == 32 ? ~0u : (1u << p.KW) - 1u;
+#pragma unroll 1
+        for (int h = 0; h < p.KH; ++h)
+#pragma unroll
+            for (int i = 0; i < AI; ++i)
+                a_out[i] |= (a_ok[i] && (unsigned)(a_ih0[i] + h) < (unsigned)p.H ? cols[i] : all) << (h * p.KW);
+    }
+    unsigned b_off[BI];                      // copy i: weight block (row block (BI * wave + i) / KS, k block (BI * wave + i) % KS of the step)
+#pragma unroll
+    for (int i = 0; i < BI; ++i) {
+        const int blk = BI * wave + i, nb = (n_base >> 4) + blk / KS;
+        b_off[i] = nb < NB ? ((unsigned)(nb * KB + blk % KS) * 64u + (unsigned)lane) * 16u : OOB;
+    }
+
+    // ---- position along K of the step copied next
+    const int kt_begin = blockIdx.y * p.kt_per, kt_end = min(p.KT, kt_begin + p.kt_per);
+    int kt_run = kt_begin;
+    int k_run = kt_begin * BK + kc, kh = 0, kw = 0, ci = AMODE == A_GENERAL ? k_run : kt_begin * BK;   // uniform but for A_GENERAL
+    if (AMODE != A_MATRIX && p.KH * p.KW != 1) {
+        const int tap = ci / p.Cin;
+        ci -= tap * p.Cin;
+        kh = tap / p.KW;
+        kw = tap - kh * p.KW;
+    }
+    unsigned tap_off = (unsigned)((kh * p.W + kw) * p.ldx + ci) * 2u;
+    int tap = kh * p.KW + kw;                                         // A_UNIFORM (uniform)
+    const int k_lim = min(p.K, kt_end * BK), kb_lim = min(KB, kt_end * KS);
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)smem;
+    // copies beyond the end of the slice read nothing (their descriptor is empty): the loads in flight stay countable
+    auto copy_a = [&](auto ic, unsigned slot) {
+        constexpr int i = decltype(ic)::value;
+        u32x4 r = rx;
+        if (AMODE != A_GENERAL) r.z = kt_run < kt_end ? p.x_bytes : 0u;
+        unsigned v = a_off[i], s = 0;
+        if (AMODE == A_MATRIX) s = (unsigned)kt_run * (BK * 2u);
+        else if (AMODE == A_UNIFORM) v = (v + tap_off) | (unsigned)((int)(a_out[i] << (31 - tap)) >> 31);
+        else {
+            const int ok = (int)a_ok[i] & (int)((unsigned)(a_ih0[i] + kh) < (unsigned)p.H) & (int)((unsigned)(a_iw0[i] + kw) < (unsigned)p.W) &
+                           (int)(k_run < k_lim);
+            v = ok ? v + tap_off : OOB;
+        }
+        dma_lds16(r, v, s, lds0 + slot + (unsigned)(AI * wave + i) * 1024u);
+    };
+    auto copy_b = [&](auto ic, unsigned slot) {
+        constexpr int i = decltype(ic)::value;
+        u32x4 r = rw;
+        const int kb = kt_run * KS + (AMODE == A_GENERAL ? (BI * wave + i) % KS : 0);
+        r.z = kb < kb_lim ? p.w_bytes : 0u;
+        dma_lds16(r, b_off[i], (unsigned)kt_run * (KS * 1024u), lds0 + slot + BM * BK * 2u + (unsigned)(BI * wave + i) * 1024u);
+    };
+    // The weights of a large model are in no cache: the workgroups that share a tile column (and an L2) take turns touching the
+    // lines of the step PD steps ahead of the copies (BERT-large FFN2 on 96 CUs, served: 36 -> 31 us; with the weights in the
+    // last-level cache it costs 1 us of 28).
+    constexpr int PD = 6, LINES = BN * BK / 64;                         // 128-byte lines of a step's weights
+    const int share = p.raster == 2 ? p.tiles_m : (p.tiles_m + 7) >> 3, part = p.raster == 2 ? tile_m : tile_m >> 3;
+    int turn = part;
+    const unsigned t_line = (unsigned)(wave * 64 + lane), t_blk = t_line / (8 * KS);
+    const unsigned t_off = t_line < LINES ? ((unsigned)((n_base >> 4) + (int)t_blk) * (unsigned)KB * 1024u + (t_line % (8 * KS)) * 128u) : OOB;
+    auto touch_b = [&]() {
+        u32x4 r = rw;
+        r.z = turn == 0 && kt_run + PD < kt_end ? p.w_bytes : 0u;
+        dma_touch(r, t_off, (unsigned)(kt_run + PD) * (KS * 1024u), lds0 + ST * STAGE);
+        turn = turn == 0 ? share - 1 : turn - 1;
+    };
+    auto advance = [&]() {
+        ++kt_run;
+        if (AMODE == A_UNIFORM) {
+            ci += BK;
+            if (ci >= p.Cin) {
+                ci = 0;
+                ++tap;
+                if (++kw == p.KW) { kw = 0; ++kh; }
+            }
+        } else if (AMODE == A_GENERAL) {
+            k_run += BK;
+            ci += BK;
+#pragma unroll
+            for (int u = 0; u < BK / 8; ++u) {       // Cin >= 8
+                const int wrap = ci >= p.Cin;
+                ci -= wrap ? p.Cin : 0;
+                kw += wrap;
+                const int wrap2 = kw == p.KW;
+                kw = wrap2 ? 0 : kw;
+                kh += wrap2;
+            }
+        }
+        if (AMODE != A_MATRIX) tap_off = (unsigned)((kh * p.W + kw) * p.ldx + ci) * 2u;
+    };
+
+    // ---- fragments: half ks of a step
+    const int r15 = lane & 15;
+    const unsigned a_rd0 = (unsigned)(wm * (BM / WM) + r15) * (BK * 2u) + (unsigned)((lane >> 4) ^ swizzle(r15)) * 16u;
+    const unsigned b_rd0 = BM * BK * 2u + (unsigned)(wn * (BN / WN) / 16) * (KS * 1024u) + (unsigned)lane * 16u;
+    uint4 fa[2][TM], fb[2][TN];
+    const char *lds_c = reinterpret_cast<const char *>(smem);
+    auto read_one = [&](auto qc, auto setc, unsigned slot) {           // q-th of the TM + TN fragments of half step ks into register set `set`
+        constexpr int q = decltype(qc)::value, set = decltype(setc)::value, ks = KS == 2 ? set : 0;
+        if constexpr (q < TN) fb[set][q] = *reinterpret_cast<const uint4 *>(lds_c + slot + b_rd0 + q * (KS * 1024) + ks * 1024);
+        else fa[set][q - TN] = *reinterpret_cast<const uint4 *>(lds_c + slot + (a_rd0 ^ (ks * 64u)) + (q - TN) * (BK * 32));
+    };
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // copies per step; with two half steps the last L - L2 of them go out in the first half of the next one
+    constexpr int L = AI + BI + TOUCH, L2 = KS == 2 ? L / 2 : L, R = TM + TN;
+    auto copy = [&](auto qc, unsigned slot) {
+        constexpr int q = decltype(qc)::value;
+        if constexpr (q < AI) copy_a(qc, slot);
+        else if constexpr (q < AI + BI) copy_b(std::integral_constant<int, q - AI>{}, slot);
+        else touch_b();
+    };
+    // The matrix instructions of register set `set`, copies C0 .. C0 + C - 1 of a step and the reads of the other register set, spread
+    // evenly: a burst of copies fills the queue towards memory (64 bytes per clock), and a wavefront waiting to issue a copy
+    // issues no matrix instructions either (128 x 128 tile, K step of 64: 0.40 us with the copies in one half, 0.35 spread).
+    auto half_step = [&](auto setc, auto c0c, auto cc, unsigned copy_slot, unsigned read_slot) {
+        constexpr int set = decltype(setc)::value, C0 = decltype(c0c)::value, C = decltype(cc)::value, Q = C + R;
+        static_for<NM>([&](auto mc) {
+            constexpr int m = decltype(mc)::value, i = m / TN, j = m % TN;
+            if constexpr (dma_acc_in_agprs(BM, BN, NW)) mma_agpr<T>(fb[set][j], fa[set][i], acc[i][j]);
+            else acc[i][j] = Mma<T>::run(fb[set][j], fa[set][i], acc[i][j]);
+            constexpr int q0 = m * Q / NM, q1 = (m + 1) * Q / NM;
+            static_for<q1 - q0>([&](auto dc) {
+                constexpr int q = q0 + decltype(dc)::value, c0 = q * C / Q, c1 = (q + 1) * C / Q;
+                if constexpr (c1 > c0) copy(std::integral_constant<int, C0 + c0>{}, copy_slot);
+                else read_one(std::integral_constant<int, q - c0>{}, std::integral_constant<int, 1 - set>{}, read_slot);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using IL2 = std::integral_constant<int, L2>;
+    using IL1 = std::integral_constant<int, L - L2>;
+    static_for<ST>([&](auto sc) {
+        constexpr int st = decltype(sc)::value;
+        static_for<(st == ST - 1 ? L2 : L)>([&](auto qc) { copy(qc, st * STAGE); });
+        if constexpr (st < ST - 1 || KS == 1) advance();
+    });
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((ST - 2) * L + L2) : "memory");
+    __builtin_amdgcn_s_barrier();
+    static_for<R>([&](auto qc) { read_one(qc, I0{}, 0u); });
+
+    // Every wavefront has read all of the current step and its copies of the next one have landed; after the barrier so have everyone's
+    auto meet = [&]() {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((ST - 2) * L) : "memory");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto after = [&](unsigned slot) { return slot + STAGE == ST * STAGE ? 0u : slot + STAGE; };
+    unsigned slot = 0, prev = (ST - 1) * STAGE;                        // stages of step kt and of step kt - 1 (= kt + ST - 1)
+    if constexpr (KS == 2) {
+        for (int kt = kt_begin; kt < kt_end; ++kt) {
+            const unsigned next = after(slot);
+            half_step(I0{}, IL2{}, IL1{}, prev, slot);
+            advance();
+            meet();
+            half_step(I1{}, I0{}, IL2{}, slot, next);
+            prev = slot;
+            slot = next;
+        }
+    } else {
+        for (int kt = kt_begin; kt < kt_end; kt += 2) {                // a step beyond the slice multiplies zeros
+            meet();
+            unsigned next = after(slot);
+            half_step(I0{}, I0{}, IL2{}, slot, next);
+            advance();
+            slot = next;
+            meet();
+            next = after(slot);
+            half_step(I1{}, I0{}, IL2{}, slot, next);
+            advance();
+            slot = next;
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15" ::: "memory");      // (the compiler does not see the latency of mma_agpr)
+    __builtin_amdgcn_s_barrier();
+    if (p.splits == 1 && p.y && (p.N & 7) == 0) {
+#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true>(p, acc, m_base, n_base, wm, wn) \
+                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false>(p, acc, m_base, n_base, wm, wn)
+        ECLIP_ACT_SWITCH(p.act, EPI)
+#undef EPI
+        return;
+    }
+    tile_epilogue<T, BM, BN, WM, WN, TM, TN>(p, acc, smem, m_base, n_base, blockIdx.y);
+}
+
+}  // namespace eclip

@@ -208,8 +208,31 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev &p, f32x4 (&acc)[TM]
     }
 }
 
+// Output tile of workgroup `bid` (false: it has none).  Workgroups are handed to the 8 XCDs round-robin (workgroup b runs on
+// XCD b % 8), each XCD has its own L2, and the 32 CUs of an XCD run 32 consecutive workgroups of that XCD at a time.  Raster
+// 1 (large problems): those 32 workgroups form an 8 x 4 block of tiles, so that one K step pulls 8 + 4 operand tiles into
+// the L2 instead of up to 32 + 1; blocks are dealt to the XCDs in row-major order.  Raster 2 (3): an XCD owns a contiguous
+// range of the tiles, counted down the tile columns (along the tile rows).
+__device__ __forceinline__ bool gemm_tile_of(const GemmDev &p, uint32_t bid, int &tile_m, int &tile_n)
+{
+    if (p.raster == 1) {
+        const int b = (int)bid, l = b >> 3, w = l & 31;
+        const int sb = (l >> 5) * 8 + (b & 7);
+        const int sbm = (p.tiles_m + 7) >> 3;
+        tile_m = (sb % sbm) * 8 + (w & 7);
+        tile_n = (sb / sbm) * 4 + (w >> 3);
+        return tile_m < p.tiles_m && tile_n < p.tiles_n;
+    }
+    const uint32_t t = p.raster ? xcd_range_item(bid, (uint32_t)(p.tiles_m * p.tiles_n)) : bid;
+    if (t == 0xffffffffu) return false;
+    const int fast = p.raster == 3 ? p.tiles_n : p.tiles_m, slow = (int)t / fast, rem = (int)t - slow * fast;
+    tile_m = p.raster == 3 ? slow : rem;
+    tile_n = p.raster == 3 ? rem : slow;
+    return true;
+}
+
 // K-loop schedules
-enum { LOOP_PLAIN = 0, LOOP_PINGPONG = 2, LOOP_PP_BDIRECT = 3 };
+enum { LOOP_PLAIN = 0, LOOP_PINGPONG = 2, LOOP_PP_BDIRECT = 3, LOOP_DMA = 4 /* conv_gemm_dma_kernel, gemm_dma.h */ };
 
 // How the im2col operand is addressed along K (chosen per launch from the layer's shape):
 //   A_GENERAL  any window, any channel count: every thread tracks the (kh, kw, ci) position of its own chunk
@@ -244,28 +267,9 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p, SeDe
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
-    // Workgroups are handed to the 8 XCDs round-robin (workgroup b runs on XCD b % 8), each XCD has its own
-    // L2, and the 32 CUs of an XCD run 32 consecutive workgroups of that XCD at a time.  With `raster` set
-    // (large problems) those 32 workgroups form an 8 x 4 block of tiles, so that one K step pulls 8 + 4
-    // operand tiles into the L2 instead of up to 32 + 1; blocks are dealt to the XCDs in row-major order.
-    // Raster 2 (3): an XCD owns a contiguous range of the tiles, counted down the tile columns (along the tile rows).
     int tile_m, tile_n;
     const uint32_t bid = se_dealt_block(deal, blockIdx.x);
-    if (bid == 0xffffffffu) return;
-    if (p.raster == 1) {
-        const int b = (int)bid, l = b >> 3, w = l & 31;
-        const int sb = (l >> 5) * 8 + (b & 7);
-        const int sbm = (p.tiles_m + 7) >> 3;
-        tile_m = (sb % sbm) * 8 + (w & 7);
-        tile_n = (sb / sbm) * 4 + (w >> 3);
-        if (tile_m >= p.tiles_m || tile_n >= p.tiles_n) return;
-    } else {
-        const uint32_t t = p.raster ? xcd_range_item(bid, (uint32_t)(p.tiles_m * p.tiles_n)) : bid;
-        if (t == 0xffffffffu) return;
-        const int fast = p.raster == 3 ? p.tiles_n : p.tiles_m, slow = (int)t / fast, rem = (int)t - slow * fast;
-        tile_m = p.raster == 3 ? slow : rem;
-        tile_n = p.raster == 3 ? rem : slow;
-    }
+    if (bid == 0xffffffffu || !gemm_tile_of(p, bid, tile_m, tile_n)) return;
     const int m_base = tile_m * BM, n_base = tile_n * BN;
 
     // ---- per-thread, per-chunk addressing that does not change along K
@@ -626,7 +630,11 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p, SeDe
     X(5, 256, 256, 32, 2, LOOP_PP_BDIRECT) X(6, 128, 256, 64, 2, LOOP_PP_BDIRECT) X(7, 192, 128, 32, 2, LOOP_PP_BDIRECT)    \
     X(8, 192, 128, 64, 2, LOOP_PP_BDIRECT) X(9, 128, 128, 64, 2, LOOP_PP_BDIRECT) X(10, 256, 128, 32, 2, LOOP_PP_BDIRECT)   \
     X(11, 192, 256, 32, 2, LOOP_PP_BDIRECT) X(12, 256, 192, 32, 2, LOOP_PP_BDIRECT) X(13, 64, 128, 64, 2, LOOP_PP_BDIRECT)  \
-    X(14, 128, 64, 64, 2, LOOP_PP_BDIRECT) X(15, 96, 64, 64, 2, LOOP_PP_BDIRECT) X(16, 96, 192, 64, 2, LOOP_PP_BDIRECT)
+    X(14, 128, 64, 64, 2, LOOP_PP_BDIRECT) X(15, 96, 64, 64, 2, LOOP_PP_BDIRECT) X(16, 96, 192, 64, 2, LOOP_PP_BDIRECT)    \
+    X(17, 256, 256, 32, 5, LOOP_DMA) X(18, 256, 128, 64, 3, LOOP_DMA) X(19, 128, 256, 64, 3, LOOP_DMA)                      \
+    X(20, 128, 128, 64, 4, LOOP_DMA) X(21, 192, 128, 64, 3, LOOP_DMA) X(22, 128, 64, 64, 3, LOOP_DMA)                       \
+    X(23, 64, 128, 64, 3, LOOP_DMA) X(24, 256, 192, 32, 5, LOOP_DMA) X(25, 192, 256, 32, 5, LOOP_DMA)                       \
+    X(26, 64, 64, 64, 4, LOOP_DMA) X(27, 128, 64, 32, 3, LOOP_DMA) X(28, 128, 128, 32, 3, LOOP_DMA)
 
 struct PPTile { int id, bm, bn, bk, rs, loop; };
 constexpr PPTile kPPTiles[] = {
@@ -649,13 +657,20 @@ constexpr size_t lds_bytes(int bm, int bn, int bk, int pad = 8, bool weights_in_
     const size_t stage = pad == 16 ? (size_t)8 * 32 * (bn / 4 + 4) * 4 : 0;
     return ring > stage ? ring : stage;
 }
+// the same for conv_gemm_dma_kernel with 4 wavefronts: its ring of `stages` K steps, or the staged epilogue
+constexpr bool dma_touches(int bm, int bn, int bk, int stages) { return (size_t)stages * (bm + bn) * bk * 2 + 256 <= 160 * 1024; }
+constexpr size_t dma_lds_bytes(int bm, int bn, int bk, int stages)
+{
+    const size_t ring = (size_t)stages * (bm + bn) * bk * 2 + (dma_touches(bm, bn, bk, stages) ? 256 : 0), stage = (size_t)4 * 32 * (bn / 2 + 4) * 4;
+    return ring > stage ? ring : stage;
+}
 
 // Which addressing form a launch may take (see conv_gemm_kernel)
 inline int gemm_amode(const GemmDev &d, int bk)
 {
     if (d.nchw_c) return A_GENERAL;
     if (d.KH * d.KW == 1 && d.pad == 0 && d.K % bk == 0) return A_MATRIX;
-    if (d.Cin % bk == 0) return A_UNIFORM;
+    if (d.Cin % bk == 0 && d.KH * d.KW <= 32) return A_UNIFORM;      // (conv_gemm_dma_kernel keeps one bit per tap)
     return A_GENERAL;
 }
 

@@ -223,7 +223,7 @@ std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, siz
             set_xcd_split(pl, M, N);
             out.push_back(pl);
         }
-    for (int v : {0, 1, 3, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16}) {
+    for (int v : {0, 1, 3, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28}) {
         int bm, bn, bk;
         conv_gemm_tile(v, &bm, &bn, &bk);
         if (bm > 2 * M + 32 || bn > 2 * N + 32) continue;
@@ -290,12 +290,17 @@ GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats)
     // minus the 2.5 us launch cost that all single-launch candidates share (as in wsk_cost).  Checked against an exhaustive
     // sweep of every candidate on every GEMM shape of the benchmark models: the picks cost 0-8 % more than the
     // per-layer optimum in total on 256 compute units, up to 14 % on 96; eclip_model_tune closes that gap by measurement.
-    struct LdsTile { int variant; double step, fixed; bool pair; };
-    static const LdsTile lds[] = {{0, 0.3613, 0.02038, true}, {1, 0.3664, 0.1703, true},
-                                  {3, 0.582, 5.6, false},  {5, 0.616, 4.6, false},  {6, 0.72, 2.5, false},  {7, 0.36, 1.4, false},
-                                  {8, 0.571, 3.0, false},  {9, 0.473, 0.6, false},  {10, 0.395, 1.5, false}, {11, 0.505, 3.8, false},
-                                  {12, 0.481, 3.8, false}, {13, 0.406, 0.0, true},  {14, 0.373, 0.2, true},
-                                  {15, 0.3134, 0.83, true}, {16, 0.4837, 4.2, false}};
+    // Ids from 17 on (both operands copied into LDS; same procedure, 3 x 3 windows at batch 8 added): `more` us for every further
+    // round of workgroups on a compute unit -- fill and epilogue again, less what several small workgroups hide of each other.
+    struct LdsTile { int variant; double step, fixed; bool pair; double more; };
+    static const LdsTile lds[] = {{0, 0.3613, 0.02038, true, 0.0}, {1, 0.3664, 0.1703, true, 0.0},
+                                  {3, 0.582, 5.6, false, 0.0},  {5, 0.616, 4.6, false, 0.0},  {6, 0.72, 2.5, false, 0.0},   {7, 0.36, 1.4, false, 0.0},
+                                  {8, 0.571, 3.0, false, 0.0},  {9, 0.473, 0.6, false, 0.0},  {10, 0.395, 1.5, false, 0.0}, {11, 0.505, 3.8, false, 0.0},
+                                  {12, 0.481, 3.8, false, 0.0}, {13, 0.406, 0.0, true, 0.0},  {14, 0.373, 0.2, true, 0.0},
+                                  {15, 0.3134, 0.83, true, 0.0}, {16, 0.4837, 4.2, false, 0.0},
+                                  {17, 0.448, 11.0, false, 9.0}, {18, 0.487, 4.5, false, 4.5}, {19, 0.487, 4.6, false, 4.5}, {20, 0.313, 2.7, false, 2.7},
+                                  {21, 0.404, 4.1, false, 4.0},  {22, 0.281, 1.8, true, 2.0}, {23, 0.281, 1.8, true, 2.0}, {24, 0.346, 6.1, false, 5.0},
+                                  {25, 0.346, 6.3, false, 5.0},  {26, 0.21, 1.7, true, 1.5},   {27, 0.175, 1.6, true, 1.1},  {28, 0.21, 2.4, true, 1.5}};
     for (const LdsTile &c : lds) {
         int bm, bn, bk;
         conv_gemm_tile(c.variant, &bm, &bn, &bk);
@@ -316,7 +321,7 @@ GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats)
                 const double load = wgs >= n_cu ? 1.0 : (double)wgs / n_cu;
                 double rounds = (double)cdiv(wgs, n_cu);
                 if (c.pair && rounds >= 2.0) rounds = 0.87 * (double)wgs / n_cu > 1.0 ? 0.87 * (double)wgs / n_cu : 1.0;
-                cost = c.fixed + rounds * (double)cdiv(KT, sp) * c.step * (1.0 + 0.15 * load * load);
+                cost = c.fixed + (rounds - 1.0) * c.more + rounds * (double)cdiv(KT, sp) * c.step * (1.0 + 0.15 * load * load);
             }
             if (sp > 1) cost += 15.48 + (double)M * N * (4.0 * sp + 2.0) / 4.243e6;
             if (cost < best) {

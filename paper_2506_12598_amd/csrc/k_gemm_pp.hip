@@ -1,7 +1,7 @@
 // One ping-pong tile shape of the LDS-tiled matrix-core kernel (gemm_tile.h), selected by ECLIP_PP_ID at compile time:
 // both 16-bit types and the three addressing forms.  One translation unit per shape keeps the build parallel; the
 // build script compiles this file once for every id listed in ECLIP_PP_TILES.
-#include "gemm_tile.h"
+#include "gemm_dma.h"
 
 #ifndef ECLIP_PP_ID
 #error "compile with -DECLIP_PP_ID=<variant id>"
@@ -17,7 +17,11 @@ static_assert(kTile.id == ECLIP_PP_ID, "ECLIP_PP_ID is not in ECLIP_PP_TILES");
 template <typename T, int AMODE>
 hipError_t launch_one(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream_t s)
 {
-    hipLaunchKernelGGL((conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>), grid, dim3(512),
+    if constexpr (kTile.loop == LOOP_DMA)
+        hipLaunchKernelGGL((conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE>), grid, dim3(256),
+                           dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs), s, d, deal);
+    else
+        hipLaunchKernelGGL((conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>), grid, dim3(512),
                        lds_bytes(kTile.bm, kTile.bn, kTile.bk, 16, kTile.loop != LOOP_PP_BDIRECT), s, d, deal);
     return hipGetLastError();
 }
@@ -35,7 +39,11 @@ hipError_t launch_mode(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStrea
 template <typename T, int AMODE>
 hipError_t init_one()
 {
-    return hipFuncSetAttribute((const void *)conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>,
+    if constexpr (kTile.loop == LOOP_DMA)
+        return hipFuncSetAttribute((const void *)conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs));
+    else
+        return hipFuncSetAttribute((const void *)conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(kTile.bm, kTile.bn, kTile.bk, 16, kTile.loop != LOOP_PP_BDIRECT));
 }
 
