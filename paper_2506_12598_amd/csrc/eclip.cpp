@@ -479,7 +479,7 @@ struct eclip_model {
     uint32_t n_groups = 0;
     std::vector<uint32_t> mask_of_group;
     bool has_alloc = false;
-    bool stem_direct = false;      // layer 0 is the only reader of an IMAGE input of <= 4 channels and a matrix-core convolution:
+    bool stem_direct = false;      // layer 0 is the only reader of an IMAGE input (16-bit models: of <= 4 channels) and a convolution:
                                    // it may read the caller's tensor itself instead of the channels-last copy
 
     char *d_weights = nullptr;
@@ -750,15 +750,15 @@ static eclip_status plan_model(const eclip_model_desc *d, size_t weight_elems, e
         const LayerPlan &S = m->layers[0];
         bool only_reader = true;
         for (uint32_t j = 1; j < d->n_layers; ++j) only_reader &= m->layers[j].L.in0 != -1 && m->layers[j].L.in1 != -1;
-        m->stem_direct = d->in_kind == ECLIP_IN_IMAGE && d->in_c <= 4 && m->in_cp == 8 && S.L.op == ECLIP_OP_CONV && S.gemm &&
+        m->stem_direct = d->in_kind == ECLIP_IN_IMAGE && S.L.op == ECLIP_OP_CONV && (f32 ? S.L.groups <= 1 : d->in_c <= 4 && m->in_cp == 8 && S.gemm) &&
                          S.L.in0 == -1 && S.L.in1 != -1 && only_reader && d->n_layers > 1;
     }
-    // Pool + classifier candidates: a GAP layer read only by the matrix-core linear layer right after it, same group,
+    // Pool + classifier candidates: a GAP layer read only by the linear layer right after it, same group,
     // the linear layer taking no second operand.  Whether the fused kernel pays depends on the batch (decided per request).
     for (uint32_t i = 0; i + 1 < d->n_layers; ++i) {
         LayerPlan &A = m->layers[i];
         const LayerPlan &B = m->layers[i + 1];
-        if (A.L.op != ECLIP_OP_GAP || B.L.op != ECLIP_OP_LINEAR || !B.gemm || B.L.in0 != (int)i || B.L.in1 >= 0) continue;
+        if (A.L.op != ECLIP_OP_GAP || B.L.op != ECLIP_OP_LINEAR || !(B.gemm || f32) || B.L.in0 != (int)i || B.L.in1 >= 0) continue;
         if (d->group_of_layer[i] != d->group_of_layer[i + 1] || B.in.kind == ECLIP_KIND_IMAGE) continue;
         bool other_reader = false;
         for (uint32_t j = i + 2; j < d->n_layers; ++j) other_reader |= m->layers[j].L.in0 == (int)i || m->layers[j].L.in1 == (int)i;
@@ -1426,8 +1426,17 @@ static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, c
     *done = false;
     const LayerPlan &P = m->layers[0];
     const GemmShape g = gemm_shape(P, batch);
+    if (m->dtype == ECLIP_F32) {
+        if (getenv("ECLIP_NO_PAIRS")) return hipSuccess;
+        ConvF32Args a{(const float *)d_in, (const float *)wptr(m, P.w_dev), (const float *)wptr(m, P.b_dev), nullptr, (float *)out_ptr(m, P),
+                      g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, P.L.act};
+        a.nchw = true;
+        *done = true;
+        *n_launched += 1;
+        return launch_conv_f32(a, s);
+    }
     GemmPlan pl;
-    if (!conv_gemm_plan_stem((long)g.B * g.Ho * g.Wo, g.Cout, (long)g.KH * g.KW * g.Cin, cu.n_cu, m->ws_floats, 2.0, &pl)) return hipSuccess;
+    if (!conv_gemm_plan_stem((long)g.B * g.Ho * g.Wo, g.Cout, (long)g.KH * g.KW * g.Cin, cu.n_cu, m->ws_floats, 4.0, &pl)) return hipSuccess;
     ConvGemmArgs a{d_in, wptr(m, P.w_dev), wptr(m, P.b_dev), nullptr, out_ptr(m, P), nullptr, m->ws,
                    g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, P.L.act, m->dtype};
     a.nchw_c = m->in_c;

@@ -31,30 +31,52 @@ inline unsigned banded_blocks_for(long n_threads, int block) { return (blocks_fo
         }                                                                          \
     } while (0)
 
-// ---------------- float32 direct convolution: one thread per output element ----------------------
-__global__ __launch_bounds__(256) void conv_f32_kernel(ConvF32Args a, long total)
+// ---------------- float32 direct convolution --------------------------------------------------------
+// A lane owns one output element, the NW wavefronts of a workgroup share the sum of 64 of them: each takes a contiguous slice of
+// k = (kh, kw, ci), its loads U at a time and without a branch between them, and the partial sums meet in LDS in wavefront
+// order.  At batch 1 this is latency and nothing else: one thread per output and one load after the other took 18.4 us for
+// 16 x 16 x 32 outputs of a 3 x 3 window over 16 channels (5.8 us now).
+template <int NW, int U>
+__global__ __launch_bounds__(NW * 64) void conv_f32_kernel(ConvF32Args a, unsigned total)
 {
-    const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const unsigned ui = (unsigned)idx;
+    __shared__ float part[NW][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned idx = blockIdx.x * 64u + lane, ui = idx < total ? idx : total - 1u;
     const int n = (int)(ui % (unsigned)a.Cout);
     const unsigned m = ui / (unsigned)a.Cout;
     const int ow = (int)(m % (unsigned)a.Wo);
     const unsigned mh = m / (unsigned)a.Wo;
-    const int oh = (int)(mh % (unsigned)a.Ho);
-    const int b = (int)(mh / (unsigned)a.Ho);
-    float acc = a.bias ? a.bias[n] : 0.0f;
-    for (int kh = 0; kh < a.KH; ++kh) {
-        const int ih = oh * a.stride - a.pad + kh;
-        if ((unsigned)ih >= (unsigned)a.H) continue;
-        for (int kw = 0; kw < a.KW; ++kw) {
-            const int iw = ow * a.stride - a.pad + kw;
-            if ((unsigned)iw >= (unsigned)a.W) continue;
-            const float *xp = a.x + (((long)b * a.H + ih) * a.W + iw) * a.Cin;
-            const float *wp = a.w + ((long)(kh * a.KW + kw) * a.Cin) * a.Cout + n;
-            for (int ci = 0; ci < a.Cin; ++ci) acc = fmaf(xp[ci], wp[(long)ci * a.Cout], acc);
+    const int ih0 = (int)(mh % (unsigned)a.Ho) * a.stride - a.pad, iw0 = ow * a.stride - a.pad;
+    // element strides of x: channels-last, or the caller's [B][C][H][W]
+    const int xc = a.nchw ? a.H * a.W : 1, xw = a.nchw ? 1 : a.Cin, xh = xw * a.W;
+    const float *x = a.x + (long)(mh / (unsigned)a.Ho) * a.H * a.W * a.Cin;
+    const int K = a.KH * a.KW * a.Cin, per = (K + NW - 1) / NW, k0 = wave * per, k1 = min(K, k0 + per);
+    const int tap = k0 / a.Cin;
+    int ci = k0 - tap * a.Cin, kh = tap / a.KW, kw = tap - kh * a.KW;
+    float acc = 0.0f;
+    for (int k = k0; k < k1; k += U) {
+        float xv[U], wv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int ih = ih0 + kh, iw = iw0 + kw;
+            const bool ok = k + u < k1 && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
+            const float v = x[ok ? ih * xh + iw * xw + ci * xc : 0];
+            xv[u] = ok ? v : 0.0f;
+            wv[u] = a.w[(long)min(k + u, K - 1) * a.Cout + n];
+            if (++ci == a.Cin) {
+                ci = 0;
+                if (++kw == a.KW) { kw = 0; ++kh; }
+            }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = fmaf(xv[u], wv[u], acc);
     }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave || idx >= total) return;
+    acc = a.bias ? a.bias[n] : 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) acc += part[w][lane];
     if (a.res) acc += a.res[idx];
     a.y[idx] = apply_act(a.act, acc);
 }
@@ -845,7 +867,8 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, long n)
 hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t s)
 {
     const long total = (long)a.B * a.Ho * a.Wo * a.Cout;
-    hipLaunchKernelGGL(conv_f32_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, s, a, total);
+    if (a.KH * a.KW * a.Cin <= 32) hipLaunchKernelGGL((conv_f32_kernel<4, 8>), dim3(blocks_for(total, 64)), dim3(256), 0, s, a, (unsigned)total);
+    else hipLaunchKernelGGL((conv_f32_kernel<8, 9>), dim3(blocks_for(total, 64)), dim3(512), 0, s, a, (unsigned)total);
     return hipGetLastError();
 }
 
@@ -1008,20 +1031,25 @@ hipError_t launch_gap(const void *x, void *y, float *y32, float *ws, size_t ws_f
 // ---------------- global average pool + classifier in one launch ------------------------------------------------
 // y[b][n] = act(bias[n] + sum_c mean_hw(x[b][hw][c]) * w[n][c]) for a small batch.  Every kernel costs a few
 // microseconds whatever it does, and after the pooling a classifier at batch 1 is a matrix-vector product: one launch
-// saves one of the two.  A workgroup first pools all C channels into LDS (float; each thread sums a share of the
-// pixels of one 16-byte channel chunk), then each of its 4 wavefronts takes one block of 16 outputs and walks the
-// weights in their blocked layout (1 KB blocks of 16 outputs x 32 channels, lane l = output l & 15, channels
-// 8 (l >> 4) .. +7), so that every weight load of a wavefront is one contiguous kilobyte.  The pooled vector is read
-// once per workgroup, which is what limits the form to moderate C x HW (the caller decides).
+// saves one of the two.  A workgroup of 16 wavefronts first pools all C channels into LDS (float; each thread sums a share of
+// the pixels of one 16-byte channel chunk), then computes one block of 16 outputs, every wavefront a slice of the channels,
+// from the weights in their blocked layout (1 KB blocks of 16 outputs x 32 channels, lane l = output l & 15, channels
+// 8 (l >> 4) .. +7), so that every weight load of a wavefront is one contiguous kilobyte.  Both halves are one or two memory
+// round trips deep (with 4 wavefronts and a block of outputs each they were twelve and ten: 1280 channels x 49 pixels ->
+// 1000 outputs at batch 3 took 12.8 us, 9.2 now).  Every workgroup pools for itself, which is what limits the form to
+// moderate C x HW (the caller decides).
+constexpr int GAPFC_NW = 16;
 template <typename T>
-__global__ __launch_bounds__(256) void gapfc_kernel(const T *x, const uint4 *wb, const T *bias, T *y, float *y32, int HW, int C, int N,
-                                                    int KB, int act)
+__global__ __launch_bounds__(GAPFC_NW * 64) void gapfc_kernel(const T *x, const uint4 *wb, const T *bias, T *y, float *y32, int HW, int C, int N,
+                                                              int KB, int act)
 {
+    constexpr int NT = GAPFC_NW * 64;
     extern __shared__ __attribute__((aligned(16))) float gsm[];       // pooled[KB * 32], then part[parts][C]
     float *pooled = gsm, *part = gsm + KB * 32;
+    __shared__ float sums[GAPFC_NW][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = blockIdx.y;
-    const int cv = C >> 3, parts = 256 / cv;                           // C % 8 == 0 and C <= 2048 (checked by the caller)
+    const int b = blockIdx.y, nb = blockIdx.x;
+    const int cv = C >> 3, parts = NT / cv;                            // C % 8 == 0 and C <= 2048 (checked by the caller)
     if (tid < parts * cv) {
         const int chunk = tid % cv, pt = tid / cv;
         const T *src = x + ((long)b * HW) * C + chunk * 8;
@@ -1029,93 +1057,143 @@ __global__ __launch_bounds__(256) void gapfc_kernel(const T *x, const uint4 *wb,
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
         int px = pt;
-        for (; px + 3 * parts < HW; px += 4 * parts) {                 // four loads in flight
-            float v[4][8];
+        for (; px + 7 * parts < HW; px += 8 * parts) {                 // eight loads in flight
+            float v[8][8];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) Pack<T, 8>::load(src + (long)(px + u * parts) * C, v[u]);
+            for (int u = 0; u < 8; ++u) Pack<T, 8>::load(src + (long)(px + u * parts) * C, v[u]);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < 8; ++u)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) acc[e] += v[u][e];
         }
-        for (; px < HW; px += parts) {
-            float v[8];
-            Pack<T, 8>::load(src + (long)px * C, v);
+        if (px < HW) {                                                 // the rest at once: repeated loads count as zero
+            float v[8][8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] += v[e];
+            for (int u = 0; u < 8; ++u) Pack<T, 8>::load(src + (long)(px + u * parts < HW ? px + u * parts : px) * C, v[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] += px + u * parts < HW ? v[u][e] : 0.0f;
         }
         float *dst = part + pt * C + chunk * 8;
         *reinterpret_cast<float4 *>(dst) = make_float4(acc[0], acc[1], acc[2], acc[3]);
         *reinterpret_cast<float4 *>(dst + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
     }
+    // this wavefront's weight blocks, requested before the pooling is waited for
+    constexpr int U = 4;                                               // KB <= 64
+    const int per = (KB + GAPFC_NW - 1) / GAPFC_NW, kb0 = wave * per, kb1 = min(KB, kb0 + per);
+    const uint4 *wrow = wb + (long)nb * KB * 64 + lane;
+    uint4 q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) q[u] = wrow[(kb0 + u < kb1 ? kb0 + u : 0) * 64];
     __syncthreads();
     const float inv = 1.0f / (float)HW;
-    for (int c = tid; c < KB * 32; c += 256) {
+    for (int c = tid; c < KB * 32; c += NT) {
         float sum = 0.0f;
         if (c < C)
             for (int pt = 0; pt < parts; ++pt) sum += part[pt * C + c];
         pooled[c] = sum * inv;                                         // zero beyond C: the weight blocks are padded too
     }
     __syncthreads();
-    const int nb = blockIdx.x * 4 + wave;
-    if (nb * 16 >= N) return;
-    const uint4 *wrow = wb + (long)nb * KB * 64 + lane;
     const float *pv = pooled + (lane >> 4) * 8;
     float acc = 0.0f;
-    int kb = 0;
-    for (; kb + 4 <= KB; kb += 4) {
-        uint4 q[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) q[u] = wrow[(kb + u) * 64];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t ws4[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
-            const float4 p0 = *reinterpret_cast<const float4 *>(pv + (kb + u) * 32), p1 = *reinterpret_cast<const float4 *>(pv + (kb + u) * 32 + 4);
-            const float pe[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc = fmaf(Cvt<T>::from_bits(ws4[e] & 0xffffu), pe[2 * e], acc);
-                acc = fmaf(Cvt<T>::from_bits(ws4[e] >> 16), pe[2 * e + 1], acc);
-            }
-        }
-    }
-    for (; kb < KB; ++kb) {
-        const uint4 q = wrow[kb * 64];
-        const uint32_t ws4[4] = {q.x, q.y, q.z, q.w};
+    for (int u = 0; u < U; ++u) {
+        if (kb0 + u >= kb1) break;
+        const uint32_t ws4[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+        const float4 p0 = *reinterpret_cast<const float4 *>(pv + (kb0 + u) * 32), p1 = *reinterpret_cast<const float4 *>(pv + (kb0 + u) * 32 + 4);
+        const float pe[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            acc = fmaf(Cvt<T>::from_bits(ws4[e] & 0xffffu), pv[kb * 32 + 2 * e], acc);
-            acc = fmaf(Cvt<T>::from_bits(ws4[e] >> 16), pv[kb * 32 + 2 * e + 1], acc);
+            acc = fmaf(Cvt<T>::from_bits(ws4[e] & 0xffffu), pe[2 * e], acc);
+            acc = fmaf(Cvt<T>::from_bits(ws4[e] >> 16), pe[2 * e + 1], acc);
         }
     }
     acc += __shfl_xor(acc, 16, 64);
     acc += __shfl_xor(acc, 32, 64);
-    const int n = nb * 16 + lane;
-    if (lane < 16 && n < N) {
-        float v = acc + (bias ? Cvt<T>::load(bias + n) : 0.0f);
+    if (lane < 16) sums[wave][lane] = acc;
+    __syncthreads();
+    const int n = nb * 16 + tid;
+    if (tid < 16 && n < N) {
+        float v = bias ? Cvt<T>::load(bias + n) : 0.0f;
+#pragma unroll
+        for (int w = 0; w < GAPFC_NW; ++w) v += sums[w][tid];
         v = apply_act(act, v);
         if (y32) y32[(long)b * N + n] = v;
         else Cvt<T>::store(y + (long)b * N + n, v);
     }
 }
 
+// The same for float32 models (weights [C][N]): one workgroup per batch item pools, then S slices of the channels for every output.
+__global__ __launch_bounds__(256) void gapfc_f32_kernel(const float *x, const float *w, const float *bias, float *y, int HW, int C, int N, int act)
+{
+    __shared__ float pooled[1024];
+    __shared__ __attribute__((aligned(16))) float part[1024];
+    const int tid = threadIdx.x, b = blockIdx.x;
+    const int cv = C >> 2, parts = 256 / cv;                           // C % 4 == 0 and C <= 1024 (checked by the caller)
+    if (tid < parts * cv) {
+        const int chunk = tid % cv, pt = tid / cv;
+        const float4 *src = reinterpret_cast<const float4 *>(x + (long)b * HW * C) + chunk;
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int px = pt; px < HW; px += 8 * parts) {
+            float4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = src[(long)(px + u * parts < HW ? px + u * parts : px) * cv];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (px + u * parts < HW) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+        }
+        *reinterpret_cast<float4 *>(&part[pt * C + chunk * 4]) = acc;
+    }
+    __syncthreads();
+    const float inv = 1.0f / (float)HW;
+    for (int c = tid; c < C; c += 256) {
+        float sum = 0.0f;
+        for (int pt = 0; pt < parts; ++pt) sum += part[pt * C + c];
+        pooled[c] = sum * inv;
+    }
+    const int cols = N >= 256 ? 256 : (N + 31) / 32 * 32, S = 256 / cols, sl = tid / cols, per = (C + S - 1) / S;
+    for (int n0 = 0; n0 < N; n0 += cols) {
+        const int n = n0 + tid - sl * cols;
+        __syncthreads();                                               // pooled is ready; part is free
+        float acc = 0.0f;
+        if (sl < S && n < N) {
+            const int c1 = min(C, (sl + 1) * per);
+#pragma unroll 8
+            for (int c = sl * per; c < c1; ++c) acc = fmaf(w[(long)c * N + n], pooled[c], acc);
+        }
+        part[tid] = acc;
+        __syncthreads();
+        if (tid < cols && n < N) {
+            float v = bias ? bias[n] : 0.0f;
+            for (int i = 0; i < S; ++i) v += part[i * cols + tid];
+            y[(long)b * N + n] = apply_act(act, v);
+        }
+    }
+}
+
 bool gapfc_supported(int B, int HW, int C, int dtype)
 {
     // the pooled tensor is re-read by every workgroup and the weights by every batch item: small cases only
-    return (dtype == DT_BF16 || dtype == DT_F16) && B <= 8 && C % 8 == 0 && C >= 8 && C <= 2048 && (long)HW * C <= 64 * 1024;
+    if (dtype == DT_F32) return C % 4 == 0 && C <= 1024 && (long)HW * C <= 64 * 1024;
+    return B <= 8 && C % 8 == 0 && C >= 8 && C <= 2048 && (long)HW * C <= 128 * 1024;
 }
 
-hipError_t launch_gapfc(const void *x, const void *w_blocked, const void *bias, void *y, float *y32, int B, int HW, int C, int N, int act,
+hipError_t launch_gapfc(const void *x, const void *w, const void *bias, void *y, float *y32, int B, int HW, int C, int N, int act,
                         int dtype, hipStream_t s)
 {
     if (!gapfc_supported(B, HW, C, dtype)) return hipErrorInvalidValue;
-    const int KB = (C + 31) / 32, NB = (N + 15) / 16, parts = 256 / (C / 8);
+    if (dtype == DT_F32) {
+        hipLaunchKernelGGL(gapfc_f32_kernel, dim3((unsigned)B), dim3(256), 0, s, (const float *)x, (const float *)w, (const float *)bias, y32 ? y32 : (float *)y, HW, C, N, act);
+        return hipGetLastError();
+    }
+    const int KB = (C + 31) / 32, NB = (N + 15) / 16, parts = GAPFC_NW * 64 / (C / 8);
     const size_t lds = ((size_t)KB * 32 + (size_t)parts * C) * sizeof(float);
-    const dim3 grid((unsigned)((NB + 3) / 4), (unsigned)B);
+    const dim3 grid((unsigned)NB, (unsigned)B);
     if (dtype == DT_BF16)
-        hipLaunchKernelGGL(gapfc_kernel<bf16_t>, grid, dim3(256), lds, s, (const bf16_t *)x, (const uint4 *)w_blocked, (const bf16_t *)bias, (bf16_t *)y, y32, HW, C, N, KB, act);
+        hipLaunchKernelGGL(gapfc_kernel<bf16_t>, grid, dim3(GAPFC_NW * 64), lds, s, (const bf16_t *)x, (const uint4 *)w, (const bf16_t *)bias, (bf16_t *)y, y32, HW, C, N, KB, act);
     else
-        hipLaunchKernelGGL(gapfc_kernel<f16_t>, grid, dim3(256), lds, s, (const f16_t *)x, (const uint4 *)w_blocked, (const f16_t *)bias, (f16_t *)y, y32, HW, C, N, KB, act);
+        hipLaunchKernelGGL(gapfc_kernel<f16_t>, grid, dim3(GAPFC_NW * 64), lds, s, (const f16_t *)x, (const uint4 *)w, (const f16_t *)bias, (f16_t *)y, y32, HW, C, N, KB, act);
     return hipGetLastError();
 }
 

@@ -75,6 +75,7 @@ struct ConvF32Args {
     const float *bias, *res;
     float *y;            // [M][Cout]
     int B, H, W, Cin, Ho, Wo, Cout, KH, KW, stride, pad, act;
+    bool nchw = false;   // x is [B][Cin][H][W]
 };
 hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t s);
 
@@ -120,9 +121,9 @@ hipError_t launch_gap(const void *x, void *y, float *y32, float *ws, size_t ws_f
                       hipStream_t s, uint32_t *n_launched);
 
 // global average pool and the linear layer that follows it in one launch (small batch, moderate C x HW):
-// x [B][HW][C], w in the blocked GEMM layout of an N x C matrix, y [B][N] (model dtype) or y32 (float)
+// x [B][HW][C], w in the blocked GEMM layout of an N x C matrix (float32: [C][N]), y [B][N] (model dtype) or y32 (float)
 bool gapfc_supported(int B, int HW, int C, int dtype);
-hipError_t launch_gapfc(const void *x, const void *w_blocked, const void *bias, void *y, float *y32, int B, int HW, int C, int N, int act,
+hipError_t launch_gapfc(const void *x, const void *w, const void *bias, void *y, float *y32, int B, int HW, int C, int N, int act,
                         int dtype, hipStream_t s);
 
 struct RowArgs {
