@@ -39,6 +39,7 @@ struct GemmPlan {
     int nw;        // kind 1: wavefronts per workgroup, each taking 1/nw of K
     int raster;    // how workgroups walk the tiles: 2 (3) = an XCD owns a contiguous range of tiles counted down the tile columns
                    // (along the tile rows); 1 (kind 0) = 8 x 4 blocks of tiles per XCD.  `tiles` counts the padding of the walk
+    double cost = 0.0;   // modelled time, us without the launch; 0: chosen by measurement or forced
 };
 bool conv_gemm_plan_stem(long M, long N, long K, int n_cu, size_t ws_floats, double stage_us, GemmPlan *out);   // ConvGemmArgs::nchw_c
 enum { CONV_GEMM_VARIANTS = 29 };        // 0..2: 128x128x32, 64x64x64, 32x64x64 (4 wavefronts); 3, 4: 256x256x32, 128x256x64 (8 wavefronts on the
