@@ -15,14 +15,28 @@
 #pragma once
 #include "gemm_tile.h"
 
+// The compiler calls m0 reserved and warns of every statement that names it; it does take the name as a definition of m0.
+#pragma clang diagnostic ignored "-Winline-asm"
+
 namespace eclip {
 
 // Copies 16 bytes per lane from `rsrc` (byte offset voff + soff; zeros beyond its end) to LDS byte lds + 16 * lane.  Written out
-// because the compiler would otherwise wait for every such load before any later LDS read; the waits are explicit.
+// because the compiler would otherwise wait for every such load before any later LDS read; the waits are explicit.  m0 holds the
+// LDS address of the copy and belongs to the compiler, which uses it too: it is named as overwritten.
 __device__ __forceinline__ void dma_lds16(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
+
+// Waits until at most VM of this wavefront's memory accesses and (LGKM) none of its LDS accesses are outstanding, then for all
+// wavefronts of the workgroup.  To the compiler s_barrier itself touches no memory, so an LDS read of what another wavefront copies
+// could be moved in front of a bare one: the wait and the barrier are one statement that reads of memory do not pass.
+template <int VM, bool LGKM = true> __device__ __forceinline__ void wait_and_meet()
+{
+    if constexpr (LGKM) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(VM) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(VM) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Accumulators that leave no room for the rest in the 256 vector registers go to the accumulation registers (one wavefront
@@ -113,7 +127,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
 __device__ __forceinline__ void dma_touch(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
 
 template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE>
@@ -319,16 +333,11 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
         static_for<(st == ST - 1 ? L2 : L)>([&](auto qc) { copy(qc, st * STAGE); });
         if constexpr (st < ST - 1 || KS == 1) advance();
     });
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((ST - 2) * L + L2) : "memory");
-    __builtin_amdgcn_s_barrier();
+    wait_and_meet<(ST - 2) * L + L2, false>();
     static_for<R>([&](auto qc) { read_one(qc, I0{}, 0u); });
 
     // Every wavefront has read all of the current step and its copies of the next one have landed; after the barrier so have everyone's
-    auto meet = [&]() {
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((ST - 2) * L) : "memory");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-    };
+    auto meet = [&]() { wait_and_meet<(ST - 2) * L>(); };
     auto after = [&](unsigned slot) { return slot + STAGE == ST * STAGE ? 0u : slot + STAGE; };
     unsigned slot = 0, prev = (ST - 1) * STAGE;                        // stages of step kt and of step kt - 1 (= kt + ST - 1)
     if constexpr (KS == 2) {
@@ -355,8 +364,8 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
             slot = next;
         }
     }
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15" ::: "memory");      // (the compiler does not see the latency of mma_agpr)
-    __builtin_amdgcn_s_barrier();
+    asm volatile("s_nop 15");                                          // the compiler does not see the latency of mma_agpr
+    wait_and_meet<0>();
     if (p.splits == 1 && p.y && (p.N & 7) == 0) {
 #define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true>(p, acc, m_base, n_base, wm, wn) \
                      : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false>(p, acc, m_base, n_base, wm, wn)
