@@ -1205,7 +1205,7 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
             const GemmPlan pl = plan_of(model, (long)out->m, (long)out->n, (long)out->k, (int)model->pool->streams[mask_id].n_cu);
             int bm, bn, bk;
             if (pl.kind == 1) { conv_wsk_tile(pl.variant, &bm, &bn); name = "conv_wsk_kernel"; out->threads = (uint32_t)pl.nw * 64; }
-            else { conv_gemm_tile(pl.variant, &bm, &bn, &bk); name = "conv_gemm_kernel"; }
+            else { conv_gemm_tile(pl.variant, &bm, &bn, &bk); name = conv_gemm_kernel_name(pl.variant); out->threads = (uint32_t)conv_gemm_threads(pl.variant); }
             out->tile_m = (uint32_t)bm; out->tile_n = (uint32_t)bn;
             out->k_splits = (uint32_t)pl.splits;
             out->workgroups = (uint32_t)pl.tiles * (uint32_t)pl.splits;
@@ -1222,10 +1222,13 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
             da.dtype = model->dtype == ECLIP_F32 ? DT_F32 : (model->dtype == ECLIP_BF16 ? DT_BF16 : DT_F16);
             const int dw_cu = (int)model->pool->streams[mask_id].n_cu;
             name = dwconv_strip_rows(da, dw_cu) ? "dwconv3_strip_kernel" : dwconv_pixels_per_thread(da, dw_cu) == 4 ? "dwconv3_row_kernel" : "dwconv_kernel";
-            out->workgroups = (uint32_t)((rows * (P.L.c / ((P.L.c % 8 || model->dtype == ECLIP_F32) ? (model->dtype == ECLIP_F32 && P.L.c % 4 == 0 ? 4 : 1) : 8)) + 255) / 256);
+            out->workgroups = dwconv_workgroups(da, dw_cu);
         } else {
+            const ConvF32Args fa{nullptr, nullptr, nullptr, nullptr, nullptr, g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, P.L.act};
+            const ConvF32Plan fp = conv_f32_plan(fa);
             name = "conv_f32_kernel";
-            out->workgroups = (uint32_t)((rows * P.L.c + 255) / 256);
+            out->workgroups = fp.workgroups;
+            out->threads = fp.threads;
         }
         break;
     }

@@ -122,6 +122,9 @@ void conv_gemm_tile(int variant, int *bm, int *bn, int *bk)
     *bk = kVariants[v].bk;
 }
 
+const char *conv_gemm_kernel_name(int variant) { return pp_tile(variant).loop == LOOP_DMA ? "conv_gemm_dma_kernel" : "conv_gemm_kernel"; }
+int conv_gemm_threads(int variant) { return pp_tile(variant).id < 0 || pp_tile(variant).loop == LOOP_DMA ? 256 : 512; }
+
 static long cdiv(long a, long b) { return (a + b - 1) / b; }
 
 // Large un-split problems are launched on the 8 x 4 block raster: the grid grows to whole blocks, 8 at a time.

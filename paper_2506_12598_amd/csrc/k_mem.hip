@@ -864,11 +864,17 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, long n)
 
 }  // namespace
 
+ConvF32Plan conv_f32_plan(const ConvF32Args &a)
+{
+    return ConvF32Plan{blocks_for((long)a.B * a.Ho * a.Wo * a.Cout, 64), a.KH * a.KW * a.Cin <= 32 ? 256u : 512u};
+}
+
 hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t s)
 {
     const long total = (long)a.B * a.Ho * a.Wo * a.Cout;
-    if (a.KH * a.KW * a.Cin <= 32) hipLaunchKernelGGL((conv_f32_kernel<4, 8>), dim3(blocks_for(total, 64)), dim3(256), 0, s, a, (unsigned)total);
-    else hipLaunchKernelGGL((conv_f32_kernel<8, 9>), dim3(blocks_for(total, 64)), dim3(512), 0, s, a, (unsigned)total);
+    const ConvF32Plan p = conv_f32_plan(a);
+    if (p.threads == 256) hipLaunchKernelGGL((conv_f32_kernel<4, 8>), dim3(p.workgroups), dim3(p.threads), 0, s, a, (unsigned)total);
+    else hipLaunchKernelGGL((conv_f32_kernel<8, 9>), dim3(p.workgroups), dim3(p.threads), 0, s, a, (unsigned)total);
     return hipGetLastError();
 }
 
@@ -893,34 +899,38 @@ int dwconv_strip_rows(const DwConvArgs &a, int n_cu)
     return 0;
 }
 
+unsigned dwconv_workgroups(const DwConvArgs &a, int n_cu)
+{
+    if (const int ph = dwconv_strip_rows(a, n_cu)) return banded_blocks_for((long)a.B * ((a.Ho + ph - 1) / ph) * ((a.Wo + 1) / 2) * (a.C / 8), 256);
+    if (dwconv_pixels_per_thread(a, n_cu) == 4) return banded_blocks_for((long)a.B * a.Ho * ((a.Wo + 3) / 4) * (a.C / 8), 256);
+    const int v = a.dtype == DT_F32 ? (a.C % 4 ? 1 : 4) : a.C % 8 ? 1 : 8;
+    return blocks_for((long)a.B * a.Ho * a.Wo * (a.C / v), 256);
+}
+
 hipError_t launch_dwconv(const DwConvArgs &a, int n_cu, hipStream_t s)
 {
+    const dim3 grid(dwconv_workgroups(a, n_cu));
     if (dwconv_pixels_per_thread(a, n_cu) == 4) {
         const unsigned wq = (unsigned)(a.Wo + 3) / 4;
         const int ph = dwconv_strip_rows(a, n_cu);
         if (ph) {                                            // tall stride-1 images: 2 x ph output pixels per thread
             const unsigned hq = (unsigned)(a.Ho + ph - 1) / ph, wq2 = (unsigned)(a.Wo + 1) / 2;
             const long strips = (long)a.B * hq * wq2 * (a.C / 8);
-            const dim3 grid(banded_blocks_for(strips, 256));
             if (a.dtype == DT_BF16) hipLaunchKernelGGL((dwconv3_strip_kernel<bf16_t, 3>), grid, dim3(256), 0, s, a, (unsigned)strips, wq2, hq, ph);
             else hipLaunchKernelGGL((dwconv3_strip_kernel<f16_t, 3>), grid, dim3(256), 0, s, a, (unsigned)strips, wq2, hq, ph);
             return hipGetLastError();
         }
         const long total = (long)a.B * a.Ho * wq * (a.C / 8);
-        {
-            const dim3 grid(banded_blocks_for(total, 256));
 #define ROW(T)                                                                                                          \
     if (a.stride == 1) hipLaunchKernelGGL((dwconv3_row_kernel<T, 4, 1>), grid, dim3(256), 0, s, a, (unsigned)total, wq); \
     else hipLaunchKernelGGL((dwconv3_row_kernel<T, 4, 2>), grid, dim3(256), 0, s, a, (unsigned)total, wq);
-            if (a.dtype == DT_BF16) { ROW(bf16_t) } else { ROW(f16_t) }
+        if (a.dtype == DT_BF16) { ROW(bf16_t) } else { ROW(f16_t) }
 #undef ROW
-            return hipGetLastError();
-        }
+        return hipGetLastError();
     }
 #define CALL(T, V)                                                                                              \
     {                                                                                                           \
         const long total = (long)a.B * a.Ho * a.Wo * (a.C / V);                                                 \
-        const dim3 grid(blocks_for(total, 256));                                                                \
         if (a.KH == 3 && a.KW == 3) hipLaunchKernelGGL((dwconv_kernel<T, V, 3>), grid, dim3(256), 0, s, a, total); \
         else hipLaunchKernelGGL((dwconv_kernel<T, V, 0>), grid, dim3(256), 0, s, a, total);                     \
     }

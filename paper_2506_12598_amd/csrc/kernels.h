@@ -50,6 +50,8 @@ enum { CONV_GEMM_VARIANTS = 29 };        // 0..2: 128x128x32, 64x64x64, 32x64x64
                                          // 64x128x64, 256x192x32, 192x256x32, 64x64x64; 27, 28: 128x64x32, 128x128x32 (small rings: three
                                          // or four workgroups per CU)
 void conv_gemm_tile(int variant, int *bm, int *bn, int *bk);
+const char *conv_gemm_kernel_name(int variant);
+int conv_gemm_threads(int variant);
 enum { CONV_WSK_VARIANTS = 6 };          // 16x64, 32x64, 64x64, 16x16, 16x32, 32x32
 void conv_wsk_tile(int variant, int *bm, int *bn);
 size_t conv_wsk_lds_bytes(int variant, int nw);
@@ -78,6 +80,8 @@ struct ConvF32Args {
     int B, H, W, Cin, Ho, Wo, Cout, KH, KW, stride, pad, act;
     bool nchw = false;   // x is [B][Cin][H][W]
 };
+struct ConvF32Plan { unsigned workgroups, threads; };
+ConvF32Plan conv_f32_plan(const ConvF32Args &a);
 hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t s);
 
 // ---- memory-bound kernels ---------------------------------------------------------------------
@@ -88,6 +92,7 @@ struct DwConvArgs {
 };
 int dwconv_pixels_per_thread(const DwConvArgs &a, int n_cu);   // 4 (large 3x3 layers, 16-bit types) or 1
 int dwconv_strip_rows(const DwConvArgs &a, int n_cu);          // rows per thread of the strip kernel, or 0
+unsigned dwconv_workgroups(const DwConvArgs &a, int n_cu);     // of 256 threads
 hipError_t launch_dwconv(const DwConvArgs &a, int n_cu, hipStream_t s);
 
 // grouped convolution, 1 < groups < C: one thread per output element, weights [Cout][KH][KW][Cin/groups]

@@ -334,7 +334,7 @@ def test_measured_plan_selection_keeps_the_results():
             for got in (before, after, other):
                 assert rel_to_range(got, exp) <= 2e-2
             info = g.h.kernel_info(len(m.layers) - 1, 2, batch)
-            assert info["kernel"] in ("conv_wsk_kernel", "conv_gemm_kernel", "gap_kernel", "row_kernel")
+            assert info["kernel"] in ("conv_wsk_kernel", "conv_gemm_kernel", "conv_gemm_dma_kernel", "gap_kernel", "row_kernel")
         finally:
             g.free()
 
