@@ -1225,7 +1225,7 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
             out->workgroups = dwconv_workgroups(da, dw_cu);
         } else {
             const ConvF32Args fa{nullptr, nullptr, nullptr, nullptr, nullptr, g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, P.L.act};
-            const ConvF32Plan fp = conv_f32_plan(fa);
+            const ConvF32Plan fp = conv_f32_plan(fa, (int)model->pool->streams[mask_id].n_cu);
             name = "conv_f32_kernel";
             out->workgroups = fp.workgroups;
             out->threads = fp.threads;
@@ -1321,7 +1321,7 @@ static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_
             if (d_out32 && chan_last_out) { yf = d_out32; y32 = d_out32; }
             ConvF32Args a{(const float *)src(L.in0), (const float *)wptr(m, P.w_dev), (const float *)wptr(m, P.b_dev), (const float *)src(L.in1), yf,
                           g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, L.act};
-            e = launch_conv_f32(a, s);
+            e = launch_conv_f32(a, n_cu, s);
         }
         break;
     }
@@ -1436,7 +1436,7 @@ static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, c
         a.nchw = true;
         *done = true;
         *n_launched += 1;
-        return launch_conv_f32(a, s);
+        return launch_conv_f32(a, cu.n_cu, s);
     }
     GemmPlan pl;
     if (!conv_gemm_plan_stem((long)g.B * g.Ho * g.Wo, g.Cout, (long)g.KH * g.KW * g.Cin, cu.n_cu, m->ws_floats, 4.0, &pl)) return hipSuccess;

@@ -32,53 +32,91 @@ inline unsigned banded_blocks_for(long n_threads, int block) { return (blocks_fo
     } while (0)
 
 // ---------------- float32 direct convolution --------------------------------------------------------
-// A lane owns one output element, the NW wavefronts of a workgroup share the sum of 64 of them: each takes a contiguous slice of
-// k = (kh, kw, ci), its loads U at a time and without a branch between them, and the partial sums meet in LDS in wavefront
-// order.  At batch 1 this is latency and nothing else: one thread per output and one load after the other took 18.4 us for
-// 16 x 16 x 32 outputs of a 3 x 3 window over 16 channels (5.8 us now).
-template <int NW, int U>
-__global__ __launch_bounds__(NW * 64) void conv_f32_kernel(ConvF32Args a, unsigned total)
+// v(0) + ... + v(N - 1) in pairs, N a power of two
+template <int N, typename F> __device__ __forceinline__ float tree_sum(F v)
 {
-    __shared__ float part[NW][64];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned idx = blockIdx.x * 64u + lane, ui = idx < total ? idx : total - 1u;
+    if constexpr (N == 1) return v(0);
+    else return tree_sum<N / 2>(v) + tree_sum<N / 2>([&](int i) { return v(i + N / 2); });
+}
+
+// A lane owns one output element; NW wavefronts share the sum of 64 of them, each a contiguous slice of k = (kh, kw, ci), and the
+// partial sums meet in LDS.  The window position is kept per tap and not per term, a lane whose tap lies outside the image sits
+// that tap out, and with V = 4 (channels-last x, Cin a multiple of 4, x 16-byte aligned) four channels are one 16-byte load.  Few
+// outputs are bound by latency (one wavefront per 64 outputs of 8192 x 144 terms on 256 CUs: 6.7 us, 8 wavefronts 3.6), many by the
+// instructions per term: with border test and position per term (loads in one unrolled run over all taps, the form before)
+// a 3 x 3 layer of 1.6 M outputs x 576 terms took 578 us against 200.  A wavefront keeps eight running sums (V = 1: four, and
+// no fewer than two wavefronts, four beyond 32 terms): no chain of additions is longer than in a sum shared by eight wavefronts,
+// and against 64 bits no shape measured (16 to 4608 terms) came out further off than in that form.
+template <int NW, int V>
+__global__ __launch_bounds__(NW < 4 ? 256 : NW * 64) void conv_f32_kernel(ConvF32Args a, unsigned total)
+{
+    constexpr int G = NW < 4 ? 4 / NW : 1, U = V == 4 ? 8 : 4;             // groups of 64 outputs per workgroup, terms at a time
+    __shared__ float part[NW == 1 ? 1 : G * NW][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slice = wave % NW;
+    const unsigned idx = (blockIdx.x * (unsigned)G + (unsigned)(wave / NW)) * 64u + lane, ui = idx < total ? idx : total - 1u;
     const int n = (int)(ui % (unsigned)a.Cout);
     const unsigned m = ui / (unsigned)a.Cout;
     const int ow = (int)(m % (unsigned)a.Wo);
     const unsigned mh = m / (unsigned)a.Wo;
     const int ih0 = (int)(mh % (unsigned)a.Ho) * a.stride - a.pad, iw0 = ow * a.stride - a.pad;
-    // element strides of x: channels-last, or the caller's [B][C][H][W]
-    const int xc = a.nchw ? a.H * a.W : 1, xw = a.nchw ? 1 : a.Cin, xh = xw * a.W;
+    const int xc = a.nchw ? a.H * a.W : 1, xw = a.nchw ? 1 : a.Cin, xh = xw * a.W;      // element strides of x
     const float *x = a.x + (long)(mh / (unsigned)a.Ho) * a.H * a.W * a.Cin;
-    const int K = a.KH * a.KW * a.Cin, per = (K + NW - 1) / NW, k0 = wave * per, k1 = min(K, k0 + per);
+    const int K = a.KH * a.KW * a.Cin, per = (K / V + NW - 1) / NW * V, k0 = min(K, slice * per), k1 = min(K, k0 + per);
     const int tap = k0 / a.Cin;
     int ci = k0 - tap * a.Cin, kh = tap / a.KW, kw = tap - kh * a.KW;
-    float acc = 0.0f;
-    for (int k = k0; k < k1; k += U) {
-        float xv[U], wv[U];
+    float acc[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int ih = ih0 + kh, iw = iw0 + kw;
-            const bool ok = k + u < k1 && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-            const float v = x[ok ? ih * xh + iw * xw + ci * xc : 0];
-            xv[u] = ok ? v : 0.0f;
-            wv[u] = a.w[(long)min(k + u, K - 1) * a.Cout + n];
-            if (++ci == a.Cin) {
-                ci = 0;
-                if (++kw == a.KW) { kw = 0; ++kh; }
+    for (int u = 0; u < U; ++u) acc[u] = 0.0f;
+    for (int k = k0; k < k1;) {
+        const int ih = ih0 + kh, iw = iw0 + kw, run = min(a.Cin - ci, k1 - k);
+        if ((unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W) {
+            const float *xp = x + (ih * xh + iw * xw + ci * xc), *wp = a.w + (long)k * a.Cout + n;
+            int c = 0;
+            for (; c + U <= run; c += U) {
+                float xv[U], wv[U];
+                if constexpr (V == 4) {
+#pragma unroll
+                    for (int u = 0; u < U; u += 4) {
+                        const float4 q = *reinterpret_cast<const float4 *>(xp + c + u);
+                        xv[u] = q.x; xv[u + 1] = q.y; xv[u + 2] = q.z; xv[u + 3] = q.w;
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) xv[u] = xp[(c + u) * xc];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) wv[u] = wp[(long)(c + u) * a.Cout];
+#pragma unroll
+                for (int u = 0; u < U; ++u) acc[u] = fmaf(xv[u], wv[u], acc[u]);
+            }
+            if (c < run) {                                                 // up to U - 1 terms: the loads beyond repeat the last one
+                float xv[U], wv[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int cc = min(c + u, run - 1);
+                    xv[u] = xp[cc * xc];
+                    wv[u] = wp[(long)cc * a.Cout];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (c + u < run) acc[u] = fmaf(xv[u], wv[u], acc[u]);
             }
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc = fmaf(xv[u], wv[u], acc);
+        k += run;
+        ci = 0;
+        if (++kw == a.KW) { kw = 0; ++kh; }
     }
-    part[wave][lane] = acc;
-    __syncthreads();
-    if (wave || idx >= total) return;
-    acc = a.bias ? a.bias[n] : 0.0f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) acc += part[w][lane];
-    if (a.res) acc += a.res[idx];
-    a.y[idx] = apply_act(a.act, acc);
+    float sum = tree_sum<U>([&](int u) { return acc[u]; });
+    if constexpr (NW > 1) {
+        part[wave][lane] = sum;
+        __syncthreads();
+        if (slice) return;
+        sum = tree_sum<NW>([&](int w) { return part[wave + w][lane]; });
+    }
+    if (idx >= total) return;
+    if (a.bias) sum += a.bias[n];
+    if (a.res) sum += a.res[idx];
+    a.y[idx] = apply_act(a.act, sum);
 }
 
 // ---------------- depthwise convolution --------------------------------------------------------------
@@ -864,17 +902,34 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, long n)
 
 }  // namespace
 
-ConvF32Plan conv_f32_plan(const ConvF32Args &a)
+// Wavefronts per sum: doubled while the GPU has fewer than 16 wavefronts per compute unit and a slice stays at 12 terms or more
+// (V = 1: 6), and beyond that while it stays at 128.  (Times of 1, 2, 4, 8, 16 wavefronts, us, on 256 CUs: 8192 outputs x 144 terms
+// 6.7, 4.6, 3.9, 3.6, 3.7; 262144 x 144: 11.2, 11.0, 12.1, 16.0, 23.1; 6.4 M x 64: 98, 104, 132, 221, 582; 25088 x 4608: 152,
+// 71, 45, 37, 36; 200704 x 4608: 260, 202, 194, 180, 177; 1000 x 512: 16.2, 9.4, 5.8, 4.7, 4.4.)
+ConvF32Plan conv_f32_plan(const ConvF32Args &a, int n_cu)
 {
-    return ConvF32Plan{blocks_for((long)a.B * a.Ho * a.Wo * a.Cout, 64), a.KH * a.KW * a.Cin <= 32 ? 256u : 512u};
+    const long groups = ((long)a.B * a.Ho * a.Wo * a.Cout + 63) / 64, K = (long)a.KH * a.KW * a.Cin;
+    const bool v4 = !a.nchw && a.Cin % 4 == 0 && ((uintptr_t)a.x & 15) == 0;
+    int nw = v4 ? 1 : K <= 32 ? 2 : 4;
+    while (nw < 16 && nw * groups < 16L * n_cu && K >= (v4 ? 24L : 12L) * nw) nw *= 2;
+    while (nw < 16 && K >= 256L * nw) nw *= 2;
+    const int per_wg = nw < 4 ? 4 / nw : 1;
+    return ConvF32Plan{(unsigned)((groups + per_wg - 1) / per_wg), (unsigned)(per_wg * nw * 64), nw, v4 ? 4 : 1};
 }
 
-hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t s)
+hipError_t launch_conv_f32(const ConvF32Args &a, int n_cu, hipStream_t s)
 {
-    const long total = (long)a.B * a.Ho * a.Wo * a.Cout;
-    const ConvF32Plan p = conv_f32_plan(a);
-    if (p.threads == 256) hipLaunchKernelGGL((conv_f32_kernel<4, 8>), dim3(p.workgroups), dim3(p.threads), 0, s, a, (unsigned)total);
-    else hipLaunchKernelGGL((conv_f32_kernel<8, 9>), dim3(p.workgroups), dim3(p.threads), 0, s, a, (unsigned)total);
+    const unsigned total = (unsigned)((long)a.B * a.Ho * a.Wo * a.Cout);
+    const ConvF32Plan p = conv_f32_plan(a, n_cu);
+#define CALL(NW, V) hipLaunchKernelGGL((conv_f32_kernel<NW, V>), dim3(p.workgroups), dim3(p.threads), 0, s, a, total)
+    switch (p.nw) {
+    case 1: CALL(1, 4); break;
+    case 2: if (p.vec == 4) CALL(2, 4); else CALL(2, 1); break;
+    case 4: if (p.vec == 4) CALL(4, 4); else CALL(4, 1); break;
+    case 8: if (p.vec == 4) CALL(8, 4); else CALL(8, 1); break;
+    default: if (p.vec == 4) CALL(16, 4); else CALL(16, 1);
+    }
+#undef CALL
     return hipGetLastError();
 }
 

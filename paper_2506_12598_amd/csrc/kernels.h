@@ -80,9 +80,12 @@ struct ConvF32Args {
     int B, H, W, Cin, Ho, Wo, Cout, KH, KW, stride, pad, act;
     bool nchw = false;   // x is [B][Cin][H][W]
 };
-struct ConvF32Plan { unsigned workgroups, threads; };
-ConvF32Plan conv_f32_plan(const ConvF32Args &a);
-hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t s);
+struct ConvF32Plan {
+    unsigned workgroups, threads;
+    int nw, vec;         // wavefronts per sum, channels per load of x
+};
+ConvF32Plan conv_f32_plan(const ConvF32Args &a, int n_cu);
+hipError_t launch_conv_f32(const ConvF32Args &a, int n_cu, hipStream_t s);
 
 // ---- memory-bound kernels ---------------------------------------------------------------------
 struct DwConvArgs {
