@@ -754,7 +754,7 @@ static eclip_status plan_model(const eclip_model_desc *d, size_t weight_elems, e
                          S.L.in0 == -1 && S.L.in1 != -1 && only_reader && d->n_layers > 1;
     }
     // Pool + classifier candidates: a GAP layer read only by the linear layer right after it, same group,
-    // the linear layer taking no second operand.  Whether the fused kernel pays depends on the batch (decided per request).
+    // the linear layer taking no second operand.  Whether the fused kernel pays depends on batch and compute units (decided per request).
     for (uint32_t i = 0; i + 1 < d->n_layers; ++i) {
         LayerPlan &A = m->layers[i];
         const LayerPlan &B = m->layers[i + 1];
@@ -1409,17 +1409,17 @@ static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t
 }
 
 // Launches the GAP layer i and the linear layer i + 1 (gapfc_next) as one kernel when the shape suits it.
-static hipError_t launch_gapfc_pair(eclip_model *m, uint32_t i, int batch, hipStream_t s, const void *d_in, float *d_out32, uint32_t *n_launched, bool *done)
+static hipError_t launch_gapfc_pair(eclip_model *m, uint32_t i, int batch, hipStream_t s, int n_cu, const void *d_in, float *d_out32, uint32_t *n_launched, bool *done)
 {
     *done = false;
     const LayerPlan &G = m->layers[i], &F = m->layers[i + 1];
     const int HW = G.in.h * G.in.w, C = G.L.c;
-    if (getenv("ECLIP_NO_PAIRS") || !gapfc_supported(batch, HW, C, m->dtype)) return hipSuccess;
+    if (getenv("ECLIP_NO_PAIRS") || !gapfc_supported(batch, HW, C, F.L.c, m->dtype, n_cu)) return hipSuccess;
     const void *x = G.L.in0 == -1 ? (m->in_kind == ECLIP_IN_IMAGE ? (const void *)m->d_in_stage : d_in) : (const void *)out_ptr(m, m->layers[G.L.in0]);
     *done = true;
     *n_launched += 1;
     return launch_gapfc(x, wptr(m, F.w_dev), wptr(m, F.b_dev), d_out32 ? nullptr : (void *)out_ptr(m, F), d_out32, batch, HW, C, F.L.c, F.L.act,
-                        m->dtype, s);
+                        m->dtype, n_cu, s);
 }
 
 // First layer straight from the caller's NCHW tensor (stem_direct), when a plan of that form is within the cost of the
@@ -1479,7 +1479,7 @@ static hipError_t launch_unit(eclip_model *m, uint32_t i, int batch, hipStream_t
     }
     if (m->layers[i].gapfc_next) {
         bool fused = false;
-        if ((e = launch_gapfc_pair(m, i, batch, s, d_in, i + 2 == n_layers ? d_out : nullptr, n_launched, &fused)) != hipSuccess) return e;
+        if ((e = launch_gapfc_pair(m, i, batch, s, cu.n_cu, d_in, i + 2 == n_layers ? d_out : nullptr, n_launched, &fused)) != hipSuccess) return e;
         if (fused) { *consumed = 2; return hipSuccess; }
     }
     return launch_layer(m, i, batch, s, cu, d_in, i + 1 == n_layers ? d_out : nullptr, n_launched);

@@ -1102,7 +1102,7 @@ hipError_t launch_gap(const void *x, void *y, float *y32, float *ws, size_t ws_f
 // 8 (l >> 4) .. +7), so that every weight load of a wavefront is one contiguous kilobyte.  Both halves are one or two memory
 // round trips deep (with 4 wavefronts and a block of outputs each they were twelve and ten: 1280 channels x 49 pixels ->
 // 1000 outputs at batch 3 took 12.8 us, 9.2 now).  Every workgroup pools for itself, which is what limits the form to
-// moderate C x HW (the caller decides).
+// moderate C x HW (gapfc_supported decides).
 constexpr int GAPFC_NW = 16;
 template <typename T>
 __global__ __launch_bounds__(GAPFC_NW * 64) void gapfc_kernel(const T *x, const uint4 *wb, const T *bias, T *y, float *y32, int HW, int C, int N,
@@ -1189,13 +1189,17 @@ __global__ __launch_bounds__(GAPFC_NW * 64) void gapfc_kernel(const T *x, const 
     }
 }
 
-// The same for float32 models (weights [C][N]): one workgroup per batch item pools, then S slices of the channels for every output.
-__global__ __launch_bounds__(256) void gapfc_f32_kernel(const float *x, const float *w, const float *bias, float *y, int HW, int C, int N, int act)
+// The same for float32 models (weights [C][N]): a workgroup pools for itself and computes 32 outputs, each from NT / 32 slices of the
+// channels, so that neither half is more than a few memory round trips deep whatever N is (512 x 49 -> 1000 at batch 1 5.2 us; one
+// workgroup per batch item for all outputs took 52).
+template <int NT, int U>
+__global__ __launch_bounds__(NT) void gapfc_f32_kernel(const float *x, const float *w, const float *bias, float *y, int HW, int C, int N, int act)
 {
+    constexpr int COLS = 32, S = NT / COLS;
     __shared__ float pooled[1024];
-    __shared__ __attribute__((aligned(16))) float part[1024];
-    const int tid = threadIdx.x, b = blockIdx.x;
-    const int cv = C >> 2, parts = 256 / cv;                           // C % 4 == 0 and C <= 1024 (checked by the caller)
+    __shared__ __attribute__((aligned(16))) float part[NT * 4];
+    const int tid = threadIdx.x, b = blockIdx.y;
+    const int cv = C >> 2, parts = NT / cv;                            // C % 4 == 0 and C <= 4 NT (checked by the caller)
     if (tid < parts * cv) {
         const int chunk = tid % cv, pt = tid / cv;
         const float4 *src = reinterpret_cast<const float4 *>(x + (long)b * HW * C) + chunk;
@@ -1212,44 +1216,55 @@ __global__ __launch_bounds__(256) void gapfc_f32_kernel(const float *x, const fl
     }
     __syncthreads();
     const float inv = 1.0f / (float)HW;
-    for (int c = tid; c < C; c += 256) {
+    for (int c = tid; c < C; c += NT) {
         float sum = 0.0f;
         for (int pt = 0; pt < parts; ++pt) sum += part[pt * C + c];
         pooled[c] = sum * inv;
     }
-    const int cols = N >= 256 ? 256 : (N + 31) / 32 * 32, S = 256 / cols, sl = tid / cols, per = (C + S - 1) / S;
-    for (int n0 = 0; n0 < N; n0 += cols) {
-        const int n = n0 + tid - sl * cols;
-        __syncthreads();                                               // pooled is ready; part is free
-        float acc = 0.0f;
-        if (sl < S && n < N) {
-            const int c1 = min(C, (sl + 1) * per);
-#pragma unroll 8
-            for (int c = sl * per; c < c1; ++c) acc = fmaf(w[(long)c * N + n], pooled[c], acc);
-        }
-        part[tid] = acc;
-        __syncthreads();
-        if (tid < cols && n < N) {
-            float v = bias ? bias[n] : 0.0f;
-            for (int i = 0; i < S; ++i) v += part[i * cols + tid];
-            y[(long)b * N + n] = apply_act(act, v);
-        }
+    __syncthreads();                                                   // pooled is ready; part is free
+    const int sl = tid / COLS, n = blockIdx.x * COLS + tid % COLS, per = (C + S - 1) / S, c0 = min(C, sl * per), c1 = min(C, c0 + per);
+    const float *wn = w + (n < N ? n : 0);
+    float acc = 0.0f;
+    for (int c = c0; c < c1; c += U) {
+        float q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) q[u] = wn[(long)min(c + u, c1 - 1) * N];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c + u < c1) acc = fmaf(q[u], pooled[c + u], acc);
+    }
+    part[tid] = acc;
+    __syncthreads();
+    if (tid < COLS && n < N) {
+        float v = tree_sum<S>([&](int i) { return part[i * COLS + tid]; });
+        if (bias) v += bias[n];
+        y[(long)b * N + n] = apply_act(act, v);
     }
 }
 
-bool gapfc_supported(int B, int HW, int C, int dtype)
+// Whether pool + classifier in one launch are faster than one launch each.  Every workgroup pools its whole batch item for itself,
+// so the form lives on all of them running at once: 16 bit, 2048 channels x 49 pixels -> 1000 outputs, 63 workgroups per item
+// (input re-layout included): batch 4 on 256 CUs 11.9 us against 13.6 apart, batch 8 19.4 against 13.8, batch 8 on 32 CUs 88
+// against 22.  A second round still pays where pooling is light (1280 x 49, batch 6 on 256 CUs 14.1 against 13.7, 512 x 49
+// 11.9 against 13.4; on 16 CUs, five rounds at batch 1, 16.2 against 11.8).  float32, 512 x 49 -> 1000, 32 workgroups per item: batch
+// 8 on 256 CUs 6.0 us against 7.6, batch 16 10.0 against 7.9; its small workgroups (up to 128 channels) fit a CU several at a
+// time (64 x 1024 -> 100, batch 32 on 32 CUs 12.0 against 12.6).
+bool gapfc_supported(int B, int HW, int C, int N, int dtype, int n_cu)
 {
-    // the pooled tensor is re-read by every workgroup and the weights by every batch item: small cases only
-    if (dtype == DT_F32) return C % 4 == 0 && C <= 1024 && (long)HW * C <= 64 * 1024;
-    return B <= 8 && C % 8 == 0 && C >= 8 && C <= 2048 && (long)HW * C <= 128 * 1024;
+    const long px = (long)HW * C;
+    if (dtype == DT_F32) return C % 4 == 0 && C <= 1024 && px <= 64 * 1024 && (long)B * ((N + 31) / 32) <= (C <= 128 ? 4L : 1L) * n_cu;
+    return B <= 8 && C % 8 == 0 && C >= 8 && C <= 2048 && px <= 128 * 1024 && (long)B * ((N + 15) / 16) <= (px <= 64 * 1024 ? 2L : 1L) * n_cu;
 }
 
 hipError_t launch_gapfc(const void *x, const void *w, const void *bias, void *y, float *y32, int B, int HW, int C, int N, int act,
-                        int dtype, hipStream_t s)
+                        int dtype, int n_cu, hipStream_t s)
 {
-    if (!gapfc_supported(B, HW, C, dtype)) return hipErrorInvalidValue;
+    if (!gapfc_supported(B, HW, C, N, dtype, n_cu)) return hipErrorInvalidValue;
     if (dtype == DT_F32) {
-        hipLaunchKernelGGL(gapfc_f32_kernel, dim3((unsigned)B), dim3(256), 0, s, (const float *)x, (const float *)w, (const float *)bias, y32 ? y32 : (float *)y, HW, C, N, act);
+        float *yf = y32 ? y32 : (float *)y;
+        const dim3 grid((unsigned)(N + 31) / 32, (unsigned)B);
+        if (C <= 128) hipLaunchKernelGGL((gapfc_f32_kernel<256, 8>), grid, dim3(256), 0, s, (const float *)x, (const float *)w, (const float *)bias, yf, HW, C, N, act);
+        else hipLaunchKernelGGL((gapfc_f32_kernel<1024, 16>), grid, dim3(1024), 0, s, (const float *)x, (const float *)w, (const float *)bias, yf, HW, C, N, act);
         return hipGetLastError();
     }
     const int KB = (C + 31) / 32, NB = (N + 15) / 16, parts = GAPFC_NW * 64 / (C / 8);

@@ -129,11 +129,11 @@ int gap_parts(int B, int HW, int C, int n_cu);
 hipError_t launch_gap(const void *x, void *y, float *y32, float *ws, size_t ws_floats, int B, int HW, int C, int dtype, int n_cu,
                       hipStream_t s, uint32_t *n_launched);
 
-// global average pool and the linear layer that follows it in one launch (small batch, moderate C x HW):
+// global average pool and the linear layer that follows it in one launch (see gapfc_supported):
 // x [B][HW][C], w in the blocked GEMM layout of an N x C matrix (float32: [C][N]), y [B][N] (model dtype) or y32 (float)
-bool gapfc_supported(int B, int HW, int C, int dtype);
+bool gapfc_supported(int B, int HW, int C, int N, int dtype, int n_cu);
 hipError_t launch_gapfc(const void *x, const void *w, const void *bias, void *y, float *y32, int B, int HW, int C, int N, int act,
-                        int dtype, hipStream_t s);
+                        int dtype, int n_cu, hipStream_t s);
 
 struct RowArgs {
     const void *x, *res, *gamma, *beta;
