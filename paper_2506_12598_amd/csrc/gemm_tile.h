@@ -665,12 +665,12 @@ constexpr size_t dma_lds_bytes(int bm, int bn, int bk, int stages)
     return ring > stage ? ring : stage;
 }
 
-// Which addressing form a launch may take (see conv_gemm_kernel)
-inline int gemm_amode(const GemmDev &d, int bk)
+// Which addressing form a launch may take (see conv_gemm_kernel); conv_gemm_dma_kernel keeps one bit per window tap and row
+inline int gemm_amode(const GemmDev &d, int bk, int loop)
 {
     if (d.nchw_c) return A_GENERAL;
     if (d.KH * d.KW == 1 && d.pad == 0 && d.K % bk == 0) return A_MATRIX;
-    if (d.Cin % bk == 0 && d.KH * d.KW <= 32) return A_UNIFORM;      // (conv_gemm_dma_kernel keeps one bit per tap)
+    if (d.Cin % bk == 0 && (loop != LOOP_DMA || d.KH * d.KW <= 32)) return A_UNIFORM;
     return A_GENERAL;
 }
 

@@ -29,7 +29,7 @@ hipError_t launch_one(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream
 template <typename T>
 hipError_t launch_mode(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream_t s)
 {
-    switch (gemm_amode(d, kTile.bk)) {
+    switch (gemm_amode(d, kTile.bk, kTile.loop)) {
     case A_MATRIX: return launch_one<T, A_MATRIX>(d, deal, grid, s);
     case A_UNIFORM: return launch_one<T, A_UNIFORM>(d, deal, grid, s);
     default: return launch_one<T, A_GENERAL>(d, deal, grid, s);

@@ -1,0 +1,54 @@
+"""Rules that choose a launch on the host, called directly: a small program around the library's own headers, built once."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include "gemm_tile.h"
+using namespace eclip;
+int main()
+{
+    char what;
+    int v[8];
+    while (std::scanf(" %c", &what) == 1) {
+        if (what == 'a') {                                   // addressing form: KH KW Cin K-step loop
+            std::scanf("%d %d %d %d %d", v, v + 1, v + 2, v + 3, v + 4);
+            GemmDev d{};
+            d.KH = v[0]; d.KW = v[1]; d.Cin = v[2]; d.K = v[0] * v[1] * v[2];
+            std::printf("%d\n", gemm_amode(d, v[3], v[4]));
+        }
+    }
+}
+"""
+GENERAL, UNIFORM, MATRIX = range(3)
+PINGPONG, BDIRECT, DMA = 2, 3, 4
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, exe = d / "rules.hip", d / "rules"
+    src.write_text(PROGRAM)
+    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2506_12598_amd", "csrc"),
+                    "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe)], check=True, capture_output=True)
+
+    def ask(line):
+        return subprocess.run([str(exe)], input=line, capture_output=True, text=True, check=True).stdout.split()
+    return ask
+
+
+@pytest.mark.parametrize("loop", [PINGPONG, BDIRECT, DMA])
+@pytest.mark.parametrize("kh,kw,cin,bk,form", [
+    (1, 1, 128, 64, MATRIX), (1, 1, 96, 64, GENERAL), (3, 3, 64, 64, UNIFORM), (3, 3, 96, 64, GENERAL), (3, 3, 96, 32, UNIFORM),
+    (4, 8, 64, 64, UNIFORM),                                  # 32 taps: the last window whose taps fit a word of bits
+    (3, 11, 64, 64, None), (7, 7, 512, 32, None),             # more: a limit of the kernel that keeps those bits, and of no other
+])
+def test_addressing_form(rules, kh, kw, cin, bk, loop, form):
+    want = (GENERAL if loop == DMA else UNIFORM) if form is None else form
+    assert rules(f"a {kh} {kw} {cin} {bk} {loop}\n") == [str(want)]
