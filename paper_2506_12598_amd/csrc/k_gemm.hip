@@ -208,7 +208,10 @@ static double wsk_cost(long M, long N, long K, int n_cu, int v, int nw)
 }
 
 // wsk_cost on the scale of the LDS tiles' costs: what every wave-split-K launch pays before and after its loop, and what
-// each further round of workgroups on a compute unit pays again (same fit as the LDS tiles' table)
+// each further round of workgroups on a compute unit pays again (same fit as the LDS tiles' table).  The fit priced the shape that
+// wsk_cost picks, and only there does it hold: it decides between that shape and the LDS tiles, not among the wave-split-K
+// shapes.  Picking those by it too makes 64 x 64 tiles win wherever they save a round: 160 kinds of request (12 networks, batch 1 to
+// 8, 64 to 256 compute units) took 5.7 % longer, VGG-16 at batch 8 on 160 CUs 1141 us instead of 755.
 static double wsk_whole_cost(long M, long N, long K, int n_cu, int v, int nw)
 {
     int bm, bn;
@@ -303,10 +306,9 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // 1536 rows, 70 convolutions of ResNet, VGG and MobileNet shapes at batch 1, 3 and 8, each on 64, 96, 160 and 256 compute units), every
     // plan timed in a chain of four to eight layers with weights of their own, so that no layer finds its weights in an L2.
     // The picks cost 3.9 % more than the best plan on average; eclip_model_tune closes that gap by
-    // measurement.  The shapes of ids 6, 7, 9 to 12 and 14 have a cheaper twin among the others and are left to it.
-    // `behind`: in a network a layer's input was just written by the layer before it, all over the chip, where those chains read one
-    // input again and again; four wavefronts per workgroup wait for it longer than the many of the wave-split-K kernel.
-    const double behind = 1.2;
+    // measurement.  (A further 1.2 us on every tile, for inputs that the layer before has just written, made the same 160 kinds of
+    // request 1.1 % slower, none faster by more than 1.5 % and ResNeXt at batch 8 on 160 CUs 651 us instead of 589; 2.4 us another 1.5 %.)
+    // The shapes of ids 6, 7, 9 to 12 and 14 have a cheaper twin among the others and are left to it.
     struct LdsTile { int variant; double step, fixed, more, two; };
     static const LdsTile lds[] = {
                                   {0, 0.509, 4.049, 7.322, 1.373}, {3, 0.568, 8.784, 16.049, 0}, {5, 0.595, 8.271, 16.021, 0}, {8, 0.525, 5.267, 9.068, 0},
@@ -324,7 +326,7 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
             const double load = wgs >= n_cu ? 1.0 : (double)wgs / n_cu;
             double rounds = (double)cdiv(wgs, n_cu);
             if (c.two > 0.0 && rounds >= 2.0) rounds = c.two * ((double)wgs / n_cu > 2.0 ? (double)wgs / (2.0 * n_cu) : 1.0);
-            double cost = behind + c.fixed + (rounds - 1.0) * c.more + rounds * (double)cdiv(KT, sp) * c.step * (1.0 + 0.15 * load * load);
+            double cost = c.fixed + (rounds - 1.0) * c.more + rounds * (double)cdiv(KT, sp) * c.step * (1.0 + 0.15 * load * load);
             if (sp > 1) cost += 15.48 + (double)M * N * (4.0 * sp + 2.0) / 4.243e6;
             if (cost < best) {
                 best = cost;

@@ -1,4 +1,4 @@
-"""Rules that choose a launch on the host, called directly: a small program around the library's own headers, built once."""
+"""Rules that choose a launch on the host, called directly: a small program around the library and its headers, built once."""
 import os
 import shutil
 import subprocess
@@ -22,6 +22,10 @@ int main()
             GemmDev d{};
             d.KH = v[0]; d.KW = v[1]; d.Cin = v[2]; d.K = v[0] * v[1] * v[2];
             std::printf("%d\n", gemm_amode(d, v[3], v[4]));
+        } else if (what == 'p') {                            // plan of a problem: M N K compute-units
+            std::scanf("%d %d %d %d", v, v + 1, v + 2, v + 3);
+            const GemmPlan p = conv_gemm_plan(v[0], v[1], v[2], v[3], (size_t)16 << 20);
+            std::printf("%d %d %d %.6f\n", p.kind, p.variant, p.splits, p.cost);
         }
     }
 }
@@ -33,13 +37,15 @@ PINGPONG, BDIRECT, DMA = 2, 3, 4
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("rules")
-    src, exe = d / "rules.hip", d / "rules"
-    src.write_text(PROGRAM)
-    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2506_12598_amd", "csrc"),
-                    "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe)], check=True, capture_output=True)
+    src, obj, exe = str(d / "rules.hip"), str(d / "rules.o"), str(d / "rules")
+    open(src, "w").write(PROGRAM)
+    pkg = os.path.join(ROOT, "paper_2506_12598_amd")
+    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-c", "-I", os.path.join(pkg, "csrc"),
+                    "-I", os.path.join(ROOT, "include"), src, "-o", obj], check=True, capture_output=True)
+    subprocess.run(["hipcc", obj, "-o", exe, os.path.join(pkg, "libeclip.so"), "-Wl,-rpath," + pkg], check=True, capture_output=True)
 
     def ask(line):
-        return subprocess.run([str(exe)], input=line, capture_output=True, text=True, check=True).stdout.split()
+        return subprocess.run([exe], input=line, capture_output=True, text=True, check=True).stdout.split()
     return ask
 
 
@@ -52,3 +58,14 @@ def rules(tmp_path_factory):
 def test_addressing_form(rules, kh, kw, cin, bk, loop, form):
     want = (GENERAL if loop == DMA else UNIFORM) if form is None else form
     assert rules(f"a {kh} {kw} {cin} {bk} {loop}\n") == [str(want)]
+
+
+@pytest.mark.parametrize("m,n,k,n_cu,variant,cost", [
+    (1536, 4096, 1024, 96, 3, 8.784 + 32 * 0.568 * 1.15),                               # 96 tiles of 256 x 256, one per CU
+    (1536, 1024, 4096, 96, 20, 4.272 + 64 * 0.337 * 1.15),                              # 96 tiles of 128 x 128
+])
+def test_a_tile_is_priced_as_its_row_of_the_table_says(rules, m, n, k, n_cu, variant, cost):
+    # fixed cost + K steps x cost per step, slower by 15 % on a full GPU, and nothing on top that the fit does not contain
+    got = rules(f"p {m} {n} {k} {n_cu}\n")
+    assert got[:3] == ["0", str(variant), "1"]
+    assert float(got[3]) == pytest.approx(cost, abs=1e-4)
