@@ -26,6 +26,13 @@ int main()
             std::scanf("%d %d %d %d", v, v + 1, v + 2, v + 3);
             const GemmPlan p = conv_gemm_plan(v[0], v[1], v[2], v[3], (size_t)16 << 20);
             std::printf("%d %d %d %.6f\n", p.kind, p.variant, p.splits, p.cost);
+        } else if (what == 's') {                            // shape of a first layer that reads the caller's planes: M N K compute-units
+            std::scanf("%d %d %d %d", v, v + 1, v + 2, v + 3);
+            GemmPlan p{};
+            std::printf("%d\n", conv_gemm_plan_stem(v[0], v[1], v[2], v[3], 0, 1e9, &p) ? p.variant : -1);
+        } else if (what == 'w') {                            // cost of a wave-split-K shape with 4 wavefronts: M N K compute-units shape
+            std::scanf("%d %d %d %d %d", v, v + 1, v + 2, v + 3, v + 4);
+            std::printf("%.6f\n", conv_wsk_cost_estimate(v[0], v[1], v[2], v[3], v[4], 4));
         }
     }
 }
@@ -69,3 +76,12 @@ def test_a_tile_is_priced_as_its_row_of_the_table_says(rules, m, n, k, n_cu, var
     got = rules(f"p {m} {n} {k} {n_cu}\n")
     assert got[:3] == ["0", str(variant), "1"]
     assert float(got[3]) == pytest.approx(cost, abs=1e-4)
+
+
+@pytest.mark.parametrize("n_cu", [64, 96, 128, 160, 192, 256])
+@pytest.mark.parametrize("m,n,k", [(12544, 64, 392), (3 * 12544, 32, 72), (25088, 64, 392), (50176, 64, 72), (12 * 6400, 64, 392)])
+def test_first_layer_takes_the_shape_whose_loop_is_cheapest(rules, m, n, k, n_cu):
+    # wave-split-K shapes are compared by the cost of their loops; the price against other kernels only decides whether one is taken
+    shapes = [0, 1, 5]
+    cost = [float(c) for c in rules("".join(f"w {m} {n} {k} {n_cu} {v}\n" for v in shapes))]
+    assert rules(f"s {m} {n} {k} {n_cu}\n") == [str(shapes[cost.index(min(cost))])]
