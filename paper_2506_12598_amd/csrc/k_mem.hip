@@ -1097,23 +1097,24 @@ hipError_t launch_gap(const void *x, void *y, float *y32, float *ws, size_t ws_f
 // y[b][n] = act(bias[n] + sum_c mean_hw(x[b][hw][c]) * w[n][c]) for a small batch.  Every kernel costs a few
 // microseconds whatever it does, and after the pooling a classifier at batch 1 is a matrix-vector product: one launch
 // saves one of the two.  A workgroup of 16 wavefronts first pools all C channels into LDS (float; each thread sums a share of
-// the pixels of one 16-byte channel chunk), then computes one block of 16 outputs, every wavefront a slice of the channels,
+// the pixels of one 16-byte channel chunk), then computes blocks of 16 outputs, every wavefront a slice of the channels,
 // from the weights in their blocked layout (1 KB blocks of 16 outputs x 32 channels, lane l = output l & 15, channels
 // 8 (l >> 4) .. +7), so that every weight load of a wavefront is one contiguous kilobyte.  Both halves are one or two memory
 // round trips deep (with 4 wavefronts and a block of outputs each they were twelve and ten: 1280 channels x 49 pixels ->
 // 1000 outputs at batch 3 took 12.8 us, 9.2 now).  Every workgroup pools for itself, which is what limits the form to
-// moderate C x HW (gapfc_supported decides).
+// moderate C x HW (gapfc_supported decides) and why there are no more workgroups than run at once: each takes as many blocks as
+// that leaves it, the weights of the next one on their way while one is summed.
 constexpr int GAPFC_NW = 16;
-template <typename T>
+template <typename T, bool ONE>
 __global__ __launch_bounds__(GAPFC_NW * 64) void gapfc_kernel(const T *x, const uint4 *wb, const T *bias, T *y, float *y32, int HW, int C, int N,
                                                               int KB, int act)
 {
     constexpr int NT = GAPFC_NW * 64;
     extern __shared__ __attribute__((aligned(16))) float gsm[];       // pooled[KB * 32], then part[parts][C]
     float *pooled = gsm, *part = gsm + KB * 32;
-    __shared__ float sums[GAPFC_NW][16];
+    __shared__ float sums[2][GAPFC_NW][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = blockIdx.y, nb = blockIdx.x;
+    const int b = blockIdx.y, NB = (N + 15) / 16;
     const int cv = C >> 3, parts = NT / cv;                            // C % 8 == 0 and C <= 2048 (checked by the caller)
     if (tid < parts * cv) {
         const int chunk = tid % cv, pt = tid / cv;
@@ -1147,10 +1148,13 @@ __global__ __launch_bounds__(GAPFC_NW * 64) void gapfc_kernel(const T *x, const 
     // this wavefront's weight blocks, requested before the pooling is waited for
     constexpr int U = 4;                                               // KB <= 64
     const int per = (KB + GAPFC_NW - 1) / GAPFC_NW, kb0 = wave * per, kb1 = min(KB, kb0 + per);
-    const uint4 *wrow = wb + (long)nb * KB * 64 + lane;
     uint4 q[U];
+    auto load = [&](int nb) {
+        const uint4 *wrow = wb + (long)nb * KB * 64 + lane;
 #pragma unroll
-    for (int u = 0; u < U; ++u) q[u] = wrow[(kb0 + u < kb1 ? kb0 + u : 0) * 64];
+        for (int u = 0; u < U; ++u) q[u] = wrow[(kb0 + u < kb1 ? kb0 + u : 0) * 64];
+    };
+    load(blockIdx.x);
     __syncthreads();
     const float inv = 1.0f / (float)HW;
     for (int c = tid; c < KB * 32; c += NT) {
@@ -1161,31 +1165,35 @@ __global__ __launch_bounds__(GAPFC_NW * 64) void gapfc_kernel(const T *x, const 
     }
     __syncthreads();
     const float *pv = pooled + (lane >> 4) * 8;
-    float acc = 0.0f;
+    for (int nb = blockIdx.x, half = 0; nb < NB; nb += gridDim.x, half ^= 1) {
+        float acc = 0.0f;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if (kb0 + u >= kb1) break;
-        const uint32_t ws4[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
-        const float4 p0 = *reinterpret_cast<const float4 *>(pv + (kb0 + u) * 32), p1 = *reinterpret_cast<const float4 *>(pv + (kb0 + u) * 32 + 4);
-        const float pe[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+        for (int u = 0; u < U; ++u) {
+            if (kb0 + u >= kb1) break;
+            const uint32_t ws4[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+            const float4 p0 = *reinterpret_cast<const float4 *>(pv + (kb0 + u) * 32), p1 = *reinterpret_cast<const float4 *>(pv + (kb0 + u) * 32 + 4);
+            const float pe[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc = fmaf(Cvt<T>::from_bits(ws4[e] & 0xffffu), pe[2 * e], acc);
-            acc = fmaf(Cvt<T>::from_bits(ws4[e] >> 16), pe[2 * e + 1], acc);
+            for (int e = 0; e < 4; ++e) {
+                acc = fmaf(Cvt<T>::from_bits(ws4[e] & 0xffffu), pe[2 * e], acc);
+                acc = fmaf(Cvt<T>::from_bits(ws4[e] >> 16), pe[2 * e + 1], acc);
+            }
         }
-    }
-    acc += __shfl_xor(acc, 16, 64);
-    acc += __shfl_xor(acc, 32, 64);
-    if (lane < 16) sums[wave][lane] = acc;
-    __syncthreads();
-    const int n = nb * 16 + tid;
-    if (tid < 16 && n < N) {
-        float v = bias ? Cvt<T>::load(bias + n) : 0.0f;
+        if (!ONE && nb + (int)gridDim.x < NB) load(nb + gridDim.x);
+        acc += __shfl_xor(acc, 16, 64);
+        acc += __shfl_xor(acc, 32, 64);
+        if (lane < 16) sums[half][wave][lane] = acc;                   // the other half may still be read: one barrier per block
+        __syncthreads();
+        const int n = nb * 16 + tid;
+        if (tid < 16 && n < N) {
+            float v = bias ? Cvt<T>::load(bias + n) : 0.0f;
 #pragma unroll
-        for (int w = 0; w < GAPFC_NW; ++w) v += sums[w][tid];
-        v = apply_act(act, v);
-        if (y32) y32[(long)b * N + n] = v;
-        else Cvt<T>::store(y + (long)b * N + n, v);
+            for (int w = 0; w < GAPFC_NW; ++w) v += sums[half][w][tid];
+            v = apply_act(act, v);
+            if (y32) y32[(long)b * N + n] = v;
+            else Cvt<T>::store(y + (long)b * N + n, v);
+        }
+        if (ONE) break;
     }
 }
 
@@ -1242,18 +1250,18 @@ __global__ __launch_bounds__(NT) void gapfc_f32_kernel(const float *x, const flo
     }
 }
 
-// Whether pool + classifier in one launch are faster than one launch each.  Every workgroup pools its whole batch item for itself,
-// so the form lives on all of them running at once: 16 bit, 2048 channels x 49 pixels -> 1000 outputs, 63 workgroups per item
-// (input re-layout included): batch 4 on 256 CUs 11.9 us against 13.6 apart, batch 8 19.4 against 13.8, batch 8 on 32 CUs 88
-// against 22.  A second round still pays where pooling is light (1280 x 49, batch 6 on 256 CUs 14.1 against 13.7, 512 x 49
-// 11.9 against 13.4; on 16 CUs, five rounds at batch 1, 16.2 against 11.8).  float32, 512 x 49 -> 1000, 32 workgroups per item: batch
-// 8 on 256 CUs 6.0 us against 7.6, batch 16 10.0 against 7.9; its small workgroups (up to 128 channels) fit a CU several at a
+// Whether pool + classifier go out in one launch.  16 bit: the pooled vector stays float32 in LDS, where two launches would round it,
+// so the rule is about shapes only and the grid adapts: one workgroup per compute unit at most, each with several blocks of
+// outputs (2048 channels x 49 pixels -> 1000 outputs at batch 8, input re-layout included: on 256 CUs 14.1 us, 19.2 with a
+// workgroup per block; on 32 30.7 against 87.8; two workgroups per compute unit 19.2 and 35.2; two launches 12.4 and 22).
+// float32, where both ways hold the same bits: while all workgroups of 32 outputs run at once (512 x 49 -> 1000, batch 8 on 256 CUs
+// 6.0 us against 7.6 in two launches, batch 16 10.0 against 7.9); the small ones (up to 128 channels) fit a CU several at a
 // time (64 x 1024 -> 100, batch 32 on 32 CUs 12.0 against 12.6).
 bool gapfc_supported(int B, int HW, int C, int N, int dtype, int n_cu)
 {
     const long px = (long)HW * C;
     if (dtype == DT_F32) return C % 4 == 0 && C <= 1024 && px <= 64 * 1024 && (long)B * ((N + 31) / 32) <= (C <= 128 ? 4L : 1L) * n_cu;
-    return B <= 8 && C % 8 == 0 && C >= 8 && C <= 2048 && px <= 128 * 1024 && (long)B * ((N + 15) / 16) <= (px <= 64 * 1024 ? 2L : 1L) * n_cu;
+    return B <= 8 && C % 8 == 0 && C >= 8 && C <= 2048 && px <= 128 * 1024;
 }
 
 hipError_t launch_gapfc(const void *x, const void *w, const void *bias, void *y, float *y32, int B, int HW, int C, int N, int act,
@@ -1269,11 +1277,13 @@ hipError_t launch_gapfc(const void *x, const void *w, const void *bias, void *y,
     }
     const int KB = (C + 31) / 32, NB = (N + 15) / 16, parts = GAPFC_NW * 64 / (C / 8);
     const size_t lds = ((size_t)KB * 32 + (size_t)parts * C) * sizeof(float);
-    const dim3 grid((unsigned)NB, (unsigned)B);
-    if (dtype == DT_BF16)
-        hipLaunchKernelGGL(gapfc_kernel<bf16_t>, grid, dim3(GAPFC_NW * 64), lds, s, (const bf16_t *)x, (const uint4 *)w, (const bf16_t *)bias, (bf16_t *)y, y32, HW, C, N, KB, act);
-    else
-        hipLaunchKernelGGL(gapfc_kernel<f16_t>, grid, dim3(GAPFC_NW * 64), lds, s, (const f16_t *)x, (const uint4 *)w, (const f16_t *)bias, (f16_t *)y, y32, HW, C, N, KB, act);
+    const int per_item = n_cu / B > 0 ? n_cu / B : 1;                     // workgroups
+    const dim3 grid((unsigned)(NB < per_item ? NB : per_item), (unsigned)B);
+#define CALL(T, ONE) \
+    hipLaunchKernelGGL((gapfc_kernel<T, ONE>), grid, dim3(GAPFC_NW * 64), lds, s, (const T *)x, (const uint4 *)w, (const T *)bias, (T *)y, y32, HW, C, N, KB, act)
+    if (dtype == DT_BF16) { if ((int)grid.x == NB) CALL(bf16_t, true); else CALL(bf16_t, false); }
+    else { if ((int)grid.x == NB) CALL(f16_t, true); else CALL(f16_t, false); }
+#undef CALL
     return hipGetLastError();
 }
 

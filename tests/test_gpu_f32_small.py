@@ -54,11 +54,11 @@ def test_pool_and_classifier(dt, c, h, w, n, batch):
     (wl.DT_F32, 512, 7, 7, 1000, 1, 0, True), (wl.DT_F32, 512, 7, 7, 1000, 8, 0, True),      # 32 workgroups per item on 256 CUs
     (wl.DT_F32, 512, 7, 7, 1000, 9, 0, False), (wl.DT_F32, 512, 7, 7, 1000, 2, 1, False),    # ... and on 32
     (wl.DT_F32, 128, 7, 7, 1000, 4, 1, True), (wl.DT_F32, 128, 7, 7, 1000, 5, 1, False),     # small workgroups: four per CU
-    (wl.DT_BF16, 2048, 7, 7, 1000, 4, 0, True), (wl.DT_F16, 2048, 7, 7, 1000, 5, 0, False),  # 63 per item, one round
-    (wl.DT_BF16, 512, 7, 7, 1000, 8, 0, True), (wl.DT_F16, 512, 7, 7, 1000, 1, 1, True),     # light pooling: two rounds
-    (wl.DT_BF16, 512, 7, 7, 1000, 2, 1, False),
+    (wl.DT_BF16, 2048, 7, 7, 1000, 8, 0, True), (wl.DT_F16, 2048, 7, 7, 1000, 5, 1, True),   # 16 bit: several blocks of 16 outputs per
+    (wl.DT_BF16, 512, 7, 7, 1001, 1, 1, True), (wl.DT_F16, 136, 9, 9, 530, 8, 1, True),      # workgroup, their number ragged
+    (wl.DT_BF16, 64, 3, 3, 8000, 3, 1, True), (wl.DT_F16, 512, 7, 7, 1000, 9, 0, False),
 ])
-def test_pool_and_classifier_share_a_launch_while_all_workgroups_run_at_once(dt, c, h, w, n, batch, mask_id, fused):
+def test_pool_and_classifier_on_few_compute_units(dt, c, h, w, n, batch, mask_id, fused):
     m = wl.single_layer("gapfc", dt, seed=c + n, c=c, h=h, w=w, n=n, bias_std=0.3, std=1.0 / np.sqrt(c))
     x = wl.make_input(m, batch)
     g = GpuModel(m, max_batch=batch)
