@@ -30,7 +30,8 @@
  * Environment variables (read by the library; for tuning and tests, never needed in service)
  *   ECLIP_GEMM_FORCE="kind,variant,n"  every matrix-core layer takes this plan instead of the planner's or the tuned
  *                         one: kind 0 = LDS-tiled kernel (variant = tile id, n = K slices), kind 1 = wave-split-K
- *                         kernel (variant = tile id, n = 4, 8 or 16 wavefronts); also turns launch sharing off
+ *                         kernel (variant = tile id, n = 4, 8 or 16 wavefronts); a tile id that does not exist
+ *                         leaves the choice to the planner; also turns launch sharing off
  *   ECLIP_NO_PAIRS=1      independent layers never share a launch (pairs of convolutions, pool + classifier, first
  *                         convolution reading the caller's tensor)
  *   ECLIP_GCONV_DIRECT=1  read at eclip_model_load: grouped convolutions take the direct kernel, not the matrix cores

@@ -64,12 +64,8 @@ __global__ __launch_bounds__(64) void splitk_reduce_kernel(const float *ws, int 
 #undef EPI
 }
 
-struct Variant { int bm, bn, bk; };
-constexpr Variant kVariants[CONV_GEMM_VARIANTS] = {{128, 128, 32}, {64, 64, 64}, {32, 64, 64},
-#define X(ID, BM, BN, BK, RS, LP) {BM, BN, BK},
-                                                   ECLIP_PP_TILES(X)
-#undef X
-};
+constexpr PPTile kPlainTiles[] = {{0, 128, 128, 32, 2, LOOP_PLAIN}, {1, 64, 64, 64, 4, LOOP_PLAIN}};
+constexpr PPTile tile_of_id(int id) { return id == 0 || id == 1 ? kPlainTiles[id] : pp_tile(id); }
 
 template <typename T>
 hipError_t launch_pp_split(const GemmDev &d, const GemmPlan &pl, hipStream_t s, hipError_t e);
@@ -81,7 +77,6 @@ hipError_t launch_t(const GemmDev &d, const GemmPlan &pl, SeDeal deal, hipStream
     switch (pl.variant) {
     case 0: hipLaunchKernelGGL((conv_gemm_kernel<T, 128, 128, 32, 2, 2, 2>), grid, dim3(256), lds_bytes(128, 128, 32), s, d, deal); break;
     case 1: hipLaunchKernelGGL((conv_gemm_kernel<T, 64, 64, 64, 2, 2, 4>), grid, dim3(256), lds_bytes(64, 64, 64), s, d, deal); break;
-    case 2: hipLaunchKernelGGL((conv_gemm_kernel<T, 32, 64, 64, 1, 4, 4>), grid, dim3(256), lds_bytes(32, 64, 64), s, d, deal); break;
 #define X(ID, BM, BN, BK, RS, LP) \
     case ID: return launch_pp_split<T>(d, pl, s, launch_pp<ID>(d, deal, std::is_same<T, bf16_t>::value ? DT_BF16 : DT_F16, grid, s));
         ECLIP_PP_TILES(X)
@@ -116,14 +111,14 @@ hipError_t conv_gemm_init()
 
 void conv_gemm_tile(int variant, int *bm, int *bn, int *bk)
 {
-    const int v = variant < 0 ? 0 : (variant >= CONV_GEMM_VARIANTS ? CONV_GEMM_VARIANTS - 1 : variant);
-    *bm = kVariants[v].bm;
-    *bn = kVariants[v].bn;
-    *bk = kVariants[v].bk;
+    const PPTile t = tile_of_id(variant);
+    *bm = t.bm;
+    *bn = t.bn;
+    *bk = t.bk;
 }
 
-const char *conv_gemm_kernel_name(int variant) { return pp_tile(variant).loop == LOOP_DMA ? "conv_gemm_dma_kernel" : "conv_gemm_kernel"; }
-int conv_gemm_threads(int variant) { return pp_tile(variant).id < 0 || pp_tile(variant).loop == LOOP_DMA ? 256 : 512; }
+const char *conv_gemm_kernel_name(int variant) { return tile_of_id(variant).loop == LOOP_DMA ? "conv_gemm_dma_kernel" : "conv_gemm_kernel"; }
+int conv_gemm_threads(int variant) { return tile_of_id(variant).loop == LOOP_DMA || tile_of_id(variant).loop == LOOP_PLAIN ? 256 : 512; }
 
 static long cdiv(long a, long b) { return (a + b - 1) / b; }
 
@@ -133,7 +128,6 @@ static void set_raster(GemmPlan &pl, long M, long N)
     int bm, bn, bk;
     conv_gemm_tile(pl.variant, &bm, &bn, &bk);
     const long tm = cdiv(M, bm), tn = cdiv(N, bn);
-    if (pl.kind != 0) return;
     if (tm * tn < 256 || pl.splits != 1) {
         // fewer tiles than CUs (or K slices in grid.y): deal whole tile columns or rows to the XCDs when they divide
         // evenly, so that each L2 holds 1/8 of one operand instead of all of both.  (Uneven ranges of tiles per XCD were
@@ -224,8 +218,9 @@ static double wsk_whole_cost(long M, long N, long K, int n_cu, int v, int nw)
 double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int v, int nw) { return wsk_cost(M, N, K, n_cu, v, nw); }
 
 // Every plan worth timing for a problem (eclip_model_tune): all wave-split-K tiles and wavefront counts that fit LDS, and
-// every LDS-tiled shape whole and with K cut in two or four where the workspace allows.  Tiles far larger than the
-// problem are left out (a 256-row tile for a 64-row problem only wastes the measurement).
+// every 8-wavefront or copied LDS tile whole and with K cut in two or four where the workspace allows (the plain tiles were best on
+// none of 900 problems).  Tiles far larger than the problem are left out (a 256-row tile for a 64-row problem only wastes
+// the measurement).
 std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, size_t ws_floats)
 {
     std::vector<GemmPlan> out;
@@ -239,9 +234,8 @@ std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, siz
             set_xcd_split(pl, M, N);
             out.push_back(pl);
         }
-    for (int v : {0, 1, 3, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28}) {
-        int bm, bn, bk;
-        conv_gemm_tile(v, &bm, &bn, &bk);
+    for (const PPTile &t : kPPTiles) {
+        const int v = t.id, bm = t.bm, bn = t.bn, bk = t.bk;
         if (bm > 2 * M + 32 || bn > 2 * N + 32) continue;
         const long KT = cdiv(K, bk);
         for (long sp = 1; sp <= 4; sp *= 2) {
@@ -265,7 +259,7 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     auto wsk_tiles = [&](int v) { int bm, bn; conv_wsk_tile(v, &bm, &bn); return cdiv(M, bm) * cdiv(N, bn); };
     GemmPlan pl{0, 1, 1, 0, 4, 0};
     // tuning aid: ECLIP_GEMM_FORCE="kind,variant,n" overrides the heuristic; n = K splits (kind 0, clamped to the
-    // workspace) or wavefronts per workgroup (kind 1: 4, 8 or 16)
+    // workspace) or wavefronts per workgroup (kind 1: 4, 8 or 16); ids without a tile leave the choice to the planner
     const char *force = getenv("ECLIP_GEMM_FORCE");
     int f_kind = -1, f_variant = -1, f_n = -1;
     if (force) sscanf(force, "%d,%d,%d", &f_kind, &f_variant, &f_n);
@@ -275,7 +269,7 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
         set_xcd_split(pl, M, N);
         return pl;
     }
-    if (f_kind == 0 && f_variant >= 0 && f_variant < CONV_GEMM_VARIANTS) {
+    if (f_kind == 0 && tile_of_id(f_variant).id >= 0) {
         pl.variant = f_variant;
         pl.tiles = (int)tiles(pl.variant);
         int bm, bn, bk;
@@ -308,7 +302,6 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // The picks cost 3.9 % more than the best plan on average; eclip_model_tune closes that gap by
     // measurement.  (A further 1.2 us on every tile, for inputs that the layer before has just written, made the same 160 kinds of
     // request 1.1 % slower, none faster by more than 1.5 % and ResNeXt at batch 8 on 160 CUs 651 us instead of 589; 2.4 us another 1.5 %.)
-    // The shapes of ids 6, 7, 9 to 12 and 14 have a cheaper twin among the others and are left to it.
     struct LdsTile { int variant; double step, fixed, more, two; };
     static const LdsTile lds[] = {
                                   {0, 0.509, 4.049, 7.322, 1.373}, {3, 0.568, 8.784, 16.049, 0}, {5, 0.595, 8.271, 16.021, 0}, {8, 0.525, 5.267, 9.068, 0},
@@ -411,19 +404,15 @@ static GemmDev make_dev(const ConvGemmArgs &a, const GemmPlan &pl)
     d.ldy = a.ldy ? a.ldy : a.Cout;
     d.x_bytes = (unsigned)((size_t)a.B * a.H * a.W * (a.nchw_c ? a.nchw_c : d.ldx) * 2);
     d.w_bytes = (unsigned)((size_t)((d.N + 15) / 16) * ((d.K + 31) / 32) * 1024);   // blocked layout, see ConvGemmArgs::w
-    int bm, bn, bk;
-    conv_gemm_tile(pl.variant, &bm, &bn, &bk);
+    int bm, bn, bk = 32;
+    if (pl.kind == 1) conv_wsk_tile(pl.variant, &bm, &bn);
+    else conv_gemm_tile(pl.variant, &bm, &bn, &bk);
     d.KT = (d.K + bk - 1) / bk;
     d.splits = pl.splits;
     d.kt_per = (d.KT + pl.splits - 1) / pl.splits;
     d.tiles_m = (d.M + bm - 1) / bm;
     d.tiles_n = (d.N + bn - 1) / bn;
     d.raster = pl.raster;
-    if (pl.kind == 1) {
-        conv_wsk_tile(pl.variant, &bm, &bn);
-        d.tiles_m = (d.M + bm - 1) / bm;
-        d.tiles_n = (d.N + bn - 1) / bn;
-    }
     return d;
 }
 

@@ -42,13 +42,11 @@ struct GemmPlan {
     double cost = 0.0;   // modelled time, us without the launch; 0: chosen by measurement or forced
 };
 bool conv_gemm_plan_stem(long M, long N, long K, int n_cu, size_t ws_floats, double stage_us, GemmPlan *out);   // ConvGemmArgs::nchw_c
-enum { CONV_GEMM_VARIANTS = 29 };        // 0..2: 128x128x32, 64x64x64, 32x64x64 (4 wavefronts); 3, 4: 256x256x32, 128x256x64 (8 wavefronts on the
-                                         // ping-pong schedule, both operands in LDS); 5..14: ping-pong with the weights straight from memory:
-                                         // 256x256x32, 128x256x64, 192x128x32, 192x128x64, 128x128x64, 256x128x32, 192x256x32, 256x192x32,
-                                         // 64x128x64, 128x64x64, 96x64x64, 96x192x64; 17..28: both operands copied straight into LDS
-                                         // (4 wavefronts): 256x256x32, 256x128x64, 128x256x64, 128x128x64, 192x128x64, 128x64x64,
-                                         // 64x128x64, 256x192x32, 192x256x32, 64x64x64; 27, 28: 128x64x32, 128x128x32 (small rings: three
-                                         // or four workgroups per CU)
+// Tile ids of the LDS-tiled kernels.  0, 1: 128x128x32, 64x64x64 (4 wavefronts); 3: 256x256x32 (8 wavefronts on the ping-pong
+// schedule, both operands in LDS); 5, 8, 13, 15, 16: ping-pong with the weights straight from memory: 256x256x32, 192x128x64, 64x128x64,
+// 96x64x64, 96x192x64; 17..28: both operands copied straight into LDS (4 wavefronts): 256x256x32, 256x128x64, 128x256x64, 128x128x64,
+// 192x128x64, 128x64x64, 64x128x64, 256x192x32, 192x256x32, 64x64x64; 27, 28: 128x64x32, 128x128x32 (small rings: three or four
+// workgroups per CU)
 void conv_gemm_tile(int variant, int *bm, int *bn, int *bk);
 const char *conv_gemm_kernel_name(int variant);
 int conv_gemm_threads(int variant);
