@@ -505,6 +505,44 @@ def kernels_mode(only=None, extra_gemms=None, tune=True, cus=256):
 # ---------------------------------------------------------------------------------------------------
 # hardware characterisation (the paper's Sec. II-C experiments, on this GPU)
 # ---------------------------------------------------------------------------------------------------
+def plans_mode(shapes, cus):
+    """Every launch plan of a linear layer, timed in a chain of layers with weights of their own (128 MB of them, so that no layer
+    finds its weights in an L2), and the planner's pick among them.  One line per shape and share: what the constants of the
+    planner's cost model can be held against."""
+    import workloads as wl
+    import workloads.graphs as G
+    import paper_2506_12598_amd as ec
+    wsk = [(16, 64), (32, 64), (64, 64), (16, 16), (16, 32), (32, 32)]
+    plans = [f"1,{v},{nw}" for v, (bm, bn) in enumerate(wsk) for nw in (4, 8, 16) if nw * bm * bn * 4 <= 131072]
+    plans += [f"0,{v},1" for v in (0, 1, 3, 5, 8, 13, 15, 16, *range(17, 29))]
+    pool = ec.Pool([(ec.eclip_mask_layout(256, 16, 1, 0, c // 16), 0) for c in cus])
+    print("M,N,K  CUs: planner's pick, us per layer | best plan (kind,variant,n), us | pick / best")
+    ratios = []
+    for m_, n_, k_ in shapes:
+        b = G._Builder("chain", wl.DT_BF16, 0, G.IN_SEQ, k_, 1, m_)
+        layers = max(4, min(64, -(-(128 << 20) // (n_ * k_ * 2))))
+        for _ in range(layers):
+            b.linear(-1, n_, std=0.02)
+        m = b.finish()
+        h = ec.Model(pool, m, wl.to_storage(m.weights, m.dtype), max_batch=1)
+        for sid, c in enumerate(cus):
+            def us(var, val):
+                os.environ[var] = val
+                try:
+                    return h.profile_group_served(0, sid, 1, 4)[0] / layers / 1e3
+                finally:
+                    del os.environ[var]
+            own = min(us("ECLIP_NO_PAIRS", "1") for _ in range(2))
+            times = {p: us("ECLIP_GEMM_FORCE", p) for p in plans}
+            best = min(times, key=times.get)
+            ratios.append(own / min(own, times[best]))
+            print(f"{m_},{n_},{k_}  {c}: {own:.2f} | {best} {times[best]:.2f} | {ratios[-1]:.3f}", flush=True)
+        h.free()
+    pool.destroy()
+    print(f"{len(ratios)} problems: the planner's picks cost {100 * (sum(ratios) / len(ratios) - 1):.1f} % more than the best plan on average, "
+          f"{100 * (max(ratios) - 1):.0f} % at worst")
+
+
 def characterize_mode():
     import collections
     import paper_2506_12598_amd as ec
@@ -717,6 +755,8 @@ def main():
     ap.add_argument("--kernels", action="store_true", help="time single kernels at roofline shapes and print a table")
     ap.add_argument("--cus", type=int, default=256, help="with --kernels: run on a stream masked to this many CUs (a multiple of 16)")
     ap.add_argument("--gemm", default=None, help="with --kernels: time linear layers of these shapes, 'M,N,K;M,N,K;...'")
+    ap.add_argument("--plans", default=None, metavar="M,N,K;...", help="time every launch plan of these linear layers, in chains with weights of "
+                                                                       "their own, on 64, 96, 160 and 256 CUs, against the planner's pick")
     ap.add_argument("--only", default=None, help="with --kernels: comma-separated case keys (layernorm, softmax, maxpool, dwconv, "
                     "gap, gelu, copy, fc, gemm8192, gemm4096, ffn1, ffn2, qkv, proj, base_ffn1)")
     ap.add_argument("--policies", action="store_true", help="compare the paper's partitioning scenarios and sweep the switch budget")
@@ -753,6 +793,9 @@ def main():
     torch.cuda.init()
     if args.kernels:
         kernels_mode(args.only, args.gemm, tune=not args.no_tune, cus=args.cus)
+        return
+    if args.plans:
+        plans_mode([tuple(int(v) for v in s.split(",")) for s in args.plans.split(";")], (64, 96, 160, 256))
         return
     if args.characterize:
         characterize_mode()

@@ -621,7 +621,7 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p, SeDe
 }
 
 
-// Ping-pong tiles (8 wavefronts): X(variant id, BM, BN, BK, register stages, K-loop schedule).  Each is compiled in a
+// Ping-pong tiles (8 wavefronts) and copied tiles (4): X(variant id, BM, BN, BK, stages, K-loop schedule).  Each is compiled in a
 // translation unit of its own (k_gemm_pp.hip with ECLIP_PP_ID set), which exports launch_pp<ID> and init_pp<ID>.
 // Id 3 keeps both operands in LDS; 5..16 fetch the weights straight into registers; 17..28 copy both operands straight into LDS
 // (rs: stages of the ring).  Ids without a tile (2, 4, 6, 7, 9..12, 14) had one that the planner never picked and that measuring

@@ -299,9 +299,11 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // candidates share (as in wsk_cost).  Constants fitted, together with wsk_whole_cost's, to 440 problems x 36 plans (40 linear layers of 128 to
     // 1536 rows, 70 convolutions of ResNet, VGG and MobileNet shapes at batch 1, 3 and 8, each on 64, 96, 160 and 256 compute units), every
     // plan timed in a chain of four to eight layers with weights of their own, so that no layer finds its weights in an L2.
-    // The picks cost 3.9 % more than the best plan on average; eclip_model_tune closes that gap by
-    // measurement.  (A further 1.2 us on every tile, for inputs that the layer before has just written, made the same 160 kinds of
-    // request 1.1 % slower, none faster by more than 1.5 % and ResNeXt at batch 8 on 160 CUs 651 us instead of 589; 2.4 us another 1.5 %.)
+    // `bench.py --plans` repeats that measurement for linear layers: over 26 shapes on the four shares the picks cost 5.7 % more than the
+    // best plan on average; most of it on 160 compute units, whose shader engines hold 8, 8, 2 and 2 per XCD: the wave-split-K
+    // kernel is not dealt to them (se_deal.h) and this model does not know.  eclip_model_tune closes the gap by measurement.
+    // (A further 1.2 us on every tile, for inputs that the layer before has just written, made the 160 kinds of request above
+    // 1.1 % slower, none faster by more than 1.5 % and ResNeXt at batch 8 on 160 CUs 651 us instead of 589; 2.4 us another 1.5 %.)
     struct LdsTile { int variant; double step, fixed, more, two; };
     static const LdsTile lds[] = {
                                   {0, 0.509, 4.049, 7.322, 1.373}, {3, 0.568, 8.784, 16.049, 0}, {5, 0.595, 8.271, 16.021, 0}, {8, 0.525, 5.267, 9.068, 0},

@@ -1,4 +1,4 @@
-// One ping-pong tile shape of the LDS-tiled matrix-core kernel (gemm_tile.h), selected by ECLIP_PP_ID at compile time:
+// One ping-pong or copied tile shape of the LDS-tiled matrix-core kernels (gemm_tile.h, gemm_dma.h), selected by ECLIP_PP_ID at compile time:
 // both 16-bit types and the three addressing forms.  One translation unit per shape keeps the build parallel; the
 // build script compiles this file once for every id listed in ECLIP_PP_TILES.
 #include "gemm_dma.h"

@@ -53,7 +53,7 @@ int conv_gemm_threads(int variant);
 enum { CONV_WSK_VARIANTS = 6 };          // 16x64, 32x64, 64x64, 16x16, 16x32, 32x32
 void conv_wsk_tile(int variant, int *bm, int *bn);
 size_t conv_wsk_lds_bytes(int variant, int nw);
-hipError_t conv_gemm_init();   // raises the dynamic LDS limit of the 256x256 tile once per process
+hipError_t conv_gemm_init();   // raises the dynamic LDS limit of the LDS-tiled kernels once per process
 hipError_t conv_wsk_init();    // raises the dynamic LDS limit of the wave-split-K kernels once per process
 // Chooses tile shape and K split for a stream restricted to n_cu compute units.
 GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats);
