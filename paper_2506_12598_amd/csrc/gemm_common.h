@@ -20,6 +20,18 @@ struct GemmDev {
                                              // a channel range of a wider buffer: concatenation in place); res is null when ldy != N
 };
 
+// n / d for n < 2^31: (2 n * mul >> 32) >> shift with mul = floor(2^(31 + shift) / d) + 1, shift = ceil(log2 d)
+struct Magic {
+    unsigned d, mul, shift;
+};
+inline Magic magic_of(unsigned d)
+{
+    Magic m{d, 0, 0};
+    while ((1ull << m.shift) < d) ++m.shift;
+    m.mul = (unsigned)((1ull << (31 + m.shift)) / d + 1);
+    return m;
+}
+
 template <typename T> struct Mma;
 template <> struct Mma<bf16_t> {
     __device__ static __forceinline__ f32x4 run(uint4 a, uint4 b, f32x4 c)
@@ -128,5 +140,10 @@ __device__ __forceinline__ void epilogue_store8_ragged(const uint16_t *bias, con
 hipError_t launch_conv_wsk(const GemmDev &d, int dtype, int variant, int nw, int tiles, hipStream_t s);
 // two independent layers of the same tile shape and wavefront count in one launch
 hipError_t launch_conv_wsk_pair(const GemmDev &d0, int tiles0, const GemmDev &d1, int tiles1, int dtype, int variant, int nw, hipStream_t s);
+// its lean form (k_wsk_lean.hip): the address form of a layer (of two layers in one launch), -1 where only the general form serves
+int wsk_lean_form(const GemmDev &d);
+int wsk_lean_pair_form(const GemmDev &d0, const GemmDev &d1);
+hipError_t wsk_lean_init();
+hipError_t launch_wsk_lean(const GemmDev &d0, const GemmDev &d1, int n0, int dtype, int form, int variant, int nw, int tiles, hipStream_t s);
 
 }  // namespace eclip

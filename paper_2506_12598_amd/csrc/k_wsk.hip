@@ -335,17 +335,21 @@ hipError_t conv_wsk_init()
     SET(bf16_t)
     SET(f16_t)
 #undef SET
-    return hipSuccess;
+    return wsk_lean_init();
 }
 
 hipError_t launch_conv_wsk(const GemmDev &d, int dtype, int variant, int nw, int tiles, hipStream_t s)
 {
+    const int form = wsk_lean_form(d);
+    if (form >= 0) return launch_wsk_lean(d, d, tiles, dtype, form, variant, nw, tiles, s);
     if (dtype == DT_BF16) return launch_tile<bf16_t>(d, d, tiles, variant, nw, tiles, s);
     return launch_tile<f16_t>(d, d, tiles, variant, nw, tiles, s);
 }
 
 hipError_t launch_conv_wsk_pair(const GemmDev &d0, int tiles0, const GemmDev &d1, int tiles1, int dtype, int variant, int nw, hipStream_t s)
 {
+    const int form = wsk_lean_pair_form(d0, d1);
+    if (form >= 0) return launch_wsk_lean(d0, d1, tiles0, dtype, form, variant, nw, tiles0 + tiles1, s);
     if (dtype == DT_BF16) return launch_tile<bf16_t>(d0, d1, tiles0, variant, nw, tiles0 + tiles1, s);
     return launch_tile<f16_t>(d0, d1, tiles0, variant, nw, tiles0 + tiles1, s);
 }
