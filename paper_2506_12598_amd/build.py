@@ -23,6 +23,9 @@ def pp_tile_ids():
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
+# kernels whose first arguments are to arrive in scalar registers with the wavefront
+MORE_FLAGS = {"k_wsk_lean.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=14"]}
+
 
 def _needs(obj: str, deps) -> bool:
     return not os.path.exists(obj) or any(os.path.getmtime(d) > os.path.getmtime(obj) for d in deps)
@@ -48,7 +51,7 @@ def build(force: bool = False, verbose: bool = False) -> str:
         return obj
 
     # the slowest translation units first, so that the pool stays full to the end
-    jobs = [("k_gemm_pp.hip", [f"-DECLIP_PP_ID={i}"], f".{i}") for i in pp_tile_ids()] + [(src, [], "") for src in SOURCES]
+    jobs = [("k_gemm_pp.hip", [f"-DECLIP_PP_ID={i}"], f".{i}") for i in pp_tile_ids()] + [(src, MORE_FLAGS.get(src, []), "") for src in SOURCES]
     with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(compile_one, jobs))
     if force or _needs(LIB, objs):

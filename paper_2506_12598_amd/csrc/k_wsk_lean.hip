@@ -10,13 +10,14 @@
 // three address forms need one or three vector instructions per load:
 //   ROWS       1 x 1 window, stride 1, no padding: pixel m of the operand is row m; the position along K is the load's scalar offset
 //   ROWS_TAIL  the same with K not a multiple of 32: the last step's lanes beyond K load zeros
-//   WINDOW     Cin a multiple of 32, at most 32 taps: a K step lies inside one tap, so the tap's offset is a scalar
+//   WINDOW     Cin a multiple of 32, at most 31 taps: a K step lies inside one tap, so the tap's offset is a scalar
 //              and one bit per row and tap says whether the tap lies inside the image
 // Bias and residual are fetched while the K loop waits for its operands, through descriptors of zero bytes when there are
 // none; the partial tiles lie in LDS so that the summing threads store whole rows.
 // Chains of layers with weights of their own, M x N x K, 256 CUs, us per launch in the general form and in this one: 196 x 128 x 512 4.24,
-// 2.61; 3136 x 64 x 256 3.96, 2.78; 128 x 768 x 768 4.17, 3.30; 128 x 3072 x 768 6.06, 4.72; 3 x 3 windows 3136 x 64 x 576 5.15, 3.64 and
-// 49 x 512 x 4608 8.05, 7.29.  What is left of the short ones is the dispatch and one trip to memory.
+// 2.37; 3136 x 64 x 256 4.02, 2.58; 128 x 768 x 768 4.16, 3.19; 128 x 3072 x 768 6.03, 4.34; 3 x 3 windows 3136 x 64 x 576 5.07, 3.14 and
+// 49 x 512 x 4608 8.02, 6.79.  What is left of the short ones is the dispatch and one trip to memory.  (Without the arguments in
+// registers 2.75, 2.91, 3.54, 4.81, 3.60, 7.03.)
 #include "gemm_common.h"
 #include "kernels.h"
 
@@ -30,63 +31,68 @@ enum { WSK_ROWS, WSK_ROWS_TAIL, WSK_WINDOW, WSK_FORMS };
 
 __device__ __forceinline__ unsigned div_by(unsigned n, const Magic &m) { return __umulhi(n + n, m.mul) >> m.shift; }
 
-// One layer as the kernel wants it.
-struct WskDev {
-    const uint16_t *x, *w, *bias, *res;
+// n bits from bit `at` on; n < 32
+__device__ __forceinline__ unsigned bits_from(int at, int n) { return ((1u << n) - 1u) << (at & 31); }
+
+// One layer as the kernel wants it, in two parts.  The head is what the loads of the K loop need: 14 words of it (with the first
+// layer's workgroups) are separate arguments, which the hardware puts into scalar registers before the wavefront starts, where a
+// trip to the cold argument block costs 150 to 630 cycles.
+struct WskHead {
+    const uint16_t *x, *w;
+    unsigned x_bytes;
+    int M, last_nb, steps;                   // rows; last 16-row block of the weights; K steps of 32
+    int px;                                  // bytes between pixels of x
+    unsigned walk;                           // bits 0-1: GemmPlan::raster 2 or 3 (0: plain); bits 8-15: shift of the division by inner_d
+    int per;                                 // tile columns (rows) per XCD
+    unsigned inner_d, inner_mul;             // tiles along the other dimension, and the multiplier of the division by them
+};
+struct WskRest {
+    const uint16_t *bias, *res;
     void *y;
-    unsigned x_bytes, w_bytes, bias_bytes, res_bytes, y_bytes;      // 0 for an absent bias / residual: loads return zeros
-    int M, N, steps, per_wave;               // K steps of 32, and how many of them a wavefront takes
-    int px, ldy;                             // bytes between pixels of x, elements between rows of y
+    unsigned bias_bytes, res_bytes, y_bytes; // 0 for an absent bias / residual: loads return zeros
+    int N, ldy;                              // elements between rows of y
     int act, f32;                            // f32: y holds floats
-    int dealt, per, limit;                   // GemmPlan::raster 2 or 3: tile columns (rows) per XCD and in all
-    Magic inner;                             // tiles along the other dimension
     int k_tail;                              // ROWS_TAIL: k's of the last step
     // WINDOW
     Magic howo, wo, cb;                      // output pixels per image and per row; K steps per tap
-    int W, H, KW, KH, stride, pad, img;      // img: bytes of an image of x
+    int W, H, KW, KH, stride, pad;
+    unsigned taps_col;                       // one bit at the first tap of every window row
     int next_col, next_row;                  // added to the byte offset from a tap's last step to the next tap's first, and at a row's end
 };
 
-// All arguments in scalar registers here, fetched together: left to itself the compiler fetches each where it is needed, four
-// trips to a cold cache one after the other.
-__device__ __forceinline__ void fetch_now(WskDev &p, int &n0)
-{
-    asm volatile("" : "+s"(p.x), "+s"(p.w), "+s"(p.bias), "+s"(p.res), "+s"(p.y), "+s"(p.x_bytes), "+s"(p.w_bytes), "+s"(p.bias_bytes), "+s"(p.res_bytes),
-                 "+s"(p.y_bytes), "+s"(p.M), "+s"(p.N), "+s"(p.steps), "+s"(p.per_wave), "+s"(p.px), "+s"(p.ldy), "+s"(p.dealt),
-                 "+s"(p.per), "+s"(p.limit), "+s"(p.inner.d), "+s"(p.inner.mul), "+s"(p.inner.shift), "+s"(n0));
-}
-
 template <typename T, int TM, int TN, int NW, int D, int FORM>
-__global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(WskDev p0, WskDev p1, int n0)
+__global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int last_nb, int steps,
+                                                           int px, unsigned walk, int per, unsigned inner_d, unsigned inner_mul, int n0,
+                                                           WskRest r0, WskHead h1, WskRest r1)
 {
     extern __shared__ __attribute__((aligned(16))) float red[];    // [NW][TM*TN][64][4]
     constexpr int BM = TM * 16, BN = TN * 16, BLK = TM * TN;
     constexpr unsigned OOB = 0xffffffffu;
-    // one launch can carry two independent layers: workgroups 0 .. n0-1 work on p0, the rest on p1
-    WskDev p = p0;
-    fetch_now(p, n0);
+    // one launch can carry two independent layers: workgroups 0 .. n0-1 work on the first, the rest on the second
     int bid = (int)blockIdx.x;
+    WskRest p = r0;
     if (__builtin_expect(bid >= n0, 0)) {
-        p = p1;
         bid -= n0;
+        x = h1.x; w = h1.w; x_bytes = h1.x_bytes; M = h1.M; last_nb = h1.last_nb; steps = h1.steps; px = h1.px; walk = h1.walk;
+        per = h1.per; inner_d = h1.inner_d; inner_mul = h1.inner_mul;
+        p = r1;
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tile_m, tile_n;
     {
-        const unsigned xcd = p.dealt ? bid & 7 : 0, q = p.dealt ? bid >> 3 : bid;
-        const unsigned r = div_by(q, p.inner), rem = q - r * p.inner.d;
-        const unsigned a = xcd * (unsigned)p.per + r;
-        if (p.dealt && (r >= (unsigned)p.per || a >= (unsigned)p.limit)) return;
-        tile_m = p.dealt == 3 ? a : rem;
-        tile_n = p.dealt == 3 ? rem : a;
+        const unsigned dealt = walk & 3u, xcd = dealt ? bid & 7 : 0, q = dealt ? bid >> 3 : bid;
+        const unsigned r = div_by(q, Magic{inner_d, inner_mul, walk >> 8}), rem = q - r * inner_d;
+        const unsigned a = xcd * (unsigned)per + r;
+        tile_m = dealt == 3 ? a : rem;
+        tile_n = dealt == 3 ? rem : a;
     }
     const int m_base = tile_m * BM, n_base = tile_n * BN;
 
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)p.x, 0, (int)p.x_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)p.w, 0, (int)p.w_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, (int)x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)w, 0, (last_nb + 1) * steps * 1024, 0x00020000);
 
     // this wavefront's K steps
-    const int ks0 = wave * p.per_wave, n_steps = min(p.per_wave, p.steps - ks0);
+    const int per_wave = (steps + NW - 1) / NW, ks0 = wave * per_wave, n_steps = min(per_wave, steps - ks0);
 
     // im2col operand in tile order: lane l takes row l >> 2, 16-byte chunk l & 3 of the step's 64 bytes; it changes lanes before use
     const int row = lane >> 2, g = lane & 3;
@@ -100,73 +106,82 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(WskDev p0, WskDev p1,
         left = (int)p.cb.d - cs;
         int kh = 0;
         for (kw = tap; kw >= p.KW; kw -= p.KW) ++kh;
-        so = (kh * p.W + kw) * p.px + cs * 64;
+        so = (kh * p.W + kw) * px + cs * 64;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int m = m_base + i * 16 + row;
             const unsigned b = div_by((unsigned)m, p.howo), r = m - b * p.howo.d;
             const unsigned oh = div_by(r, p.wo), ow = r - oh * p.wo.d;
             const int ih = (int)oh * p.stride - p.pad, iw = (int)ow * p.stride - p.pad;
-            a_off[i] = b * (unsigned)p.img + (unsigned)((ih * p.W + iw) * p.px + g * 16);
-            // columns lo .. hi of the window lie inside the image's row
-            const int lo = max(-iw, 0), hi = min(p.W - iw, p.KW);
-            const unsigned cols = hi > lo ? ((2u << (hi - 1)) - 1u) & ~((1u << lo) - 1u) : 0u;
-            unsigned ok = 0;
-            for (int k = 0; k < p.KH; ++k) ok |= ((unsigned)(ih + k) < (unsigned)p.H ? cols : 0u) << (k * p.KW);
-            bad[i] = m < p.M ? ~ok : ~0u;
+            a_off[i] = (unsigned)(((int)b * p.H + ih) * p.W + iw) * (unsigned)px + (unsigned)g * 16u;
+            // taps of columns lo_w .. hi_w - 1 and rows lo_h .. hi_h - 1 lie inside the image
+            const int lo_w = max(-iw, 0), n_w = max(min(p.W - iw, p.KW) - lo_w, 0);
+            const int lo_h = max(-ih, 0), n_h = max(min(p.H - ih, p.KH) - lo_h, 0);
+            const unsigned cols = bits_from(lo_w, n_w), rows = p.taps_col & bits_from(lo_h * p.KW, n_h * p.KW);
+            bad[i] = m < M ? ~(cols * rows) : ~0u;
         }
     } else {
         so = ks0 * 64;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int m = m_base + i * 16 + row;
-            a_off[i] = m < p.M ? (unsigned)(m * p.px + g * 16) : OOB;
+            a_off[i] = m < M ? (unsigned)m * (unsigned)px + (unsigned)g * 16u : OOB;
         }
     }
     // weights: 1 KB blocks of 16 rows x 32 k in lane order; tile columns beyond the last block read that one again (their results
     // are not stored)
     int b_so[TN];
-    const int last_nb = ((p.N + 15) >> 4) - 1;
 #pragma unroll
-    for (int j = 0; j < TN; ++j) b_so[j] = (min((n_base >> 4) + j, last_nb) * p.steps + ks0) * 1024;
-    int tail_in = FORM == WSK_ROWS_TAIL ? p.steps - 1 - ks0 : 0;     // steps until the ragged one
+    for (int j = 0; j < TN; ++j) b_so[j] = (min((n_base >> 4) + j, last_nb) * steps + ks0) * 1024;
+    int tail_in = FORM == WSK_ROWS_TAIL ? steps - 1 - ks0 : 0;       // steps until the ragged one
 
     struct Frag { uint4 a[TM]; uint4 b[TN]; };
-    // Loads the next K step.  RUNS_ON: the load may lie beyond the slice (its values are then not used); the scalar offsets stay
-    // inside the tensors, as the descriptor's bounds are only relied on for the lanes' own offsets.
-    const int so_max = (p.steps - 1) * 64, b_max = (int)(p.w_bytes - 1024u);
-    auto load = [&](Frag &f, auto runs_on) {
-        if constexpr (decltype(runs_on)::value && FORM != WSK_WINDOW) so = min(so, so_max);
+    // Loads the next K step.  runs_on: it may lie beyond the slice; then every lane's offset is beyond the tensor and the scalar
+    // offsets are 0, so that nothing is fetched.
+    auto load = [&](Frag &f, auto runs_on, int more) {
+        unsigned none = 0;
+        int so_a = so, so_b[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) so_b[j] = b_so[j];
+        if constexpr (decltype(runs_on)::value) {
+            none = more > 0 ? 0u : OOB;
+            so_a = more > 0 ? so : 0;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) so_b[j] = more > 0 ? b_so[j] : 0;
+        }
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             u32x4 v;
             if constexpr (FORM == WSK_WINDOW) {
                 const unsigned out = (unsigned)__builtin_amdgcn_sbfe((int)bad[i], tap, 1);
-                v = __builtin_amdgcn_raw_buffer_load_b128(rx, (a_off[i] + (unsigned)so) | out, 0, 0);
+                v = __builtin_amdgcn_raw_buffer_load_b128(rx, (a_off[i] + (unsigned)so) | out | none, 0, 0);
             } else if constexpr (FORM == WSK_ROWS_TAIL) {
-                v = __builtin_amdgcn_raw_buffer_load_b128(rx, tail_in == 0 && g * 8 >= p.k_tail ? OOB : a_off[i], so, 0);
+                v = __builtin_amdgcn_raw_buffer_load_b128(rx, tail_in == 0 && g * 8 >= p.k_tail ? OOB : a_off[i] | none, so_a, 0);
             } else {
-                v = __builtin_amdgcn_raw_buffer_load_b128(rx, a_off[i], so, 0);
+                v = __builtin_amdgcn_raw_buffer_load_b128(rx, a_off[i] | none, so_a, 0);
             }
             f.a[i] = make_uint4(v.x, v.y, v.z, v.w);
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            if constexpr (decltype(runs_on)::value) b_so[j] = (int)min((unsigned)b_so[j], (unsigned)b_max);
-            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16, b_so[j], 0);
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, (unsigned)lane * 16u | none, so_b[j], 0);
             f.b[j] = make_uint4(v.x, v.y, v.z, v.w);
             b_so[j] += 1024;
         }
         so += 64;
         if constexpr (FORM == WSK_ROWS_TAIL) --tail_in;
         if constexpr (FORM == WSK_WINDOW) {
-            const bool wrap = --left == 0;
-            left = wrap ? (int)p.cb.d : left;
-            tap += wrap;
-            kw += wrap;
-            const bool wrap2 = kw == p.KW;
-            kw = wrap2 ? 0 : kw;
-            so += (wrap ? p.next_col : 0) + (wrap2 ? p.next_row : 0);
+            if (--left == 0) {
+                asm volatile("");                // stays a branch: as selects it would cost every step 14 scalar instructions
+                left = (int)p.cb.d;
+                ++tap;
+                so += p.next_col;
+                if (++kw == p.KW) {
+                    asm volatile("");
+                    kw = 0;
+                    so += p.next_row;
+                }
+            }
         }
     };
 
@@ -194,17 +209,17 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(WskDev p0, WskDev p1,
     Frag f[D];
     int rest = n_steps;
     if (__builtin_expect(rest > D, 0)) {
-        static_for<D>([&](auto dc) { load(f[decltype(dc)::value], std::false_type()); });
+        static_for<D>([&](auto dc) { load(f[decltype(dc)::value], std::false_type(), 0); });
         do {
             static_for<D>([&](auto dc) {
                 consume(f[decltype(dc)::value]);
-                load(f[decltype(dc)::value], std::true_type());
+                load(f[decltype(dc)::value], std::true_type(), rest - D - decltype(dc)::value);
             });
             rest -= D;
         } while (rest > D);
     } else {
         static_for<D>([&](auto dc) {
-            if (decltype(dc)::value < rest) load(f[decltype(dc)::value], std::false_type());
+            if (decltype(dc)::value < rest) load(f[decltype(dc)::value], std::false_type(), 0);
         });
     }
 
@@ -219,7 +234,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(WskDev p0, WskDev p1,
     for (int u = 0; u < SLOTS; ++u) {
         const int s = u * NW * 64 + tid, c4 = s % C4, r = s / C4;
         const int m = m_base + r, n = n_base + c4 * 4;
-        const bool in = sums && m < p.M && n < p.N;
+        const bool in = sums && m < M && n < p.N;
         off[u] = in ? (unsigned)(m * p.ldy + n) * 2u : OOB;
         bias[u] = __builtin_amdgcn_raw_buffer_load_b64(rb, in ? n * 2 : OOB, 0, 0);
         res[u] = __builtin_amdgcn_raw_buffer_load_b64(rr, off[u], 0, 0);
@@ -281,31 +296,34 @@ template <int TM, int TN, int NW> struct LeanDepth {
                                  : (TM + TN) <= 5 ? (NW == 16 ? 4 : 6) : (TM + TN) <= 6 ? (NW == 16 ? 2 : 4) : 3;
 };
 
-WskDev wsk_dev(const GemmDev &d, int nw, int bm, int bn)
+WskHead wsk_head(const GemmDev &d, int bm, int bn)
 {
-    WskDev v{};
-    v.x = d.x; v.w = d.w; v.bias = d.bias; v.res = d.res;
+    WskHead v{};
+    v.x = d.x; v.w = d.w; v.x_bytes = d.x_bytes;
+    v.M = d.M; v.last_nb = (d.N + 15) / 16 - 1; v.steps = (d.K + 31) / 32; v.px = d.ldx * 2;
+    const int tm = (d.M + bm - 1) / bm, tn = (d.N + bn - 1) / bn;
+    v.per = d.raster ? (d.raster == 3 ? tm : tn) / 8 : 0;
+    const Magic inner = magic_of((unsigned)(d.raster == 3 ? tn : tm));
+    v.inner_d = inner.d; v.inner_mul = inner.mul;
+    v.walk = (unsigned)d.raster | inner.shift << 8;
+    return v;
+}
+WskRest wsk_rest(const GemmDev &d)
+{
+    WskRest v{};
+    v.bias = d.bias; v.res = d.res;
     v.f32 = d.y32 != nullptr;
     v.y = v.f32 ? (void *)d.y32 : (void *)d.y;
-    v.x_bytes = d.x_bytes; v.w_bytes = d.w_bytes;
     v.bias_bytes = d.bias ? (unsigned)d.N * 2u : 0u;
     v.res_bytes = d.res ? (unsigned)d.M * (unsigned)d.N * 2u : 0u;
     v.y_bytes = ((unsigned)(d.M - 1) * (unsigned)d.ldy + (unsigned)d.N) * (v.f32 ? 4u : 2u);
-    v.M = d.M; v.N = d.N;
-    v.steps = (d.K + 31) / 32;
-    v.per_wave = (v.steps + nw - 1) / nw;
-    v.px = d.ldx * 2; v.ldy = d.ldy; v.act = d.act;
-    v.dealt = d.raster;
-    const int tm = (d.M + bm - 1) / bm, tn = (d.N + bn - 1) / bn;
-    v.limit = d.raster == 3 ? tm : tn;
-    v.per = d.raster ? (v.limit + 7) / 8 : 0;
-    v.inner = magic_of((unsigned)(d.raster == 3 ? tn : tm));
-    v.k_tail = d.K - 32 * (v.steps - 1);
+    v.N = d.N; v.ldy = d.ldy; v.act = d.act;
+    v.k_tail = d.K - 32 * ((d.K + 31) / 32 - 1);
     v.howo = magic_of((unsigned)(d.Ho * d.Wo)); v.wo = magic_of((unsigned)d.Wo); v.cb = magic_of((unsigned)(d.Cin >= 32 ? d.Cin / 32 : 1));
     v.W = d.W; v.H = d.H; v.KW = d.KW; v.KH = d.KH; v.stride = d.stride; v.pad = d.pad;
-    v.img = d.H * d.W * v.px;
-    v.next_col = v.px - d.Cin * 2;
-    v.next_row = (d.W - d.KW) * v.px;
+    for (int k = 0; k < d.KH && k * d.KW < 32; ++k) v.taps_col |= 1u << (k * d.KW);
+    v.next_col = d.ldx * 2 - d.Cin * 2;
+    v.next_row = (d.W - d.KW) * d.ldx * 2;
     return v;
 }
 
@@ -353,7 +371,7 @@ int wsk_lean_form(const GemmDev &d)
 {
     if (d.nchw_c || d.N % 4 || d.ldy % 4) return -1;
     if (d.KH == 1 && d.KW == 1 && d.stride == 1 && d.pad == 0) return d.K % 32 ? WSK_ROWS_TAIL : WSK_ROWS;
-    return d.Cin % 32 == 0 && d.KH * d.KW <= 32 ? WSK_WINDOW : -1;
+    return d.Cin % 32 == 0 && d.KH * d.KW < 32 ? WSK_WINDOW : -1;
 }
 
 // The form that serves two layers of one launch: their common one, or WINDOW, of which ROWS is a case.
@@ -383,8 +401,12 @@ hipError_t launch_wsk_lean(const GemmDev &d0, const GemmDev &d1, int n0, int dty
     if (!k) return hipErrorInvalidValue;
     int bm, bn;
     conv_wsk_tile(variant, &bm, &bn);
-    WskDev p0 = wsk_dev(d0, nw, bm, bn), p1 = &d1 == &d0 ? p0 : wsk_dev(d1, nw, bm, bn);
-    void *args[] = {&p0, &p1, &n0};
+    WskHead h0 = wsk_head(d0, bm, bn), h1 = wsk_head(d1, bm, bn);
+    // a walk by XCD covers whole eighths of the tiles
+    for (const GemmDev *d : {&d0, &d1})
+        if (d->raster && (d->raster == 3 ? d->tiles_m : d->tiles_n) % 8) return hipErrorInvalidValue;
+    WskRest r0 = wsk_rest(d0), r1 = wsk_rest(d1);
+    void *args[] = {&h0.x, &h0.w, &h0.x_bytes, &h0.M, &h0.last_nb, &h0.steps, &h0.px, &h0.walk, &h0.per, &h0.inner_d, &h0.inner_mul, &n0, &r0, &h1, &r1};
     return hipLaunchKernel(k, dim3((unsigned)tiles), dim3((unsigned)nw * 64), args, conv_wsk_lds_bytes(variant, nw), s);
 }
 

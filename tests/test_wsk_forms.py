@@ -69,7 +69,7 @@ LAYERS = [
     ((1, 1, 1, 0, 64, 64, 64, 0), ROWS), ((1, 1, 1, 0, 72, 64, 64, 0), ROWS_TAIL), ((1, 1, 1, 0, 8, 4, 4, 0), ROWS_TAIL),
     ((1, 1, 2, 0, 64, 64, 64, 0), WINDOW), ((1, 1, 2, 0, 72, 64, 64, 0), GENERAL), ((1, 1, 1, 1, 64, 64, 64, 0), WINDOW),
     ((3, 3, 1, 1, 32, 32, 256, 0), WINDOW), ((3, 3, 1, 1, 48, 32, 32, 0), GENERAL),
-    ((4, 8, 1, 0, 32, 32, 32, 0), WINDOW), ((3, 11, 1, 0, 32, 32, 32, 0), GENERAL),      # 32 taps are the most a word of bits holds
+    ((1, 31, 1, 0, 32, 32, 32, 0), WINDOW), ((4, 8, 1, 0, 32, 32, 32, 0), GENERAL),      # a run of up to 31 taps is one mask instruction
     ((1, 1, 1, 0, 64, 10, 10, 0), GENERAL), ((1, 1, 1, 0, 64, 12, 12, 0), ROWS),         # four channels per thread
     ((7, 7, 2, 3, 8, 64, 64, 3), GENERAL),                                               # reads the caller's planes
 ]
