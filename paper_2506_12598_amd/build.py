@@ -24,7 +24,8 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Xclang", "-tar
          "-packed-fp32-ops", "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 # kernels whose first arguments are to arrive in scalar registers with the wavefront
-MORE_FLAGS = {"k_wsk_lean.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=14"]}
+PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
+MORE_FLAGS = {"k_wsk_lean.hip": PRELOAD, "k_mem.hip": PRELOAD}
 
 
 def _needs(obj: str, deps) -> bool:

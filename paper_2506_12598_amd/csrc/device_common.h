@@ -175,34 +175,42 @@ __device__ __forceinline__ float apply_act_c(float v)
     default:        CALL(ACT_NONE); break;   \
     }
 
-// Sum / max over the 64 lanes of a wavefront; every lane receives the result.
-__device__ __forceinline__ float wave_sum(float v)
+// Sum / max over aligned groups of W lanes (W = 16, 32 or 64) of a wavefront; every lane receives the result of its own group, and every
+// lane has to take part.  Within a row of 16 lanes the operands move inside the vector instruction (DPP), across rows they are
+// traded by v_permlane16_swap / v_permlane32_swap: six exchanges of a few cycles each, where __shfl_xor sends each through
+// the LDS crossbar (about 100 cycles, one after the other).
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int W, typename F>
+__device__ __forceinline__ float group_reduce(float v, F f)
+{
+    typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+    v = f(v, dpp_move<0xb1>(v));             // lane ^ 1 (quad_perm 1,0,3,2)
+    v = f(v, dpp_move<0x4e>(v));             // lane ^ 2 (quad_perm 2,3,0,1)
+    v = f(v, dpp_move<0x141>(v));            // lane i of 8 <-> 7 - i
+    v = f(v, dpp_move<0x140>(v));            // lane i of 16 <-> 15 - i
+    if constexpr (W >= 32) {
+        const u32x2_t s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = f(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    }
+    if constexpr (W == 64) {
+        const u32x2_t s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = f(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    }
     return v;
 }
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-// The same over aligned groups of W lanes (W = 16, 32 or 64): every lane receives the result of its own group.
 template <int W>
 __device__ __forceinline__ float group_sum(float v)
 {
-#pragma unroll
-    for (int o = W / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return group_reduce<W>(v, [](float a, float b) { return a + b; });
 }
 template <int W>
 __device__ __forceinline__ float group_max(float v)
 {
-#pragma unroll
-    for (int o = W / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    return group_reduce<W>(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 }  // namespace eclip

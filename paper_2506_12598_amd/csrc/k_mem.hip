@@ -679,35 +679,74 @@ __global__ __launch_bounds__(256) void gap_finish_kernel(const float *part_in, T
 // wavefront leave lanes idle and very few bytes in flight per wavefront (a 384-element row is 48 chunks of 16 bytes: a
 // quarter of the lanes had nothing to do and a wavefront had 768 bytes on their way); with 16 lanes per row every lane
 // works, the reductions take 4 exchanges instead of 6, and a wavefront has four rows in flight.
+//
+// A launch over the few rows of a batch-1 encoder is one chain of latencies.  The 14 words of arguments arrive in scalar registers
+// with the wavefront; gamma and beta are fetched together with the row, not after the statistics; the reductions stay
+// inside the vector unit (group_reduce).  BERT-base at batch 1 has 25 of these (128 rows of 768): request 467 -> 408 us, 4.65 -> 2.3 us each.
+// One operand of a row kernel: V elements at a byte offset, zeros beyond the end.
+constexpr unsigned ROW_OOB = 0xffffffffu;
+template <typename T, int V> struct RowLoad {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    typedef typename std::conditional<V == 1, unsigned, u32x4>::type Raw;
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ RowLoad(const T *p, unsigned bytes) : r(__builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)(p ? bytes : 0u), 0x00020000)) {}
+    __device__ __forceinline__ Raw get(unsigned off) const
+    {
+        if constexpr (V > 1) return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+        else if constexpr (sizeof(T) == 4) return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+        else return (unsigned)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0) & 0xffffu;
+    }
+    __device__ static __forceinline__ void floats(Raw q, float (&v)[V])
+    {
+        if constexpr (V == 1 && sizeof(T) == 4) v[0] = __uint_as_float(q);
+        else if constexpr (V == 1) v[0] = Cvt<T>::from_bits(q);
+        else
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (sizeof(T) == 4) v[i] = __uint_as_float(q[i]);
+                else { v[2 * i] = Cvt<T>::from_bits(q[i] & 0xffffu); v[2 * i + 1] = Cvt<T>::from_bits(q[i] >> 16); }
+            }
+    }
+};
+
 template <typename T, int V, int NCH, int LPR, bool SOFTMAX>
-__global__ __launch_bounds__(256) void row_kernel(RowArgs a)
+__global__ __launch_bounds__(256) void row_kernel(const T *x, const T *res, const T *gamma, const T *beta, void *y, unsigned rows, int width,
+                                                  float eps, int f32)
 {
     constexpr int RPW = 64 / LPR;                     // rows per wavefront
+    constexpr bool EARLY = NCH <= 4;                  // gamma and beta held in registers from the start
     const int lane = threadIdx.x & 63, sub = lane & (LPR - 1);
-    const long row = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW + lane / LPR;
-    const bool live = row < a.rows;                   // lanes of rows past the end still take part in the exchanges
-    const int nchunk = a.width / V;
-    const T *x = (const T *)a.x + (live ? row : 0) * a.width;
-    const T *r = a.res ? (const T *)a.res + (live ? row : 0) * a.width : nullptr;
-    float v[NCH][V];
-    float s = 0.0f, mx = -INFINITY;
+    const unsigned row = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW + lane / LPR;
+    const bool live = row < rows;                     // lanes of rows past the end still take part in the exchanges
+    const int nchunk = width / V;
+    const unsigned base = (live ? row : 0) * (unsigned)width;      // tensors hold fewer than 2^30 elements
+    // All loads leave together and without a branch: an absent operand has a descriptor of zero bytes and reads as zeros, as do chunks
+    // beyond the row.  (Behind branches the compiler converts every operand right after its load: eight trips to memory in a row.)
+    const unsigned all = rows * (unsigned)width * (unsigned)sizeof(T), one = (unsigned)width * (unsigned)sizeof(T);
+    const RowLoad<T, V> lx(x, all), lr(res, all), lg(gamma, one), lb(beta, one);
+    typename RowLoad<T, V>::Raw xq[NCH], rq[NCH], gq[EARLY ? NCH : 1], bq[EARLY ? NCH : 1];
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
         const int ch = sub + j * LPR;
-        if (ch < nchunk) Pack<T, V>::load(x + ch * V, v[j]);
-    }
-    if (r) {
-#pragma unroll
-        for (int j = 0; j < NCH; ++j) {
-            const int ch = sub + j * LPR;
-            if (ch < nchunk) {
-                float rv[V];
-                Pack<T, V>::load(r + ch * V, rv);
-#pragma unroll
-                for (int i = 0; i < V; ++i) v[j][i] += rv[i];
-            }
+        const unsigned in_row = ch < nchunk ? (unsigned)(ch * V) * (unsigned)sizeof(T) : ROW_OOB;
+        const unsigned off = ch < nchunk ? (base + ch * V) * (unsigned)sizeof(T) : ROW_OOB;
+        xq[j] = lx.get(off);
+        rq[j] = lr.get(off);
+        if constexpr (EARLY && !SOFTMAX) {
+            gq[j] = lg.get(in_row);
+            bq[j] = lb.get(in_row);
         }
     }
+    float v[NCH][V];
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) {
+        float rv[V];
+        RowLoad<T, V>::floats(xq[j], v[j]);
+        RowLoad<T, V>::floats(rq[j], rv);
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[j][i] += rv[i];
+    }
+    float s = 0.0f, mx = -INFINITY;
 #pragma unroll
     for (int j = 0; j < NCH; ++j)
         if (sub + j * LPR < nchunk)
@@ -726,15 +765,15 @@ __global__ __launch_bounds__(256) void row_kernel(RowArgs a)
         scale = 1.0f / es;
         shift = 0.0f;
     } else {
-        const float mean = group_sum<LPR>(s) / (float)a.width;
+        const float mean = group_sum<LPR>(s) / (float)width;
         float q = 0.0f;
 #pragma unroll
         for (int j = 0; j < NCH; ++j)
             if (sub + j * LPR < nchunk)
 #pragma unroll
                 for (int i = 0; i < V; ++i) { const float d = v[j][i] - mean; q += d * d; }
-        const float var = group_sum<LPR>(q) / (float)a.width;
-        scale = rsqrtf(var + a.eps);
+        const float var = group_sum<LPR>(q) / (float)width;
+        scale = rsqrtf(var + eps);
         shift = mean;
     }
     if (!live) return;
@@ -746,24 +785,25 @@ __global__ __launch_bounds__(256) void row_kernel(RowArgs a)
 #pragma unroll
             for (int i = 0; i < V; ++i) o[i] = (v[j][i] - shift) * scale;
             if (!SOFTMAX) {
-                if (a.gamma) {
-                    float g[V];
-                    Pack<T, V>::load((const T *)a.gamma + ch * V, g);
+                float g[V], be[V];
+                RowLoad<T, V>::floats(EARLY ? gq[EARLY ? j : 0] : lg.get((unsigned)(ch * V) * (unsigned)sizeof(T)), g);
+                RowLoad<T, V>::floats(EARLY ? bq[EARLY ? j : 0] : lb.get((unsigned)(ch * V) * (unsigned)sizeof(T)), be);
 #pragma unroll
-                    for (int i = 0; i < V; ++i) o[i] *= g[i];
-                }
-                if (a.beta) {
-                    float be[V];
-                    Pack<T, V>::load((const T *)a.beta + ch * V, be);
+                for (int i = 0; i < V; ++i) o[i] = gamma ? o[i] * g[i] : o[i];
 #pragma unroll
-                    for (int i = 0; i < V; ++i) o[i] += be[i];
-                }
+                for (int i = 0; i < V; ++i) o[i] += be[i];
             }
-            if (a.y32) {
+            const unsigned at = base + ch * V;
+            if (f32) {
+                float *const yf = (float *)y + at;
+                if constexpr (V == 1) {
+                    yf[0] = o[0];
+                } else {
 #pragma unroll
-                for (int i = 0; i < V; ++i) a.y32[row * a.width + ch * V + i] = o[i];
+                    for (int i = 0; i < V; i += 4) *reinterpret_cast<float4 *>(yf + i) = make_float4(o[i], o[i + 1], o[i + 2], o[i + 3]);
+                }
             } else {
-                Pack<T, V>::store((T *)a.y + row * a.width + ch * V, o);
+                Pack<T, V>::store((T *)y + at, o);
             }
         }
     }
@@ -1294,7 +1334,9 @@ static hipError_t launch_row(const RowArgs &a, hipStream_t s)
     // peak); wider rows take a whole wavefront (two rows of 128 chunks per wavefront on 32 lanes each measured slower:
     // LayerNorm over 1024 elements 72 -> 69 %)
 #define ROWK(T, V, NCH, LPR) \
-    hipLaunchKernelGGL((row_kernel<T, V, NCH, LPR, SOFTMAX>), dim3(blocks_for(a.rows, 4 * (64 / LPR))), dim3(256), 0, s, a)
+    hipLaunchKernelGGL((row_kernel<T, V, NCH, LPR, SOFTMAX>), dim3(blocks_for(a.rows, 4 * (64 / LPR))), dim3(256), 0, s, (const T *)a.x,      \
+                       (const T *)a.res, (const T *)a.gamma, (const T *)a.beta, a.y32 ? (void *)a.y32 : a.y, (unsigned)a.rows, a.width, a.eps, \
+                       a.y32 ? 1 : 0)
 #define CALL(T, V)                                                                                  \
     {                                                                                               \
         const int nchunk = a.width / V;                                                             \
