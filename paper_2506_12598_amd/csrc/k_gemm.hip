@@ -217,6 +217,23 @@ static double wsk_whole_cost(long M, long N, long K, int n_cu, int v, int nw)
 // the planner's estimate for one wave-split-K candidate (tuning aid; tile `v`, `nw` wavefronts)
 double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int v, int nw) { return wsk_cost(M, N, K, n_cu, v, nw); }
 
+// Grouped convolutions: 4 or 8 wavefronts, all tiles but 64 x 64.
+GemmPlan conv_wsk_plan_columns(long M, long N, long K, int n_cu, int columns)
+{
+    GemmPlan pl{1, 3, 1, 0, 4, 0};
+    double best = 1e30;
+    for (int v = 0; v < CONV_WSK_VARIANTS; ++v)
+        for (int nw = 4; nw <= 8; nw *= 2) {
+            int bm, bn;
+            conv_wsk_tile(v, &bm, &bn);
+            if (bm * bn > 32 * 64 || (columns && columns % bn)) continue;
+            const double c = wsk_cost(M, N, K, n_cu, v, nw);
+            if (c < best) { best = c; pl = GemmPlan{1, v, 1, (int)(cdiv(M, bm) * cdiv(N, bn)), nw, 0}; }
+        }
+    set_xcd_split(pl, M, N);
+    return pl;
+}
+
 // Every plan worth timing for a problem (eclip_model_tune): all wave-split-K tiles and wavefront counts that fit LDS, and
 // every 8-wavefront or copied LDS tile whole and with K cut in two or four where the workspace allows (the plain tiles were best on
 // none of 900 problems).  Tiles far larger than the problem are left out (a 256-row tile for a 64-row problem only wastes

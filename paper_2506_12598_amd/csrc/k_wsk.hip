@@ -123,6 +123,11 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(GemmDev p0, GemmDev p
         if constexpr (NCHW) a_off0[i] = ((unsigned)(b * p.nchw_c) * (unsigned)(p.H * p.W) + (unsigned)(a_ih0[i] * p.W + a_iw0[i])) * 2u;
         else a_off0[i] = ((unsigned)b * (unsigned)(p.H * p.W) + (unsigned)(a_ih0[i] * p.W + a_iw0[i])) * (unsigned)p.ldx * 2u;
     }
+    if (p.n_groups > 0) {                        // the channels of x that this tile column's group reads
+        const unsigned group = (unsigned)(n_base / (p.N / p.n_groups)) * (unsigned)p.Cin * 2u;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a_off0[i] += group;
+    }
     const unsigned plane = (unsigned)(p.H * p.W) * 2u;            // NCHW: bytes between the planes of two channels
     // weights: 1 KB blocks of 16 rows x 32 k in lane order, so a fragment is one contiguous load
     const int KB = (p.K + 31) >> 5, NB = (p.N + 15) >> 4;

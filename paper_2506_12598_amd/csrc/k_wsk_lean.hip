@@ -42,7 +42,8 @@ struct WskHead {
     unsigned x_bytes;
     int M, last_nb, steps;                   // rows; last 16-row block of the weights; K steps of 32
     int px;                                  // bytes between pixels of x
-    unsigned walk;                           // bits 0-1: GemmPlan::raster 2 or 3 (0: plain); bits 8-15: shift of the division by inner_d
+    unsigned walk;                           // bits 0-1: GemmPlan::raster 2 or 3 (0: plain); bits 8-15: shift of the division by inner_d;
+                                             // bits 16-23: log2 of the tile columns of a group of channels, 255: not a power of two (group)
     int per;                                 // tile columns (rows) per XCD
     unsigned inner_d, inner_mul;             // tiles along the other dimension, and the multiplier of the division by them
 };
@@ -53,6 +54,7 @@ struct WskRest {
     int N, ldy;                              // elements between rows of y
     int act, f32;                            // f32: y holds floats
     int k_tail;                              // ROWS_TAIL: k's of the last step
+    Magic group;                             // gconv_mfma_kernel: tile columns of a group
     // WINDOW
     Magic howo, wo, cb;                      // output pixels per image and per row; K steps per tap
     int W, H, KW, KH, stride, pad;
@@ -60,12 +62,13 @@ struct WskRest {
     int next_col, next_row;                  // added to the byte offset from a tap's last step to the next tap's first, and at a row's end
 };
 
-template <typename T, int TM, int TN, int NW, int D, int FORM>
-__global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int last_nb, int steps,
-                                                           int px, unsigned walk, int per, unsigned inner_d, unsigned inner_mul, int n0,
-                                                           WskRest r0, WskHead h1, WskRest r1)
+// GROUPED: the channels fall into groups and a tile column's K runs over its own group's input channels, which are consecutive
+// and as many as a window tap has K steps of.
+template <typename T, int TM, int TN, int NW, int D, int FORM, bool GROUPED>
+__device__ __forceinline__ void wsk_body(float *red, const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int last_nb, int steps,
+                                         int px, unsigned walk, int per, unsigned inner_d, unsigned inner_mul, int n0,
+                                         const WskRest &r0, const WskHead &h1, const WskRest &r1)
 {
-    extern __shared__ __attribute__((aligned(16))) float red[];    // [NW][TM*TN][64][4]
     constexpr int BM = TM * 16, BN = TN * 16, BLK = TM * TN;
     constexpr unsigned OOB = 0xffffffffu;
     // one launch can carry two independent layers: workgroups 0 .. n0-1 work on the first, the rest on the second
@@ -81,7 +84,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(const uint16_t *x, co
     int tile_m, tile_n;
     {
         const unsigned dealt = walk & 3u, xcd = dealt ? bid & 7 : 0, q = dealt ? bid >> 3 : bid;
-        const unsigned r = div_by(q, Magic{inner_d, inner_mul, walk >> 8}), rem = q - r * inner_d;
+        const unsigned r = div_by(q, Magic{inner_d, inner_mul, walk >> 8 & 255u}), rem = q - r * inner_d;
         const unsigned a = xcd * (unsigned)per + r;
         tile_m = dealt == 3 ? a : rem;
         tile_n = dealt == 3 ? rem : a;
@@ -93,6 +96,13 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(const uint16_t *x, co
 
     // this wavefront's K steps
     const int per_wave = (steps + NW - 1) / NW, ks0 = wave * per_wave, n_steps = min(per_wave, steps - ks0);
+
+    // byte offset of the tile's group in a pixel
+    unsigned group = 0;
+    if constexpr (GROUPED) {
+        const unsigned shift = walk >> 16, idx = shift == 255u ? div_by((unsigned)tile_n, p.group) : (unsigned)tile_n >> shift;
+        group = idx * (unsigned)(FORM == WSK_WINDOW ? (int)p.cb.d : steps) * 64u;
+    }
 
     // im2col operand in tile order: lane l takes row l >> 2, 16-byte chunk l & 3 of the step's 64 bytes; it changes lanes before use
     const int row = lane >> 2, g = lane & 3;
@@ -113,7 +123,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(const uint16_t *x, co
             const unsigned b = div_by((unsigned)m, p.howo), r = m - b * p.howo.d;
             const unsigned oh = div_by(r, p.wo), ow = r - oh * p.wo.d;
             const int ih = (int)oh * p.stride - p.pad, iw = (int)ow * p.stride - p.pad;
-            a_off[i] = (unsigned)(((int)b * p.H + ih) * p.W + iw) * (unsigned)px + (unsigned)g * 16u;
+            a_off[i] = (unsigned)(((int)b * p.H + ih) * p.W + iw) * (unsigned)px + (unsigned)g * 16u + group;
             // taps of columns lo_w .. hi_w - 1 and rows lo_h .. hi_h - 1 lie inside the image
             const int lo_w = max(-iw, 0), n_w = max(min(p.W - iw, p.KW) - lo_w, 0);
             const int lo_h = max(-ih, 0), n_h = max(min(p.H - ih, p.KH) - lo_h, 0);
@@ -125,7 +135,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(const uint16_t *x, co
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int m = m_base + i * 16 + row;
-            a_off[i] = m < M ? (unsigned)m * (unsigned)px + (unsigned)g * 16u : OOB;
+            a_off[i] = m < M ? (unsigned)m * (unsigned)px + (unsigned)g * 16u + group : OOB;
         }
     }
     // weights: 1 KB blocks of 16 rows x 32 k in lane order; tile columns beyond the last block read that one again (their results
@@ -290,6 +300,25 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(const uint16_t *x, co
     }
 }
 
+#define WSK_ARGS                                                                                                                          \
+    const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int last_nb, int steps, int px, unsigned walk, int per, unsigned inner_d, \
+        unsigned inner_mul, int n0, WskRest r0, WskHead h1, WskRest r1
+template <typename T, int TM, int TN, int NW, int D, int FORM>
+__global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(WSK_ARGS)
+{
+    extern __shared__ __attribute__((aligned(16))) float red[];    // [NW][TM*TN][64][4]
+    wsk_body<T, TM, TN, NW, D, FORM, false>(red, x, w, x_bytes, M, last_nb, steps, px, walk, per, inner_d, inner_mul, n0, r0, h1, r1);
+}
+// Grouped convolutions whose super-groups (k_gconv.hip) are multiples of a tile's channels, or one: the same, each tile column on
+// its own channels of x.
+template <typename T, int TM, int TN, int NW, int D, int FORM>
+__global__ __launch_bounds__(NW * 64) void gconv_mfma_kernel(WSK_ARGS)
+{
+    extern __shared__ __attribute__((aligned(16))) float red[];
+    wsk_body<T, TM, TN, NW, D, FORM, true>(red, x, w, x_bytes, M, last_nb, steps, px, walk, per, inner_d, inner_mul, n0, r0, h1, r1);
+}
+#undef WSK_ARGS
+
 // K steps in flight per wavefront: as many as fit about 100 registers (16 wavefronts leave 128 per lane)
 template <int TM, int TN, int NW> struct LeanDepth {
     static constexpr int value = (TM + TN) <= 2 ? (NW == 16 ? 8 : 12) : (TM + TN) <= 3 ? (NW == 16 ? 6 : 8) : (TM + TN) <= 4 ? (NW == 16 ? 4 : 6)
@@ -306,9 +335,15 @@ WskHead wsk_head(const GemmDev &d, int bm, int bn)
     const Magic inner = magic_of((unsigned)(d.raster == 3 ? tn : tm));
     v.inner_d = inner.d; v.inner_mul = inner.mul;
     v.walk = (unsigned)d.raster | inner.shift << 8;
+    if (d.n_groups > 1) {
+        const unsigned columns = (unsigned)(d.N / d.n_groups / bn);
+        v.walk |= (columns & (columns - 1) ? 255u : (unsigned)__builtin_ctz(columns)) << 16;
+    } else if (d.n_groups == 1) {
+        v.walk |= 31u << 16;                 // every tile column is in it
+    }
     return v;
 }
-WskRest wsk_rest(const GemmDev &d)
+WskRest wsk_rest(const GemmDev &d, int bn)
 {
     WskRest v{};
     v.bias = d.bias; v.res = d.res;
@@ -319,6 +354,7 @@ WskRest wsk_rest(const GemmDev &d)
     v.y_bytes = ((unsigned)(d.M - 1) * (unsigned)d.ldy + (unsigned)d.N) * (v.f32 ? 4u : 2u);
     v.N = d.N; v.ldy = d.ldy; v.act = d.act;
     v.k_tail = d.K - 32 * ((d.K + 31) / 32 - 1);
+    v.group = magic_of((unsigned)(d.n_groups > 1 ? d.N / d.n_groups / bn : 1));
     v.howo = magic_of((unsigned)(d.Ho * d.Wo)); v.wo = magic_of((unsigned)d.Wo); v.cb = magic_of((unsigned)(d.Cin >= 32 ? d.Cin / 32 : 1));
     v.W = d.W; v.H = d.H; v.KW = d.KW; v.KH = d.KH; v.stride = d.stride; v.pad = d.pad;
     for (int k = 0; k < d.KH && k * d.KW < 32; ++k) v.taps_col |= 1u << (k * d.KW);
@@ -328,9 +364,15 @@ WskRest wsk_rest(const GemmDev &d)
 }
 
 template <typename T, int TM, int TN, int NW>
-const void *kernel_of(int form)
+const void *kernel_of(int form, bool grouped)
 {
     constexpr int D = LeanDepth<TM, TN, NW>::value;
+    if (grouped) {                               // see conv_wsk_plan_columns
+        if constexpr (TM * TN > 8 || NW > 8) return nullptr;
+        else if (form == WSK_ROWS) return (const void *)gconv_mfma_kernel<T, TM, TN, NW, D, WSK_ROWS>;
+        else if (form == WSK_WINDOW) return (const void *)gconv_mfma_kernel<T, TM, TN, NW, D, WSK_WINDOW>;
+        else return nullptr;
+    }
     switch (form) {
     case WSK_ROWS: return (const void *)conv_wsk_kernel<T, TM, TN, NW, D, WSK_ROWS>;
     case WSK_ROWS_TAIL: return (const void *)conv_wsk_kernel<T, TM, TN, NW, D, WSK_ROWS_TAIL>;
@@ -338,27 +380,27 @@ const void *kernel_of(int form)
     }
 }
 template <typename T, int TM, int TN>
-const void *kernel_of(int nw, int form)
+const void *kernel_of(int nw, int form, bool grouped)
 {
     switch (nw) {
-    case 4: return kernel_of<T, TM, TN, 4>(form);
-    case 8: return kernel_of<T, TM, TN, 8>(form);
+    case 4: return kernel_of<T, TM, TN, 4>(form, grouped);
+    case 8: return kernel_of<T, TM, TN, 8>(form, grouped);
     case 16:
-        if constexpr (TM * TN <= 8) return kernel_of<T, TM, TN, 16>(form);
+        if constexpr (TM * TN <= 8) return kernel_of<T, TM, TN, 16>(form, grouped);
         return nullptr;                          // 16 partial 64x64 tiles would not fit in LDS
     default: return nullptr;
     }
 }
 template <typename T>
-const void *kernel_of(int variant, int nw, int form)
+const void *kernel_of(int variant, int nw, int form, bool grouped)
 {
     switch (variant) {
-    case 0: return kernel_of<T, 1, 4>(nw, form);
-    case 1: return kernel_of<T, 2, 4>(nw, form);
-    case 2: return kernel_of<T, 4, 4>(nw, form);
-    case 3: return kernel_of<T, 1, 1>(nw, form);
-    case 4: return kernel_of<T, 1, 2>(nw, form);
-    case 5: return kernel_of<T, 2, 2>(nw, form);
+    case 0: return kernel_of<T, 1, 4>(nw, form, grouped);
+    case 1: return kernel_of<T, 2, 4>(nw, form, grouped);
+    case 2: return kernel_of<T, 4, 4>(nw, form, grouped);
+    case 3: return kernel_of<T, 1, 1>(nw, form, grouped);
+    case 4: return kernel_of<T, 1, 2>(nw, form, grouped);
+    case 5: return kernel_of<T, 2, 2>(nw, form, grouped);
     default: return nullptr;
     }
 }
@@ -387,7 +429,8 @@ hipError_t wsk_lean_init()
     for (int v = 0; v < CONV_WSK_VARIANTS; ++v)
         for (int nw = 4; nw <= 16; nw *= 2)
             for (int form = 0; form < WSK_FORMS; ++form)
-                for (const void *k : {kernel_of<bf16_t>(v, nw, form), kernel_of<f16_t>(v, nw, form)}) {
+                for (const void *k : {kernel_of<bf16_t>(v, nw, form, false), kernel_of<f16_t>(v, nw, form, false), kernel_of<bf16_t>(v, nw, form, true),
+                                      kernel_of<f16_t>(v, nw, form, true)}) {
                     if (!k) continue;
                     const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
                     if (e != hipSuccess) return e;
@@ -397,7 +440,7 @@ hipError_t wsk_lean_init()
 
 hipError_t launch_wsk_lean(const GemmDev &d0, const GemmDev &d1, int n0, int dtype, int form, int variant, int nw, int tiles, hipStream_t s)
 {
-    const void *k = dtype == DT_BF16 ? kernel_of<bf16_t>(variant, nw, form) : kernel_of<f16_t>(variant, nw, form);
+    const void *k = dtype == DT_BF16 ? kernel_of<bf16_t>(variant, nw, form, d0.n_groups > 0) : kernel_of<f16_t>(variant, nw, form, d0.n_groups > 0);
     if (!k) return hipErrorInvalidValue;
     int bm, bn;
     conv_wsk_tile(variant, &bm, &bn);
@@ -405,7 +448,8 @@ hipError_t launch_wsk_lean(const GemmDev &d0, const GemmDev &d1, int n0, int dty
     // a walk by XCD covers whole eighths of the tiles
     for (const GemmDev *d : {&d0, &d1})
         if (d->raster && (d->raster == 3 ? d->tiles_m : d->tiles_n) % 8) return hipErrorInvalidValue;
-    WskRest r0 = wsk_rest(d0), r1 = wsk_rest(d1);
+    WskRest r0 = wsk_rest(d0, bn), r1 = wsk_rest(d1, bn);
+    if (d0.n_groups > 1 && d0.N / d0.n_groups % bn) return hipErrorInvalidValue;
     void *args[] = {&h0.x, &h0.w, &h0.x_bytes, &h0.M, &h0.last_nb, &h0.steps, &h0.px, &h0.walk, &h0.per, &h0.inner_d, &h0.inner_mul, &n0, &r0, &h1, &r1};
     return hipLaunchKernel(k, dim3((unsigned)tiles), dim3((unsigned)nw * 64), args, conv_wsk_lds_bytes(variant, nw), s);
 }

@@ -60,6 +60,8 @@ GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats);
 // every plan worth timing for a problem (measured plan selection)
 std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, size_t ws_floats);
 double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int variant, int nw);   // the planner's estimate, us without the launch
+// the wave-split-K shape of the lowest estimate whose tile columns divide `columns` channels (0: any)
+GemmPlan conv_wsk_plan_columns(long M, long N, long K, int n_cu, int columns);
 // *n_launched (optional) is increased by the number of kernels launched (2 when K is split).
 hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &p, const SeDeal &deal, hipStream_t s, uint32_t *n_launched);
 // Two layers that do not depend on each other in one launch (wave-split-K kernel only).  conv_gemm_plan_pair takes
@@ -108,7 +110,8 @@ hipError_t launch_gconv(const GConvArgs &a, int n_cu, hipStream_t s);
 // must then be in the direct kernel's layout, otherwise in the super-group blocks described in k_gconv.hip.
 bool gconv_mfma_pick(int groups, int cig, int cog, int *S_out);
 hipError_t launch_gconv_mfma(const GConvArgs &a, int S, int n_cu, hipStream_t s);
-long gconv_mfma_workgroups(long M, int groups, int cog, int S, int n_cu);   // the grid launch_gconv_mfma uses (M = B*Ho*Wo)
+GemmPlan gconv_mfma_plan(const GConvArgs &a, int S, int n_cu);               // tile and grid launch_gconv_mfma uses
+const char *gconv_mfma_kernel_name(const GConvArgs &a);
 // y[m][0 .. c0) = a[m][:], y[m][c0 .. c0 + c1) = b[m][:]
 hipError_t launch_concat(const void *a, const void *b, void *y, long rows, int c0, int c1, int dtype, hipStream_t s);
 // y[m][0 .. c) = x[m][:], rows of y ld channels apart (16-bit types, c and ld multiples of 8)

@@ -63,3 +63,20 @@ def test_an_infinite_row_stays_in_its_row(k):
     x[0, 11, :] = 0
     exp = np.delete(orc.run_model(m, x).reshape(35, 40), 11, axis=0)
     assert rel_to_range(rows, exp) <= 2e-4
+
+
+@pytest.mark.parametrize("cin,cout,groups,k,stride,h,w,batch", [
+    (64, 64, 2, 7, 1, 9, 8, 2),           # 49 taps: the general form
+    (64, 64, 2, 5, 2, 9, 8, 2),           # 25 taps
+    (192, 240, 1 * 3, 1, 1, 7, 9, 3),     # 64 -> 80 channels per group: five tile columns of 16
+    (96, 96, 3, 3, 1, 5, 6, 1),           # 32 -> 32 channels per group
+    (480, 128, 4, 1, 1, 7, 7, 2),         # one super-group of 480 channels
+])
+@pytest.mark.parametrize("dt", [wl.DT_BF16, wl.DT_F16])
+def test_grouped(cin, cout, groups, k, stride, h, w, batch, dt):
+    m = wl.single_layer("conv", dt, seed=k + cin, cin=cin, cout=cout, h=h, w=w, k=k, stride=stride, pad=k // 2, groups=groups, act=wl.ACT_RELU,
+                        bias_std=0.5)
+    x = wl.make_input(m, batch)
+    got = run_gpu(m, x)
+    assert np.isfinite(got).all()
+    assert rel_to_range(got, orc.run_model(m, x)) <= (2.0 ** -8 if dt == wl.DT_BF16 else 2.0 ** -11)
