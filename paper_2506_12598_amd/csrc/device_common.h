@@ -22,6 +22,19 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// n / d for n < 2^31: (2 n * mul >> 32) >> shift with mul = floor(2^(31 + shift) / d) + 1, shift = ceil(log2 d)
+struct Magic {
+    unsigned d, mul, shift;
+};
+inline Magic magic_of(unsigned d)
+{
+    Magic m{d, 0, 0};
+    while ((1ull << m.shift) < d) ++m.shift;
+    m.mul = (unsigned)((1ull << (31 + m.shift)) / d + 1);
+    return m;
+}
+__device__ __forceinline__ unsigned div_by(unsigned n, const Magic &m) { return __umulhi(n + n, m.mul) >> m.shift; }
+
 enum { ACT_NONE = 0, ACT_RELU = 1, ACT_RELU6 = 2, ACT_GELU = 3 };
 
 // 16-bit storage types are carried as raw bit patterns; the tag types select the conversions.
@@ -202,6 +215,18 @@ __device__ __forceinline__ float group_reduce(float v, F f)
     }
     return v;
 }
+// The same over the four lanes that share lane & 15.
+template <typename F>
+__device__ __forceinline__ float rows_reduce(float v, F f)
+{
+    typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+    const u32x2_t s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    const u32x2_t t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return f(__uint_as_float(t[0]), __uint_as_float(t[1]));
+}
+__device__ __forceinline__ float rows_sum(float v) { return rows_reduce(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float rows_max(float v) { return rows_reduce(v, [](float a, float b) { return fmaxf(a, b); }); }
 template <int W>
 __device__ __forceinline__ float group_sum(float v)
 {

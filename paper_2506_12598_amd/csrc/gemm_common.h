@@ -22,18 +22,6 @@ struct GemmDev {
                                              // a channel range of a wider buffer: concatenation in place); res is null when ldy != N
 };
 
-// n / d for n < 2^31: (2 n * mul >> 32) >> shift with mul = floor(2^(31 + shift) / d) + 1, shift = ceil(log2 d)
-struct Magic {
-    unsigned d, mul, shift;
-};
-inline Magic magic_of(unsigned d)
-{
-    Magic m{d, 0, 0};
-    while ((1ull << m.shift) < d) ++m.shift;
-    m.mul = (unsigned)((1ull << (31 + m.shift)) / d + 1);
-    return m;
-}
-
 template <typename T> struct Mma;
 template <> struct Mma<bf16_t> {
     __device__ static __forceinline__ f32x4 run(uint4 a, uint4 b, f32x4 c)

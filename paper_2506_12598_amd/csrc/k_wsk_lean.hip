@@ -29,7 +29,6 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 enum { WSK_ROWS, WSK_ROWS_TAIL, WSK_WINDOW, WSK_FORMS };
 
-__device__ __forceinline__ unsigned div_by(unsigned n, const Magic &m) { return __umulhi(n + n, m.mul) >> m.shift; }
 
 // n bits from bit `at` on; n < 32
 __device__ __forceinline__ unsigned bits_from(int at, int n) { return ((1u << n) - 1u) << (at & 31); }
