@@ -52,7 +52,7 @@ def build(force: bool = False, verbose: bool = False) -> str:
         return obj
 
     # the slowest translation units first, so that the pool stays full to the end
-    jobs = [("k_gemm_pp.hip", [f"-DECLIP_PP_ID={i}"], f".{i}") for i in pp_tile_ids()] + [(src, MORE_FLAGS.get(src, []), "") for src in SOURCES]
+    jobs = [("k_gemm_pp.hip", [f"-DECLIP_PP_ID={i}"] + PRELOAD, f".{i}") for i in pp_tile_ids()] + [(src, MORE_FLAGS.get(src, []), "") for src in SOURCES]
     with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(compile_one, jobs))
     if force or _needs(LIB, objs):

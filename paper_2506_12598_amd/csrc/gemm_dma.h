@@ -20,13 +20,14 @@
 
 namespace eclip {
 
-// Copies 16 bytes per lane from `rsrc` (byte offset voff + soff; zeros beyond its end) to LDS byte lds + 16 * lane.  Written out
+// Copies 16 bytes per lane from `rsrc` (byte offset voff + soff; zeros beyond its end) to LDS byte lds + AT + 16 * lane.  Written out
 // because the compiler would otherwise wait for every such load before any later LDS read; the waits are explicit.  m0 holds the
 // LDS address of the copy and belongs to the compiler, which uses it too: it is named as overwritten.
+template <unsigned AT>
 __device__ __forceinline__ void dma_lds16(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff), "n"(AT) : "memory", "m0", "scc");
 }
 
 // Waits until at most VM of this wavefront's memory accesses and (LGKM) none of its LDS accesses are outstanding, then for all
@@ -55,8 +56,8 @@ template <typename T> __device__ __forceinline__ void mma_agpr(uint4 a, uint4 b,
 // of a branch per store, accumulators taken block row by block row.
 // (256 x 192 tile: 5.5 us with
 // the general epilogue, 5.0 with this one.  Passing the accumulators through LDS to a short rolled loop was slower, 7 us.)
-template <typename T, int BM, int BN, int WM, int WN, int TM, int TN, int ACT, bool RES>
-__device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][TN], int m_base, int n_base, int wm, int wn)
+template <typename T, int BM, int BN, int WM, int WN, int TM, int TN, int ACT, bool RES, bool EARLY>
+__device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][TN], const u32x4 (&bq)[TN / 2], int m_base, int n_base, int wm, int wn)
 {
     static_assert(TN % 2 == 0, "pairs of blocks");
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -73,7 +74,10 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
         off[jp] = n0 + 32 * jp < p.N ? ((unsigned)m0 * (unsigned)p.ldy + (unsigned)(n0 + 32 * jp)) * 2u : OOB;
 #pragma unroll
         for (int e = 0; e < 8; ++e) bv[jp][e] = 0.f;
-        if (p.bias && n0 + 32 * jp < p.N) Pack<T, 8>::load(reinterpret_cast<const T *>(p.bias) + n0 + 32 * jp, bv[jp]);
+        if constexpr (EARLY) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { bv[jp][2 * e] = Cvt<T>::from_bits(bq[jp][e] & 0xffffu); bv[jp][2 * e + 1] = Cvt<T>::from_bits(bq[jp][e] >> 16); }
+        } else if (p.bias && n0 + 32 * jp < p.N) Pack<T, 8>::load(reinterpret_cast<const T *>(p.bias) + n0 + 32 * jp, bv[jp]);
     });
     const unsigned row16 = 32u * (unsigned)p.ldy;
     u32x4 rq[2][TN / 2];
@@ -130,9 +134,40 @@ __device__ __forceinline__ void dma_touch(u32x4 rsrc, unsigned voff, unsigned so
                  :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
 
-template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE>
-__global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1 : 2) void conv_gemm_dma_kernel(GemmDev p, SeDeal deal)
+// Raster, from bit 8 on the shift of the division by the tiles of the walk's first dimension, and two flags: pixel m is row m (stride 1,
+// no padding; asked for 1 x 1 windows), the workgroups are dealt (se_deal.h).
+enum : unsigned { DMA_ROWS = 1u << 16, DMA_DEALT = 1u << 17 };
+inline unsigned dma_walk(const GemmDev &d, const SeDeal &deal)
 {
+    return (unsigned)d.raster | d.fast.shift << 8 | (d.stride == 1 && d.pad == 0 ? DMA_ROWS : 0u) | (deal.level ? DMA_DEALT : 0u);
+}
+
+// A position in the ring of stages: a constant, or a number carried in a register.
+template <typename S> struct RingPos {
+    static constexpr unsigned fixed = S::value;
+    __device__ static __forceinline__ unsigned moving(S) { return 0u; }
+};
+template <> struct RingPos<unsigned> {
+    static constexpr unsigned fixed = 0u;
+    __device__ static __forceinline__ unsigned moving(unsigned s) { return s; }
+};
+
+// n bits (0 to 32) from bit `at` on
+__device__ __forceinline__ unsigned bits_run(int at, int n) { return (n >= 32 ? ~0u : (1u << n) - 1u) << (at & 31); }
+
+template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE>
+__global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 1024 ? 1 : 2) void conv_gemm_dma_kernel(const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int N, int K, int ldx, int kt_per, unsigned walk, unsigned tiles,
+                          unsigned fast_d, unsigned fast_mul, GemmDev p, SeDeal deal)
+{
+    // What the first copies need comes as 14 words of separate arguments, which the hardware puts into scalar registers before the
+    // wavefront starts (dma_walk packs the last things); what the other forms need beyond that is fetched together.
+    p.x = x; p.w = w; p.x_bytes = x_bytes; p.M = M; p.N = N; p.K = K; p.ldx = ldx; p.kt_per = kt_per; p.KT = (K + BK - 1) / BK;
+    p.raster = (int)(walk & 255u);
+    p.fast = Magic{fast_d, fast_mul, walk >> 8 & 255u};
+    p.w_bytes = (unsigned)((N + 15) >> 4) * (unsigned)((K + 31) >> 5) * 1024u;
+    if constexpr (AMODE != A_MATRIX)
+        asm volatile("" : "+s"(p.H), "+s"(p.W), "+s"(p.Cin), "+s"(p.KH), "+s"(p.KW), "+s"(p.stride), "+s"(p.pad), "+s"(p.howo.d), "+s"(p.howo.mul),
+                     "+s"(p.howo.shift), "+s"(p.wo.d), "+s"(p.wo.mul), "+s"(p.wo.shift));
     constexpr int NW = WM * WN, KS = BK / 32;                           // KS: matrix instructions along K per step and block
     static_assert(KS == 1 || KS == 2, "K step of 32 or 64");
     constexpr int TM = BM / WM / 16, TN = BN / WN / 16, NM = TM * TN;
@@ -147,8 +182,8 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     int tile_m, tile_n;
-    const uint32_t bid = se_dealt_block(deal, blockIdx.x);
-    if (bid == 0xffffffffu || !gemm_tile_of(p, bid, tile_m, tile_n)) return;
+    const uint32_t bid = walk & DMA_DEALT ? se_dealt_block(deal, blockIdx.x) : blockIdx.x;
+    if (bid == 0xffffffffu || !gemm_tile_of(p, tiles, bid, tile_m, tile_n)) return;
     const int m_base = tile_m * BM, n_base = tile_n * BN;
     constexpr unsigned OOB = 0xffffffffu;
     u32x4 rx, rw;
@@ -157,7 +192,7 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
 
     // ---- per-lane addressing that does not change along K: copy i of this wavefront is rows RPC (AI * wave + i) .. of the tile
     const int KB = (p.K + 31) >> 5, NB = (p.N + 15) >> 4;
-    const int HoWo = p.Ho * p.Wo;
+    const bool rows = walk & DMA_ROWS;                                // A_MATRIX: row m of the operand is pixel m
     bool a_ok[AI];
     unsigned a_off[AI];                      // byte offset of this lane's chunk at window tap (0, 0), channel 0 (modulo 2^32 when padded)
     int a_ih0[AI], a_iw0[AI];
@@ -171,11 +206,15 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
         if (AMODE == A_GENERAL) kc = chunk * 8;
         a_ok[i] = m < p.M;
         const int mm = a_ok[i] ? m : 0;
-        const int b = mm / HoWo, r = mm - b * HoWo;
-        const int oh = r / p.Wo, ow = r - oh * p.Wo;
-        a_ih0[i] = oh * p.stride - p.pad;
-        a_iw0[i] = ow * p.stride - p.pad;
-        a_off[i] = ((unsigned)b * (unsigned)(p.H * p.W) + (unsigned)(a_ih0[i] * p.W + a_iw0[i])) * (unsigned)p.ldx * 2u;
+        if (AMODE == A_MATRIX && rows) {
+            a_off[i] = (unsigned)mm * (unsigned)p.ldx * 2u;
+        } else {
+            const int b = (int)div_by((unsigned)mm, p.howo), r = mm - b * (int)p.howo.d;
+            const int oh = (int)div_by((unsigned)r, p.wo), ow = r - oh * (int)p.wo.d;
+            a_ih0[i] = oh * p.stride - p.pad;
+            a_iw0[i] = ow * p.stride - p.pad;
+            a_off[i] = (unsigned)((b * p.H + a_ih0[i]) * p.W + a_iw0[i]) * (unsigned)p.ldx * 2u;
+        }
         if (AMODE != A_GENERAL) a_off[i] += (unsigned)chunk * 16u;
         if (AMODE == A_MATRIX && !a_ok[i]) a_off[i] = OOB;
     }
@@ -184,19 +223,16 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
     // waits out every hop between its vector and scalar halves (128 x 128 tile, 3 x 3 window, 72 K steps: 36.6 -> 33.0 us).
     unsigned a_out[AI];
     if (AMODE == A_UNIFORM) {
-        unsigned cols[AI];                                              // bit kw: the column is outside
-#pragma unroll
-        for (int i = 0; i < AI; ++i) { cols[i] = 0u; a_out[i] = 0u; }
+        unsigned starts = 0;                                            // the first tap of every window row
 #pragma unroll 1
-        for (int w = 0; w < p.KW; ++w)
+        for (int h = 0; h < p.KH; ++h) starts |= 1u << (h * p.KW);
 #pragma unroll
-            for (int i = 0; i < AI; ++i) cols[i] |= ((unsigned)(a_iw0[i] + w) < (unsigned)p.W ? 0u : 1u) << w;
-        const unsigned all = p.KW == 32 ? ~0u : (1u << p.KW) - 1u;
-#pragma unroll 1
-        for (int h = 0; h < p.KH; ++h)
-#pragma unroll
-            for (int i = 0; i < AI; ++i)
-                a_out[i] |= (a_ok[i] && (unsigned)(a_ih0[i] + h) < (unsigned)p.H ? cols[i] : all) << (h * p.KW);
+        for (int i = 0; i < AI; ++i) {
+            // taps of columns lo_w .. and rows lo_h .. lie inside the image: a run of bits repeated in a run of rows
+            const int lo_w = max(-a_iw0[i], 0), n_w = max(min(p.W - a_iw0[i], p.KW) - lo_w, 0);
+            const int lo_h = max(-a_ih0[i], 0), n_h = max(min(p.H - a_ih0[i], p.KH) - lo_h, 0);
+            a_out[i] = a_ok[i] ? ~(bits_run(lo_w, n_w) * (starts & bits_run(lo_h * p.KW, n_h * p.KW))) : ~0u;
+        }
     }
     unsigned b_off[BI];                      // copy i: weight block (row block (BI * wave + i) / KS, k block (BI * wave + i) % KS of the step)
 #pragma unroll
@@ -219,44 +255,54 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
     int tap = kh * p.KW + kw;                                         // A_UNIFORM (uniform)
     const int k_lim = min(p.K, kt_end * BK), kb_lim = min(KB, kt_end * KS);
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)smem;
-    // copies beyond the end of the slice read nothing (their descriptor is empty): the loads in flight stay countable
-    auto copy_a = [&](auto ic, unsigned slot) {
+    // Copies beyond the end of the slice read nothing: the descriptors are emptied when the slice ends, so the loads in flight stay
+    // countable.  LDS positions are a scalar per wavefront and a constant.
+    const unsigned lds_a = lds0 + (unsigned)(AI * wave) * 1024u, lds_b = lds0 + BM * BK * 2u + (unsigned)(BI * wave) * 1024u;
+    unsigned a_soff = (unsigned)kt_begin * (BK * 2u), b_soff = (unsigned)kt_begin * (KS * 1024u);
+    auto copy_a = [&](auto ic, auto slot) {
         constexpr int i = decltype(ic)::value;
-        u32x4 r = rx;
-        if (AMODE != A_GENERAL) r.z = kt_run < kt_end ? p.x_bytes : 0u;
         unsigned v = a_off[i], s = 0;
-        if (AMODE == A_MATRIX) s = (unsigned)kt_run * (BK * 2u);
+        if (AMODE == A_MATRIX) s = a_soff;
         else if (AMODE == A_UNIFORM) v = (v + tap_off) | (unsigned)((int)(a_out[i] << (31 - tap)) >> 31);
         else {
             const int ok = (int)a_ok[i] & (int)((unsigned)(a_ih0[i] + kh) < (unsigned)p.H) & (int)((unsigned)(a_iw0[i] + kw) < (unsigned)p.W) &
                            (int)(k_run < k_lim);
             v = ok ? v + tap_off : OOB;
         }
-        dma_lds16(r, v, s, lds0 + slot + (unsigned)(AI * wave + i) * 1024u);
+        dma_lds16<RingPos<decltype(slot)>::fixed + i * 1024u>(rx, v, s, lds_a + RingPos<decltype(slot)>::moving(slot));
     };
-    auto copy_b = [&](auto ic, unsigned slot) {
+    auto copy_b = [&](auto ic, auto slot) {
         constexpr int i = decltype(ic)::value;
         u32x4 r = rw;
-        const int kb = kt_run * KS + (AMODE == A_GENERAL ? (BI * wave + i) % KS : 0);
-        r.z = kb < kb_lim ? p.w_bytes : 0u;
-        dma_lds16(r, b_off[i], (unsigned)kt_run * (KS * 1024u), lds0 + slot + BM * BK * 2u + (unsigned)(BI * wave + i) * 1024u);
+        if (AMODE == A_GENERAL) r.z = kt_run * KS + (BI * wave + i) % KS < kb_lim ? p.w_bytes : 0u;
+        const unsigned soff = AMODE == A_GENERAL ? (unsigned)__builtin_amdgcn_readfirstlane((int)b_soff) : b_soff;   // (of 128 x 64 x 32 it lands in a vector register)
+        dma_lds16<RingPos<decltype(slot)>::fixed + i * 1024u>(r, b_off[i], soff, lds_b + RingPos<decltype(slot)>::moving(slot));
     };
     // The weights of a large model are in no cache: the workgroups that share a tile column (and an L2) take turns touching the
     // lines of the step PD steps ahead of the copies (BERT-large FFN2 on 96 CUs, served: 36 -> 31 us; with the weights in the
     // last-level cache it costs 1 us of 28).
     constexpr int PD = 6, LINES = BN * BK / 64;                         // 128-byte lines of a step's weights
     const int share = p.raster == 2 ? p.tiles_m : (p.tiles_m + 7) >> 3, part = p.raster == 2 ? tile_m : tile_m >> 3;
-    int turn = part;
     const unsigned t_line = (unsigned)(wave * 64 + lane), t_blk = t_line / (8 * KS);
     const unsigned t_off = t_line < LINES ? ((unsigned)((n_base >> 4) + (int)t_blk) * (unsigned)KB * 1024u + (t_line % (8 * KS)) * 128u) : OOB;
+    int turn = kt_begin + part + PD < kt_end ? part : 1 << 30;        // steps until this workgroup's next turn
+    const u32x4 rw_all = rw, rw_none = {rw.x, rw.y, 0u, rw.w};
     auto touch_b = [&]() {
-        u32x4 r = rw;
-        r.z = turn == 0 && kt_run + PD < kt_end ? p.w_bytes : 0u;
-        dma_touch(r, t_off, (unsigned)(kt_run + PD) * (KS * 1024u), lds0 + ST * STAGE);
-        turn = turn == 0 ? share - 1 : turn - 1;
+        if (--turn < 0) {
+            dma_touch(rw_all, t_off, b_soff + PD * (KS * 1024u), lds0 + ST * STAGE);
+            turn = kt_run + share + PD < kt_end ? share - 1 : 1 << 30;
+        } else {
+            dma_touch(rw_none, t_off, 0, lds0 + ST * STAGE);          // as many accesses in flight as in the other branch
+        }
     };
     auto advance = [&]() {
         ++kt_run;
+        a_soff += BK * 2u;
+        b_soff += KS * 1024u;
+        if (AMODE != A_GENERAL && kt_run == kt_end) {
+            asm volatile("");                                          // a branch: as selects the descriptors would move every step
+            rx.z = rw.z = 0u;
+        }
         if (AMODE == A_UNIFORM) {
             ci += BK;
             if (ci >= p.Cin) {
@@ -286,7 +332,7 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
     const unsigned b_rd0 = BM * BK * 2u + (unsigned)(wn * (BN / WN) / 16) * (KS * 1024u) + (unsigned)lane * 16u;
     uint4 fa[2][TM], fb[2][TN];
     const char *lds_c = reinterpret_cast<const char *>(smem);
-    auto read_one = [&](auto qc, auto setc, unsigned slot) {           // q-th of the TM + TN fragments of half step ks into register set `set`
+    auto read_one = [&](auto qc, auto setc, auto slot) {            // q-th of the TM + TN fragments of half step ks into register set `set`
         constexpr int q = decltype(qc)::value, set = decltype(setc)::value, ks = KS == 2 ? set : 0;
         if constexpr (q < TN) fb[set][q] = *reinterpret_cast<const uint4 *>(lds_c + slot + b_rd0 + q * (KS * 1024) + ks * 1024);
         else fa[set][q - TN] = *reinterpret_cast<const uint4 *>(lds_c + slot + (a_rd0 ^ (ks * 64u)) + (q - TN) * (BK * 32));
@@ -300,7 +346,7 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
 
     // copies per step; with two half steps the last L - L2 of them go out in the first half of the next one
     constexpr int L = AI + BI + TOUCH, L2 = KS == 2 ? L / 2 : L, R = TM + TN;
-    auto copy = [&](auto qc, unsigned slot) {
+    auto copy = [&](auto qc, auto slot) {
         constexpr int q = decltype(qc)::value;
         if constexpr (q < AI) copy_a(qc, slot);
         else if constexpr (q < AI + BI) copy_b(std::integral_constant<int, q - AI>{}, slot);
@@ -309,7 +355,7 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
     // The matrix instructions of register set `set`, copies C0 .. C0 + C - 1 of a step and the reads of the other register set, spread
     // evenly: a burst of copies fills the queue towards memory (64 bytes per clock), and a wavefront waiting to issue a copy
     // issues no matrix instructions either (128 x 128 tile, K step of 64: 0.40 us with the copies in one half, 0.35 spread).
-    auto half_step = [&](auto setc, auto c0c, auto cc, unsigned copy_slot, unsigned read_slot) {
+    auto half_step = [&](auto setc, auto c0c, auto cc, auto copy_slot, auto read_slot) {
         constexpr int set = decltype(setc)::value, C0 = decltype(c0c)::value, C = decltype(cc)::value, Q = C + R;
         static_for<NM>([&](auto mc) {
             constexpr int m = decltype(mc)::value, i = m / TN, j = m % TN;
@@ -328,30 +374,34 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
     using I1 = std::integral_constant<int, 1>;
     using IL2 = std::integral_constant<int, L2>;
     using IL1 = std::integral_constant<int, L - L2>;
+    // The bias of this wavefront's channels is on its way before the first operand, where the registers allow: the epilogue
+    // starts with the accumulators, not with a trip to memory.
+    constexpr bool EARLY = !dma_acc_in_agprs(BM, BN, NW);
+    u32x4 bq[TN / 2];
+    if constexpr (EARLY) {
+        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void *)p.bias, 0, p.bias ? p.N * 2 : 0, 0x00020000);
+        const int n0 = n_base + wn * (BN / WN) + 16 * ((lane >> 4) & 1) + 8 * (lane >> 5);
+#pragma unroll
+        for (int jp = 0; jp < TN / 2; ++jp) bq[jp] = __builtin_amdgcn_raw_buffer_load_b128(rb, n0 + 32 * jp < p.N ? (unsigned)(n0 + 32 * jp) * 2u : OOB, 0, 0);
+    }
     static_for<ST>([&](auto sc) {
         constexpr int st = decltype(sc)::value;
-        static_for<(st == ST - 1 ? L2 : L)>([&](auto qc) { copy(qc, st * STAGE); });
+        static_for<(st == ST - 1 ? L2 : L)>([&](auto qc) { copy(qc, std::integral_constant<unsigned, st * STAGE>{}); });
         if constexpr (st < ST - 1 || KS == 1) advance();
     });
     wait_and_meet<(ST - 2) * L + L2, false>();
-    static_for<R>([&](auto qc) { read_one(qc, I0{}, 0u); });
+    static_for<R>([&](auto qc) { read_one(qc, I0{}, std::integral_constant<unsigned, 0u>{}); });
 
     // Every wavefront has read all of the current step and its copies of the next one have landed; after the barrier so have everyone's
     auto meet = [&]() { wait_and_meet<(ST - 2) * L>(); };
-    auto after = [&](unsigned slot) { return slot + STAGE == ST * STAGE ? 0u : slot + STAGE; };
-    unsigned slot = 0, prev = (ST - 1) * STAGE;                        // stages of step kt and of step kt - 1 (= kt + ST - 1)
-    if constexpr (KS == 2) {
-        for (int kt = kt_begin; kt < kt_end; ++kt) {
-            const unsigned next = after(slot);
-            half_step(I0{}, IL2{}, IL1{}, prev, slot);
-            advance();
-            meet();
-            half_step(I1{}, I0{}, IL2{}, slot, next);
-            prev = slot;
-            slot = next;
-        }
-    } else {
-        for (int kt = kt_begin; kt < kt_end; kt += 2) {                // a step beyond the slice multiplies zeros
+    int kt = kt_begin;
+    if constexpr (dma_acc_in_agprs(BM, BN, NW)) {
+        // the largest tiles carry the stage in a register: their matrix instructions leave time for it, and unrolled over the ring
+        // they would spill 80 registers
+        auto after = [&](unsigned slot) { return slot + STAGE == ST * STAGE ? 0u : slot + STAGE; };
+        static_assert(KS == 1, "two steps per turn");
+        unsigned slot = 0;
+        for (; kt < kt_end; kt += 2) {                                 // a step beyond the slice multiplies zeros
             meet();
             unsigned next = after(slot);
             half_step(I0{}, I0{}, IL2{}, slot, next);
@@ -363,12 +413,41 @@ __global__ __launch_bounds__(WM * WN * 64, dma_acc_in_agprs(BM, BN, WM * WN) ? 1
             advance();
             slot = next;
         }
+    } else {
+        // Unrolled over the ring, so that every LDS position is a constant: a lone wavefront issues one instruction in four to five
+        // cycles, and carrying the stage and rebuilding descriptors cost 15 to 20 of them per step.  1568 x 512 x 4608 on 64 x 64 x 64
+        // tiles 18.5 -> 15.8 us (256 CUs), 6272 x 512 x 4608 on 128 x 128 x 64 32.9 -> 30.3, 1536 x 1024 x 4096 on 96 CUs 28.4 -> 27.7; the
+        // prologue (divisions by multiplier, arguments in registers, window masks without loops, bias fetched first) is the
+        // other part: 1536 x 1024 x 1024 on 64 x 128 x 64 8.4 -> 7.6, 25088 x 64 x 256 5.3 -> 4.6.
+        constexpr int TURNS = KS == 2 || ST % 2 == 0 ? ST : 2 * ST;    // steps until stage and register set repeat
+        bool more = true;
+        do {
+            static_for<TURNS>([&](auto uc) {
+                constexpr int u = decltype(uc)::value;
+                using Prev = std::integral_constant<unsigned, (u + ST - 1) % ST * STAGE>;    // stage of step kt - 1 (= kt + ST - 1)
+                using Slot = std::integral_constant<unsigned, u % ST * STAGE>;
+                using Next = std::integral_constant<unsigned, (u + 1) % ST * STAGE>;
+                if (more) {
+                    if constexpr (KS == 2) {
+                        half_step(I0{}, IL2{}, IL1{}, Prev{}, Slot{});
+                        advance();
+                        meet();
+                        half_step(I1{}, I0{}, IL2{}, Slot{}, Next{});
+                    } else {
+                        meet();
+                        half_step(std::integral_constant<int, u % 2>{}, I0{}, IL2{}, Slot{}, Next{});
+                        advance();
+                    }
+                    more = ++kt < kt_end;
+                }
+            });
+        } while (more);
     }
     asm volatile("s_nop 15");                                          // the compiler does not see the latency of mma_agpr
     wait_and_meet<0>();
     if (p.splits == 1 && p.y && (p.N & 7) == 0) {
-#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true>(p, acc, m_base, n_base, wm, wn) \
-                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false>(p, acc, m_base, n_base, wm, wn)
+#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY>(p, acc, bq, m_base, n_base, wm, wn) \
+                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY>(p, acc, bq, m_base, n_base, wm, wn)
         ECLIP_ACT_SWITCH(p.act, EPI)
 #undef EPI
         return;

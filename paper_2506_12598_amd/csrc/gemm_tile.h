@@ -213,7 +213,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev &p, f32x4 (&acc)[TM]
 // 1 (large problems): those 32 workgroups form an 8 x 4 block of tiles, so that one K step pulls 8 + 4 operand tiles into
 // the L2 instead of up to 32 + 1; blocks are dealt to the XCDs in row-major order.  Raster 2 (3): an XCD owns a contiguous
 // range of the tiles, counted down the tile columns (along the tile rows).
-__device__ __forceinline__ bool gemm_tile_of(const GemmDev &p, uint32_t bid, int &tile_m, int &tile_n)
+__device__ __forceinline__ bool gemm_tile_of(const GemmDev &p, uint32_t tiles, uint32_t bid, int &tile_m, int &tile_n)
 {
     if (p.raster == 1) {
         const int b = (int)bid, l = b >> 3, w = l & 31;
@@ -223,9 +223,9 @@ __device__ __forceinline__ bool gemm_tile_of(const GemmDev &p, uint32_t bid, int
         tile_n = (sb / sbm) * 4 + (w >> 3);
         return tile_m < p.tiles_m && tile_n < p.tiles_n;
     }
-    const uint32_t t = p.raster ? xcd_range_item(bid, (uint32_t)(p.tiles_m * p.tiles_n)) : bid;
+    const uint32_t t = p.raster ? xcd_range_item(bid, tiles) : bid;
     if (t == 0xffffffffu) return false;
-    const int fast = p.raster == 3 ? p.tiles_n : p.tiles_m, slow = (int)t / fast, rem = (int)t - slow * fast;
+    const int slow = (int)div_by(t, p.fast), rem = (int)(t - (unsigned)slow * p.fast.d);
     tile_m = p.raster == 3 ? slow : rem;
     tile_n = p.raster == 3 ? rem : slow;
     return true;
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p, SeDe
     const int wm = wave / WN, wn = wave % WN;
     int tile_m, tile_n;
     const uint32_t bid = se_dealt_block(deal, blockIdx.x);
-    if (bid == 0xffffffffu || !gemm_tile_of(p, bid, tile_m, tile_n)) return;
+    if (bid == 0xffffffffu || !gemm_tile_of(p, (uint32_t)(p.tiles_m * p.tiles_n), bid, tile_m, tile_n)) return;
     const int m_base = tile_m * BM, n_base = tile_n * BN;
 
     // ---- per-thread, per-chunk addressing that does not change along K
@@ -282,15 +282,14 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p, SeDe
     bool a_ok[A_IT];
     unsigned a_off0[A_IT];                   // byte offset of pixel (ih0, iw0) of the row's image (modulo 2^32 when padded)
     int a_ih0[A_IT], a_iw0[A_IT];
-    const int HoWo = p.Ho * p.Wo;
 #pragma unroll
     for (int it = 0; it < A_IT; ++it) {
         const int c = tid + it * NT;
         const int m = m_base + c / CPR;
         a_ok[it] = (A_CH % NT == 0 || c < A_CH) && (m < p.M);
         const int mm = a_ok[it] ? m : 0;
-        const int b = mm / HoWo, r = mm - b * HoWo;
-        const int oh = r / p.Wo, ow = r - oh * p.Wo;
+        const int b = (int)div_by((unsigned)mm, p.howo), r = mm - b * (int)p.howo.d;
+        const int oh = (int)div_by((unsigned)r, p.wo), ow = r - oh * (int)p.wo.d;
         a_ih0[it] = oh * p.stride - p.pad;
         a_iw0[it] = ow * p.stride - p.pad;
         a_off0[it] = ((unsigned)b * (unsigned)(p.H * p.W) + (unsigned)(a_ih0[it] * p.W + a_iw0[it])) * (unsigned)p.ldx * 2u;

@@ -62,6 +62,8 @@ hipError_t launch_gconv_mfma(const GConvArgs &a, int S, int n_cu, hipStream_t s)
     d.tiles_m = (int)((M + bm - 1) / bm); d.tiles_n = (a.Cout + bn - 1) / bn;
     d.splits = 1;
     d.raster = pl.raster;
+    d.howo = magic_of((unsigned)(a.Ho * a.Wo));
+    d.wo = magic_of((unsigned)a.Wo);
     return launch_conv_wsk(d, a.dtype, pl.variant, pl.nw, pl.tiles, s);
 }
 

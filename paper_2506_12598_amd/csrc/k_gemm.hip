@@ -432,6 +432,9 @@ static GemmDev make_dev(const ConvGemmArgs &a, const GemmPlan &pl)
     d.tiles_m = (d.M + bm - 1) / bm;
     d.tiles_n = (d.N + bn - 1) / bn;
     d.raster = pl.raster;
+    d.howo = magic_of((unsigned)(a.Ho * a.Wo));
+    d.wo = magic_of((unsigned)a.Wo);
+    d.fast = magic_of((unsigned)(pl.raster == 3 ? d.tiles_n : d.tiles_m));
     return d;
 }
 

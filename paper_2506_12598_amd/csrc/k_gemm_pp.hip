@@ -19,7 +19,8 @@ hipError_t launch_one(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream
 {
     if constexpr (kTile.loop == LOOP_DMA)
         hipLaunchKernelGGL((conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE>), grid, dim3(256),
-                           dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs), s, d, deal);
+                           dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs), s, d.x, d.w, d.x_bytes, d.M, d.N, d.K, d.ldx, d.kt_per,
+                           dma_walk(d, deal), (unsigned)(d.tiles_m * d.tiles_n), d.fast.d, d.fast.mul, d, deal);
     else
         hipLaunchKernelGGL((conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>), grid, dim3(512),
                        lds_bytes(kTile.bm, kTile.bn, kTile.bk, 16, kTile.loop != LOOP_PP_BDIRECT), s, d, deal);

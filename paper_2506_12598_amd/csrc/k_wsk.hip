@@ -110,14 +110,13 @@ __global__ __launch_bounds__(NW * 64) void conv_wsk_kernel(GemmDev p0, GemmDev p
     int a_ok[TM];
     unsigned a_off0[TM];                     // byte offset of pixel (ih0, iw0) of the row's image (modulo 2^32 when padded)
     int a_ih0[TM], a_iw0[TM];
-    const int HoWo = p.Ho * p.Wo;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int m = m_base + i * 16 + row;
         a_ok[i] = m < p.M;
         const int mm = a_ok[i] ? m : 0;
-        const int b = mm / HoWo, r = mm - b * HoWo;
-        const int oh = r / p.Wo, ow = r - oh * p.Wo;
+        const int b = (int)div_by((unsigned)mm, p.howo), r = mm - b * (int)p.howo.d;
+        const int oh = (int)div_by((unsigned)r, p.wo), ow = r - oh * (int)p.wo.d;
         a_ih0[i] = oh * p.stride - p.pad;
         a_iw0[i] = ow * p.stride - p.pad;
         if constexpr (NCHW) a_off0[i] = ((unsigned)(b * p.nchw_c) * (unsigned)(p.H * p.W) + (unsigned)(a_ih0[i] * p.W + a_iw0[i])) * 2u;
