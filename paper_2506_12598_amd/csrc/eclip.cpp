@@ -1010,13 +1010,15 @@ static GemmShape gemm_shape(const LayerPlan &P, int batch)
 
 // The launch plan of a matrix-core layer: the measured choice when eclip_model_tune has seen this problem on a stream of
 // this CU count, else the planner's cost model.
-static GemmPlan plan_of(const eclip_model *m, long M, long N, long K, int n_cu)
+static bool lean_of(const GemmShape &g) { return conv_wsk_is_lean(g.KH, g.KW, g.stride, g.pad, g.Cin, g.Cout); }
+static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, int n_cu)
 {
+    const long M = (long)g.B * g.Ho * g.Wo, N = g.Cout, K = (long)g.KH * g.KW * g.Cin;
     if (!m->tuned.empty() && !getenv("ECLIP_GEMM_FORCE")) {
         const auto it = m->tuned.find(std::array<long, 4>{M, N, K, (long)n_cu});
         if (it != m->tuned.end()) return it->second;
     }
-    return conv_gemm_plan(M, N, K, n_cu, m->ws_floats);
+    return conv_gemm_plan(M, N, K, n_cu, m->ws_floats, lean_of(g));
 }
 
 extern "C" eclip_status eclip_model_load(eclip_pool *pool, const eclip_model_desc *desc, const void *weights,
@@ -1202,7 +1204,7 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
         const GemmShape g = gemm_shape(P, (int)batch);
         out->m = (uint64_t)g.B * g.Ho * g.Wo; out->n = (uint64_t)g.Cout; out->k = (uint64_t)g.KH * g.KW * g.Cin;
         if (P.gemm) {
-            const GemmPlan pl = plan_of(model, (long)out->m, (long)out->n, (long)out->k, (int)model->pool->streams[mask_id].n_cu);
+            const GemmPlan pl = plan_of(model, g, (int)model->pool->streams[mask_id].n_cu);
             int bm, bn, bk;
             if (pl.kind == 1) { conv_wsk_tile(pl.variant, &bm, &bn); name = "conv_wsk_kernel"; out->threads = (uint32_t)pl.nw * 64; }
             else { conv_gemm_tile(pl.variant, &bm, &bn, &bk); name = conv_gemm_kernel_name(pl.variant); out->threads = (uint32_t)conv_gemm_threads(pl.variant); }
@@ -1311,7 +1313,7 @@ static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_
                            g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, L.act, dt};
             a.ldx = pitch_of(m, L.in0);
             a.ldy = P.ld;
-            const GemmPlan pl = plan_of(m, (long)g.B * g.Ho * g.Wo, g.Cout, (long)g.KH * g.KW * g.Cin, n_cu);
+            const GemmPlan pl = plan_of(m, g, n_cu);
             *n_launched -= 1;
             e = launch_conv_gemm(a, pl, cu.deal, s, n_launched);
         } else if (L.op == ECLIP_OP_CONV && L.groups > 1 && !(L.groups == g.Cin && L.c == L.groups)) {
@@ -1391,6 +1393,7 @@ static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t
     GemmPlan own[2], pl[2];
     const int n_cu = cu.n_cu;
     long mnk[2][3];
+    bool lean[2];
     for (int k = 0; k < 2; ++k) {
         const LayerPlan &P = m->layers[i + k];
         const eclip_layer &L = P.L;
@@ -1405,9 +1408,10 @@ static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t
         a[k].ldx = pitch_of(m, L.in0);
         a[k].ldy = P.ld;
         mnk[k][0] = (long)g.B * g.Ho * g.Wo; mnk[k][1] = g.Cout; mnk[k][2] = (long)g.KH * g.KW * g.Cin;
-        own[k] = plan_of(m, mnk[k][0], mnk[k][1], mnk[k][2], n_cu);
+        own[k] = plan_of(m, g, n_cu);
+        lean[k] = lean_of(g);
     }
-    if (!conv_gemm_plan_pair(own[0], mnk[0][0], mnk[0][1], mnk[0][2], own[1], mnk[1][0], mnk[1][1], mnk[1][2], n_cu, &pl[0], &pl[1]))
+    if (!conv_gemm_plan_pair(own[0], mnk[0][0], mnk[0][1], mnk[0][2], lean[0], own[1], mnk[1][0], mnk[1][1], mnk[1][2], lean[1], n_cu, &pl[0], &pl[1]))
         return hipSuccess;
     *done = true;
     return launch_conv_gemm_pair(a[0], pl[0], a[1], pl[1], s, n_launched);
@@ -1823,7 +1827,7 @@ extern "C" eclip_status eclip_model_tune(eclip_model *model, uint32_t mask_id, u
                        model->ws, g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, L.act, model->dtype};
         a.ldx = pitch_of(model, L.in0);
         a.ldy = P.ld;
-        const GemmPlan own = conv_gemm_plan(M, N, K, n_cu, model->ws_floats);
+        const GemmPlan own = conv_gemm_plan(M, N, K, n_cu, model->ws_floats, lean_of(g));
         std::vector<GemmPlan> cand = conv_gemm_candidates(M, N, K, n_cu, model->ws_floats);
         cand.insert(cand.begin(), own);
         float best_ms = 1e30f, own_ms = 1e30f;

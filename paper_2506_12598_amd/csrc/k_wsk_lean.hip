@@ -406,6 +406,20 @@ const void *kernel_of(int variant, int nw, int form, bool grouped)
 
 }  // namespace
 
+bool conv_wsk_is_lean(int KH, int KW, int stride, int pad, int Cin, int Cout)
+{
+    GemmDev d{};
+    d.KH = KH; d.KW = KW; d.stride = stride; d.pad = pad; d.Cin = Cin; d.N = d.ldy = Cout; d.K = KH * KW * Cin;
+    return wsk_lean_form(d) >= 0;
+}
+int conv_wsk_lean_depth(int variant, int nw)
+{
+    static const int depth[CONV_WSK_VARIANTS][2] = {{LeanDepth<1, 4, 8>::value, LeanDepth<1, 4, 16>::value}, {LeanDepth<2, 4, 8>::value, LeanDepth<2, 4, 16>::value},
+                                                    {LeanDepth<4, 4, 8>::value, LeanDepth<4, 4, 16>::value}, {LeanDepth<1, 1, 8>::value, LeanDepth<1, 1, 16>::value},
+                                                    {LeanDepth<1, 2, 8>::value, LeanDepth<1, 2, 16>::value}, {LeanDepth<2, 2, 8>::value, LeanDepth<2, 2, 16>::value}};
+    return depth[variant][nw == 16];
+}
+
 // The address form of a layer, or -1 when only the general kernel takes it.  Four output channels per summing thread need N and the
 // row pitch of y to be multiples of 4.
 int wsk_lean_form(const GemmDev &d)
