@@ -5,6 +5,7 @@ configurations max-abs error <= 2e-2 x (max - min of the oracle output).  Single
 rounding is float32 accumulation are held to a much tighter bound so that a dropped K-slice, a wrong tap
 or a transposed operand cannot hide inside the model-level tolerance.
 """
+import math
 import os
 
 import numpy as np
@@ -236,6 +237,20 @@ def test_eltwise_and_embed(dt):
     exp = orc.run_model(m, x)
     got = run_gpu(m, x)
     assert np.abs(got - exp).max() <= (1e-6 if dt == wl.DT_F32 else 2.0 ** -7 * np.abs(exp).max())
+
+
+@pytest.mark.parametrize("lo,hi,rel", [(-1e-3, -1.0, 9e-7), (-1.0, -2.0, 4e-6), (-2.0, -3.0, 6e-5), (-3.0, -4.0, 5e-4), (-4.0, -6.0, 4e-3),
+                                       (-6.0, -8.0, 1.1e-2), (0.0, 8.0, None), (-8.0, -80.0, None), (80.0, 3e38, None)])
+def test_gelu_error_by_range(lo, hi, rel):
+    """Negative branch: relative error no larger than that of the rational form of erf (Abramowitz & Stegun 7.1.26) in float32,
+    per range, plus one unit of the hardware exp2 (1.2e-7).  Elsewhere absolute: 2.2e-7 (its error bound 1.5e-7 in exact
+    arithmetic plus the same unit times the largest a Q(a), 0.17, and slack) and half a unit of the result."""
+    m = wl.single_layer("eltwise", wl.DT_F32, seed=1, rows=64, width=64, act=wl.ACT_GELU, residual=False)
+    x = np.linspace(lo, hi, 4096).astype(np.float32).reshape(wl.make_input(m, 1).shape)
+    exp = np.array([0.5 * v * math.erfc(-v / math.sqrt(2.0)) for v in x.reshape(-1).tolist()])      # 1 + erf cancels in the tail
+    err = np.abs(run_gpu(m, x).astype(np.float64).reshape(-1) - exp)
+    ref = np.abs(exp)
+    assert np.all(err <= (ref * rel if rel else 2.2e-7 + ref * 2.0 ** -23)), (err / np.maximum(ref, 1e-30)).max()
 
 
 # ---------------- attention -----------------------------------------------------------------------------------------
