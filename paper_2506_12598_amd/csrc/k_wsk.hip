@@ -1,5 +1,10 @@
 // Wave-split-K implicit GEMM for the small, latency-bound layers of batch-1 inference.
 //
+// This file holds the method's general form and the launchers.  Nearly all layers take the lean form in k_wsk_lean.hip
+// (wsk_lean_form); this one is left with windows and strides over channels that are no multiple of 32, windows of more than 31
+// taps, output channels or row pitches that are no multiple of 4, the first layer read from the caller's planes, and launches of
+// two layers that no lean form serves together (wsk_lean_pair_form).
+//
 // Same contraction as the LDS-tiled kernel (y[m][n] = act(sum_k A[m][k] w[n][k] + bias + res)), but the
 // parallelism is taken from K *inside* the workgroup instead of from a second kernel:
 //   - a workgroup of NW wavefronts owns one (TM*16) x (TN*16) output tile;

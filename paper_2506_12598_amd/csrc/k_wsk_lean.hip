@@ -2,11 +2,11 @@
 // takes everything else).
 //
 // A launch of a batch-1 layer lasts four to six microseconds, of which 1.6 are the dispatch and about 0.7 the weights' way from
-// memory.  Cycle stamps in the general form put the rest into instructions: a wavefront issues one vector instruction
-// in four to five cycles, the code is cold at every launch and arrives at about a byte per cycle, and the general form spends
-// 1400 bytes on the prologue (four integer divisions), 250 to 400 on every K step it loads (each lane walks its own window
-// position) and 1600 cycles after the last barrier, where bias, residual and the epilogue's code are fetched one after the
-// other.  Here the host prepares what is uniform (steps per wavefront, magic numbers for the divisions, sizes in bytes), and the
+// memory.  Cycle stamps in the general form put the rest into the number of instructions that a wavefront issues one after the
+// other, four to five cycles each, scalar or vector (two kilobytes of straight code run at that rate the first time too: in a
+// chain of layers the code does not arrive late).  The general form spends 1400 bytes of code on the prologue (four integer
+// divisions), 250 to 400 on every K step it loads (each lane walks its own window position) and 1600 cycles after the last
+// barrier, where bias and residual are fetched one after the other.  Here the host prepares what is uniform (steps per wavefront, magic numbers for the divisions, sizes in bytes), and the
 // three address forms need one or three vector instructions per load:
 //   ROWS       1 x 1 window, stride 1, no padding: pixel m of the operand is row m; the position along K is the load's scalar offset
 //   ROWS_TAIL  the same with K not a multiple of 32: the last step's lanes beyond K load zeros
