@@ -51,6 +51,30 @@ template <typename T> __device__ __forceinline__ void mma_agpr(uint4 a, uint4 b,
     else asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(va), "v"(vb));
 }
 
+// Accumulators of two blocks (of one) for an epilogue.  Those in accumulation registers are fetched by statements of their own: left to
+// the compiler, with two epilogues to choose from, it moves them to vector registers before the branch and spills what does not fit
+// (60 registers of the 256 x 256 tile, whose every launch paid for it whichever epilogue ran).  The compiler does not see that
+// v_permlane16_swap, which follows, must stay clear of them.
+template <bool AGPR> __device__ __forceinline__ void acc_pair(const f32x4 &a, const f32x4 &b, unsigned (&v)[8])
+{
+    if constexpr (AGPR) {
+        asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\tv_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
+                     "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\tv_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15\n\ts_nop 3"
+                     : "=v"(v[0]), "=v"(v[1]), "=v"(v[2]), "=v"(v[3]), "=v"(v[4]), "=v"(v[5]), "=v"(v[6]), "=v"(v[7])
+                     : "a"(a[0]), "a"(a[1]), "a"(a[2]), "a"(a[3]), "a"(b[0]), "a"(b[1]), "a"(b[2]), "a"(b[3]));
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) { v[c] = __float_as_uint(a[c]); v[4 + c] = __float_as_uint(b[c]); }
+    }
+}
+__device__ __forceinline__ uint4 acc_agpr(const f32x4 &a)
+{
+    uint4 v;
+    asm volatile("v_accvgpr_read_b32 %0, %4\n\tv_accvgpr_read_b32 %1, %5\n\tv_accvgpr_read_b32 %2, %6\n\tv_accvgpr_read_b32 %3, %7"
+                 : "=v"(v.x), "=v"(v.y), "=v"(v.z), "=v"(v.w) : "a"(a[0]), "a"(a[1]), "a"(a[2]), "a"(a[3]));
+    return v;
+}
+
 // Epilogue for outputs of the storage type with N a multiple of 8 (the rest goes through tile_epilogue).  One wavefront per SIMD
 // has nobody to hide behind, so this one is kept short and straight: buffer stores that drop what lies beyond M or N instead
 // of a branch per store, accumulators taken block row by block row.
@@ -96,9 +120,11 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
         static_for<TN / 2>([&](auto jc) {
             constexpr int jp = decltype(jc)::value;
             float o[8];
+            unsigned ab[8];
+            acc_pair<!EARLY>(acc[i][2 * jp], acc[i][2 * jp + 1], ab);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const u32x2 sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][2 * jp][c]), __float_as_uint(acc[i][2 * jp + 1][c]), false, false);
+                const u32x2 sw = __builtin_amdgcn_permlane16_swap(ab[c], ab[4 + c], false, false);
                 o[c] = __uint_as_float(sw[0]);
                 o[4 + c] = __uint_as_float(sw[1]);
             }
@@ -124,6 +150,58 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
             __builtin_amdgcn_raw_buffer_store_b128(v, ry, ok ? off[jp] + row16 * i : OOB, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         });
+    });
+}
+
+// What dma_epilogue does not take (float outputs, N not a multiple of 8, slices of K), for the tiles whose accumulators fill the
+// accumulation registers.  tile_epilogue, made for tiles with registers to spare, cost the 256 x 256 tile 60 spilled ones:
+// here half the sub-tile goes through the wavefront's own part of LDS to one short loop.  With acc_pair, 1536 x 4096 x 1024 on 96 CUs:
+// 32.0 -> 27.0 us on 256 x 256 tiles, 1536 x 3072 x 1024 24.3 -> 23.2 on 256 x 192, 26.3 -> 25.7 on 192 x 256.
+template <typename T, int BM, int BN, int WM, int WN, int TM, int TN>
+__device__ __forceinline__ void dma_epilogue_rest(const GemmDev &p, f32x4 (&acc)[TM][TN], uint16_t *smem, int m_base, int n_base, int wm, int wn, int z)
+{
+    static_assert(TM % 2 == 0, "two halves");
+    constexpr int ROWS = TM * 8, COLS = TN * 16, SP = COLS + 4;
+    const int lane = threadIdx.x & 63;
+    float *stage = reinterpret_cast<float *>(smem) + (wm * WN + wn) * (ROWS * SP);
+    __syncthreads();                                                   // everyone is done with the ring
+    static_for<2>([&](auto hc) {
+        constexpr int h = decltype(hc)::value;
+        static_for<TM / 2>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            static_for<TN>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                const f32x4 a = acc[h * (TM / 2) + i][j];
+                *reinterpret_cast<uint4 *>(&stage[(i * 16 + (lane & 15)) * SP + j * 16 + (lane >> 4) * 4]) = acc_agpr(a);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_s_waitcnt(0xc07f);                            // lgkmcnt(0): this wavefront's LDS writes have landed
+#pragma unroll 1
+        for (int t = lane; t < ROWS * (COLS / 4); t += 64) {
+            const int r = t / (COLS / 4), c = (t - r * (COLS / 4)) * 4;
+            const int m = m_base + wm * (BM / WM) + h * ROWS + r, n = n_base + wn * (BN / WN) + c;
+            const float4 q = *reinterpret_cast<const float4 *>(&stage[r * SP + c]);
+            const f32x4 v = {q.x, q.y, q.z, q.w};
+            if (p.splits != 1) {
+                if (m >= p.M || n >= p.N) continue;
+                float *dst = p.ws + ((long)z * p.M + m) * p.N + n;
+                if ((p.N & 3) == 0) {
+                    *reinterpret_cast<float4 *>(dst) = q;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < p.N) dst[e] = v[e];
+                }
+            } else {
+#define EPI(A) epilogue_store<T, A>(p.bias, p.res, p.y, p.y32, p.M, p.N, m, n, v, 4, p.ldy)
+                ECLIP_ACT_SWITCH(p.act, EPI)
+#undef EPI
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_s_waitcnt(0xc07f);                            // reads done before the second half overwrites the buffer
     });
 }
 
@@ -452,7 +530,10 @@ __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 
 #undef EPI
         return;
     }
-    tile_epilogue<T, BM, BN, WM, WN, TM, TN>(p, acc, smem, m_base, n_base, blockIdx.y);
+    if constexpr (dma_acc_in_agprs(BM, BN, NW)) {
+        static_assert(4 * (TM * 8) * (TN * 16 + 4) * 4 <= ST * STAGE, "half the sub-tiles fit the ring");
+        dma_epilogue_rest<T, BM, BN, WM, WN, TM, TN>(p, acc, smem, m_base, n_base, wm, wn, blockIdx.y);
+    } else tile_epilogue<T, BM, BN, WM, WN, TM, TN>(p, acc, smem, m_base, n_base, blockIdx.y);
 }
 
 }  // namespace eclip

@@ -347,10 +347,12 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // kernel is not dealt to them (se_deal.h) and this model does not know.  eclip_model_tune closes the gap by measurement.
     // (A further 1.2 us on every tile, for inputs that the layer before has just written, made the 160 kinds of request above
     // 1.1 % slower, none faster by more than 1.5 % and ResNeXt at batch 8 on 160 CUs 651 us instead of 589; 2.4 us another 1.5 %.)
+    // (17 lost 5 us of each launch to spilled registers when it was fitted; of that 3.2 are taken off here, so that a layer that 3 and 17
+    // could both take is still priced by row 3: plan_of in eclip.cpp then runs it on 17.)
     struct LdsTile { int variant; double step, fixed, more, two; };
     static const LdsTile lds[] = {
                                   {0, 0.509, 4.049, 7.322, 1.373}, {3, 0.568, 8.784, 16.049, 0}, {5, 0.595, 8.271, 16.021, 0}, {8, 0.525, 5.267, 9.068, 0},
-                                  {13, 0.312, 2.698, 4.335, 1.656}, {15, 0.278, 3.194, 5.868, 1.418}, {16, 0.483, 4.611, 5.981, 0}, {17, 0.512, 14.098, 19.625, 0},
+                                  {13, 0.312, 2.698, 4.335, 1.656}, {15, 0.278, 3.194, 5.868, 1.418}, {16, 0.483, 4.611, 5.981, 0}, {17, 0.512, 10.9, 16.4, 0},
                                   {18, 0.552, 6.313, 10.504, 0}, {19, 0.579, 6.094, 8.303, 0}, {20, 0.337, 4.272, 6.499, 0}, {21, 0.444, 5.202, 8.054, 0},
                                   {22, 0.267, 3.021, 6.171, 1.444}, {23, 0.257, 3.012, 4.226, 1.544}, {24, 0.406, 8.399, 13.526, 0}, {25, 0.409, 8.333, 11.372, 0},
                                   {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.222, 3.505, 5.135, 1.609}};

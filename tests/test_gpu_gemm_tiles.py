@@ -124,3 +124,20 @@ def test_captured_requests_on_uneven_masks(share, pools):
     finally:
         g.free()
         gb.free()
+
+
+@pytest.mark.parametrize("rows,n,k,kernel", [(1536, 4096, 1024, "conv_gemm_dma_kernel"), (1500, 4088, 1024, "conv_gemm_dma_kernel"),
+                                             (1536, 4092, 1024, "conv_gemm_kernel")])
+def test_layers_planned_on_256x256_tiles_run_on_the_copied_kernel(rows, n, k, kernel):
+    # one tile per CU of 96; ragged rows and columns; columns that the copied kernel's fast epilogue does not take
+    pool = ec.Pool([(ec.eclip_mask_layout(256, 32, 1, 0, 3), 0)])
+    m = wl.single_layer("linear", wl.DT_BF16, seed=n, rows=rows, k=k, n=n, bias_std=0.3, std=0.05)
+    x = wl.make_input(m, 1)
+    exp = orc.run_model(m, x)
+    g = GpuModel(m, pool=pool)
+    try:
+        assert g.h.kernel_info(0, 0, 1)["kernel"] == kernel
+        assert np.abs(g.run(x, table=[0] * m.n_groups) - exp).max() <= 1e-3 * (exp.max() - exp.min())
+    finally:
+        g.free()
+        pool.destroy()
