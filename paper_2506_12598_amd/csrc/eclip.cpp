@@ -1011,14 +1011,16 @@ static GemmShape gemm_shape(const LayerPlan &P, int batch)
 // The launch plan of a matrix-core layer: the measured choice when eclip_model_tune has seen this problem on a stream of
 // this CU count, else the planner's cost model.
 static bool lean_of(const GemmShape &g) { return conv_wsk_is_lean(g.KH, g.KW, g.stride, g.pad, g.Cin, g.Cout); }
-static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, int n_cu)
+static GemmTraits traits_of(const GemmShape &g, const CuShare &cu) { return GemmTraits{lean_of(g), cu.even_cu()}; }
+static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, const CuShare &cu)
 {
+    const int n_cu = cu.n_cu;
     const long M = (long)g.B * g.Ho * g.Wo, N = g.Cout, K = (long)g.KH * g.KW * g.Cin;
     if (!m->tuned.empty() && !getenv("ECLIP_GEMM_FORCE")) {
         const auto it = m->tuned.find(std::array<long, 4>{M, N, K, (long)n_cu});
         if (it != m->tuned.end()) return it->second;
     }
-    GemmPlan pl = conv_gemm_plan(M, N, K, n_cu, m->ws_floats, lean_of(g));
+    GemmPlan pl = conv_gemm_plan(M, N, K, n_cu, m->ws_floats, traits_of(g, cu));
     // The planner prices 256 x 256 tiles by the ping-pong kernel's row.  Where the operands fit the copied kernel's fast address
     // forms it serves the same tiles in less time from 256 terms on (its K step costs 0.51 instead of 0.57 us and its fill 0.3 more):
     // 1536 x 4096 on 96 CUs, K = 1024, 2048, 4096: 29.1, 47.9, 85.3 us on the ping-pong kernel, 27.0, 43.6, 76.3 on this one.
@@ -1210,7 +1212,7 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
         const GemmShape g = gemm_shape(P, (int)batch);
         out->m = (uint64_t)g.B * g.Ho * g.Wo; out->n = (uint64_t)g.Cout; out->k = (uint64_t)g.KH * g.KW * g.Cin;
         if (P.gemm) {
-            const GemmPlan pl = plan_of(model, g, (int)model->pool->streams[mask_id].n_cu);
+            const GemmPlan pl = plan_of(model, g, share_of(model->pool->streams[mask_id]));
             int bm, bn, bk;
             if (pl.kind == 1) { conv_wsk_tile(pl.variant, &bm, &bn); name = "conv_wsk_kernel"; out->threads = (uint32_t)pl.nw * 64; }
             else { conv_gemm_tile(pl.variant, &bm, &bn, &bk); name = conv_gemm_kernel_name(pl.variant); out->threads = (uint32_t)conv_gemm_threads(pl.variant); }
@@ -1224,7 +1226,7 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
             if (P.gc_super) {
                 const GConvArgs ga{nullptr, nullptr, nullptr, nullptr, nullptr, g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad,
                                    P.L.groups, P.L.act, model->dtype};
-                const GemmPlan pl = gconv_mfma_plan(ga, P.gc_super, (int)model->pool->streams[mask_id].n_cu);
+                const GemmPlan pl = gconv_mfma_plan(ga, P.gc_super, share_of(model->pool->streams[mask_id]).even_cu());
                 name = gconv_mfma_kernel_name(ga);
                 out->workgroups = (uint32_t)pl.tiles;
                 out->threads = (uint32_t)pl.nw * 64;
@@ -1319,13 +1321,13 @@ static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_
                            g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, L.act, dt};
             a.ldx = pitch_of(m, L.in0);
             a.ldy = P.ld;
-            const GemmPlan pl = plan_of(m, g, n_cu);
+            const GemmPlan pl = plan_of(m, g, cu);
             *n_launched -= 1;
             e = launch_conv_gemm(a, pl, cu.deal, s, n_launched);
         } else if (L.op == ECLIP_OP_CONV && L.groups > 1 && !(L.groups == g.Cin && L.c == L.groups)) {
             GConvArgs a{src(L.in0), wptr(m, P.w_dev), wptr(m, P.b_dev), src(L.in1), y, g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout,
                         g.KH, g.KW, g.stride, g.pad, L.groups, L.act, dt};
-            e = P.gc_super ? launch_gconv_mfma(a, P.gc_super, n_cu, s) : launch_gconv(a, n_cu, s);
+            e = P.gc_super ? launch_gconv_mfma(a, P.gc_super, cu.even_cu(), s) : launch_gconv(a, n_cu, s);
         } else if (L.op == ECLIP_OP_CONV && L.groups > 1) {
             DwConvArgs a{src(L.in0), wptr(m, P.w_dev), wptr(m, P.b_dev), src(L.in1), y, g.B, g.H, g.W, L.c, g.Ho, g.Wo, g.KH, g.KW, g.stride, g.pad, L.act, dt};
             e = launch_dwconv(a, n_cu, s);
@@ -1397,7 +1399,6 @@ static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t
     *done = false;
     ConvGemmArgs a[2];
     GemmPlan own[2], pl[2];
-    const int n_cu = cu.n_cu;
     long mnk[2][3];
     bool lean[2];
     for (int k = 0; k < 2; ++k) {
@@ -1414,10 +1415,10 @@ static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t
         a[k].ldx = pitch_of(m, L.in0);
         a[k].ldy = P.ld;
         mnk[k][0] = (long)g.B * g.Ho * g.Wo; mnk[k][1] = g.Cout; mnk[k][2] = (long)g.KH * g.KW * g.Cin;
-        own[k] = plan_of(m, g, n_cu);
+        own[k] = plan_of(m, g, cu);
         lean[k] = lean_of(g);
     }
-    if (!conv_gemm_plan_pair(own[0], mnk[0][0], mnk[0][1], mnk[0][2], lean[0], own[1], mnk[1][0], mnk[1][1], mnk[1][2], lean[1], n_cu, &pl[0], &pl[1]))
+    if (!conv_gemm_plan_pair(own[0], mnk[0][0], mnk[0][1], mnk[0][2], lean[0], own[1], mnk[1][0], mnk[1][1], mnk[1][2], lean[1], cu.even_cu(), &pl[0], &pl[1]))
         return hipSuccess;
     *done = true;
     return launch_conv_gemm_pair(a[0], pl[0], a[1], pl[1], s, n_launched);
@@ -1454,7 +1455,7 @@ static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, c
         return launch_conv_f32(a, cu.n_cu, s);
     }
     GemmPlan pl;
-    if (!conv_gemm_plan_stem((long)g.B * g.Ho * g.Wo, g.Cout, (long)g.KH * g.KW * g.Cin, cu.n_cu, m->ws_floats, 4.0, &pl)) return hipSuccess;
+    if (!conv_gemm_plan_stem((long)g.B * g.Ho * g.Wo, g.Cout, (long)g.KH * g.KW * g.Cin, cu.n_cu, m->ws_floats, 4.0, &pl, cu.even_cu())) return hipSuccess;
     ConvGemmArgs a{d_in, wptr(m, P.w_dev), wptr(m, P.b_dev), nullptr, out_ptr(m, P), nullptr, m->ws,
                    g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, P.L.act, m->dtype};
     a.nchw_c = m->in_c;
@@ -1833,7 +1834,7 @@ extern "C" eclip_status eclip_model_tune(eclip_model *model, uint32_t mask_id, u
                        model->ws, g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, L.act, model->dtype};
         a.ldx = pitch_of(model, L.in0);
         a.ldy = P.ld;
-        const GemmPlan own = conv_gemm_plan(M, N, K, n_cu, model->ws_floats, lean_of(g));
+        const GemmPlan own = conv_gemm_plan(M, N, K, n_cu, model->ws_floats, traits_of(g, share_of(ps)));
         std::vector<GemmPlan> cand = conv_gemm_candidates(M, N, K, n_cu, model->ws_floats);
         cand.insert(cand.begin(), own);
         float best_ms = 1e30f, own_ms = 1e30f;

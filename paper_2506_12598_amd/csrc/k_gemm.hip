@@ -295,9 +295,12 @@ std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, siz
 }
 
 // conv_gemm_plan; *cost receives the modelled time of the plan (us, without the launch)
-static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_floats, bool lean, double *cost_out)
+static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits, double *cost_out)
 {
     *cost_out = 0.0;
+    const bool lean = traits.lean;
+    // wave-split-K launches are not dealt to the shader engines (se_deal.h); LDS tiles are where they need to be
+    const int even_cu = traits.even_cu > 0 ? traits.even_cu : n_cu;
     auto tiles = [&](int v) { int bm, bn, bk; conv_gemm_tile(v, &bm, &bn, &bk); return cdiv(M, bm) * cdiv(N, bn); };
     auto wsk_tiles = [&](int v) { int bm, bn; conv_wsk_tile(v, &bm, &bn); return cdiv(M, bm) * cdiv(N, bn); };
     GemmPlan pl{0, 1, 1, 0, 4, 0};
@@ -330,10 +333,10 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     double best = 1e30;
     for (int v = 0; v < CONV_WSK_VARIANTS; ++v)
         for (int nw = 4; nw <= 16; nw *= 2) {
-            const double cost = lean ? wsk_lean_cost(M, N, K, n_cu, v, nw) : wsk_cost(M, N, K, n_cu, v, nw);
+            const double cost = lean ? wsk_lean_cost(M, N, K, even_cu, v, nw) : wsk_cost(M, N, K, even_cu, v, nw);
             if (cost < best) { best = cost; pl = GemmPlan{1, v, 1, (int)wsk_tiles(v), nw, 0}; }
         }
-    if (!lean) best = wsk_whole_cost(M, N, K, n_cu, pl.variant, pl.nw);
+    if (!lean) best = wsk_whole_cost(M, N, K, even_cu, pl.variant, pl.nw);
     // LDS-tiled kernels, optionally with K cut into slices (second launch: its cost plus the traffic of the partial sums).
     // A tile costs `fixed` us once (fill of the pipeline, epilogue) and `step` us per K step of its own depth when it has a
     // compute unit to itself; every further round of workgroups on a compute unit pays the steps again and `more` us; where two
@@ -342,9 +345,13 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // candidates share (as in wsk_cost).  Constants fitted, together with wsk_whole_cost's, to 440 problems x 36 plans (40 linear layers of 128 to
     // 1536 rows, 70 convolutions of ResNet, VGG and MobileNet shapes at batch 1, 3 and 8, each on 64, 96, 160 and 256 compute units), every
     // plan timed in a chain of four to eight layers with weights of their own, so that no layer finds its weights in an L2.
-    // `bench.py --plans` repeats that measurement for linear layers: over 26 shapes on the four shares the picks cost 5.7 % more than the
-    // best plan on average; most of it on 160 compute units, whose shader engines hold 8, 8, 2 and 2 per XCD: the wave-split-K
-    // kernel is not dealt to them (se_deal.h) and this model does not know.  eclip_model_tune closes the gap by measurement.
+    // `bench.py --plans` repeats that measurement for linear layers.  eclip_model_tune closes what is left by measurement.
+    // Shares whose shader engines hold unequal numbers of CUs (160 in granules of 16: 8, 8, 2 and 2 per XCD): LDS tiles are dealt to them
+    // (se_deal.h), which costs 1.1 us (the note read from memory, the surplus workgroups; 240 launches of one round on 144, 160 and 192
+    // CUs against the same on even shares) and 2.1 when it takes a second round; wave-split-K launches are not dealt and priced by the CUs the smallest engine leaves
+    // them (CuShare::even_cu).  Over 63 layers (45 linear, 18 convolutions) on 144, 160 and 192 CUs, replayed from a graph, the picks
+    // cost 4.7, 5.8 and 3.9 % more than the best plan, and 32, 16 and 10 % when all kernels were priced as if the mask were even
+    // (at worst 29 instead of 175 %: 1176 x 128 in nine taps of 128 on 144 CUs 22.0 us, now 8.0).
     // (A further 1.2 us on every tile, for inputs that the layer before has just written, made the 160 kinds of request above
     // 1.1 % slower, none faster by more than 1.5 % and ResNeXt at batch 8 on 160 CUs 651 us instead of 589; 2.4 us another 1.5 %.)
     // (17 lost 5 us of each launch to spilled registers when it was fitted; of that 3.2 are taken off here, so that a layer that 3 and 17
@@ -363,10 +370,13 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
         for (long sp = 1; sp <= 4; sp *= 2) {
             if (sp > 1 && (K < 512 * sp || (size_t)(sp * M * N) > ws_floats)) continue;
             const long wgs = tiles(c.variant) * sp;
-            const double load = wgs >= n_cu ? 1.0 : (double)wgs / n_cu;
-            double rounds = (double)cdiv(wgs, n_cu);
-            if (c.two > 0.0 && rounds >= 2.0) rounds = c.two * ((double)wgs / n_cu > 2.0 ? (double)wgs / (2.0 * n_cu) : 1.0);
+            const bool dealt = tiles(c.variant) > even_cu;
+            const int cus = dealt || wgs <= even_cu ? n_cu : even_cu;            // few tiles in many slices: not dealt
+            const double load = wgs >= cus ? 1.0 : (double)wgs / cus;
+            double rounds = (double)cdiv(wgs, cus);
+            if (c.two > 0.0 && rounds >= 2.0) rounds = c.two * ((double)wgs / cus > 2.0 ? (double)wgs / (2.0 * cus) : 1.0);
             double cost = c.fixed + (rounds - 1.0) * c.more + rounds * (double)cdiv(KT, sp) * c.step * (1.0 + 0.15 * load * load);
+            if (dealt && even_cu < n_cu) cost += wgs > n_cu ? 2.1 : 1.1;
             if (sp > 1) cost += 15.48 + (double)M * N * (4.0 * sp + 2.0) / 4.243e6;
             if (cost < best) {
                 best = cost;
@@ -381,10 +391,10 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     *cost_out = pl.cost = best;
     return pl;
 }
-GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats, bool lean)
+GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits)
 {
     double cost;
-    return plan_with_cost(M, N, K, n_cu, ws_floats, lean, &cost);
+    return plan_with_cost(M, N, K, n_cu, ws_floats, traits, &cost);
 }
 
 // Two independent layers in one launch of the wave-split-K kernel: possible when both are planned on that kernel and
@@ -392,18 +402,19 @@ GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats, bool
 // Plan for a first layer that reads the caller's NCHW tensor itself (see conv_wsk_kernel): the cheapest of the tile
 // shapes that exist in that form, if it costs at most `stage_us` (the separate re-layout kernel it saves) more than
 // the unrestricted plan.  (Shape by wsk_cost, as everywhere: ResNet-18 at batch 1 on 160 CUs 181 us, by wsk_whole_cost 188.)
-bool conv_gemm_plan_stem(long M, long N, long K, int n_cu, size_t ws_floats, double stage_us, GemmPlan *out)
+bool conv_gemm_plan_stem(long M, long N, long K, int n_cu, size_t ws_floats, double stage_us, GemmPlan *out, int even_cu)
 {
     if (getenv("ECLIP_GEMM_FORCE") || getenv("ECLIP_NO_PAIRS")) return false;
+    if (even_cu <= 0) even_cu = n_cu;
     double any_cost;
-    (void)plan_with_cost(M, N, K, n_cu, ws_floats, false, &any_cost);
+    (void)plan_with_cost(M, N, K, n_cu, ws_floats, GemmTraits{false, even_cu}, &any_cost);
     double best = 1e30;
     int bv = -1;
     for (int v : {0, 1, 5}) {
-        const double c = wsk_cost(M, N, K, n_cu, v, 4);
+        const double c = wsk_cost(M, N, K, even_cu, v, 4);
         if (c < best) { best = c; bv = v; }
     }
-    if (bv < 0 || wsk_whole_cost(M, N, K, n_cu, bv, 4) > any_cost + stage_us) return false;
+    if (bv < 0 || wsk_whole_cost(M, N, K, even_cu, bv, 4) > any_cost + stage_us) return false;
     int bm, bn;
     conv_wsk_tile(bv, &bm, &bn);
     GemmPlan pl{1, bv, 1, (int)(cdiv(M, bm) * cdiv(N, bn)), 4, 0};

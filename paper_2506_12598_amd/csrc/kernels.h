@@ -41,7 +41,7 @@ struct GemmPlan {
                    // (along the tile rows); 1 (kind 0) = 8 x 4 blocks of tiles per XCD.  `tiles` counts the padding of the walk
     double cost = 0.0;   // modelled time, us without the launch; 0: chosen by measurement or forced
 };
-bool conv_gemm_plan_stem(long M, long N, long K, int n_cu, size_t ws_floats, double stage_us, GemmPlan *out);   // ConvGemmArgs::nchw_c
+bool conv_gemm_plan_stem(long M, long N, long K, int n_cu, size_t ws_floats, double stage_us, GemmPlan *out, int even_cu = 0);   // ConvGemmArgs::nchw_c
 // Tile ids of the LDS-tiled kernels.  0, 1: 128x128x32, 64x64x64 (4 wavefronts); 3: 256x256x32 (8 wavefronts on the ping-pong
 // schedule, both operands in LDS); 5, 8, 13, 15, 16: ping-pong with the weights straight from memory: 256x256x32, 192x128x64, 64x128x64,
 // 96x64x64, 96x192x64; 17..28: both operands copied straight into LDS (4 wavefronts): 256x256x32, 256x128x64, 128x256x64, 128x128x64,
@@ -58,17 +58,23 @@ hipError_t conv_wsk_init();    // raises the dynamic LDS limit of the wave-split
 // the layers that the lean form of the wave-split-K kernel takes (k_wsk_lean.hip), which is priced differently
 bool conv_wsk_is_lean(int KH, int KW, int stride, int pad, int Cin, int Cout);
 int conv_wsk_lean_depth(int variant, int nw);         // K steps its wavefronts keep in flight
+// What the planner has to know beyond the size of a problem and of its share.
+struct GemmTraits {
+    bool lean = true;    // the lean form of the wave-split-K kernel takes the layer
+    int even_cu = 0;     // CuShare::even_cu of the stream; 0: the same as n_cu
+};
 // Chooses tile shape and K split for a stream restricted to n_cu compute units.
-GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats, bool lean = true);
+GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits = GemmTraits());
 // every plan worth timing for a problem (measured plan selection)
 std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, size_t ws_floats);
 double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int variant, int nw);   // the planner's estimate, us without the launch
-// the wave-split-K shape of the lowest estimate whose tile columns divide `columns` channels (0: any)
+// the wave-split-K shape of the lowest estimate whose tile columns divide `columns` channels (0: any); n_cu: CuShare::even_cu
 GemmPlan conv_wsk_plan_columns(long M, long N, long K, int n_cu, int columns);
 // *n_launched (optional) is increased by the number of kernels launched (2 when K is split).
 hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &p, const SeDeal &deal, hipStream_t s, uint32_t *n_launched);
 // Two layers that do not depend on each other in one launch (wave-split-K kernel only).  conv_gemm_plan_pair takes
 // the layers' own plans and returns true, with a common plan for each, when sharing a launch is modelled to pay.
+// n_cu: CuShare::even_cu of the stream.
 bool conv_gemm_plan_pair(const GemmPlan &s0, long M0, long N0, long K0, bool lean0, const GemmPlan &s1, long M1, long N1, long K1, bool lean1, int n_cu,
                          GemmPlan *p0, GemmPlan *p1);
 hipError_t launch_conv_gemm_pair(const ConvGemmArgs &a0, const GemmPlan &p0, const ConvGemmArgs &a1, const GemmPlan &p1, hipStream_t s,
@@ -112,7 +118,7 @@ hipError_t launch_gconv(const GConvArgs &a, int n_cu, hipStream_t s);
 // returns false when no S <= 16 dividing `groups` makes S*cig a multiple of 32 and S*cog a multiple of 16; the weights
 // must then be in the direct kernel's layout, otherwise in the super-group blocks described in k_gconv.hip.
 bool gconv_mfma_pick(int groups, int cig, int cog, int *S_out);
-hipError_t launch_gconv_mfma(const GConvArgs &a, int S, int n_cu, hipStream_t s);
+hipError_t launch_gconv_mfma(const GConvArgs &a, int S, int n_cu, hipStream_t s);      // n_cu: CuShare::even_cu of the stream
 GemmPlan gconv_mfma_plan(const GConvArgs &a, int S, int n_cu);               // tile and grid launch_gconv_mfma uses
 const char *gconv_mfma_kernel_name(const GConvArgs &a);
 // y[m][0 .. c0) = a[m][:], y[m][c0 .. c0 + c1) = b[m][:]

@@ -39,6 +39,18 @@ struct SeDeal {
 struct CuShare {
     int n_cu = 0;
     SeDeal deal;
+    // Those a launch that is not dealt has the use of: every shader engine is handed as many workgroups as the one with the fewest
+    // enabled CUs, and that one finishes last.
+    int even_cu() const
+    {
+        if (deal.level == 0) return n_cu;
+        uint32_t cmin = deal.level;
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t c = deal.se_caps >> (8 * q) & 255u;
+            if (c && c < cmin) cmin = c;
+        }
+        return (int)(8 * deal.slots * cmin);
+    }
 };
 
 __host__ __device__ inline uint32_t se_cap_sum(uint32_t caps) { return (caps & 255u) + (caps >> 8 & 255u) + (caps >> 16 & 255u) + (caps >> 24); }

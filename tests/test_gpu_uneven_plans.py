@@ -1,0 +1,33 @@
+"""Layers that fill a share whose shader engines hold unequal numbers of compute units run on tiles that are dealt to the engines."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import paper_2506_12598_amd as ec
+import workloads as wl
+from oracle import forward as orc
+from gpu_util import GpuModel, rel_to_range
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cus", [144, 160, 192])                # 8 + 8 + 1 + 1, 8 + 8 + 2 + 2 and 8 + 8 + 4 + 4 CUs per XCD
+@pytest.mark.parametrize("kw,batch,tol", [
+    (dict(op="linear", dtype=wl.DT_BF16, rows=1005, k=3072, n=768, bias_std=0.3, std=0.02), 1, 2e-4),      # float32 output
+    (dict(op="conv", dtype=wl.DT_F16, cin=128, cout=128, h=28, w=28, k=3, stride=1, pad=1, act=wl.ACT_RELU, bias_std=0.5), 3, 2.0 ** -11),
+])
+def test_dealt_tiles(cus, kw, batch, tol):
+    kw = dict(kw)
+    pool = ec.Pool([(ec.eclip_mask_layout(256, 16, 1, 0, cus // 16), 0)])
+    m = wl.single_layer(kw.pop("op"), kw.pop("dtype"), seed=cus, **kw)
+    x = wl.make_input(m, batch)
+    g = GpuModel(m, max_batch=batch, pool=pool)
+    try:
+        assert g.h.kernel_info(0, 0, batch)["kernel"] in ("conv_gemm_dma_kernel", "conv_gemm_kernel")
+        got = g.run(x, table=[0] * m.n_groups)
+        assert np.isfinite(got).all()
+        assert rel_to_range(got, orc.run_model(m, x)) <= tol
+    finally:
+        g.free()
+        pool.destroy()

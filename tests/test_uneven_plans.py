@@ -1,0 +1,90 @@
+"""The planner on shares whose shader engines hold unequal numbers of compute units: called directly on the host."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include "kernels.h"
+using namespace eclip;
+int main()
+{
+    char what;
+    int v[6];
+    while (std::scanf(" %c", &what) == 1) {
+        const int n = what == 'e' ? 5 : 6;
+        for (int i = 0; i < n; ++i) std::scanf("%d", v + i);
+        if (what == 'e') {                                   // n_cu and the enabled CUs of the four shader engines
+            CuShare cu{v[0], SeDeal()};
+            int lo = 255;
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t c = (uint32_t)v[1 + q];
+                if (c == 0) continue;
+                cu.deal.se_caps |= c << (8 * q);
+                cu.deal.slots++;
+                if (c > cu.deal.level) cu.deal.level = c;
+                if ((int)c < lo) lo = (int)c;
+            }
+            if ((int)cu.deal.level == lo) cu.deal.level = 0;
+            std::printf("%d\n", cu.even_cu());
+        } else {                                             // M N K n_cu even_cu lean
+            GemmTraits t;
+            t.even_cu = v[4];
+            t.lean = v[5] != 0;
+            const GemmPlan p = conv_gemm_plan(v[0], v[1], v[2], v[3], (size_t)16 << 20, t);
+            std::printf("%d %.4f\n", p.kind, p.cost);
+        }
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plans")
+    src, obj, exe = str(d / "plans.hip"), str(d / "plans.o"), str(d / "plans")
+    open(src, "w").write(PROGRAM)
+    pkg = os.path.join(ROOT, "paper_2506_12598_amd")
+    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-c", "-I", os.path.join(pkg, "csrc"),
+                    "-I", os.path.join(ROOT, "include"), src, "-o", obj], check=True, capture_output=True)
+    subprocess.run(["hipcc", obj, "-o", exe, os.path.join(pkg, "libeclip.so"), "-Wl,-rpath," + pkg], check=True, capture_output=True)
+
+    def ask(line):
+        return subprocess.run([exe], input=line, capture_output=True, text=True, check=True).stdout.split()
+    return ask
+
+
+@pytest.mark.parametrize("n_cu,engines,even", [
+    (256, (8, 8, 8, 8), 256), (160, (5, 5, 5, 5), 160), (128, (8, 8, 0, 0), 128),                   # nothing to deal
+    (144, (8, 8, 1, 1), 32), (160, (8, 8, 2, 2), 64), (160, (2, 2, 8, 8), 64), (192, (8, 8, 4, 4), 128), (240, (8, 8, 7, 7), 224),
+    (88, (0, 8, 0, 3), 48),
+])
+def test_cus_an_undealt_launch_can_count_on(plans, n_cu, engines, even):
+    assert plans(f"e {n_cu} " + " ".join(map(str, engines)) + "\n") == [str(even)]
+
+
+@pytest.mark.parametrize("m,n,k,n_cu,even", [
+    # us on wave-split-K, us on the dealt tile
+    (128, 3072, 768, 144, 32), (128, 3072, 768, 160, 64),             # 12.5, 6.9; 9.8, 6.2
+    (384, 1024, 1024, 144, 32), (384, 1024, 1024, 160, 64),           # 12.4, 7.1; 10.7, 6.4
+    (1005, 768, 3072, 192, 128), (1176, 128, 1152, 144, 32),          # 25.1, 14.3; 22.0, 8.0
+])
+def test_layers_that_fill_an_uneven_share_take_a_dealt_tile(plans, m, n, k, n_cu, even):
+    assert plans(f"p {m} {n} {k} {n_cu} {even} 1\n")[0] == "0"
+
+
+@pytest.mark.parametrize("lean", [0, 1])
+@pytest.mark.parametrize("m,n,k", [(49, 512, 512), (128, 768, 768), (784, 128, 512), (3136, 64, 576), (1005, 768, 3072)])
+def test_an_uneven_share_never_looks_cheaper_than_an_even_one(plans, m, n, k, lean):
+    even, uneven, fewer = (float(plans(f"p {m} {n} {k} {c} {e} {lean}\n")[1]) for c, e in ((192, 192), (192, 128), (144, 32)))
+    assert even <= uneven <= fewer
+
+
+def test_even_share_is_the_default(plans):
+    for m, n, k in ((128, 3072, 768), (1536, 1024, 4096), (49, 2048, 512)):
+        assert plans(f"p {m} {n} {k} 160 0 1\n") == plans(f"p {m} {n} {k} 160 160 1\n")
