@@ -221,6 +221,8 @@ static double wsk_whole_cost(long M, long N, long K, int n_cu, int v, int nw)
 // is by how much the LDS tiles' table prices the small copied tiles of that measurement too high.  Of all plans the picks cost 5.3 % more than the
 // best on average (7.3 % with the general form's constants) and 24 % at worst (48 %); the host submits a launch in 2.5 us,
 // which blurs the shortest.  64 x 64 tiles carry 0.8 us that the fit does not ask for: where it errs, it errs towards them.
+// With 256 CUs few of those layers had a second round.  On 64 and 96 CUs 32 x 64 tiles of 8 wavefronts take 0.6 us more for each (up to three) than
+// the rest of the model knows (2304 x 768 by 64 rows on 64 CUs, 72 workgroups: 7.5 us; with 4 wavefronts, which it takes now, 6.6).
 static double wsk_lean_cost(long M, long N, long K, int n_cu, int v, int nw)
 {
     const double ra = 8.348e4, rw = 1.332e5, rm = 2.791e6, lat = 0.368, c_out = 2.165e-6, c_red = 1.1165e-4, l2 = 9.0e7, c_wg = 0.014, base = 0.324;
@@ -237,7 +239,8 @@ static double wsk_lean_cost(long M, long N, long K, int n_cu, int v, int nw)
     const double all = t * (a_b + w_b) / l2;
     static const double offset[CONV_WSK_VARIANTS][3] = {{0.0, -0.324, -1.127}, {-0.347, -1.156, -2.773}, {0.21, -1.517, 0.0},
                                                         {0.582, 0.529, 0.356}, {0.336, 0.166, -0.264},   {0.01, -0.333, -1.203}};
-    return (cu > all ? cu : all) + lat * (double)cdiv(cdiv(cdiv(K, 32), nw), depth) + base + offset[v][nw == 4 ? 0 : nw == 8 ? 1 : 2];
+    const double again = v == 1 && nw == 8 && per_cu > 1.0 ? 0.6 * ((per_cu < 4.0 ? per_cu : 4.0) - 1.0) : 0.0;
+    return (cu > all ? cu : all) + lat * (double)cdiv(cdiv(cdiv(K, 32), nw), depth) + base + offset[v][nw == 4 ? 0 : nw == 8 ? 1 : 2] + again;
 }
 
 // the planner's estimate for one wave-split-K candidate (tuning aid; tile `v`, `nw` wavefronts)
@@ -354,12 +357,14 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // (at worst 29 instead of 175 %: 1176 x 128 in nine taps of 128 on 144 CUs 22.0 us, now 8.0).
     // (A further 1.2 us on every tile, for inputs that the layer before has just written, made the 160 kinds of request above
     // 1.1 % slower, none faster by more than 1.5 % and ResNeXt at batch 8 on 160 CUs 651 us instead of 589; 2.4 us another 1.5 %.)
+    // (13 carries 0.2 us more than it was fitted at: the copied tiles next to it have a shorter prologue since, 784 x 512 x 128 on 64 CUs takes
+    // 4.6 us on it and 3.6 on 27.)
     // (17 lost 5 us of each launch to spilled registers when it was fitted; of that 3.2 are taken off here, so that a layer that 3 and 17
     // could both take is still priced by row 3: plan_of in eclip.cpp then runs it on 17.)
     struct LdsTile { int variant; double step, fixed, more, two; };
     static const LdsTile lds[] = {
                                   {0, 0.509, 4.049, 7.322, 1.373}, {3, 0.568, 8.784, 16.049, 0}, {5, 0.595, 8.271, 16.021, 0}, {8, 0.525, 5.267, 9.068, 0},
-                                  {13, 0.312, 2.698, 4.335, 1.656}, {15, 0.278, 3.194, 5.868, 1.418}, {16, 0.483, 4.611, 5.981, 0}, {17, 0.512, 10.9, 16.4, 0},
+                                  {13, 0.312, 2.898, 4.535, 1.656}, {15, 0.278, 3.194, 5.868, 1.418}, {16, 0.483, 4.611, 5.981, 0}, {17, 0.512, 10.9, 16.4, 0},
                                   {18, 0.552, 6.313, 10.504, 0}, {19, 0.579, 6.094, 8.303, 0}, {20, 0.337, 4.272, 6.499, 0}, {21, 0.444, 5.202, 8.054, 0},
                                   {22, 0.267, 3.021, 6.171, 1.444}, {23, 0.257, 3.012, 4.226, 1.544}, {24, 0.406, 8.399, 13.526, 0}, {25, 0.409, 8.333, 11.372, 0},
                                   {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.222, 3.505, 5.135, 1.609}};

@@ -1,4 +1,4 @@
-"""The planner on shares whose shader engines hold unequal numbers of compute units: called directly on the host."""
+"""The planner on small shares and on shares whose shader engines hold unequal numbers of compute units: called directly on the host."""
 import os
 import shutil
 import subprocess
@@ -37,7 +37,7 @@ int main()
             t.even_cu = v[4];
             t.lean = v[5] != 0;
             const GemmPlan p = conv_gemm_plan(v[0], v[1], v[2], v[3], (size_t)16 << 20, t);
-            std::printf("%d %.4f\n", p.kind, p.cost);
+            std::printf("%d %.4f %d %d\n", p.kind, p.cost, p.variant, p.nw);
         }
     }
 }
@@ -83,6 +83,12 @@ def test_layers_that_fill_an_uneven_share_take_a_dealt_tile(plans, m, n, k, n_cu
 def test_an_uneven_share_never_looks_cheaper_than_an_even_one(plans, m, n, k, lean):
     even, uneven, fewer = (float(plans(f"p {m} {n} {k} {c} {e} {lean}\n")[1]) for c, e in ((192, 192), (192, 128), (144, 32)))
     assert even <= uneven <= fewer
+
+
+@pytest.mark.parametrize("m,n,k,n_cu", [(64, 2304, 768, 64), (3136, 64, 576, 96)])      # 7.5 -> 6.6 us, 6.3 -> 5.5
+def test_a_second_round_of_32x64_tiles_of_8_wavefronts_is_not_free(plans, m, n, k, n_cu):
+    kind, _, variant, nw = plans(f"p {m} {n} {k} {n_cu} 0 1\n")
+    assert (kind, variant, nw) != ("1", "1", "8")
 
 
 def test_even_share_is_the_default(plans):
