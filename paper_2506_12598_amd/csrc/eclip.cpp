@@ -1011,7 +1011,10 @@ static GemmShape gemm_shape(const LayerPlan &P, int batch)
 // The launch plan of a matrix-core layer: the measured choice when eclip_model_tune has seen this problem on a stream of
 // this CU count, else the planner's cost model.
 static bool lean_of(const GemmShape &g) { return conv_wsk_is_lean(g.KH, g.KW, g.stride, g.pad, g.Cin, g.Cout); }
-static GemmTraits traits_of(const GemmShape &g, const CuShare &cu) { return GemmTraits{lean_of(g), cu.even_cu()}; }
+static GemmTraits traits_of(const GemmShape &g, const CuShare &cu)
+{
+    return GemmTraits{lean_of(g), cu.even_cu(), conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout)};
+}
 static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, const CuShare &cu)
 {
     const int n_cu = cu.n_cu;
@@ -1020,13 +1023,7 @@ static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, const CuShare 
         const auto it = m->tuned.find(std::array<long, 4>{M, N, K, (long)n_cu});
         if (it != m->tuned.end()) return it->second;
     }
-    GemmPlan pl = conv_gemm_plan(M, N, K, n_cu, m->ws_floats, traits_of(g, cu));
-    // The planner prices 256 x 256 tiles by the ping-pong kernel's row.  Where the operands fit the copied kernel's fast address
-    // forms it serves the same tiles in less time from 256 terms on (its K step costs 0.51 instead of 0.57 us and its fill 0.3 more):
-    // 1536 x 4096 on 96 CUs, K = 1024, 2048, 4096: 29.1, 47.9, 85.3 us on the ping-pong kernel, 27.0, 43.6, 76.3 on this one.
-    if (pl.kind == 0 && pl.variant == 3 && pl.splits == 1 && K >= 256 && g.Cin % 32 == 0 && g.KH * g.KW <= 32 && N % 8 == 0 && !getenv("ECLIP_GEMM_FORCE"))
-        pl.variant = 17;
-    return pl;
+    return conv_gemm_plan(M, N, K, n_cu, m->ws_floats, traits_of(g, cu));
 }
 
 extern "C" eclip_status eclip_model_load(eclip_pool *pool, const eclip_model_desc *desc, const void *weights,

@@ -359,16 +359,21 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // 1.1 % slower, none faster by more than 1.5 % and ResNeXt at batch 8 on 160 CUs 651 us instead of 589; 2.4 us another 1.5 %.)
     // (13 carries 0.2 us more than it was fitted at: the copied tiles next to it have a shorter prologue since, 784 x 512 x 128 on 64 CUs takes
     // 4.6 us on it and 3.6 on 27.)
-    // (17 lost 5 us of each launch to spilled registers when it was fitted; of that 3.2 are taken off here, so that a layer that 3 and 17
-    // could both take is still priced by row 3: plan_of in eclip.cpp then runs it on 17.)
+    // (17 lost 5 us of each launch to spilled registers when the rest was fitted.  Its rows, one for the layers of conv_gemm_is_copied and one for all
+    // others, are set against 3, which has the same tile: 1536 x 4096 on 96 CUs, K = 128, 256, 512, 1024, 2048, 4096: 13.4, 16.1, 21.4, 32.1, 49.8,
+    // 89.6 us on 3 and 14.0, 16.5, 21.3, 31.5, 46.7, 82.7 on 17, on 48 CUs 23.1, 28.1, 38.8, 60.2, 92.9, 168.8 and 24.3, 28.7, 38.7, 59.6, 87.5, 157.6;
+    // in its general address form K = 264, 1032, 2056: 18.7, 38.6, 62.5 and 19.8, 38.7, 60.7.  With 4092 columns it is the faster one
+    // at every K (256: 42.0 and 33.6), which the second row does not say.)
     struct LdsTile { int variant; double step, fixed, more, two; };
+    static const LdsTile copied_256 = {17, 0.515, 9.7, 16.75, 0};
     static const LdsTile lds[] = {
                                   {0, 0.509, 4.049, 7.322, 1.373}, {3, 0.568, 8.784, 16.049, 0}, {5, 0.595, 8.271, 16.021, 0}, {8, 0.525, 5.267, 9.068, 0},
                                   {13, 0.312, 2.898, 4.535, 1.656}, {15, 0.278, 3.194, 5.868, 1.418}, {16, 0.483, 4.611, 5.981, 0}, {17, 0.512, 10.9, 16.4, 0},
                                   {18, 0.552, 6.313, 10.504, 0}, {19, 0.579, 6.094, 8.303, 0}, {20, 0.337, 4.272, 6.499, 0}, {21, 0.444, 5.202, 8.054, 0},
                                   {22, 0.267, 3.021, 6.171, 1.444}, {23, 0.257, 3.012, 4.226, 1.544}, {24, 0.406, 8.399, 13.526, 0}, {25, 0.409, 8.333, 11.372, 0},
                                   {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.222, 3.505, 5.135, 1.609}};
-    for (const LdsTile &c : lds) {
+    for (const LdsTile &row : lds) {
+        const LdsTile &c = row.variant == 17 && traits.copied ? copied_256 : row;
         int bm, bn, bk;
         conv_gemm_tile(c.variant, &bm, &bn, &bk);
         const long KT = cdiv(K, bk);
@@ -396,6 +401,8 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     *cost_out = pl.cost = best;
     return pl;
 }
+bool conv_gemm_is_copied(int KH, int KW, int Cin, int Cout) { return Cin % 32 == 0 && KH * KW <= 32 && Cout % 8 == 0; }
+
 GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits)
 {
     double cost;

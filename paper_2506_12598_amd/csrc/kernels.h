@@ -62,7 +62,9 @@ int conv_wsk_lean_depth(int variant, int nw);         // K steps its wavefronts 
 struct GemmTraits {
     bool lean = true;    // the lean form of the wave-split-K kernel takes the layer
     int even_cu = 0;     // CuShare::even_cu of the stream; 0: the same as n_cu
+    bool copied = false; // the copied tiles take the layer in a fast address form and with their fast epilogue (conv_gemm_is_copied)
 };
+bool conv_gemm_is_copied(int KH, int KW, int Cin, int Cout);
 // Chooses tile shape and K split for a stream restricted to n_cu compute units.
 GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits = GemmTraits());
 // every plan worth timing for a problem (measured plan selection)

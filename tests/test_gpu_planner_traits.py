@@ -31,3 +31,19 @@ def test_dealt_tiles(cus, kw, batch, tol):
     finally:
         g.free()
         pool.destroy()
+
+
+def test_tuning_starts_from_the_plan_an_untuned_model_runs():
+    # 256 x 256 tiles on 96 CUs: the copied kernel untuned, and no slower kernel of the same tile after tuning (50 us on the ping-pong kernel, 47)
+    pool = ec.Pool([(ec.eclip_mask_layout(256, 32, 1, 0, 3), 0)])
+    m = wl.single_layer("linear", wl.DT_BF16, seed=5, rows=1536, k=2048, n=4096, std=0.02)
+    h = ec.Model(pool, m, wl.to_storage(m.weights, m.dtype))
+    try:
+        before = h.kernel_info(0, 0, 1)
+        assert before["kernel"] == "conv_gemm_dma_kernel" and before["tile"] == (256, 256)
+        assert h.tune(0, batch=1, iters=3) == 1
+        after = h.kernel_info(0, 0, 1)
+        assert after["kernel"] == "conv_gemm_dma_kernel" or after["tile"] != (256, 256)
+    finally:
+        h.free()
+        pool.destroy()

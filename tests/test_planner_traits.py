@@ -1,4 +1,5 @@
-"""The planner on small shares and on shares whose shader engines hold unequal numbers of compute units: called directly on the host."""
+"""What the planner makes of small shares, of shares whose shader engines hold unequal numbers of compute units, and of layers that only some
+kernels take in their fast form: called directly on the host."""
 import os
 import shutil
 import subprocess
@@ -17,7 +18,7 @@ int main()
     char what;
     int v[6];
     while (std::scanf(" %c", &what) == 1) {
-        const int n = what == 'e' ? 5 : 6;
+        const int n = what == 'f' ? 4 : what == 'e' ? 5 : 6;
         for (int i = 0; i < n; ++i) std::scanf("%d", v + i);
         if (what == 'e') {                                   // n_cu and the enabled CUs of the four shader engines
             CuShare cu{v[0], SeDeal()};
@@ -32,10 +33,13 @@ int main()
             }
             if ((int)cu.deal.level == lo) cu.deal.level = 0;
             std::printf("%d\n", cu.even_cu());
-        } else {                                             // M N K n_cu even_cu lean
+        } else if (what == 'f') {                            // KH KW Cin Cout
+            std::printf("%d\n", (int)conv_gemm_is_copied(v[0], v[1], v[2], v[3]));
+        } else {                                             // p or c (the copied tiles' fast form): M N K n_cu even_cu lean
             GemmTraits t;
             t.even_cu = v[4];
             t.lean = v[5] != 0;
+            t.copied = what == 'c';
             const GemmPlan p = conv_gemm_plan(v[0], v[1], v[2], v[3], (size_t)16 << 20, t);
             std::printf("%d %.4f %d %d\n", p.kind, p.cost, p.variant, p.nw);
         }
@@ -94,3 +98,26 @@ def test_a_second_round_of_32x64_tiles_of_8_wavefronts_is_not_free(plans, m, n, 
 def test_even_share_is_the_default(plans):
     for m, n, k in ((128, 3072, 768), (1536, 1024, 4096), (49, 2048, 512)):
         assert plans(f"p {m} {n} {k} 160 0 1\n") == plans(f"p {m} {n} {k} 160 160 1\n")
+
+
+@pytest.mark.parametrize("kh,kw,cin,cout,copied", [
+    (1, 1, 1024, 4096, 1), (1, 1, 1032, 4096, 0), (1, 1, 1024, 4092, 0), (3, 3, 96, 2048, 1), (3, 3, 72, 2048, 0), (4, 8, 64, 64, 1), (7, 7, 64, 2048, 0),
+])
+def test_which_layers_the_copied_tiles_take_in_their_fast_form(plans, kh, kw, cin, cout, copied):
+    assert plans(f"f {kh} {kw} {cin} {cout}\n") == [str(copied)]
+
+
+@pytest.mark.parametrize("what,k,variant,fixed,step", [
+    ("c", 1024, 17, 9.7, 0.515), ("c", 4096, 17, 9.7, 0.515),
+    ("p", 1024, 3, 8.784, 0.568), ("p", 2048, 17, 10.9, 0.512),      # general address form or ragged columns: the copied tile from 1056 on
+])
+def test_256x256_tiles_are_picked_and_priced_by_one_table(plans, what, k, variant, fixed, step):
+    # 96 tiles of 256 x 256, one per CU
+    kind, cost, v, _ = plans(f"{what} 1536 4096 {k} 96 0 1\n")
+    assert (kind, v) == ("0", str(variant))
+    assert float(cost) == pytest.approx(fixed + k / 32 * step * 1.15, abs=1e-3)
+
+
+def test_short_sums_stay_on_the_ping_pong_tiles(plans):
+    for k in (128, 256):
+        assert plans(f"c 1536 4096 {k} 96 0 1\n")[2] != "17"
