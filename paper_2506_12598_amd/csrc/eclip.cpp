@@ -1010,10 +1010,10 @@ static GemmShape gemm_shape(const LayerPlan &P, int batch)
 
 // The launch plan of a matrix-core layer: the measured choice when eclip_model_tune has seen this problem on a stream of
 // this CU count, else the planner's cost model.
-static bool lean_of(const GemmShape &g) { return conv_wsk_is_lean(g.KH, g.KW, g.stride, g.pad, g.Cin, g.Cout); }
+static int lean_form_of(const GemmShape &g) { return conv_wsk_lean_form(g.KH, g.KW, g.stride, g.pad, g.Cin, g.Cout); }
 static GemmTraits traits_of(const GemmShape &g, const CuShare &cu)
 {
-    return GemmTraits{lean_of(g), cu.even_cu(), conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout)};
+    return GemmTraits{lean_form_of(g) >= 0, cu.even_cu(), conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout)};
 }
 static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, const CuShare &cu)
 {
@@ -1397,7 +1397,7 @@ static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t
     ConvGemmArgs a[2];
     GemmPlan own[2], pl[2];
     long mnk[2][3];
-    bool lean[2];
+    int form[2];
     for (int k = 0; k < 2; ++k) {
         const LayerPlan &P = m->layers[i + k];
         const eclip_layer &L = P.L;
@@ -1413,9 +1413,9 @@ static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t
         a[k].ldy = P.ld;
         mnk[k][0] = (long)g.B * g.Ho * g.Wo; mnk[k][1] = g.Cout; mnk[k][2] = (long)g.KH * g.KW * g.Cin;
         own[k] = plan_of(m, g, cu);
-        lean[k] = lean_of(g);
+        form[k] = lean_form_of(g);
     }
-    if (!conv_gemm_plan_pair(own[0], mnk[0][0], mnk[0][1], mnk[0][2], lean[0], own[1], mnk[1][0], mnk[1][1], mnk[1][2], lean[1], cu.even_cu(), &pl[0], &pl[1]))
+    if (!conv_gemm_plan_pair(own[0], mnk[0][0], mnk[0][1], mnk[0][2], form[0], own[1], mnk[1][0], mnk[1][1], mnk[1][2], form[1], cu.even_cu(), &pl[0], &pl[1]))
         return hipSuccess;
     *done = true;
     return launch_conv_gemm_pair(a[0], pl[0], a[1], pl[1], s, n_launched);

@@ -435,16 +435,16 @@ bool conv_gemm_plan_stem(long M, long N, long K, int n_cu, size_t ws_floats, dou
     return true;
 }
 
-bool conv_gemm_plan_pair(const GemmPlan &s0, long M0, long N0, long K0, bool lean0, const GemmPlan &s1, long M1, long N1, long K1, bool lean1, int n_cu,
+bool conv_gemm_plan_pair(const GemmPlan &s0, long M0, long N0, long K0, int form0, const GemmPlan &s1, long M1, long N1, long K1, int form1, int n_cu,
                          GemmPlan *p0, GemmPlan *p1)
 {
     if (getenv("ECLIP_GEMM_FORCE") || getenv("ECLIP_NO_PAIRS")) return false;
     if ((s0.kind != 1 && s0.cost <= 0.0) || (s1.kind != 1 && s1.cost <= 0.0)) return false;      // chosen by measurement: kept
     // all on the scale of the tiles' costs
     auto wsk = [&](bool lean, long M, long N, long K, int v, int nw) { return lean ? wsk_lean_cost(M, N, K, n_cu, v, nw) : wsk_whole_cost(M, N, K, n_cu, v, nw); };
-    const double separate = (s0.kind == 1 ? wsk(lean0, M0, N0, K0, s0.variant, s0.nw) : s0.cost) +
-                            (s1.kind == 1 ? wsk(lean1, M1, N1, K1, s1.variant, s1.nw) : s1.cost);
-    const bool lean = lean0 && lean1;
+    const double separate = (s0.kind == 1 ? wsk(form0 >= 0, M0, N0, K0, s0.variant, s0.nw) : s0.cost) +
+                            (s1.kind == 1 ? wsk(form1 >= 0, M1, N1, K1, s1.variant, s1.nw) : s1.cost);
+    const bool lean = conv_wsk_lean_pair_form(form0, form1) >= 0;      // the kernel that launch_conv_wsk_pair takes
     double best = 1e30;
     int bv = -1, bnw = 0;
     for (int v = 0; v < CONV_WSK_VARIANTS; ++v)

@@ -406,11 +406,11 @@ const void *kernel_of(int variant, int nw, int form, bool grouped)
 
 }  // namespace
 
-bool conv_wsk_is_lean(int KH, int KW, int stride, int pad, int Cin, int Cout)
+int conv_wsk_lean_form(int KH, int KW, int stride, int pad, int Cin, int Cout)
 {
     GemmDev d{};
     d.KH = KH; d.KW = KW; d.stride = stride; d.pad = pad; d.Cin = Cin; d.N = d.ldy = Cout; d.K = KH * KW * Cin;
-    return wsk_lean_form(d) >= 0;
+    return wsk_lean_form(d);
 }
 int conv_wsk_lean_depth(int variant, int nw)
 {
@@ -430,12 +430,12 @@ int wsk_lean_form(const GemmDev &d)
 }
 
 // The form that serves two layers of one launch: their common one, or WINDOW, of which ROWS is a case.
-int wsk_lean_pair_form(const GemmDev &d0, const GemmDev &d1)
+int conv_wsk_lean_pair_form(int f0, int f1)
 {
-    const int f0 = wsk_lean_form(d0), f1 = wsk_lean_form(d1);
     if (f0 == f1) return f0;
     return (f0 == WSK_ROWS || f0 == WSK_WINDOW) && (f1 == WSK_ROWS || f1 == WSK_WINDOW) ? WSK_WINDOW : -1;
 }
+int wsk_lean_pair_form(const GemmDev &d0, const GemmDev &d1) { return conv_wsk_lean_pair_form(wsk_lean_form(d0), wsk_lean_form(d1)); }
 
 hipError_t wsk_lean_init()
 {

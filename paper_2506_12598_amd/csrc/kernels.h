@@ -55,8 +55,10 @@ void conv_wsk_tile(int variant, int *bm, int *bn);
 size_t conv_wsk_lds_bytes(int variant, int nw);
 hipError_t conv_gemm_init();   // raises the dynamic LDS limit of the LDS-tiled kernels once per process
 hipError_t conv_wsk_init();    // raises the dynamic LDS limit of the wave-split-K kernels once per process
-// the layers that the lean form of the wave-split-K kernel takes (k_wsk_lean.hip), which is priced differently
-bool conv_wsk_is_lean(int KH, int KW, int stride, int pad, int Cin, int Cout);
+// the address form in which the lean wave-split-K kernel takes a layer (k_wsk_lean.hip; it is priced differently), and two layers in one launch from
+// the form of each; -1: the general kernel
+int conv_wsk_lean_form(int KH, int KW, int stride, int pad, int Cin, int Cout);
+int conv_wsk_lean_pair_form(int form0, int form1);
 int conv_wsk_lean_depth(int variant, int nw);         // K steps its wavefronts keep in flight
 // What the planner has to know beyond the size of a problem and of its share.
 struct GemmTraits {
@@ -76,8 +78,8 @@ GemmPlan conv_wsk_plan_columns(long M, long N, long K, int n_cu, int columns);
 hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &p, const SeDeal &deal, hipStream_t s, uint32_t *n_launched);
 // Two layers that do not depend on each other in one launch (wave-split-K kernel only).  conv_gemm_plan_pair takes
 // the layers' own plans and returns true, with a common plan for each, when sharing a launch is modelled to pay.
-// n_cu: CuShare::even_cu of the stream.
-bool conv_gemm_plan_pair(const GemmPlan &s0, long M0, long N0, long K0, bool lean0, const GemmPlan &s1, long M1, long N1, long K1, bool lean1, int n_cu,
+// form0, form1: conv_wsk_lean_form of each; n_cu: CuShare::even_cu of the stream.
+bool conv_gemm_plan_pair(const GemmPlan &s0, long M0, long N0, long K0, int form0, const GemmPlan &s1, long M1, long N1, long K1, int form1, int n_cu,
                          GemmPlan *p0, GemmPlan *p1);
 hipError_t launch_conv_gemm_pair(const ConvGemmArgs &a0, const GemmPlan &p0, const ConvGemmArgs &a1, const GemmPlan &p1, hipStream_t s,
                                  uint32_t *n_launched);

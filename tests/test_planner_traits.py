@@ -16,9 +16,9 @@ using namespace eclip;
 int main()
 {
     char what;
-    int v[6];
+    int v[8];
     while (std::scanf(" %c", &what) == 1) {
-        const int n = what == 'f' ? 4 : what == 'e' ? 5 : 6;
+        const int n = what == 'f' ? 4 : what == 'e' ? 5 : what == 's' ? 8 : 6;
         for (int i = 0; i < n; ++i) std::scanf("%d", v + i);
         if (what == 'e') {                                   // n_cu and the enabled CUs of the four shader engines
             CuShare cu{v[0], SeDeal()};
@@ -33,6 +33,14 @@ int main()
             }
             if ((int)cu.deal.level == lo) cu.deal.level = 0;
             std::printf("%d\n", cu.even_cu());
+        } else if (what == 's') {                            // two layers: M N K and lean form of each; 1 when they share a launch on 256 CUs
+            GemmTraits t;
+            GemmPlan own[2], pl[2];
+            for (int k = 0; k < 2; ++k) {
+                t.lean = v[4 * k + 3] >= 0;
+                own[k] = conv_gemm_plan(v[4 * k], v[4 * k + 1], v[4 * k + 2], 256, (size_t)16 << 20, t);
+            }
+            std::printf("%d\n", (int)conv_gemm_plan_pair(own[0], v[0], v[1], v[2], v[3], own[1], v[4], v[5], v[6], v[7], 256, &pl[0], &pl[1]));
         } else if (what == 'f') {                            // KH KW Cin Cout
             std::printf("%d\n", (int)conv_gemm_is_copied(v[0], v[1], v[2], v[3]));
         } else {                                             // p or c (the copied tiles' fast form): M N K n_cu even_cu lean
@@ -121,3 +129,17 @@ def test_256x256_tiles_are_picked_and_priced_by_one_table(plans, what, k, varian
 def test_short_sums_stay_on_the_ping_pong_tiles(plans):
     for k in (128, 256):
         assert plans(f"c 1536 4096 {k} 96 0 1\n")[2] != "17"
+
+
+ROWS, ROWS_TAIL, WINDOW, GENERAL = 0, 1, 2, -1
+
+
+@pytest.mark.parametrize("a,b,shared", [
+    ((784, 128, 72, ROWS_TAIL), (784, 128, 2304, WINDOW), 0),      # the general kernel's price: no lean form serves both
+    ((784, 128, 72, ROWS_TAIL), (784, 128, 64, ROWS), 1),          # short sums: it pays all the same
+    ((784, 128, 64, ROWS), (784, 128, 2304, WINDOW), 1), ((784, 128, 576, WINDOW), (784, 128, 2304, WINDOW), 1),
+    ((784, 128, 72, ROWS_TAIL), (784, 128, 72, ROWS_TAIL), 1),
+])
+def test_two_layers_are_priced_on_the_kernel_that_would_run_both(plans, a, b, shared):
+    ask = lambda p, q: plans("s " + " ".join(map(str, p + q)) + "\n")
+    assert ask(a, b) == ask(b, a) == [str(shared)]
