@@ -290,9 +290,10 @@ eclip_status eclip_profile_group(eclip_model *model, uint32_t group, uint32_t ma
 
 /* Measured plan selection for the matrix-core layers (an extension of the profiling step of Sec. III-B: the library
  * writes its own kernels, so next to "how long does this kernel take on c CUs" it can also ask "which of my tile
- * shapes is fastest on c CUs").  For every distinct GEMM problem (M, N, K) among the model's CONV / LINEAR layers
- * at `batch`, every candidate launch plan is timed on pool entry `mask_id` (minimum over `iters` samples of 6
- * back-to-back launches) and the fastest is remembered for streams of that CU count -- unless the cost model's own
+ * shapes is fastest on c CUs").  For every distinct GEMM problem among the model's CONV / LINEAR layers at `batch` -- (M, N, K)
+ * and the way its operand is addressed: rows, or a window over whole or ragged runs of channels -- every candidate launch
+ * plan is timed on pool entry `mask_id` (minimum over `iters` samples of 6 back-to-back launches) and the fastest is
+ * remembered for streams of that CU count -- unless the cost model's own
  * choice is within 5 % of it, in which case that one stays.  Later eclip_submit / eclip_profile_* / kernel_info
  * calls use the remembered plans; problems or CU counts never tuned keep the cost model's plans.  Results stay
  * within the same tolerances (a different tile only reassociates the fp32 sums).  *n_tuned_out (optional) receives

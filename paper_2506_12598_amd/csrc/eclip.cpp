@@ -503,8 +503,8 @@ struct eclip_model {
     hipStream_t capture_stream = nullptr;  // private to the model: requests are captured here and replayed on pooled streams
     uint64_t stamp = 1, use_clock = 0;     // stamp changes whenever the table, the pool or the plans change
     std::vector<GraphEntry> graphs;
-    // plans chosen by measurement (eclip_model_tune), keyed by (M, N, K, CUs of the stream); the cost model decides the rest
-    std::map<std::array<long, 4>, GemmPlan> tuned;
+    // plans chosen by measurement (eclip_model_tune), keyed by (M, N, K, CUs of the stream, address forms: form_key); the cost model decides the rest
+    std::map<std::array<long, 5>, GemmPlan> tuned;
     void *d_self_in = nullptr;     // zero input / scratch output for profiling
     float *d_self_out = nullptr;
 
@@ -1015,12 +1015,14 @@ static GemmTraits traits_of(const GemmShape &g, const CuShare &cu)
 {
     return GemmTraits{lean_form_of(g) >= 0, cu.even_cu(), conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout)};
 }
+// Layers of one (M, N, K) can still be different work: which kernels take them in a fast form is part of what a measurement holds for.
+static long form_key(const GemmShape &g) { return 2 * lean_form_of(g) + (conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout) ? 1 : 0); }
 static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, const CuShare &cu)
 {
     const int n_cu = cu.n_cu;
     const long M = (long)g.B * g.Ho * g.Wo, N = g.Cout, K = (long)g.KH * g.KW * g.Cin;
     if (!m->tuned.empty() && !getenv("ECLIP_GEMM_FORCE")) {
-        const auto it = m->tuned.find(std::array<long, 4>{M, N, K, (long)n_cu});
+        const auto it = m->tuned.find(std::array<long, 5>{M, N, K, (long)n_cu, form_key(g)});
         if (it != m->tuned.end()) return it->second;
     }
     return conv_gemm_plan(M, N, K, n_cu, m->ws_floats, traits_of(g, cu));
@@ -1817,7 +1819,7 @@ extern "C" eclip_status eclip_model_tune(eclip_model *model, uint32_t mask_id, u
         const eclip_layer &L = P.L;
         const GemmShape g = gemm_shape(P, (int)batch);
         const long M = (long)g.B * g.Ho * g.Wo, N = g.Cout, K = (long)g.KH * g.KW * g.Cin;
-        const std::array<long, 4> key{M, N, K, (long)n_cu};
+        const std::array<long, 5> key{M, N, K, (long)n_cu, form_key(g)};
         if (model->tuned.count(key)) continue;
         auto src = [&](int idx) -> const void * {
             if (idx == -2) return nullptr;

@@ -6,6 +6,7 @@ import pytest
 
 import paper_2506_12598_amd as ec
 import workloads as wl
+import workloads.graphs as graphs
 from oracle import forward as orc
 from gpu_util import GpuModel, rel_to_range
 
@@ -47,3 +48,23 @@ def test_tuning_starts_from_the_plan_an_untuned_model_runs():
     finally:
         h.free()
         pool.destroy()
+
+
+def test_equal_sizes_in_different_address_forms_are_tuned_apart():
+    # M = 36, N = 64, K = 288: a 3 x 3 window over 32 channels and a 2 x 2 window over 72, which only the general kernels take
+    b = graphs._Builder("twins", wl.DT_BF16, 3, graphs.IN_IMAGE, 64, 6, 6)
+    wide = b.conv(-1, 72, 2, 1, 1)
+    slim = b.conv(-1, 32, 1)
+    p = b.conv(slim, 64, 3, 1, 1)
+    q = b.conv(wide, 64, 2)
+    b.eltwise(p, res=q)
+    m = b.finish()
+    x = wl.make_input(m, 1)
+    g = GpuModel(m)
+    try:
+        assert g.h.kernel_info(p, 0, 1)["mnk"] == g.h.kernel_info(q, 0, 1)["mnk"] == (36, 64, 288)
+        assert g.h.tune(0, batch=1, iters=1) == 4
+        assert g.h.tune(0, batch=1, iters=1) == 0
+        assert rel_to_range(g.run(x), orc.run_model(m, x)) <= 2.0 ** -6       # three roundings to bf16 in a row
+    finally:
+        g.free()
