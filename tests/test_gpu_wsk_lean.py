@@ -1,5 +1,5 @@
 """The lean form of the wave-split-K kernel: every tile shape and wavefront count, forced in turn, in its three address forms, where each can
-go wrong: slices longer than the steps in flight and wavefronts without a step, ragged rows, channels and K, windows of 1 to 32 taps."""
+go wrong: slices longer than the steps in flight and wavefronts without a step, ragged rows, channels and K, windows of 1 to 31 taps."""
 from __future__ import annotations
 
 import os
@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import workloads as wl
+import workloads.graphs as graphs
 from oracle import forward as orc
 from gpu_util import rel_to_range, run_gpu
 
@@ -24,7 +25,7 @@ CASES = [
     (dict(op="linear", dtype=wl.DT_F16, rows=17, k=8, n=12, bias_std=0.3, std=0.3), 1, 2e-4),
     (dict(op="linear", dtype=wl.DT_BF16, rows=70, k=1048, n=68, act=wl.ACT_RELU6, bias_std=2.0, std=0.1), 1, 2e-4),
     (dict(op="conv", dtype=wl.DT_F16, cin=24, cout=144, h=9, w=7, k=1, bias_std=0.5), 3, 2.0 ** -11),
-    # windows: 1 x 1 at stride 2, borders on all sides, 25 and 30 taps, several images per tile
+    # windows: 1 x 1 at stride 2, borders on all sides, 25 taps, several images per tile
     (dict(op="conv", dtype=wl.DT_BF16, cin=96, cout=72, h=19, w=17, k=1, stride=2, act=wl.ACT_RELU, bias_std=0.5), 2, 2.0 ** -8),
     (dict(op="conv", dtype=wl.DT_BF16, cin=64, cout=44, h=7, w=5, k=3, stride=1, pad=1, bias_std=0.5, residual=True), 3, 2.0 ** -7),
     (dict(op="conv", dtype=wl.DT_F16, cin=32, cout=40, h=9, w=11, k=5, stride=2, pad=2, act=wl.ACT_RELU, bias_std=0.5), 2, 2.0 ** -11),
@@ -45,6 +46,26 @@ def test_tile(variant, nw):
             assert rel_to_range(got, orc.run_model(m, x)) <= tol, (i, kw)
     finally:
         os.environ.pop("ECLIP_GEMM_FORCE", None)
+
+
+@pytest.mark.parametrize("kh,kw,stride,pad", [(5, 6, 1, 4), (6, 5, 2, 3), (1, 31, 1, 15), (31, 1, 1, 16), (2, 13, 2, 7)])
+@pytest.mark.parametrize("variant,nw", [(1, 4), (3, 16), (5, 8)])
+def test_windows_of_26_to_31_taps(kh, kw, stride, pad, variant, nw):
+    # every tap's bit of the border mask is set for some row and clear for another
+    b = graphs._Builder("wide", wl.DT_F16, kh * kw, graphs.IN_IMAGE, 32, 9, 10)
+    fan_in = 32 * kh * kw
+    w, bias = b.normal((40, 32, kh, kw), (2.0 / fan_in) ** 0.5), b.normal((40,), 0.5)
+    h, wd = (9 + 2 * pad - kh) // stride + 1, (10 + 2 * pad - kw) // stride + 1
+    b.add(graphs.Layer(graphs.OP_CONV, -1, -2, graphs.KIND_IMAGE, 40, h, wd, kh, kw, stride, pad, 1, wl.ACT_RELU, w_off=w, b_off=bias))
+    m = b.finish()
+    x = wl.make_input(m, 2)
+    os.environ["ECLIP_GEMM_FORCE"] = f"1,{variant},{nw}"
+    try:
+        got = run_gpu(m, x)
+    finally:
+        os.environ.pop("ECLIP_GEMM_FORCE", None)
+    assert np.isfinite(got).all()
+    assert rel_to_range(got, orc.run_model(m, x)) <= 2.0 ** -11
 
 
 @pytest.mark.parametrize("k", [72, 96])
