@@ -233,8 +233,8 @@ eclip_status eclip_model_switches(const eclip_model *model, uint32_t *n_switches
 
 /* Enqueue one request.  d_in: device pointer, logical layout, `dtype` elements for IMAGE/SEQ/VEC
  * inputs ([B][C][H][W] / [B][S][Hd] / [B][n]) or int32 token ids [B][S].  d_out: device pointer to
- * float32 in the last layer's logical layout.  Both stay owned by the caller and must remain valid
- * until eclip_wait succeeds.  Returns at once; kernels of group g run on the stream named by the
+ * float32 in the last layer's logical layout, aligned as floats are (4 bytes; the wider stores to it need no more).  Both
+ * stay owned by the caller and must remain valid until eclip_wait succeeds.  Returns at once; kernels of group g run on the stream named by the
  * table, and consecutive groups on different streams are ordered by an event.  Requests of one
  * model execute in submission order.  ESTATE before eclip_alloc_set; EINVAL batch == 0 or
  * > max_batch; ELIMIT more than max_inflight requests outstanding.  EHIP when a launch fails part-way: the
