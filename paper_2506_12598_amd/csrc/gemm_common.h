@@ -17,7 +17,7 @@ struct GemmDev {
     unsigned x_bytes, w_bytes;               // sizes of the x and w tensors (each below 4 GiB)
     int nchw_c;                              // > 0: x is the caller's [B][nchw_c][H][W] tensor (first layer), Cin == 8
     Magic howo, wo, fast;                    // output pixels per image and per row; tiles along the dimension that gemm_tile_of walks first
-    int n_groups = 0;                        // > 0 (k_wsk_lean.hip only): the output channels fall into this many groups, group g reads the Cin
+    int n_groups = 0;                        // > 0 (wave-split-K, both forms): the output channels fall into this many groups, group g reads the Cin
                                              // channels from g Cin on of every pixel
     int ldx, ldy;                            // elements between consecutive pixels of x / rows of y (Cin and N unless the tensor is
                                              // a channel range of a wider buffer: concatenation in place); res is null when ldy != N

@@ -243,7 +243,8 @@ static double wsk_lean_cost(long M, long N, long K, int n_cu, int v, int nw)
     return (cu > all ? cu : all) + lat * (double)cdiv(cdiv(cdiv(K, 32), nw), depth) + base + offset[v][nw == 4 ? 0 : nw == 8 ? 1 : 2] + again;
 }
 
-// the planner's estimate for one wave-split-K candidate (tuning aid; tile `v`, `nw` wavefronts)
+// What the planner compares the general form's shapes by, for a first layer that reads the caller's planes among others (tile `v`, `nw`
+// wavefronts; the lean form is compared by wsk_lean_cost).
 double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int v, int nw) { return wsk_cost(M, N, K, n_cu, v, nw); }
 
 // Grouped convolutions: 4 or 8 wavefronts, all tiles but 64 x 64.

@@ -71,7 +71,7 @@ bool conv_gemm_is_copied(int KH, int KW, int Cin, int Cout);
 GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits = GemmTraits());
 // every plan worth timing for a problem (measured plan selection)
 std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, size_t ws_floats);
-double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int variant, int nw);   // the planner's estimate, us without the launch
+double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int variant, int nw);   // the general form's loop by the planner's model, us
 // the wave-split-K shape of the lowest estimate whose tile columns divide `columns` channels (0: any); n_cu: CuShare::even_cu
 GemmPlan conv_wsk_plan_columns(long M, long N, long K, int n_cu, int columns);
 // *n_launched (optional) is increased by the number of kernels launched (2 when K is split).
