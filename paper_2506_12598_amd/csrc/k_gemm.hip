@@ -375,13 +375,14 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
                                   {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.222, 3.505, 5.135, 1.609}};
     for (const LdsTile &row : lds) {
         const LdsTile &c = row.variant == 17 && traits.copied ? copied_256 : row;
+        if (c.fixed >= best) continue;                                   // planned anew for every launch: what cannot win is not worked out
         int bm, bn, bk;
         conv_gemm_tile(c.variant, &bm, &bn, &bk);
-        const long KT = cdiv(K, bk);
+        const long KT = cdiv(K, bk), mn = cdiv(M, bm) * cdiv(N, bn);
+        const bool dealt = mn > even_cu;
         for (long sp = 1; sp <= 4; sp *= 2) {
-            if (sp > 1 && (K < 512 * sp || (size_t)(sp * M * N) > ws_floats)) continue;
-            const long wgs = tiles(c.variant) * sp;
-            const bool dealt = tiles(c.variant) > even_cu;
+            if (sp > 1 && (K < 512 * sp || (size_t)(sp * M * N) > ws_floats)) break;
+            const long wgs = mn * sp;
             const int cus = dealt || wgs <= even_cu ? n_cu : even_cu;            // few tiles in many slices: not dealt
             const double load = wgs >= cus ? 1.0 : (double)wgs / cus;
             double rounds = (double)cdiv(wgs, cus);
@@ -391,7 +392,7 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
             if (sp > 1) cost += 15.48 + (double)M * N * (4.0 * sp + 2.0) / 4.243e6;
             if (cost < best) {
                 best = cost;
-                pl = GemmPlan{0, c.variant, 1, (int)tiles(c.variant), 4, 0};
+                pl = GemmPlan{0, c.variant, 1, (int)mn, 4, 0};
                 const long kt_per = cdiv(KT, sp);
                 pl.splits = (int)cdiv(KT, kt_per);
             }
