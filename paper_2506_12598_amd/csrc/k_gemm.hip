@@ -351,11 +351,12 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // plan timed in a chain of four to eight layers with weights of their own, so that no layer finds its weights in an L2.
     // `bench.py --plans` repeats that measurement for linear layers.  eclip_model_tune closes what is left by measurement.
     // Shares whose shader engines hold unequal numbers of CUs (160 in granules of 16: 8, 8, 2 and 2 per XCD): LDS tiles are dealt to them
-    // (se_deal.h), which costs 1.1 us (the note read from memory, the surplus workgroups; 240 launches of one round on 144, 160 and 192
-    // CUs against the same on even shares) and 2.1 when it takes a second round; wave-split-K launches are not dealt and priced by the CUs the smallest engine leaves
-    // them (CuShare::even_cu).  Over 63 layers (45 linear, 18 convolutions) on 144, 160 and 192 CUs, replayed from a graph, the picks
-    // cost 4.7, 5.8 and 3.9 % more than the best plan, and 32, 16 and 10 % when all kernels were priced as if the mask were even
-    // (at worst 29 instead of 175 %: 1176 x 128 in nine taps of 128 on 144 CUs 22.0 us, now 8.0).
+    // (se_deal.h).  That costs 1.1 us (the note read from memory, the surplus workgroups) in one round of the share, and in more rounds
+    // up to 1.7 on the most uneven one (144: 8, 8, 1, 1), little from 192 on and nothing on 224 and 240: 1400 timed launches against the row's
+    // price.  Wave-split-K launches are not dealt and priced by the CUs that the smallest engine leaves them (CuShare::even_cu).
+    // Over 88 layers (65 linear, 23 convolutions), replayed from a graph with weights that no L2 holds, the picks cost on 144, 160, 176, 192, 208, 224 and
+    // 240 CUs 3.0, 5.7, 2.9, 2.7, 2.2, 3.3 and 3.6 % more than the best plan; with all kernels priced as if the mask were even 30, 16, 6, 10, 17,
+    // 13 and 4 % (1176 x 128 in nine taps of 128 on 144 CUs 22.0 us, now 8.0).
     // (A further 1.2 us on every tile, for inputs that the layer before has just written, made the 160 kinds of request above
     // 1.1 % slower, none faster by more than 1.5 % and ResNeXt at batch 8 on 160 CUs 651 us instead of 589; 2.4 us another 1.5 %.)
     // (13 carries 0.2 us more than it was fitted at: the copied tiles next to it have a shorter prologue since, 784 x 512 x 128 on 64 CUs takes
@@ -388,7 +389,7 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
             double rounds = (double)cdiv(wgs, cus);
             if (c.two > 0.0 && rounds >= 2.0) rounds = c.two * ((double)wgs / cus > 2.0 ? (double)wgs / (2.0 * cus) : 1.0);
             double cost = c.fixed + (rounds - 1.0) * c.more + rounds * (double)cdiv(KT, sp) * c.step * (1.0 + 0.15 * load * load);
-            if (dealt && even_cu < n_cu) cost += wgs > n_cu ? 2.1 : 1.1;
+            if (dealt && even_cu < n_cu) cost += wgs <= n_cu ? 1.1 : even_cu < 0.8 * n_cu ? 3.0 * (0.8 - (double)even_cu / n_cu) : 0.0;
             if (sp > 1) cost += 15.48 + (double)M * N * (4.0 * sp + 2.0) / 4.243e6;
             if (cost < best) {
                 best = cost;
