@@ -75,12 +75,12 @@ __device__ __forceinline__ uint4 acc_agpr(const f32x4 &a)
     return v;
 }
 
-// Epilogue for outputs of the storage type, or (F32) float ones, with N a multiple of 8 (the rest goes through tile_epilogue).  One wavefront per SIMD
+// Epilogue for outputs of the storage type with N a multiple of 8 (the rest goes through tile_epilogue).  One wavefront per SIMD
 // has nobody to hide behind, so this one is kept short and straight: buffer stores that drop what lies beyond M or N instead
 // of a branch per store, accumulators taken block row by block row.
 // (256 x 192 tile: 5.5 us with
 // the general epilogue, 5.0 with this one.  Passing the accumulators through LDS to a short rolled loop was slower, 7 us.)
-template <typename T, int BM, int BN, int WM, int WN, int TM, int TN, int ACT, bool RES, bool EARLY, bool F32>
+template <typename T, int BM, int BN, int WM, int WN, int TM, int TN, int ACT, bool RES, bool EARLY>
 __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][TN], const u32x4 (&bq)[TN / 2], int m_base, int n_base, int wm, int wn)
 {
     static_assert(TN % 2 == 0, "pairs of blocks");
@@ -89,7 +89,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
     const int m0 = m_base + wm * (BM / WM) + (lane & 15), n0 = n_base + wn * (BN / WN) + 16 * (q & 1) + 8 * (q >> 1);   // see tile_epilogue_impl
     constexpr unsigned OOB = 0xffffffffu;
     const unsigned bytes = (unsigned)(((size_t)(p.M - 1) * p.ldy + p.N) * 2);
-    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(F32 ? (void *)p.y32 : (void *)p.y, 0, (int)(F32 ? 2u * bytes : bytes), 0x00020000);
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void *)p.y, 0, (int)bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void *)(RES ? p.res : p.y), 0, (int)bytes, 0x00020000);
     unsigned off[TN / 2];
     float bv[TN / 2][8];
@@ -140,79 +140,20 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = apply_act_c<ACT>(o[e]);
+            u32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = Cvt<T>::pack2(o[2 * e], o[2 * e + 1]);
             // The row's offset goes into the vector offset here, not into the scalar one: with a scalar-register offset the compiler
             // leaves no gap between a 16-byte store and the next write of its data registers, and on this GPU the store then
             // now and then takes the new values (only with several workgroups on the CU).
             const bool ok = m0 + 16 * i < p.M && n0 + 32 * jp < p.N;
-            const unsigned at = off[jp] + row16 * i;
-            u32x4 v;
-            if constexpr (F32) {
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(o[4 * h + e]);
-                    __builtin_amdgcn_raw_buffer_store_b128(v, ry, ok ? 2u * at + 16u * h : OOB, 0, 0);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = Cvt<T>::pack2(o[2 * e], o[2 * e + 1]);
-                __builtin_amdgcn_raw_buffer_store_b128(v, ry, ok ? at : OOB, 0, 0);
-            }
+            __builtin_amdgcn_raw_buffer_store_b128(v, ry, ok ? off[jp] + row16 * i : OOB, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         });
     });
 }
 
-// Half a sub-tile, staged in LDS, to rows of y or y32 (N a multiple of 4).  Eight turns' bias and residual are requested together, through
-// descriptors of zero bytes when there are none: one at a time, each waiting for its bias, 1536 x 4092 x 1024 on 96 CUs took 47.7 us on 256 x 256
-// tiles, now 38.5, and 1536 x 3004 x 1024 on 256 x 192 tiles 39.9, now 31.8.
-template <typename T, int ROWS, int COLS, int SP, int ACT>
-__device__ __forceinline__ void dma_store_rows(const GemmDev &p, const float *stage, int m0, int n0)
-{
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    constexpr int C4 = COLS / 4, TURNS = ROWS * C4 / 64, U = 8;
-    static_assert(ROWS * C4 % 64 == 0 && TURNS % U == 0, "whole batches of turns");
-    constexpr unsigned OOB = 0xffffffffu;
-    const int lane = threadIdx.x & 63;
-    const unsigned bytes = (unsigned)(((size_t)(p.M - 1) * p.ldy + p.N) * 2);
-    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void *)p.bias, 0, p.bias ? p.N * 2 : 0, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void *)p.res, 0, (int)(p.res ? bytes : 0u), 0x00020000);
-    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.y32 ? (void *)p.y32 : (void *)p.y, 0, (int)(p.y32 ? 2u * bytes : bytes), 0x00020000);
-#pragma unroll 1
-    for (int t0 = lane; t0 < ROWS * C4; t0 += 64 * U) {
-        float4 q[U];
-        u32x2 bias[U], res[U];
-        unsigned off[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int t = t0 + 64 * u, r = t / C4, c = (t - r * C4) * 4, m = m0 + r, n = n0 + c;
-            const bool in = m < p.M && n < p.N;
-            off[u] = in ? ((unsigned)m * (unsigned)p.ldy + (unsigned)n) * 2u : OOB;
-            bias[u] = __builtin_amdgcn_raw_buffer_load_b64(rb, in ? (unsigned)n * 2u : OOB, 0, 0);
-            res[u] = __builtin_amdgcn_raw_buffer_load_b64(rr, off[u], 0, 0);
-            q[u] = *reinterpret_cast<const float4 *>(&stage[r * SP + c]);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float o[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
-            o[0] += Cvt<T>::from_bits(bias[u].x & 0xffffu); o[1] += Cvt<T>::from_bits(bias[u].x >> 16);
-            o[2] += Cvt<T>::from_bits(bias[u].y & 0xffffu); o[3] += Cvt<T>::from_bits(bias[u].y >> 16);
-            o[0] += Cvt<T>::from_bits(res[u].x & 0xffffu); o[1] += Cvt<T>::from_bits(res[u].x >> 16);
-            o[2] += Cvt<T>::from_bits(res[u].y & 0xffffu); o[3] += Cvt<T>::from_bits(res[u].y >> 16);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = apply_act_c<ACT>(o[e]);
-            if (p.y32) {
-                const u32x4 v = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
-                __builtin_amdgcn_raw_buffer_store_b128(v, ry, off[u] == OOB ? OOB : 2u * off[u], 0, 0);
-            } else {
-                const u32x2 v = {Cvt<T>::pack2(o[0], o[1]), Cvt<T>::pack2(o[2], o[3])};
-                __builtin_amdgcn_raw_buffer_store_b64(v, ry, off[u], 0, 0);
-            }
-        }
-    }
-}
-
-// What dma_epilogue does not take (N not a multiple of 8, slices of K), for the tiles whose accumulators fill the
+// What dma_epilogue does not take (float outputs, N not a multiple of 8, slices of K), for the tiles whose accumulators fill the
 // accumulation registers.  tile_epilogue, made for tiles with registers to spare, cost the 256 x 256 tile 60 spilled ones:
 // here half the sub-tile goes through the wavefront's own part of LDS to one short loop.  With acc_pair, 1536 x 4096 x 1024 on 96 CUs:
 // 32.0 -> 27.0 us on 256 x 256 tiles, 1536 x 3072 x 1024 24.3 -> 23.2 on 256 x 192, 26.3 -> 25.7 on 192 x 256.
@@ -237,33 +178,26 @@ __device__ __forceinline__ void dma_epilogue_rest(const GemmDev &p, f32x4 (&acc)
         });
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_s_waitcnt(0xc07f);                            // lgkmcnt(0): this wavefront's LDS writes have landed
-        const int m0 = m_base + wm * (BM / WM) + h * ROWS, n0 = n_base + wn * (BN / WN);
-        if (p.splits == 1 && (p.N & 3) == 0) {
-#define EPI(A) dma_store_rows<T, ROWS, COLS, SP, A>(p, stage, m0, n0)
-            ECLIP_ACT_SWITCH(p.act, EPI)
-#undef EPI
-        } else {
 #pragma unroll 1
-            for (int t = lane; t < ROWS * (COLS / 4); t += 64) {
-                const int r = t / (COLS / 4), c = (t - r * (COLS / 4)) * 4;
-                const int m = m0 + r, n = n0 + c;
-                const float4 q = *reinterpret_cast<const float4 *>(&stage[r * SP + c]);
-                const f32x4 v = {q.x, q.y, q.z, q.w};
-                if (p.splits != 1) {
-                    if (m >= p.M || n >= p.N) continue;
-                    float *dst = p.ws + ((long)z * p.M + m) * p.N + n;
-                    if ((p.N & 3) == 0) {
-                        *reinterpret_cast<float4 *>(dst) = q;
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (n + e < p.N) dst[e] = v[e];
-                    }
+        for (int t = lane; t < ROWS * (COLS / 4); t += 64) {
+            const int r = t / (COLS / 4), c = (t - r * (COLS / 4)) * 4;
+            const int m = m_base + wm * (BM / WM) + h * ROWS + r, n = n_base + wn * (BN / WN) + c;
+            const float4 q = *reinterpret_cast<const float4 *>(&stage[r * SP + c]);
+            const f32x4 v = {q.x, q.y, q.z, q.w};
+            if (p.splits != 1) {
+                if (m >= p.M || n >= p.N) continue;
+                float *dst = p.ws + ((long)z * p.M + m) * p.N + n;
+                if ((p.N & 3) == 0) {
+                    *reinterpret_cast<float4 *>(dst) = q;
                 } else {
-#define EPI(A) epilogue_store<T, A>(p.bias, p.res, p.y, p.y32, p.M, p.N, m, n, v, 4, p.ldy)
-                    ECLIP_ACT_SWITCH(p.act, EPI)
-#undef EPI
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < p.N) dst[e] = v[e];
                 }
+            } else {
+#define EPI(A) epilogue_store<T, A>(p.bias, p.res, p.y, p.y32, p.M, p.N, m, n, v, 4, p.ldy)
+                ECLIP_ACT_SWITCH(p.act, EPI)
+#undef EPI
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -589,25 +523,14 @@ __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 
     }
     asm volatile("s_nop 15");                                          // the compiler does not see the latency of mma_agpr
     wait_and_meet<0>();
-    // Said to be likely so that its code follows the loop's: a launch fetches it from beyond the instruction cache, and 37 KB further away it cost
-    // BERT-large at batch 4 on 96 CUs (48 launches of such tiles) 24 us a request, 3037 -> 3061.
-    if (__builtin_expect(p.splits == 1 && p.y && (p.N & 7) == 0, 1)) {
-#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY, false>(p, acc, bq, m_base, n_base, wm, wn) \
-                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY, false>(p, acc, bq, m_base, n_base, wm, wn)
+    if (p.splits == 1 && p.y && (p.N & 7) == 0) {
+#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY>(p, acc, bq, m_base, n_base, wm, wn) \
+                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY>(p, acc, bq, m_base, n_base, wm, wn)
         ECLIP_ACT_SWITCH(p.act, EPI)
 #undef EPI
         return;
     }
     if constexpr (dma_acc_in_agprs(BM, BN, NW)) {
-        // The last layer of a model, which writes the caller's floats.  (Through the short loop below, whose every turn waits for its bias, 1536 x 4096
-        // x 1024 on 96 CUs took 48 us on 256 x 256 tiles, now 35.5; 1536 x 3000 x 1024 on 256 x 192 tiles 40, now 29.)
-        if (p.splits == 1 && (p.N & 7) == 0) {
-#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY, true>(p, acc, bq, m_base, n_base, wm, wn) \
-                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY, true>(p, acc, bq, m_base, n_base, wm, wn)
-            ECLIP_ACT_SWITCH(p.act, EPI)
-#undef EPI
-            return;
-        }
         static_assert(4 * (TM * 8) * (TN * 16 + 4) * 4 <= ST * STAGE, "half the sub-tiles fit the ring");
         dma_epilogue_rest<T, BM, BN, WM, WN, TM, TN>(p, acc, smem, m_base, n_base, wm, wn, blockIdx.y);
     } else tile_epilogue<T, BM, BN, WM, WN, TM, TN>(p, acc, smem, m_base, n_base, blockIdx.y);
