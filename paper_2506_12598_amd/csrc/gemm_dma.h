@@ -75,12 +75,12 @@ __device__ __forceinline__ uint4 acc_agpr(const f32x4 &a)
     return v;
 }
 
-// Epilogue for outputs of the storage type with N a multiple of 8 (the rest goes through tile_epilogue).  One wavefront per SIMD
+// Epilogue for outputs of the storage type, or (F32) float ones, with N a multiple of 8 (the rest goes through tile_epilogue).  One wavefront per SIMD
 // has nobody to hide behind, so this one is kept short and straight: buffer stores that drop what lies beyond M or N instead
 // of a branch per store, accumulators taken block row by block row.
 // (256 x 192 tile: 5.5 us with
 // the general epilogue, 5.0 with this one.  Passing the accumulators through LDS to a short rolled loop was slower, 7 us.)
-template <typename T, int BM, int BN, int WM, int WN, int TM, int TN, int ACT, bool RES, bool EARLY>
+template <typename T, int BM, int BN, int WM, int WN, int TM, int TN, int ACT, bool RES, bool EARLY, bool F32>
 __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][TN], const u32x4 (&bq)[TN / 2], int m_base, int n_base, int wm, int wn)
 {
     static_assert(TN % 2 == 0, "pairs of blocks");
@@ -89,7 +89,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
     const int m0 = m_base + wm * (BM / WM) + (lane & 15), n0 = n_base + wn * (BN / WN) + 16 * (q & 1) + 8 * (q >> 1);   // see tile_epilogue_impl
     constexpr unsigned OOB = 0xffffffffu;
     const unsigned bytes = (unsigned)(((size_t)(p.M - 1) * p.ldy + p.N) * 2);
-    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void *)p.y, 0, (int)bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(F32 ? (void *)p.y32 : (void *)p.y, 0, (int)(F32 ? 2u * bytes : bytes), 0x00020000);
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void *)(RES ? p.res : p.y), 0, (int)bytes, 0x00020000);
     unsigned off[TN / 2];
     float bv[TN / 2][8];
@@ -140,20 +140,29 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = apply_act_c<ACT>(o[e]);
-            u32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = Cvt<T>::pack2(o[2 * e], o[2 * e + 1]);
             // The row's offset goes into the vector offset here, not into the scalar one: with a scalar-register offset the compiler
             // leaves no gap between a 16-byte store and the next write of its data registers, and on this GPU the store then
             // now and then takes the new values (only with several workgroups on the CU).
             const bool ok = m0 + 16 * i < p.M && n0 + 32 * jp < p.N;
-            __builtin_amdgcn_raw_buffer_store_b128(v, ry, ok ? off[jp] + row16 * i : OOB, 0, 0);
+            u32x4 v;
+            if constexpr (F32) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(o[4 * h + e]);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, ry, ok ? 2u * (off[jp] + row16 * i) + 16u * h : OOB, 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = Cvt<T>::pack2(o[2 * e], o[2 * e + 1]);
+                __builtin_amdgcn_raw_buffer_store_b128(v, ry, ok ? off[jp] + row16 * i : OOB, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
         });
     });
 }
 
-// What dma_epilogue does not take (float outputs, N not a multiple of 8, slices of K), for the tiles whose accumulators fill the
+// What dma_epilogue does not take (N not a multiple of 8, slices of K), for the tiles whose accumulators fill the
 // accumulation registers.  tile_epilogue, made for tiles with registers to spare, cost the 256 x 256 tile 60 spilled ones:
 // here half the sub-tile goes through the wavefront's own part of LDS to one short loop.  With acc_pair, 1536 x 4096 x 1024 on 96 CUs:
 // 32.0 -> 27.0 us on 256 x 256 tiles, 1536 x 3072 x 1024 24.3 -> 23.2 on 256 x 192, 26.3 -> 25.7 on 192 x 256.
@@ -220,6 +229,9 @@ inline unsigned dma_walk(const GemmDev &d, const SeDeal &deal)
     return (unsigned)d.raster | d.fast.shift << 8 | (d.stride == 1 && d.pad == 0 ? DMA_ROWS : 0u) | (deal.level ? DMA_DEALT : 0u);
 }
 
+// Layers that take the F32 form of their tile (conv_gemm_dma_kernel).
+inline bool dma_writes_floats(const GemmDev &d) { return d.y32 && d.splits == 1 && d.N % 8 == 0; }
+
 // A position in the ring of stages: a constant, or a number carried in a register.
 template <typename S> struct RingPos {
     static constexpr unsigned fixed = S::value;
@@ -233,7 +245,12 @@ template <> struct RingPos<unsigned> {
 // n bits (0 to 32) from bit `at` on
 __device__ __forceinline__ unsigned bits_run(int at, int n) { return (n >= 32 ? ~0u : (1u << n) - 1u) << (at & 31); }
 
-template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE>
+// F32: the form of the tiles whose accumulators fill the accumulation registers for layers that write floats (dma_writes_floats).  It is a kernel of
+// its own: as one more branch its epilogues cost the launches that do not take them 0.5 % of the stress mix, with no instruction more
+// executed but the code further apart.  (Through dma_epilogue_rest, whose short loop waits for its bias on every turn, requests of one layer with
+// float outputs took: 3000 x 4096 x 1024 on 96 CUs 97 us, now 74, on 64 CUs 136, now 98; 1536 x 3000 x 1024 on 96 48, now 39; 1005 x 3072 x 768 on 64
+// 43, now 33.)
+template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE, bool F32 = false>
 __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 1024 ? 1 : 2) void conv_gemm_dma_kernel(const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int N, int K, int ldx, int kt_per, unsigned walk, unsigned tiles,
                           unsigned fast_d, unsigned fast_mul, GemmDev p, SeDeal deal)
 {
@@ -523,9 +540,16 @@ __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 
     }
     asm volatile("s_nop 15");                                          // the compiler does not see the latency of mma_agpr
     wait_and_meet<0>();
+    if constexpr (F32) {
+#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY, true>(p, acc, bq, m_base, n_base, wm, wn) \
+                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY, true>(p, acc, bq, m_base, n_base, wm, wn)
+        ECLIP_ACT_SWITCH(p.act, EPI)
+#undef EPI
+        return;
+    }
     if (p.splits == 1 && p.y && (p.N & 7) == 0) {
-#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY>(p, acc, bq, m_base, n_base, wm, wn) \
-                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY>(p, acc, bq, m_base, n_base, wm, wn)
+#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY, false>(p, acc, bq, m_base, n_base, wm, wn) \
+                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY, false>(p, acc, bq, m_base, n_base, wm, wn)
         ECLIP_ACT_SWITCH(p.act, EPI)
 #undef EPI
         return;

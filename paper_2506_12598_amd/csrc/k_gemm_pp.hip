@@ -14,14 +14,27 @@ namespace {
 constexpr PPTile kTile = pp_tile(ECLIP_PP_ID);
 static_assert(kTile.id == ECLIP_PP_ID, "ECLIP_PP_ID is not in ECLIP_PP_TILES");
 
+constexpr bool kFloatForm = kTile.loop == LOOP_DMA && dma_acc_in_agprs(kTile.bm, kTile.bn, 4);
+
+template <typename T, int AMODE, bool F32>
+void launch_dma(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream_t s)
+{
+    hipLaunchKernelGGL((conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, F32>), grid, dim3(256),
+                       dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs), s, d.x, d.w, d.x_bytes, d.M, d.N, d.K, d.ldx, d.kt_per,
+                       dma_walk(d, deal), (unsigned)(d.tiles_m * d.tiles_n), d.fast.d, d.fast.mul, d, deal);
+}
+
 template <typename T, int AMODE>
 hipError_t launch_one(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream_t s)
 {
-    if constexpr (kTile.loop == LOOP_DMA)
-        hipLaunchKernelGGL((conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE>), grid, dim3(256),
-                           dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs), s, d.x, d.w, d.x_bytes, d.M, d.N, d.K, d.ldx, d.kt_per,
-                           dma_walk(d, deal), (unsigned)(d.tiles_m * d.tiles_n), d.fast.d, d.fast.mul, d, deal);
-    else
+    if constexpr (kTile.loop == LOOP_DMA) {
+        if constexpr (kFloatForm)
+            if (dma_writes_floats(d)) {
+                launch_dma<T, AMODE, true>(d, deal, grid, s);
+                return hipGetLastError();
+            }
+        launch_dma<T, AMODE, false>(d, deal, grid, s);
+    } else
         hipLaunchKernelGGL((conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>), grid, dim3(512),
                        lds_bytes(kTile.bm, kTile.bn, kTile.bk, 16, kTile.loop != LOOP_PP_BDIRECT), s, d, deal);
     return hipGetLastError();
@@ -40,10 +53,16 @@ hipError_t launch_mode(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStrea
 template <typename T, int AMODE>
 hipError_t init_one()
 {
-    if constexpr (kTile.loop == LOOP_DMA)
-        return hipFuncSetAttribute((const void *)conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs));
-    else
+    if constexpr (kTile.loop == LOOP_DMA) {
+        const int lds = (int)dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs);
+        if constexpr (kFloatForm) {
+            const hipError_t e = hipFuncSetAttribute((const void *)conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, true>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+        }
+        return hipFuncSetAttribute((const void *)conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, false>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    } else
         return hipFuncSetAttribute((const void *)conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(kTile.bm, kTile.bn, kTile.bk, 16, kTile.loop != LOOP_PP_BDIRECT));
 }
