@@ -482,6 +482,8 @@ struct eclip_model {
     bool has_alloc = false;
     bool stem_direct = false;      // layer 0 is the only reader of an IMAGE input (16-bit models: of <= 4 channels) and a convolution:
                                    // it may read the caller's tensor itself instead of the channels-last copy
+    size_t stem_w = NONE;          // the first layer's weights in the order of the stem kernel, when that takes it
+    bool stem_pool = false;        // and the 3 x 3 stride-2 max-pool behind it, the first layer's only reader
 
     char *d_weights = nullptr;
     char *d_act = nullptr;
@@ -754,6 +756,15 @@ static eclip_status plan_model(const eclip_model_desc *d, size_t weight_elems, e
         m->stem_direct = d->in_kind == ECLIP_IN_IMAGE && S.L.op == ECLIP_OP_CONV && (f32 ? S.L.groups <= 1 : d->in_c <= 4 && m->in_cp == 8 && S.gemm) &&
                          S.L.in0 == -1 && S.L.in1 != -1 && only_reader && d->n_layers > 1;
     }
+    // The stem kernel takes a max-pool along when nobody else reads the convolution (ResNet at 224 x 224, batch 1, 128 CUs: 5.8 us for both,
+    // 4.2 more for a pool of its own).  Maps of up to 16 x 16 keep the pool apart: requests on images that small go on launching what they did.
+    if (m->stem_direct && d->n_layers > 2) {
+        const LayerPlan &Q = m->layers[1];
+        bool only_reader = d->group_of_layer[0] == d->group_of_layer[1];
+        for (uint32_t j = 2; j < d->n_layers; ++j) only_reader &= m->layers[j].L.in0 != 0 && m->layers[j].L.in1 != 0;
+        m->stem_pool = only_reader && Q.L.op == ECLIP_OP_MAXPOOL && Q.L.in0 == 0 && Q.L.kh == 3 && Q.L.kw == 3 && Q.L.stride == 2 && Q.L.pad == 1 &&
+                       Q.out.h * Q.out.w > 256;
+    }
     // Pool + classifier candidates: a GAP layer read only by the linear layer right after it, same group,
     // the linear layer taking no second operand.  Whether the fused kernel pays depends on batch and compute units (decided per request).
     for (uint32_t i = 0; i + 1 < d->n_layers; ++i) {
@@ -984,6 +995,15 @@ static void relayout_weights(eclip_model *m, const E *w, std::vector<char> &aren
                                 if (k0 + e < K) d8[e] = plain[n * K + k0 + e];
                         }
                 P.w_dev = off;
+                if (&P == &m->layers[0] && m->stem_direct && stem_supported(m->in_c, kh, kw, L.stride, L.c) && in_elems(m) * m->max_batch * es < ((size_t)1 << 32)) {
+                    const size_t n = stem_weight_elems(kh, kw, L.c);
+                    put(arena, cursor, nullptr, n * es, &m->stem_w);
+                    E *to = reinterpret_cast<E *>(arena.data() + m->stem_w);
+                    for (size_t at = 0; at < n; ++at) {
+                        const long from = stem_weight_source(kh, kw, L.c, cin_l, at);
+                        to[at] = from < 0 ? (E)0 : src[from];
+                    }
+                }
             }
             if (L.b_off >= 0 && dw && pg) {             // a depthwise layer's channels moved with its input's: so does its bias
                 std::vector<E> t((size_t)L.c);
@@ -1454,11 +1474,23 @@ static hipError_t launch_gapfc_pair(eclip_model *m, uint32_t i, int batch, hipSt
 
 // First layer straight from the caller's NCHW tensor (stem_direct), when a plan of that form is within the cost of the
 // re-layout kernel it saves; *done tells whether it was launched.
-static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, const CuShare &cu, const void *d_in, uint32_t *n_launched, bool *done)
+static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, const CuShare &cu, const void *d_in, uint32_t *n_launched,
+                                     uint32_t *consumed, bool *done)
 {
     *done = false;
     const LayerPlan &P = m->layers[0];
     const GemmShape g = gemm_shape(P, batch);
+    // A launch, a re-layout or the gather of the NCHW form, and (stem_pool) a pool less.  First launches of requests, us, before and with it: ResNet at
+    // batch 1 on 128 CUs 16.6, 5.8; at batch 8 on 112 45.9, 15.8; VGG-16 at batch 8 on 256 32.4, 17.3; MobileNetV2 at batch 3 on 192 12.4, 5.0.
+    if (m->stem_w != NONE && !getenv("ECLIP_GEMM_FORCE") && !getenv("ECLIP_NO_PAIRS")) {
+        StemArgs a{d_in, wptr(m, m->stem_w), wptr(m, P.b_dev), nullptr, batch, m->in_c, g.H, g.W, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad,
+                   P.L.act, m->dtype, m->stem_pool};
+        a.y = out_ptr(m, m->layers[a.pool ? 1 : 0]);
+        *done = true;
+        *consumed = a.pool ? 2 : 1;
+        *n_launched += 1;
+        return launch_stem(a, cu.n_cu, s);
+    }
     if (m->dtype == ECLIP_F32) {
         if (getenv("ECLIP_NO_PAIRS")) return hipSuccess;
         ConvF32Args a{(const float *)d_in, (const float *)wptr(m, P.w_dev), (const float *)wptr(m, P.b_dev), nullptr, (float *)out_ptr(m, P),
@@ -1497,7 +1529,7 @@ static hipError_t launch_unit(eclip_model *m, uint32_t i, int batch, hipStream_t
     if (i == 0) {
         bool stem_done = false;
         if (m->stem_direct) {
-            if ((e = launch_stem_direct(m, batch, s, cu, d_in, n_launched, &stem_done)) != hipSuccess) return e;
+            if ((e = launch_stem_direct(m, batch, s, cu, d_in, n_launched, consumed, &stem_done)) != hipSuccess) return e;
             if (stem_done) return hipSuccess;
         }
         if ((e = launch_input_stage(m, batch, d_in, s, n_launched)) != hipSuccess) return e;

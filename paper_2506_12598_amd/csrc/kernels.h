@@ -84,6 +84,21 @@ bool conv_gemm_plan_pair(const GemmPlan &s0, long M0, long N0, long K0, int form
 hipError_t launch_conv_gemm_pair(const ConvGemmArgs &a0, const GemmPlan &p0, const ConvGemmArgs &a1, const GemmPlan &p1, hipStream_t s,
                                  uint32_t *n_launched);
 
+// ---- first layer of an image model, from the caller's planes (k_stem.hip) -----------------------
+struct StemArgs {
+    const void *x;       // [B][C][H][W], 16-bit
+    const void *w;       // stem_weight_elems in the kernel's order: element `at` is logical weight stem_weight_source(at), -1: zero
+    const void *bias;    // [N] or null
+    void *y;             // [B][Ho][Wo][N], or with `pool` [B][(Ho + 1) / 2][(Wo + 1) / 2][N]
+    int B, C, H, W, Ho, Wo, N, KH, KW, stride, pad, act, dtype;
+    bool pool;           // followed by a 3 x 3 max-pool of stride 2 and padding 1
+};
+int stem_window(int KH, int KW);             // window columns with their padding: 4 or 8; 0: too large
+bool stem_supported(int C, int KH, int KW, int stride, int N);
+size_t stem_weight_elems(int KH, int KW, int N);
+long stem_weight_source(int KH, int KW, int N, int C, size_t at);       // index into [N][C][KH][KW]
+hipError_t launch_stem(const StemArgs &a, int n_cu, hipStream_t s);
+
 // ---- float32 direct convolution / linear (plain FMA) -------------------------------------------
 struct ConvF32Args {
     const float *x;      // [B][H][W][Cin]
