@@ -459,6 +459,7 @@ struct LayerPlan {
     bool shuffle_noop = false;
     int perm_groups = 0;       // > 0: this layer's input arrives NOT shuffled; its weights are laid out for that order
     bool pair_next = false;    // this layer and the next are independent GEMM layers of one group: one launch may carry both
+    bool dwpw_next = false;    // depthwise 3 x 3 whose only reader is the pointwise layer that follows: one launch may do both
     bool gapfc_next = false;   // global average pool whose only reader is the linear layer that follows: one launch may do both
 };
 
@@ -880,6 +881,19 @@ static eclip_status plan_model(const eclip_model_desc *d, size_t weight_elems, e
             D.perm_groups = S.L.groups;
             Gc.perm_groups = S.L.groups;
         }
+    }
+    // Depthwise + pointwise candidates.  A grouped pointwise layer whose groups form one super-group is a dense one.  Whether the common
+    // kernel pays depends on batch and compute units (decided per request).
+    for (uint32_t i = 0; m->dtype != ECLIP_F32 && i + 2 < d->n_layers; ++i) {
+        LayerPlan &D = m->layers[i];
+        const LayerPlan &Q = m->layers[i + 1];
+        if (D.L.op != ECLIP_OP_CONV || D.L.groups < 2 || D.L.groups != D.in.c || D.L.c != D.L.groups || D.L.kh != 3 || D.L.kw != 3) continue;
+        if (D.L.c % 8 || D.L.in0 < 0 || D.L.in1 != -2 || D.L.stride > 255 || D.L.pad > 255 || m->layers[D.L.in0].ld) continue;
+        if (Q.L.op != ECLIP_OP_CONV || Q.L.in0 != (int)i || Q.L.in1 == (int)i || Q.L.in1 == -1 || Q.ld || Q.L.c % 4) continue;
+        if (Q.L.kh != 1 || Q.L.kw != 1 || Q.L.stride != 1 || Q.L.pad != 0 || !(Q.gemm || (Q.gc_super && Q.gc_super == Q.L.groups))) continue;
+        bool other_reader = d->group_of_layer[i] != d->group_of_layer[i + 1];
+        for (uint32_t j = i + 2; j < d->n_layers; ++j) other_reader |= m->layers[j].L.in0 == (int)i || m->layers[j].L.in1 == (int)i;
+        D.dwpw_next = !other_reader;
     }
     return ECLIP_OK;
 }
@@ -1472,6 +1486,21 @@ static hipError_t launch_gapfc_pair(eclip_model *m, uint32_t i, int batch, hipSt
                         m->dtype, n_cu, s);
 }
 
+// Launches the depthwise layer i and the pointwise layer i + 1 (dwpw_next) as one kernel when that pays.
+static hipError_t launch_dwpw_pair(eclip_model *m, uint32_t i, int batch, hipStream_t s, const CuShare &cu, uint32_t *n_launched, bool *done)
+{
+    *done = false;
+    const LayerPlan &D = m->layers[i], &Q = m->layers[i + 1];
+    DwPwPlan pl;
+    if (getenv("ECLIP_GEMM_FORCE") || getenv("ECLIP_NO_PAIRS") || !dwpw_plan((long)batch * Q.out.h * Q.out.w, D.L.c, Q.L.c, m->dtype, cu.even_cu(), &pl)) return hipSuccess;
+    *done = true;
+    *n_launched += 1;
+    const DwPwArgs a{out_ptr(m, m->layers[D.L.in0]), wptr(m, D.w_dev), wptr(m, D.b_dev), wptr(m, Q.w_dev), wptr(m, Q.b_dev),
+                     Q.L.in1 >= 0 ? (const void *)out_ptr(m, m->layers[Q.L.in1]) : nullptr, out_ptr(m, Q), batch, D.in.h, D.in.w, D.L.c, Q.out.h, Q.out.w,
+                     Q.L.c, D.L.stride, D.L.pad, D.L.act, Q.L.act, m->dtype};
+    return launch_dwpw(a, pl, s);
+}
+
 // First layer straight from the caller's NCHW tensor (stem_direct), when a plan of that form is within the cost of the
 // re-layout kernel it saves; *done tells whether it was launched.
 static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, const CuShare &cu, const void *d_in, uint32_t *n_launched,
@@ -1538,6 +1567,11 @@ static hipError_t launch_unit(eclip_model *m, uint32_t i, int batch, hipStream_t
         bool paired = false;
         if ((e = launch_pair(m, i, batch, s, cu, d_in, n_launched, &paired)) != hipSuccess) return e;
         if (paired) { *consumed = 2; return hipSuccess; }
+    }
+    if (m->layers[i].dwpw_next) {
+        bool fused = false;
+        if ((e = launch_dwpw_pair(m, i, batch, s, cu, n_launched, &fused)) != hipSuccess) return e;
+        if (fused) { *consumed = 2; return hipSuccess; }
     }
     if (m->layers[i].gapfc_next) {
         bool fused = false;

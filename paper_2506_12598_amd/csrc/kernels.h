@@ -126,6 +126,17 @@ int dwconv_strip_rows(const DwConvArgs &a, int n_cu);          // rows per threa
 unsigned dwconv_workgroups(const DwConvArgs &a, int n_cu);     // of 256 threads
 hipError_t launch_dwconv(const DwConvArgs &a, int n_cu, hipStream_t s);
 
+// depthwise 3x3 and the pointwise layer behind it in one launch (k_dwpw.hip): 16-bit types, C % 8 == 0, N % 4 == 0, stride and pad < 256
+struct DwPwArgs {
+    const void *x, *wd, *bias_d;             // [B][H][W][C]; [3][3][C]; [C] or null
+    const void *wp, *bias_p, *res;           // blocked GEMM layout of an N x C matrix; [N] or null; [B][Ho][Wo][N] or null
+    void *y;
+    int B, H, W, C, Ho, Wo, N, stride, pad, act_d, act_p, dtype;
+};
+struct DwPwPlan { int tn, wk, wm; };         // 16 tn output channels; wk wavefronts share K, wm the pixels
+bool dwpw_plan(long M, int C, int N, int dtype, int n_cu, DwPwPlan *out);      // false: better apart
+hipError_t launch_dwpw(const DwPwArgs &a, const DwPwPlan &p, hipStream_t s);
+
 // grouped convolution, 1 < groups < C: one thread per output element, weights [Cout][KH][KW][Cin/groups]
 struct GConvArgs {
     const void *x, *w, *bias, *res;
