@@ -55,7 +55,7 @@ struct AttnDev {
 
 // KB = number of 16-key blocks held in registers (Sp / 16 <= KB <= 16)
 template <typename T, int D, int KB, int NW>
-__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attention_kernel(AttnDev p)
+__global__ __launch_bounds__(NW * 64, 2) void attention_kernel(AttnDev p)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t vt[];    // [D][ldv]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -68,8 +68,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attention_kernel(Att
     const int qb = (int)(item - bh * p.qb.d), h = (int)(bh - b * p.hd.d);
     const long row0 = (long)b * p.S;
     // All operands come through one descriptor at 32-bit offsets: rows beyond S use one past its end and read as zeros, without
-    // a branch and without 64-bit arithmetic per load.  (With that, all loads before the first wait and the row reductions inside the
-    // vector unit, 12 heads x 128 keys at batch 1 take 6.1 us instead of 6.9.)
+    // a branch and without 64-bit arithmetic per load.
     const unsigned ld2 = 6u * (unsigned)p.Hd, hd2 = 2u * (unsigned)p.Hd;           // bytes
     const unsigned q0 = (unsigned)row0 * ld2 + (unsigned)(h * D) * 2u, k0_off = q0 + hd2, v0_off = k0_off + hd2;
     const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void *)p.qkv, 0, (int)p.qkv_bytes, 0x00020000);
@@ -410,6 +409,160 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 && KBC <= 12) ? 4 : 2) void atten
     }
 }
 
+namespace split {
+// Few queries: a workgroup handles 16 of them and its wavefronts share the keys, 16 KBW each.  What bounds such a launch is one wavefront's chain of
+// instructions, some 900 for 16 queries and 128 keys; here the chain is that of its share of the keys (5.5 -> 4.0 us, see attention_splits_keys).  Every wavefront
+// turns its own values in its own part of LDS and keeps a maximum, a sum and unnormalised outputs of its own; they are put together
+// as between the chunks of attention_chunk_kernel, one block of 16 head dims per wavefront.
+template <typename T, int D, int KBW, int NW>
+__global__ __launch_bounds__(NW * 64) void attention_kernel(AttnDev p)
+{
+    constexpr int LDV = KBW * 16 + 4, PART = D * LDV;                 // elements of a wavefront's part: V^T, later its outputs
+    static_assert(PART * 2 >= D / 16 * 1024 && PART % 8 == 0, "the outputs fit where the values were");
+    __shared__ __attribute__((aligned(16))) uint16_t vt_all[NW * PART];
+    __shared__ __attribute__((aligned(16))) float2 ms[NW][16];        // maximum and sum per query
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t vb = se_dealt_block(p.deal, blockIdx.x);
+    if (vb == 0xffffffffu) return;
+    const uint32_t item = xcd_range_item(vb, (uint32_t)(p.B * p.heads) * p.qb.d);
+    if (item == 0xffffffffu) return;
+    const unsigned bh = div_by(item, p.qb), b = div_by(bh, p.hd);
+    const int qb = (int)(item - bh * p.qb.d), h = (int)(bh - b * p.hd.d);
+    const long row0 = (long)b * p.S;
+    const unsigned ld2 = 6u * (unsigned)p.Hd, hd2 = 2u * (unsigned)p.Hd;           // bytes
+    const unsigned q0 = (unsigned)row0 * ld2 + (unsigned)(h * D) * 2u, k0_off = q0 + hd2, v0_off = k0_off + hd2;
+    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void *)p.qkv, 0, (int)p.qkv_bytes, 0x00020000);
+    constexpr unsigned OOB = 0xffffffffu;
+    auto fetch16 = [&](bool ok, unsigned off) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rq, ok ? off : OOB, 0, 0);
+        return make_uint4(v.x, v.y, v.z, v.w);
+    };
+    const int q_row = qb * 16 + (lane & 15), g = lane >> 4, key_base = wave * KBW * 16;
+    const bool q_ok = q_row < p.S;
+
+    uint4 qf[D / 32], kfr[KBW][D / 32];
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) qf[ks] = fetch16(q_ok, q0 + (unsigned)q_row * ld2 + (unsigned)(ks * 64 + g * 16));
+#pragma unroll
+    for (int kb = 0; kb < KBW; ++kb) {
+        const int key = key_base + kb * 16 + (lane & 15);
+        const unsigned off = k0_off + (unsigned)key * ld2 + (unsigned)(g * 16);
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ++ks) kfr[kb][ks] = fetch16(key < p.S, off + ks * 64);
+    }
+    constexpr int QUADS = KBW * 4, V_IT = (QUADS * (D / 8) + 63) / 64;              // 4-key x 8-dim blocks per lane
+    uint32_t vw[V_IT][4][4];
+#pragma unroll
+    for (int it = 0; it < V_IT; ++it) {
+        const int c = lane + it * 64, j8 = c / QUADS, key0 = key_base + c % QUADS * 4;
+        const unsigned off = v0_off + (unsigned)key0 * ld2 + (unsigned)(j8 * 16);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint4 q = fetch16(j8 < D / 8 && key0 + t < p.S, off + (unsigned)t * ld2);
+            vw[it][t][0] = q.x; vw[it][t][1] = q.y; vw[it][t][2] = q.z; vw[it][t][3] = q.w;
+        }
+    }
+    uint16_t *const vt = vt_all + wave * PART;
+
+    // ---- scores of this wavefront's keys and their maximum
+    f32x4 sc[KBW];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < KBW; ++kb) {
+        sc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ++ks) sc[kb] = MmaA<T>::run(kfr[kb][ks], qf[ks], sc[kb]);
+    }
+#pragma unroll
+    for (int it = 0; it < V_IT; ++it) {
+        const int c = lane + it * 64, j8 = c / QUADS, k0 = c % QUADS * 4;
+        if (j8 < D / 8) {
+            const uint32_t(&w)[4][4] = vw[it];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint2 lo = make_uint2((w[0][i] & 0xffffu) | (w[1][i] << 16), (w[2][i] & 0xffffu) | (w[3][i] << 16));
+                const uint2 hi = make_uint2((w[0][i] >> 16) | (w[1][i] & 0xffff0000u), (w[2][i] >> 16) | (w[3][i] & 0xffff0000u));
+                *reinterpret_cast<uint2 *>(&vt[(j8 * 8 + 2 * i) * LDV + k0]) = lo;
+                *reinterpret_cast<uint2 *>(&vt[(j8 * 8 + 2 * i + 1) * LDV + k0]) = hi;
+            }
+        }
+    }
+#pragma unroll
+    for (int kb = 0; kb < KBW; ++kb) {
+        if (key_base + (kb + 1) * 16 > p.S) {        // wavefront-uniform: only the last blocks hold padded keys
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (key_base + kb * 16 + 4 * g + r >= p.S) sc[kb][r] = -INFINITY;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sc[kb][r]);
+    }
+    mx = rows_max(mx);
+    // a wavefront whose keys are all padded adds nothing: exp2(-inf + 0), not exp2(-inf + inf)
+    const float c2 = p.scale * 1.4426950408889634f, off2 = key_base < p.S ? -mx * c2 : 0.0f;
+    float sum = 0.0f;
+    f32x4 o[D / 16];
+#pragma unroll
+    for (int jb = 0; jb < D / 16; ++jb) o[jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int kp = 0; kp < KBW / 2; ++kp) {
+#pragma unroll
+        for (int kb = 2 * kp; kb < 2 * kp + 2; ++kb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float e = __builtin_amdgcn_exp2f(fmaf(sc[kb][r], c2, off2));
+                sc[kb][r] = e;
+                sum += e;
+            }
+        uint4 pf;
+        pf.x = Cvt<T>::pack2(sc[2 * kp][0], sc[2 * kp][1]);
+        pf.y = Cvt<T>::pack2(sc[2 * kp][2], sc[2 * kp][3]);
+        pf.z = Cvt<T>::pack2(sc[2 * kp + 1][0], sc[2 * kp + 1][1]);
+        pf.w = Cvt<T>::pack2(sc[2 * kp + 1][2], sc[2 * kp + 1][3]);
+#pragma unroll
+        for (int jb = 0; jb < D / 16; ++jb) {
+            const uint16_t *vr = vt + (jb * 16 + (lane & 15)) * LDV + 4 * g;
+            const uint2 lo = *reinterpret_cast<const uint2 *>(vr + (2 * kp) * 16);
+            const uint2 hi = *reinterpret_cast<const uint2 *>(vr + (2 * kp + 1) * 16);
+            o[jb] = MmaA<T>::run(make_uint4(lo.x, lo.y, hi.x, hi.y), pf, o[jb]);
+        }
+    }
+    sum = rows_sum(sum);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();                 // the values have been read: their place takes the outputs
+    float4 *part = reinterpret_cast<float4 *>(vt);
+#pragma unroll
+    for (int jb = 0; jb < D / 16; ++jb) part[jb * 64 + lane] = make_float4(o[jb][0], o[jb][1], o[jb][2], o[jb][3]);
+    if (g == 0) ms[wave][lane] = make_float2(mx, sum);
+    __syncthreads();
+
+    // ---- head dims jb*16 + 4*g .. +3 of a query, over the wavefronts
+    if (wave >= D / 16) return;
+    float m = -INFINITY;
+    float2 s[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        s[w] = ms[w][lane & 15];
+        m = fmaxf(m, s[w].x);
+    }
+    float total = 0.0f, v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float f = __builtin_amdgcn_exp2f((s[w].x - m) * c2);
+        const float4 q = reinterpret_cast<const float4 *>(vt_all + w * PART)[wave * 64 + lane];
+        total = fmaf(s[w].y, f, total);
+        v[0] = fmaf(q.x, f, v[0]); v[1] = fmaf(q.y, f, v[1]); v[2] = fmaf(q.z, f, v[2]); v[3] = fmaf(q.w, f, v[3]);
+    }
+    const float inv = 1.0f / total;
+    if (!q_ok) return;
+    const long off = (row0 + q_row) * p.Hd + h * D + wave * 16 + 4 * g;
+    if (p.y32) *reinterpret_cast<float4 *>(p.y32 + off) = make_float4(v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
+    else *reinterpret_cast<uint2 *>(p.y + off) = make_uint2(Cvt<T>::pack2(v[0] * inv, v[1] * inv), Cvt<T>::pack2(v[2] * inv, v[3] * inv));
+}
+}  // namespace split
+
 inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 // LDS row pitch of V^T in elements, keys + 4: a lane reads 8 bytes of row (lane & 15), and with the pitch an odd
 // multiple of 8 bytes the 16 rows fall on 16 different pairs of banks (with keys + 8, the pitch a multiple of 16
@@ -446,6 +599,18 @@ hipError_t launch_chunked(AttnDev d, size_t lds, hipStream_t s)
     return hipGetLastError();
 }
 
+template <typename T, int D>
+hipError_t launch_split(AttnDev d, hipStream_t s)
+{
+    d.qb = magic_of((unsigned)(d.S + 15) / 16);
+    d.hd = magic_of((unsigned)d.heads);
+    const dim3 grid(se_deal_grid(d.deal, xcd_range_blocks((uint32_t)(d.B * d.heads) * d.qb.d)));
+    if (d.Sp <= 128) hipLaunchKernelGGL((split::attention_kernel<T, D, 2, 4>), grid, dim3(256), 0, s, d);
+    else if (d.Sp <= 256) hipLaunchKernelGGL((split::attention_kernel<T, D, 2, 8>), grid, dim3(512), 0, s, d);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 template <typename T, int D, int NW>
 hipError_t set_attr()
 {
@@ -455,7 +620,7 @@ hipError_t set_attr()
         if ((e = hipFuncSetAttribute((const void *)attention_chunk_kernel<T, D, 12, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)attention_chunk_kernel<T, D, 16, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)) != hipSuccess) return e;
     }
-    if constexpr (NW == 1 || NW == 4) {
+    if constexpr (NW == 4) {
         hipError_t e;
         if ((e = hipFuncSetAttribute((const void *)attention_kernel<T, D, 8, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)attention_kernel<T, D, 16, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)) != hipSuccess) return e;
@@ -479,9 +644,7 @@ hipError_t attention_init()
 {
     hipError_t e;
 #define SET(T)                                                         \
-    if ((e = set_attr<T, 32, 1>()) != hipSuccess) return e;            \
     if ((e = set_attr<T, 32, 4>()) != hipSuccess) return e;            \
-    if ((e = set_attr<T, 64, 1>()) != hipSuccess) return e;            \
     if ((e = set_attr<T, 64, 4>()) != hipSuccess) return e;            \
     if ((e = set_attr<T, 32, 8>()) != hipSuccess) return e;            \
     if ((e = set_attr<T, 64, 8>()) != hipSuccess) return e;
@@ -489,6 +652,16 @@ hipError_t attention_init()
     SET(f16_t)
 #undef SET
     return hipSuccess;
+}
+
+// Sharing the keys of 16 queries pays while workgroups of 16 queries are few: up to 3 per compute unit with 4 wavefronts (128 keys), up to 2 with
+// 8.  Beyond, a workgroup of 64 queries that stages the values once does the same work in fewer instructions.  us, 12 heads, shared keys against 64
+// queries: 128 keys, batch 1 on 256 CUs (0.4 workgroups per CU) 4.0, 5.5 (one wavefront for 16 queries: 5.5); batch 4 on 128 CUs (3.0) 6.0, 6.7; on
+// 112 (3.4) 7.0, 6.7; 256 keys, batch 2 on 256 (1.5) 7.1, 9.0; batch 4 on 256 (3.0) 9.4, 9.1; 201 keys, batch 4 on 256 (2.4) 8.6, 8.3.
+bool attention_splits_keys(int B, int S, int heads, int n_cu)
+{
+    const int Sp = round_up(S, 32);
+    return Sp <= 256 && (long)B * heads * ((S + 15) / 16) <= (long)n_cu * (Sp <= 128 ? 3 : 2);
 }
 
 hipError_t launch_attention(const AttnArgs &a, const CuShare &cu, hipStream_t s)
@@ -504,9 +677,6 @@ hipError_t launch_attention(const AttnArgs &a, const CuShare &cu, hipStream_t s)
     const int D = a.Hd / a.heads;
     d.scale = 1.0f / sqrtf((float)D);
     const size_t lds = attention_lds_bytes(a.S, D);
-    // few (batch, head) pairs: one wavefront per workgroup spreads the query blocks over more CUs
-    const long wg4 = (long)a.B * a.heads * ((a.S + 63) / 64);
-    const bool small = wg4 < n_cu;
     // more than 256 keys (keys staged in LDS chunk by chunk): 128 queries per workgroup when that still gives every
     // other CU a workgroup, else 64
     const bool longseq = d.Sp > 256;
@@ -523,9 +693,10 @@ hipError_t launch_attention(const AttnArgs &a, const CuShare &cu, hipStream_t s)
 #undef GOC
         return hipErrorInvalidValue;
     }
-#define GO(T)                                                                                  \
-    if (D == 32) return small ? launch_d<T, 32, 1>(d, lds, s) : launch_d<T, 32, 4>(d, lds, s); \
-    if (D == 64) return small ? launch_d<T, 64, 1>(d, lds, s) : launch_d<T, 64, 4>(d, lds, s);
+    const bool split = attention_splits_keys(a.B, a.S, a.heads, n_cu);
+#define GO(T)                                                                               \
+    if (D == 32) return split ? launch_split<T, 32>(d, s) : launch_d<T, 32, 4>(d, lds, s); \
+    if (D == 64) return split ? launch_split<T, 64>(d, s) : launch_d<T, 64, 4>(d, lds, s);
     if (a.dtype == DT_BF16) { GO(bf16_t) }
     else { GO(f16_t) }
 #undef GO

@@ -1,0 +1,34 @@
+"""Attention whose wavefronts share the keys of 16 queries: ragged key and query blocks, wavefronts without a key, both head sizes, peaked rows."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import forward as orc
+from gpu_util import GpuModel, rel_to_range
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dt", [wl.DT_BF16, wl.DT_F16])
+@pytest.mark.parametrize("seq,hidden,heads,batch", [(1, 64, 1, 1), (15, 64, 2, 2), (33, 192, 3, 1), (65, 128, 4, 2), (97, 256, 4, 1), (128, 128, 2, 4),
+                                                    (129, 64, 1, 3), (159, 64, 2, 1), (201, 128, 2, 2), (225, 128, 4, 1), (256, 64, 1, 2)])
+@pytest.mark.parametrize("peaked", [False, True])
+def test_shared_keys(seq, hidden, heads, batch, peaked, dt):
+    m = wl.single_layer("attention", dt, seed=seq + hidden, seq=seq, hidden=hidden, heads=heads)
+    x = wl.make_input(m, batch)
+    if peaked:                                   # most of a row's weight on keys of one wavefront, another one's for every other query
+        x[:, :, :2 * hidden] *= 4.0
+        x[:, ::2, :hidden] += 1.5
+        x[:, seq // 2:, hidden:2 * hidden] += 1.5
+        x = wl.round_to_dtype(x.astype(np.float32), dt)
+    exp = orc.run_model(m, x)
+    g = GpuModel(m, max_batch=batch)
+    try:
+        few, many = g.run(x, table=[5]), g.run(x, table=[1])       # 256 CUs, 32 CUs: for the larger cases two kernels
+    finally:
+        g.free()
+    # probabilities and values are rounded to 16 bits, float32 throughout otherwise: the bound of the other attention tests
+    for got in (few, many):
+        assert np.isfinite(got).all() and rel_to_range(got, exp) <= 6e-3
