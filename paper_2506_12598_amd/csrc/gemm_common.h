@@ -135,6 +135,6 @@ hipError_t launch_conv_wsk_pair(const GemmDev &d0, int tiles0, const GemmDev &d1
 int wsk_lean_form(const GemmDev &d);
 int wsk_lean_pair_form(const GemmDev &d0, const GemmDev &d1);
 hipError_t wsk_lean_init();
-hipError_t launch_wsk_lean(const GemmDev &d0, const GemmDev &d1, int n0, int dtype, int form, int variant, int nw, int tiles, hipStream_t s);
+hipError_t launch_wsk_lean(GemmDev d0, GemmDev d1, int n0, int dtype, int form, int variant, int nw, int tiles, hipStream_t s);
 
 }  // namespace eclip

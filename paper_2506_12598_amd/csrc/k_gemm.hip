@@ -153,7 +153,7 @@ static void set_raster(GemmPlan &pl, long M, long N)
 // Wave-split-K tiles are dealt to the 8 XCDs along one dimension when that dimension has enough tiles to keep the
 // XCDs evenly loaded (a multiple of 8 tiles): along N when N >= M (the weights,
 // N x K, are then the larger operand; the im2col operand is at most M x K), else along M; the other dimension is the
-// second choice.
+// second choice.  (The lean form deals its tiles itself where this leaves them in plain order, see launch_wsk_lean.)
 static void set_xcd_split(GemmPlan &pl, long M, long N)
 {
     int bm, bn;

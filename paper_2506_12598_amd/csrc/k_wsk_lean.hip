@@ -43,7 +43,7 @@ struct WskHead {
     int px;                                  // bytes between pixels of x
     unsigned walk;                           // bits 0-1: GemmPlan::raster 2 or 3 (0: plain); bits 8-15: shift of the division by inner_d;
                                              // bits 16-23: log2 of the tile columns of a group of channels, 255: not a power of two (group)
-    int per;                                 // tile columns (rows) per XCD
+    int per;                                 // tiles, of which an XCD owns an eighth in a row
     unsigned inner_d, inner_mul;             // tiles along the other dimension, and the multiplier of the division by them
 };
 struct WskRest {
@@ -82,11 +82,12 @@ __device__ __forceinline__ void wsk_body(float *red, const uint16_t *x, const ui
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tile_m, tile_n;
     {
-        const unsigned dealt = walk & 3u, xcd = dealt ? bid & 7 : 0, q = dealt ? bid >> 3 : bid;
-        const unsigned r = div_by(q, Magic{inner_d, inner_mul, walk >> 8 & 255u}), rem = q - r * inner_d;
-        const unsigned a = xcd * (unsigned)per + r;
-        tile_m = dealt == 3 ? a : rem;
-        tile_n = dealt == 3 ? rem : a;
+        const unsigned dealt = walk & 3u, xcd = dealt ? bid & 7 : 0;
+        const unsigned t = dealt ? ((unsigned)per * xcd >> 3) + ((unsigned)bid >> 3) : (unsigned)bid;
+        if (dealt && t >= ((unsigned)per * (xcd + 1u) >> 3)) return;
+        const unsigned r = div_by(t, Magic{inner_d, inner_mul, walk >> 8 & 255u}), rem = t - r * inner_d;
+        tile_m = dealt == 3 ? r : rem;
+        tile_n = dealt == 3 ? rem : r;
     }
     const int m_base = tile_m * BM, n_base = tile_n * BN;
 
@@ -330,7 +331,7 @@ WskHead wsk_head(const GemmDev &d, int bm, int bn)
     v.x = d.x; v.w = d.w; v.x_bytes = d.x_bytes;
     v.M = d.M; v.last_nb = (d.N + 15) / 16 - 1; v.steps = (d.K + 31) / 32; v.px = d.ldx * 2;
     const int tm = (d.M + bm - 1) / bm, tn = (d.N + bn - 1) / bn;
-    v.per = d.raster ? (d.raster == 3 ? tm : tn) / 8 : 0;
+    v.per = tm * tn;
     const Magic inner = magic_of((unsigned)(d.raster == 3 ? tn : tm));
     v.inner_d = inner.d; v.inner_mul = inner.mul;
     v.walk = (unsigned)d.raster | inner.shift << 8;
@@ -451,16 +452,27 @@ hipError_t wsk_lean_init()
     return hipSuccess;
 }
 
-hipError_t launch_wsk_lean(const GemmDev &d0, const GemmDev &d1, int n0, int dtype, int form, int variant, int nw, int tiles, hipStream_t s)
+hipError_t launch_wsk_lean(GemmDev d0, GemmDev d1, int n0, int dtype, int form, int variant, int nw, int tiles, hipStream_t s)
 {
     const void *k = dtype == DT_BF16 ? kernel_of<bf16_t>(variant, nw, form, d0.n_groups > 0) : kernel_of<f16_t>(variant, nw, form, d0.n_groups > 0);
     if (!k) return hipErrorInvalidValue;
     int bm, bn;
     conv_wsk_tile(variant, &bm, &bn);
+    // Each XCD takes an eighth of the tiles in a row, counted down the tile columns where the weights are the larger operand and along the tile
+    // rows where the activations are: its L2 then fetches an eighth of that operand from the last-level cache, not all of it (a load that hits the
+    // XCD's own L2 takes 234 cycles, one that another XCD's fetched 550).  With whole columns (rows) per XCD only where their number divides
+    // by 8, 22 kinds of request replayed as graphs took 1.4 % longer on the geometric mean, BERT-base 2 x 100 on 224 CUs 424 us instead of 398, ALBERT
+    // 200 on 256 427 instead of 402; always along the rows 2.7 %.  The second layer of a launch starts on XCD 0 too, or keeps the plain order.
+    const bool single = n0 == tiles;
+    auto deal = [&](GemmDev &d, int first) {
+        const int t = d.tiles_m * d.tiles_n;
+        if (first % 8) d.raster = 0;
+        else if (!d.raster && t >= 16) d.raster = d.N >= d.M ? 2 : 3;
+        return d.raster ? (t + 7) & ~7 : t;
+    };
+    n0 = deal(d0, 0);
+    tiles = n0 + (single ? 0 : deal(d1, n0));
     WskHead h0 = wsk_head(d0, bm, bn), h1 = wsk_head(d1, bm, bn);
-    // a walk by XCD covers whole eighths of the tiles
-    for (const GemmDev *d : {&d0, &d1})
-        if (d->raster && (d->raster == 3 ? d->tiles_m : d->tiles_n) % 8) return hipErrorInvalidValue;
     WskRest r0 = wsk_rest(d0, bn), r1 = wsk_rest(d1, bn);
     if (d0.n_groups > 1 && d0.N / d0.n_groups % bn) return hipErrorInvalidValue;
     void *args[] = {&h0.x, &h0.w, &h0.x_bytes, &h0.M, &h0.last_nb, &h0.steps, &h0.px, &h0.walk, &h0.per, &h0.inner_d, &h0.inner_mul, &n0, &r0, &h1, &r1};
