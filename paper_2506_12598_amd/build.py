@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libeclip.so")
-SOURCES = ["eclip.cpp", "alloc_solver.cpp", "k_gemm.hip", "k_wsk.hip", "k_wsk_lean.hip", "k_mem.hip", "k_attn.hip", "k_gconv.hip", "k_stem.hip", "k_dwpw.hip"]
+SOURCES = ["eclip.cpp", "alloc_solver.cpp", "k_gemm.hip", "k_wsk.hip", "k_wsk_lean.hip", "k_mem.hip", "k_attn.hip", "k_gconv.hip", "k_stem.hip", "k_dwpw.hip", "k_conv3.hip"]
 
 
 def pp_tile_ids():
@@ -25,7 +25,7 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Xclang", "-tar
 
 # kernels whose first arguments are to arrive in scalar registers with the wavefront
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
-MORE_FLAGS = {"k_wsk_lean.hip": PRELOAD, "k_mem.hip": PRELOAD, "k_dwpw.hip": PRELOAD,
+MORE_FLAGS = {"k_wsk_lean.hip": PRELOAD, "k_mem.hip": PRELOAD, "k_dwpw.hip": PRELOAD, "k_conv3.hip": PRELOAD,
               # where the linker puts the allocator's loops depends on what stands before them: 485 us for four workers' solve, up to 515 without
               "alloc_solver.cpp": ["-falign-functions=64", "-falign-loops=64"]}
 

@@ -199,6 +199,7 @@ extern "C" eclip_status eclip_pool_create(int device, const eclip_mask *masks, u
     HIP_TRY(attention_init());
     HIP_TRY(conv_gemm_init());
     HIP_TRY(conv_wsk_init());
+    HIP_TRY(conv3_init());
     TRACE("kernel attributes set");
     eclip_pool *p = new (std::nothrow) eclip_pool;
     if (!p) return fail(ECLIP_ENOMEM, "out of host memory");
@@ -1038,11 +1039,15 @@ static void relayout_weights(eclip_model *m, const E *w, std::vector<char> &aren
 }
 
 // GEMM view of a CONV / LINEAR layer
-struct GemmShape { int B, H, W, Cin, Ho, Wo, Cout, KH, KW, stride, pad; };
-static GemmShape gemm_shape(const LayerPlan &P, int batch)
+// pixel pitch (in channels) a reader of layer idx must use, 0 when the tensor is contiguous
+static int pitch_of(const eclip_model *m, int idx) { return idx >= 0 ? m->layers[idx].ld : 0; }
+
+struct GemmShape { int B, H, W, Cin, Ho, Wo, Cout, KH, KW, stride, pad, ldx; };
+static GemmShape gemm_shape(const eclip_model *m, const LayerPlan &P, int batch)
 {
     const eclip_layer &L = P.L;
     GemmShape g;
+    g.ldx = pitch_of(m, L.in0);
     g.B = batch; g.Cin = P.in.c; g.Cout = L.c;
     if (P.flat) {
         g.Cin = P.in.c * P.in.h * P.in.w;
@@ -1060,12 +1065,17 @@ static GemmShape gemm_shape(const LayerPlan &P, int batch)
 // The launch plan of a matrix-core layer: the measured choice when eclip_model_tune has seen this problem on a stream of
 // this CU count, else the planner's cost model.
 static int lean_form_of(const GemmShape &g) { return conv_wsk_lean_form(g.KH, g.KW, g.stride, g.pad, g.Cin, g.Cout); }
+static bool conv3_of(const GemmShape &g) { return conv3_takes(g.KH, g.KW, g.stride, g.pad, g.H, g.W, g.Cin, g.Cout, g.ldx ? g.ldx : g.Cin); }
 static GemmTraits traits_of(const GemmShape &g, const CuShare &cu)
 {
-    return GemmTraits{lean_form_of(g) >= 0, cu.even_cu(), conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout)};
+    return GemmTraits{lean_form_of(g) >= 0, cu.even_cu(), conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout), conv3_of(g), g.B, g.Ho, g.Wo, g.Cin, g.stride};
 }
 // Layers of one (M, N, K) can still be different work: which kernels take them in a fast form is part of what a measurement holds for.
-static long form_key(const GemmShape &g) { return 2 * lean_form_of(g) + (conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout) ? 1 : 0); }
+static long form_key(const GemmShape &g)
+{
+    const long image = conv3_of(g) ? 16 * (((long)g.H << 12 | g.W) * 2 + g.stride) : 0;       // the patch kernel's tiles follow the image
+    return image + 2 * lean_form_of(g) + (conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout) ? 1 : 0);
+}
 static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, const CuShare &cu)
 {
     const int n_cu = cu.n_cu;
@@ -1134,7 +1144,7 @@ extern "C" eclip_status eclip_model_load(eclip_pool *pool, const eclip_model_des
     for (const LayerPlan &P : m->layers) {
         if (P.L.op == ECLIP_OP_GAP) ws = std::max(ws, (size_t)m->max_batch * 64 * (size_t)P.L.c);
         if (!P.gemm) continue;
-        const GemmShape g = gemm_shape(P, (int)m->max_batch);
+        const GemmShape g = gemm_shape(m, P, (int)m->max_batch);
         const size_t MN = (size_t)g.B * g.Ho * g.Wo * g.Cout;
         const size_t KT = ((size_t)g.KH * g.KW * g.Cin + 63) / 64;
         if (MN <= (size_t)256 * 64 * 64) ws = std::max(ws, MN * std::min<size_t>(32, std::max<size_t>(1, KT / 3)));
@@ -1257,12 +1267,18 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
     switch (P.L.op) {
     case ECLIP_OP_CONV:
     case ECLIP_OP_LINEAR: {
-        const GemmShape g = gemm_shape(P, (int)batch);
+        const GemmShape g = gemm_shape(model, P, (int)batch);
         out->m = (uint64_t)g.B * g.Ho * g.Wo; out->n = (uint64_t)g.Cout; out->k = (uint64_t)g.KH * g.KW * g.Cin;
         if (P.gemm) {
             const GemmPlan pl = plan_of(model, g, share_of(model->pool->streams[mask_id]));
             int bm, bn, bk;
-            if (pl.kind == 1) { conv_wsk_tile(pl.variant, &bm, &bn); name = "conv_wsk_kernel"; out->threads = (uint32_t)pl.nw * 64; }
+            if (pl.kind == 2) {
+                int th, tw;
+                conv3_tile(pl.variant, &th, &tw, &bn);
+                bm = th * tw;
+                name = "conv3_kernel";
+                out->threads = (uint32_t)pl.nw * 64;
+            } else if (pl.kind == 1) { conv_wsk_tile(pl.variant, &bm, &bn); name = "conv_wsk_kernel"; out->threads = (uint32_t)pl.nw * 64; }
             else { conv_gemm_tile(pl.variant, &bm, &bn, &bk); name = conv_gemm_kernel_name(pl.variant); out->threads = (uint32_t)conv_gemm_threads(pl.variant); }
             out->tile_m = (uint32_t)bm; out->tile_n = (uint32_t)bn;
             out->k_splits = (uint32_t)pl.splits;
@@ -1336,9 +1352,6 @@ static char *out_ptr(const eclip_model *m, const LayerPlan &P)
 {
     return m->d_act + m->layers[P.buf].out_off + (size_t)P.c_off * (size_t)m->esize;
 }
-// pixel pitch (in channels) a reader of layer idx must use, 0 when the tensor is contiguous
-static int pitch_of(const eclip_model *m, int idx) { return idx >= 0 ? m->layers[idx].ld : 0; }
-
 // Launches layer i on `s`.  `d_out32` non-null: this is the last layer and its result goes to the caller.
 static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_t s, const CuShare &cu, const void *d_in, float *d_out32,
                                uint32_t *n_launched)
@@ -1362,7 +1375,7 @@ static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_
     switch (L.op) {
     case ECLIP_OP_CONV:
     case ECLIP_OP_LINEAR: {
-        const GemmShape g = gemm_shape(P, batch);
+        const GemmShape g = gemm_shape(m, P, batch);
         if (P.gemm) {
             if (d_out32 && chan_last_out) y32 = d_out32;
             ConvGemmArgs a{src(L.in0), wptr(m, P.w_dev), wptr(m, P.b_dev), src(L.in1), y32 ? nullptr : y, y32, m->ws,
@@ -1457,7 +1470,7 @@ static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t
             if (idx == -1) return m->in_kind == ECLIP_IN_IMAGE ? (const void *)m->d_in_stage : d_in;
             return (const void *)out_ptr(m, m->layers[idx]);
         };
-        const GemmShape g = gemm_shape(P, batch);
+        const GemmShape g = gemm_shape(m, P, batch);
         a[k] = ConvGemmArgs{src(L.in0), wptr(m, P.w_dev), wptr(m, P.b_dev), src(L.in1), out_ptr(m, P), nullptr, m->ws,
                             g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, L.act, m->dtype};
         a[k].ldx = pitch_of(m, L.in0);
@@ -1508,7 +1521,7 @@ static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, c
 {
     *done = false;
     const LayerPlan &P = m->layers[0];
-    const GemmShape g = gemm_shape(P, batch);
+    const GemmShape g = gemm_shape(m, P, batch);
     // A launch, a re-layout or the gather of the NCHW form, and (stem_pool) a pool less.  First launches of requests, us, before and with it: ResNet at
     // batch 1 on 128 CUs 16.6, 5.8; at batch 8 on 112 45.9, 15.8; VGG-16 at batch 8 on 256 32.4, 17.3; MobileNetV2 at batch 3 on 192 12.4, 5.0.
     if (m->stem_w != NONE && !getenv("ECLIP_GEMM_FORCE") && !getenv("ECLIP_NO_PAIRS")) {
@@ -1898,7 +1911,7 @@ extern "C" eclip_status eclip_model_tune(eclip_model *model, uint32_t mask_id, u
         const LayerPlan &P = model->layers[i];
         if (!P.gemm) continue;
         const eclip_layer &L = P.L;
-        const GemmShape g = gemm_shape(P, (int)batch);
+        const GemmShape g = gemm_shape(model, P, (int)batch);
         const long M = (long)g.B * g.Ho * g.Wo, N = g.Cout, K = (long)g.KH * g.KW * g.Cin;
         const std::array<long, 5> key{M, N, K, (long)n_cu, form_key(g)};
         if (model->tuned.count(key)) continue;
@@ -1915,7 +1928,7 @@ extern "C" eclip_status eclip_model_tune(eclip_model *model, uint32_t mask_id, u
         a.ldx = pitch_of(model, L.in0);
         a.ldy = P.ld;
         const GemmPlan own = conv_gemm_plan(M, N, K, n_cu, model->ws_floats, traits_of(g, share_of(ps)));
-        std::vector<GemmPlan> cand = conv_gemm_candidates(M, N, K, n_cu, model->ws_floats);
+        std::vector<GemmPlan> cand = conv_gemm_candidates(M, N, K, n_cu, model->ws_floats, traits_of(g, share_of(ps)));
         cand.insert(cand.begin(), own);
         float best_ms = 1e30f, own_ms = 1e30f;
         size_t best = 0;

@@ -268,9 +268,12 @@ GemmPlan conv_wsk_plan_columns(long M, long N, long K, int n_cu, int columns)
 // every 8-wavefront or copied LDS tile whole and with K cut in two or four where the workspace allows (the plain tiles were best on
 // none of 900 problems).  Tiles far larger than the problem are left out (a 256-row tile for a 64-row problem only wastes
 // the measurement).
-std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, size_t ws_floats)
+std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits)
 {
     std::vector<GemmPlan> out;
+    for (int v = 0; traits.conv3 && v < CONV3_VARIANTS; ++v)
+        for (int nw = 2; nw <= 16; nw *= 2)
+            if (conv3_launchable(v, nw, traits, (int)N)) out.push_back(GemmPlan{2, v, 1, (int)conv3_tiles(v, traits.B, traits.Ho, traits.Wo, (int)N), nw, 0});
     for (int v = 0; v < CONV_WSK_VARIANTS; ++v)
         for (int nw = 4; nw <= 16; nw *= 2) {
             if (conv_wsk_lds_bytes(v, nw) > 128 * 1024) continue;
@@ -319,6 +322,8 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
         set_xcd_split(pl, M, N);
         return pl;
     }
+    if (f_kind == 2 && traits.conv3 && conv3_launchable(f_variant, f_n, traits, (int)N))
+        return GemmPlan{2, f_variant, 1, (int)conv3_tiles(f_variant, traits.B, traits.Ho, traits.Wo, (int)N), f_n, 0};
     if (f_kind == 0 && tile_of_id(f_variant).id >= 0) {
         pl.variant = f_variant;
         pl.tiles = (int)tiles(pl.variant);
@@ -399,8 +404,17 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
             }
         }
     }
+    // The patch kernel is not dealt either.  Beyond eight blocks of 16 x 16 outputs for every CU that an uneven share counts as, the dealt tiles
+    // are the safer choice: 28 x 28 x 128 at batch 3 and 8 8.1 and 10.5 us on 144 CUs, 10.6 and 23.0 here; 7.6 and 11.3 on 160, 7.1 and 13.0 here.
+    if (traits.conv3 && (even_cu >= n_cu || cdiv(M, 16) * cdiv(N, 16) <= 8l * even_cu))
+        for (int v = 0; v < CONV3_VARIANTS; ++v)
+            for (int nw = 2; nw <= 16; nw *= 2) {
+                if (!conv3_launchable(v, nw, traits, (int)N)) continue;
+                const double cost = conv3_cost(v, nw, traits, N, even_cu);
+                if (cost < best) { best = cost; pl = GemmPlan{2, v, 1, (int)conv3_tiles(v, traits.B, traits.Ho, traits.Wo, (int)N), nw, 0}; }
+            }
     if (pl.kind == 0) set_raster(pl, M, N);
-    else set_xcd_split(pl, M, N);
+    else if (pl.kind == 1) set_xcd_split(pl, M, N);
     *cost_out = pl.cost = best;
     return pl;
 }
@@ -498,8 +512,9 @@ hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &pl, const SeD
 {
     if ((a.ldx && (a.ldx % 8 || a.ldx < a.Cin || a.nchw_c)) || (a.ldy && (a.ldy % 8 || a.ldy < a.Cout || a.res || a.y32 || ((uintptr_t)a.y & 15))))
         return hipErrorInvalidValue;
-    const GemmDev d = make_dev(a, pl);
     if (n_launched) *n_launched += pl.splits > 1 ? 2 : 1;
+    if (pl.kind == 2) return launch_conv3(a, pl.variant, pl.nw, s);
+    const GemmDev d = make_dev(a, pl);
     if (pl.kind == 1) return launch_conv_wsk(d, a.dtype, pl.variant, pl.nw, pl.tiles, s);
     if (a.dtype == DT_BF16) return launch_t<bf16_t>(d, pl, deal, s);
     return launch_t<f16_t>(d, pl, deal, s);

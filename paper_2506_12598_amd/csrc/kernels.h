@@ -32,11 +32,11 @@ struct ConvGemmArgs {
                          // y 16-byte aligned, res and y32 null
 };
 struct GemmPlan {
-    int kind;      // 0 = LDS-tiled kernel (large problems), 1 = wave-split-K kernel (few tiles, long K)
-    int variant;   // tile shape, see conv_gemm_tile() / conv_wsk_tile()
+    int kind;      // 0 = LDS-tiled kernel (large problems), 1 = wave-split-K kernel (few tiles, long K), 2 = 3 x 3 windows from a patch in LDS
+    int variant;   // tile shape, see conv_gemm_tile() / conv_wsk_tile() / conv3_tile()
     int splits;    // kind 0: K is cut into this many slices, summed by a second kernel
     int tiles;     // output tiles = workgroups (per slice)
-    int nw;        // kind 1: wavefronts per workgroup, each taking 1/nw of K
+    int nw;        // kinds 1, 2: wavefronts per workgroup, each taking 1/nw of K
     int raster;    // how workgroups walk the tiles: 2 (3) = an XCD owns a contiguous range of tiles counted down the tile columns
                    // (along the tile rows); 1 (kind 0) = 8 x 4 blocks of tiles per XCD.  `tiles` counts the padding of the walk
     double cost = 0.0;   // modelled time, us without the launch; 0: chosen by measurement or forced
@@ -65,12 +65,14 @@ struct GemmTraits {
     bool lean = true;    // the lean form of the wave-split-K kernel takes the layer
     int even_cu = 0;     // CuShare::even_cu of the stream; 0: the same as n_cu
     bool copied = false; // the copied tiles take the layer in a fast address form and with their fast epilogue (conv_gemm_is_copied)
+    bool conv3 = false;  // the patch kernel takes the layer (conv3_takes); then its geometry:
+    int B = 0, Ho = 0, Wo = 0, Cin = 0, stride = 0;
 };
 bool conv_gemm_is_copied(int KH, int KW, int Cin, int Cout);
 // Chooses tile shape and K split for a stream restricted to n_cu compute units.
 GemmPlan conv_gemm_plan(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits = GemmTraits());
 // every plan worth timing for a problem (measured plan selection)
-std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, size_t ws_floats);
+std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits = GemmTraits());
 double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int variant, int nw);   // the general form's loop by the planner's model, us
 // the wave-split-K shape of the lowest estimate whose tile columns divide `columns` channels (0: any); n_cu: CuShare::even_cu
 GemmPlan conv_wsk_plan_columns(long M, long N, long K, int n_cu, int columns);
@@ -83,6 +85,17 @@ bool conv_gemm_plan_pair(const GemmPlan &s0, long M0, long N0, long K0, int form
                          GemmPlan *p0, GemmPlan *p1);
 hipError_t launch_conv_gemm_pair(const ConvGemmArgs &a0, const GemmPlan &p0, const ConvGemmArgs &a1, const GemmPlan &p1, hipStream_t s,
                                  uint32_t *n_launched);
+
+// ---- 3 x 3 convolutions of small requests from an image patch in LDS (k_conv3.hip) ---------------
+enum { CONV3_VARIANTS = 6, CONV3_MAX_LDS = 128 * 1024 };         // output pixels 4x4, 8x4, 8x8 (two widths of 16 and 32 channels each)
+bool conv3_takes(int KH, int KW, int stride, int pad, int H, int W, int Cin, int Cout, int ldx);
+void conv3_tile(int variant, int *th, int *tw, int *bn);         // output pixels down and across, channels
+long conv3_tiles(int variant, int B, int Ho, int Wo, int Cout);
+size_t conv3_lds_bytes(int variant, int nw, int stride, int Cin);
+bool conv3_launchable(int variant, int nw, const GemmTraits &t, int Cout);
+double conv3_cost(int variant, int nw, const GemmTraits &t, long N, int n_cu);           // on the scale of the other plans' costs; n_cu: CuShare::even_cu
+hipError_t conv3_init();       // raises the dynamic LDS limit once per process
+hipError_t launch_conv3(const ConvGemmArgs &a, int variant, int nw, hipStream_t s);
 
 // ---- first layer of an image model, from the caller's planes (k_stem.hip) -----------------------
 struct StemArgs {
