@@ -1294,6 +1294,10 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
                 name = gconv_mfma_kernel_name(ga);
                 out->workgroups = (uint32_t)pl.tiles;
                 out->threads = (uint32_t)pl.nw * 64;
+                if (const int blocks = gconv3_blocks(ga, P.gc_super, share_of(model->pool->streams[mask_id]).even_cu())) {
+                    out->workgroups = gconv3_workgroups(ga, P.gc_super, blocks);
+                    out->threads = 256;
+                }
             }
         } else if (P.L.op == ECLIP_OP_CONV && P.L.groups > 1) {
             DwConvArgs da{};

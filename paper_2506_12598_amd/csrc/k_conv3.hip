@@ -197,6 +197,121 @@ __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const
     }
 }
 
+// Grouped convolutions whose super-groups (k_gconv.hip) read 32 channels: nine steps of the matrix instruction are all there is to sum, so a wavefront
+// does a tile of 16 TN channels by itself and stores from its registers, without a barrier; the four of a workgroup take neighbouring channels of the
+// same pixels, whose cache lines they share.
+namespace patch {
+template <typename T, int TH, int TW, int TN, int SD>
+__global__ __launch_bounds__(256) void gconv_mfma_kernel(const uint16_t *x, const uint16_t *w, unsigned packed, int tiles, unsigned cols_d, unsigned cols_mul, unsigned hw,
+                                                         unsigned px, unsigned image_d, unsigned image_mul, unsigned row_d, unsigned row_mul, Conv3Rest p)
+{
+    constexpr int TM = TH * TW, PH = (4 * TH - 1) * SD + 3, PW = (4 * TW - 1) * SD + 3, COPIES = (PH * PW * 4 + 63) / 64;
+    constexpr unsigned OOB = 0xffffffffu;
+    __shared__ __attribute__((aligned(16))) char smem[4 * COPIES * 1024];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const unsigned groups = (unsigned)(tiles + 3) >> 2, xcd = blockIdx.x & 7u, g = (groups * xcd >> 3) + (blockIdx.x >> 3);
+    const unsigned t = g * 4u + (unsigned)wave;
+    if (g >= (groups * (xcd + 1u) >> 3) || t >= (unsigned)tiles) return;
+    const unsigned tile_m = div_by(t, Magic{cols_d, cols_mul, packed >> 2 & 31u}), col = t - tile_m * cols_d;
+    const unsigned b = div_by(tile_m, Magic{image_d, image_mul, packed >> 7 & 31u}), in_image = tile_m - b * image_d;
+    const unsigned ty = div_by(in_image, Magic{row_d, row_mul, packed >> 12 & 31u}), tx = in_image - ty * row_d;
+    const int H = (int)(hw & 0xffffu), W = (int)(hw >> 16), oy0 = (int)ty * 4 * TH, ox0 = (int)tx * 4 * TW;
+
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)w, 0, (int)0xfffffffeu, 0x00020000);          // never beyond the last block
+    u32x4 wf[9][TN];
+    auto load_w = [&](auto tc) {
+        constexpr int k = decltype(tc)::value;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) wf[k][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, (unsigned)lane * 16u, (((int)col * TN + j) * 9 + k) * 1024, 0);
+    };
+    constexpr int EARLY = 3;
+    static_for<EARLY>([&](auto tc) { load_w(tc); });
+    const unsigned mine = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem + (unsigned)wave * (COPIES * 1024u);
+    // the group's 32 channels of the image; bits 17-21 of packed: log2 of the tile columns of a super-group
+    const unsigned first = (col >> (packed >> 17 & 31u)) * 64u;
+    const uint64_t at_x = (uint64_t)(uintptr_t)x + (uint64_t)b * ((unsigned)(H * W) * px) + first;
+    const u32x4 rx = {(unsigned)at_x, (unsigned)(at_x >> 32) & 0xffffu, (unsigned)(H * W) * px - first, 0x00020000u};
+    const unsigned chunk = (unsigned)((lane & 3) ^ (lane >> 4)) * 16u;
+    const int iy0 = oy0 * SD - 1, ix0 = ox0 * SD - 1;
+    static_for<COPIES>([&](auto cc) {
+        constexpr int c = decltype(cc)::value;
+        const unsigned i = c * 16u + (unsigned)(lane >> 2), py = i / PW, qx = i - py * PW;
+        const int iy = iy0 + (int)py, ix = ix0 + (int)qx;
+        const bool ok = (unsigned)iy < (unsigned)H && (unsigned)ix < (unsigned)W && i < PH * PW;
+        copy_to_lds(rx, ok ? __umul24(__umul24((unsigned)iy, (unsigned)W) + (unsigned)ix, px) + chunk : OOB, mine + c * 1024u);
+    });
+    static_for<9 - EARLY>([&](auto tc) { load_w(std::integral_constant<int, decltype(tc)::value + EARLY>()); });
+
+    const int r16 = lane & 15, q = lane >> 4, n0 = (int)col * TN * 16 + 4 * q;
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void *)p.bias, 0, (int)p.bias_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void *)p.res, 0, (int)p.res_bytes, 0x00020000);
+    u32x2 bias[TN], res[TM][TN];
+    unsigned off[TM];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bias[j] = __builtin_amdgcn_raw_buffer_load_b64(rb, (unsigned)(n0 + 16 * j) * 2u, 0, 0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int oy = oy0 + 4 * (i / TW) + (r16 >> 2), ox = ox0 + 4 * (i % TW) + (r16 & 3);
+        off[i] = oy < p.Ho && ox < p.Wo ? (unsigned)((((int)b * p.Ho + oy) * p.Wo + ox) * p.ldy + n0) * 2u : OOB;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) res[i][j] = __builtin_amdgcn_raw_buffer_load_b64(rr, off[i] == OOB ? OOB : off[i] + 32u * j, 0, 0);
+    }
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int pix0 = (r16 >> 2) * SD * PW + (r16 & 3) * SD;
+    const char *const base = smem + wave * (COPIES * 1024);
+    auto at = [&](int k) { return pix0 * 64 + ((q ^ ((((pix0 + (k & 3)) >> 2) + (k >> 2)) & 3)) << 4); };
+    // as in conv3_kernel: the patch has arrived when no more than what was fetched behind it is on its way
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((9 - EARLY) * TN + TN + TM * TN) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<9>([&](auto tc) {
+        constexpr int k9 = decltype(tc)::value;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int k = (4 * (i / TW) * SD + k9 / 3) * PW + 4 * (i % TW) * SD + k9 % 3;
+            const uint4 a = *reinterpret_cast<const uint4 *>(base + at(k) + k * 64);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = Mma<T>::run(make_uint4(wf[k9][j].x, wf[k9][j].y, wf[k9][j].z, wf[k9][j].w), a, acc[i][j]);
+        }
+    });
+    auto lo = [](unsigned v) { return Cvt<T>::from_bits(v & 0xffffu); };
+    auto hi = [](unsigned v) { return Cvt<T>::from_bits(v >> 16); };
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)p.y_bytes, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            float o[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+            o[0] += lo(bias[j].x); o[1] += hi(bias[j].x); o[2] += lo(bias[j].y); o[3] += hi(bias[j].y);
+            o[0] += lo(res[i][j].x); o[1] += hi(res[i][j].x); o[2] += lo(res[i][j].y); o[3] += hi(res[i][j].y);
+            if (p.act == ACT_GELU) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = gelu_erf(o[e]);
+            } else if (p.act != ACT_NONE) {
+                const float top = p.act == ACT_RELU6 ? 6.0f : __builtin_inff();
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = fminf(fmaxf(o[e], 0.0f), top);
+            }
+            const u32x2 v = {Cvt<T>::pack2(o[0], o[1]), Cvt<T>::pack2(o[2], o[3])};
+            __builtin_amdgcn_raw_buffer_store_b64(v, ry, off[i] == OOB ? OOB : off[i] + 32u * j, 0, 0);
+        }
+}
+
+template <typename T, int TN, int SD> const void *kernel_of(int blocks)
+{
+    return blocks == 1 ? (const void *)gconv_mfma_kernel<T, 1, 1, TN, SD> : blocks == 2 ? (const void *)gconv_mfma_kernel<T, 2, 1, TN, SD>
+                                                                                        : (const void *)gconv_mfma_kernel<T, 2, 2, TN, SD>;
+}
+template <typename T> const void *kernel_of(int tn, int sd, int blocks)
+{
+    if (tn == 2) return sd == 1 ? kernel_of<T, 2, 1>(blocks) : kernel_of<T, 2, 2>(blocks);
+    return sd == 1 ? kernel_of<T, 1, 1>(blocks) : kernel_of<T, 1, 2>(blocks);
+}
+}  // namespace patch
+
 struct Shape { int th, tw, tn; };
 constexpr Shape kShapes[CONV3_VARIANTS] = {{1, 1, 1}, {1, 1, 2}, {2, 1, 1}, {2, 1, 2}, {2, 2, 1}, {2, 2, 2}};
 
@@ -336,6 +451,46 @@ hipError_t launch_conv3(const ConvGemmArgs &a, int variant, int nw, hipStream_t 
     p.ldy = ldy; p.act = a.act; p.Ho = a.Ho; p.Wo = a.Wo;
     void *args[] = {&x, &w, &packed, &tiles, &inner.d, &inner.mul, &hw, &px_slices, &image.d, &image.mul, &row.d, &row.mul, &p};
     return hipLaunchKernel(k, dim3((unsigned)(tiles + 7) & ~7u), dim3((unsigned)nw * 64), args, lds, s);
+}
+
+// Tile of the grouped form: blocks of 4 x 4 pixels per wavefront (1, 2 or 4), 0: left to the wave-split-K kernel.  n_cu: CuShare::even_cu.  One block while
+// few workgroups share a compute unit, then two to halve the fetches of the weights, four beyond five workgroups (a lone wavefront takes a
+// microsecond longer over four).  Against the wave-split-K kernel, us in chains of 40 layers: 56 x 56 x 128 at batch 1 on 128 CUs 6.1, with two blocks 4.4 (one
+// 4.9, four 5.6); at batch 4 on 64 18.5, 11.8 (15.5, 12.1); 14 x 14 x 512 at batch 2 on 256 4.75, 3.7; 7 x 7 x 1024 at batch 8 on 128 5.95, 4.3; of
+// 132 layers none with a workgroup per CU was slower, those with fewer within what the host's pace blurs.
+int gconv3_blocks(const GConvArgs &a, int S, int n_cu)
+{
+    const int SI = S * (a.Cin / a.groups), SO = S * (a.Cout / a.groups), tn = SO % 32 ? 1 : 2, cols = SO / (16 * tn);
+    if (SI != 32 || SO % 16 || (cols & (cols - 1)) || !conv3_takes(a.KH, a.KW, a.stride, a.pad, a.H, a.W, a.Cin, a.Cout, a.Cin)) return 0;
+    if (const char *f = getenv("ECLIP_GCONV3")) return atoi(f);       // blocks; 0: the wave-split-K kernel
+    const double per_cu = (double)gconv3_workgroups(a, S, 1) / n_cu;
+    return per_cu <= 1.75 ? 1 : per_cu <= 5.0 ? 2 : 4;
+}
+unsigned gconv3_workgroups(const GConvArgs &a, int S, int blocks)
+{
+    const int th = blocks > 1 ? 8 : 4, tw = blocks > 2 ? 8 : 4, tn = S * (a.Cout / a.groups) % 32 ? 1 : 2;
+    const long tiles = (long)a.B * ((a.Ho + th - 1) / th) * ((a.Wo + tw - 1) / tw) * (a.Cout / (16 * tn));
+    return (unsigned)((tiles + 3) / 4);
+}
+
+hipError_t launch_gconv3(const GConvArgs &a, int S, int blocks, hipStream_t s)
+{
+    const int th = blocks > 1 ? 8 : 4, tw = blocks > 2 ? 8 : 4, SO = S * (a.Cout / a.groups), tn = SO % 32 ? 1 : 2;
+    const void *k = a.dtype == DT_BF16 ? patch::kernel_of<bf16_t>(tn, a.stride, blocks) : patch::kernel_of<f16_t>(tn, a.stride, blocks);
+    const uint16_t *x = (const uint16_t *)a.x, *w = (const uint16_t *)a.w;
+    const int tiles_x = (a.Wo + tw - 1) / tw, tiles_y = (a.Ho + th - 1) / th, n_cols = a.Cout / (16 * tn);
+    int tiles = a.B * tiles_x * tiles_y * n_cols;
+    Magic cols = magic_of((unsigned)n_cols), image = magic_of((unsigned)(tiles_x * tiles_y)), row = magic_of((unsigned)tiles_x);
+    unsigned packed = cols.shift << 2 | image.shift << 7 | row.shift << 12 | (unsigned)__builtin_ctz((unsigned)(SO / (16 * tn))) << 17;
+    unsigned hw = (unsigned)a.H | (unsigned)a.W << 16, px = (unsigned)a.Cin * 2u;
+    Conv3Rest p{};
+    p.bias = (const uint16_t *)a.bias; p.res = (const uint16_t *)a.res; p.y = a.y;
+    p.bias_bytes = a.bias ? (unsigned)a.Cout * 2u : 0u;
+    p.y_bytes = (unsigned)(a.B * a.Ho * a.Wo) * (unsigned)a.Cout * 2u;
+    p.res_bytes = a.res ? p.y_bytes : 0u;
+    p.ldy = a.Cout; p.act = a.act; p.Ho = a.Ho; p.Wo = a.Wo;
+    void *args[] = {&x, &w, &packed, &tiles, &cols.d, &cols.mul, &hw, &px, &image.d, &image.mul, &row.d, &row.mul, &p};
+    return hipLaunchKernel(k, dim3((gconv3_workgroups(a, S, blocks) + 7u) & ~7u), dim3(256), args, 0, s);
 }
 
 }  // namespace eclip

@@ -11,7 +11,8 @@
 // The weights lie in the 1 KB blocks the matrix instruction consumes: block (sg, nb, t) at ((sg * NB + nb) * KT + t) KB,
 // t = tap * (S*cig / 32) + kb.  Read with nb running over all super-groups this is the layout of a dense layer of Cout channels
 // and K = taps x S*cig, so the wave-split-K kernel (k_wsk_lean.hip: gconv_mfma_kernel; windows of more than 31 taps: the general form in
-// k_wsk.hip) serves it: a tile column only has to know which channels of x its super-group reads.  A kernel of its own, one
+// k_wsk.hip) serves it: a tile column only has to know which channels of x its super-group reads.  3 x 3 windows over super-groups of 32
+// channels, nine steps in all, have a form that reads a patch of the image from LDS (k_conv3.hip).  A kernel of its own without one, one
 // wavefront per 16 pixels x 32 to 64 channels over all of K, took 4.6 us instead of 2.8 to 3.2 at the ResNeXt shapes at batch
 // 1 and 2, 11.3 instead of 2.9 at 49 pixels x 960 channels, and 72.7 instead of 57.2 at batch 8 on 32 CUs.
 #include "gemm_common.h"
@@ -47,6 +48,7 @@ hipError_t launch_gconv_mfma(const GConvArgs &a, int S, int n_cu, hipStream_t s)
     const long M = (long)a.B * a.Ho * a.Wo, xb = (long)a.B * a.H * a.W * a.Cin * 2, wb = (long)(a.Cout / 16) * a.KH * a.KW * (SI / 32) * 1024;
     if (SI % 32 || SO % 16 || a.Cin % 8 || M >= (1L << 30) || xb >= (1L << 32) - 16 || wb >= (1L << 32) - 16) return hipErrorInvalidValue;
     if (a.dtype != DT_BF16 && a.dtype != DT_F16) return hipErrorInvalidValue;
+    if (const int blocks = gconv3_blocks(a, S, n_cu)) return launch_gconv3(a, S, blocks, s);
     const GemmPlan pl = gconv_mfma_plan(a, S, n_cu);
     int bm, bn;
     conv_wsk_tile(pl.variant, &bm, &bn);

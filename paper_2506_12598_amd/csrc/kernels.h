@@ -164,6 +164,10 @@ bool gconv_mfma_pick(int groups, int cig, int cog, int *S_out);
 hipError_t launch_gconv_mfma(const GConvArgs &a, int S, int n_cu, hipStream_t s);      // n_cu: CuShare::even_cu of the stream
 GemmPlan gconv_mfma_plan(const GConvArgs &a, int S, int n_cu);               // tile and grid launch_gconv_mfma uses
 const char *gconv_mfma_kernel_name(const GConvArgs &a);
+// its form for 3 x 3 windows over super-groups of 32 channels (k_conv3.hip)
+int gconv3_blocks(const GConvArgs &a, int S, int n_cu);
+unsigned gconv3_workgroups(const GConvArgs &a, int S, int blocks);
+hipError_t launch_gconv3(const GConvArgs &a, int S, int blocks, hipStream_t s);
 // y[m][0 .. c0) = a[m][:], y[m][c0 .. c0 + c1) = b[m][:]
 hipError_t launch_concat(const void *a, const void *b, void *y, long rows, int c0, int c1, int dtype, hipStream_t s);
 // y[m][0 .. c) = x[m][:], rows of y ld channels apart (16-bit types, c and ld multiples of 8)

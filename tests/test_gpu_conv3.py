@@ -66,3 +66,30 @@ def test_residual_and_channel_ranges(variant, nw, act):
     got = forced(m, x_in, t, variant, nw)
     # four layers stored in float16, 2^-12 of a value each and magnified by no more than 2 in the next: the bound is 16 of them
     assert np.isfinite(got).all() and rel_to_range(got, orc.run_model(m, x_in)) <= 2.0 ** -8
+
+
+# grouped: super-groups of 32 input channels with 16, 32 and 64 outputs; more tiles than a workgroup's four, and fewer
+@pytest.mark.parametrize("h,w,cin,cout,groups,stride,batch", [(1, 1, 64, 64, 16, 1, 1), (7, 9, 128, 128, 32, 1, 3), (13, 4, 64, 128, 8, 1, 2), (9, 17, 64, 32, 8, 2, 1),
+                                                              (16, 8, 96, 96, 3, 2, 2), (5, 5, 32, 32, 8, 1, 1)])
+@pytest.mark.parametrize("blocks", [1, 2, 4])
+@pytest.mark.parametrize("dt", [wl.DT_BF16, wl.DT_F16])
+def test_grouped(h, w, cin, cout, groups, stride, batch, blocks, dt):
+    m = wl.single_layer("conv", dt, seed=h + cin + cout, cin=cin, cout=cout, h=h, w=w, k=3, stride=stride, pad=1, groups=groups, act=wl.ACT_RELU, bias_std=0.4,
+                        residual=True)
+    x = wl.make_input(m, batch)
+    os.environ["ECLIP_GCONV3"] = str(blocks)
+    try:
+        g = GpuModel(m, max_batch=batch)
+        try:
+            info = g.h.kernel_info(1, 0, batch)
+            th, tw = (4, 8, 8)[blocks // 2], (4, 4, 8)[blocks // 2]
+            ho, wo = (h - 1) // stride + 1, (w - 1) // stride + 1
+            columns = cout // (32 if cout * 32 // cin % 32 == 0 else 16)
+            assert info["kernel"] == "gconv_mfma_kernel" and info["workgroups"] == -(-batch * -(-ho // th) * -(-wo // tw) * columns // 4)
+            got = g.run(x)
+        finally:
+            g.free()
+    finally:
+        del os.environ["ECLIP_GCONV3"]
+    # two layers stored in 16 bits, 2^-9 (2^-12) of a value each
+    assert np.isfinite(got).all() and rel_to_range(got, orc.run_model(m, x)) <= (2.0 ** -8 if dt == wl.DT_BF16 else 2.0 ** -11)
