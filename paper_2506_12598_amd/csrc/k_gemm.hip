@@ -404,9 +404,10 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
             }
         }
     }
-    // The patch kernel is not dealt either.  Beyond eight blocks of 16 x 16 outputs for every CU that an uneven share counts as, the dealt tiles
-    // are the safer choice: 28 x 28 x 128 at batch 3 and 8 8.1 and 10.5 us on 144 CUs, 10.6 and 23.0 here; 7.6 and 11.3 on 160, 7.1 and 13.0 here.
-    if (traits.conv3 && (even_cu >= n_cu || cdiv(M, 16) * cdiv(N, 16) <= 8l * even_cu))
+    // The patch kernel is not dealt either.  On the more uneven shares, beyond eight blocks of 16 x 16 outputs for every CU that the share counts as, the
+    // dealt tiles are the safer choice: 28 x 28 x 128 at batch 3 and 8 8.1 and 10.5 us on 144 CUs, 10.6 and 23.0 here; 7.6 and 11.3 on 160, 7.1 and 13.0
+    // here.  On 208 CUs (counted as 160) 56 x 56 x 64 at batch 4 takes 6.4 on the tiles and 5.2 here, on 112 (96) 7.0 and 6.0, 14 x 14 x 256 on 208 8 and 5.4.
+    if (traits.conv3 && (even_cu >= 0.75 * n_cu || cdiv(M, 16) * cdiv(N, 16) <= 8l * even_cu))
         for (int v = 0; v < CONV3_VARIANTS; ++v)
             for (int nw = 2; nw <= 16; nw *= 2) {
                 if (!conv3_launchable(v, nw, traits, (int)N)) continue;
