@@ -5,8 +5,11 @@
 // walks window positions per lane.  Here a workgroup brings the patch of the image that its outputs need into LDS once, four channels
 // side by side (8 bytes a pixel), and the matrix instruction's operand is read from there as it lies: 32 consecutive k are
 // KWP pixels of 32 / (4 KWP) window rows, so a lane's 8 k's are two neighbouring pixels, one LDS read (two where the stride is odd
-// and pairs are not 16-byte aligned).  7 x 7: KWP = 8, one K step per window row (224 products); 3 x 3: KWP = 4, two rows per step (64).  The weights
-// lie in registers for the workgroup's life.  Results go through LDS in the storage type, so that the stores are 16 bytes along the rows and the
+// and pairs are not 16-byte aligned).  7 x 7: KWP = 8, one K step per window row (224 products); 3 x 3: KWP = 4, two rows per step (64).  What lies
+// beyond a smaller window is another window's pixel, not a zero, and an infinite one times its zero weight would be NaN: it is cleared in the
+// operand (ResNet's first layer and pool on 128 CUs at batch 1 6.05 -> 6.17 us, at batch 8 14.8 -> 15.4; VGG-16's first layer at batch 8 on 256 15.2 ->
+// 15.5; looking whether a workgroup's patch holds such a value at all cost as much as clearing).  The weights lie in registers for the workgroup's life.
+// Results go through LDS in the storage type, so that the stores are 16 bytes along the rows and the
 // pool, a selection, takes exactly the values that would have been stored between the layers.
 // What bounds it: at batch 1 the dispatch and one trip to memory, on larger problems the writes.
 #include "device_common.h"
@@ -30,13 +33,14 @@ struct StemDev {
     const uint16_t *x, *w, *bias;
     uint16_t *y;
     unsigned x_bytes, bias_bytes;
-    int C, H, W, Ho, Wo, N, pad, act;
+    int C, H, W, KH, KW, Ho, Wo, N, pad, act;
     int Po, Qo;                              // rows and columns of the output (POOL: of the pool)
     Magic tiles, cols, chunks;               // tiles per image, per row of tiles; 16-byte chunks of a pixel's channels
 };
 
 // NBLK: K steps of 32; NB: blocks of 16 output channels; S: stride; TH x TW: outputs per workgroup, of the pool with POOL.
-template <typename T, int NBLK, int KWP, int NB, int S, bool POOL, int TH, int TW>
+// SMALL (KWP == 8): a window of fewer than 7 rows or columns, else only its last column may be missing.  KWP == 4: windows of 3 or 4 rows and columns.
+template <typename T, int NBLK, int KWP, int NB, int S, bool POOL, int TH, int TW, bool SMALL>
 __global__ __launch_bounds__(256) void stem_kernel(StemDev p)
 {
     constexpr unsigned OOB = 0xffffffffu;
@@ -91,6 +95,7 @@ __global__ __launch_bounds__(256) void stem_kernel(StemDev p)
 
     // ---- 16 outputs of the convolution per turn of a wavefront; lane (q4, r16) feeds k's 8 q4 .. +7 of output r16
     const int g_row = KWP == 8 ? 0 : q4 >> 1, g_col = KWP == 8 ? 2 * q4 : 2 * (q4 & 1);
+    const bool lo_in = g_col < p.KW, hi_in = g_col + 1 < p.KW;               // the lane's two pixels of a window row
     u32x4 a[NBLK];
     int r, c;
     auto fetch = [&](int f) {
@@ -113,6 +118,11 @@ __global__ __launch_bounds__(256) void stem_kernel(StemDev p)
     for (int f = wave >> 1; f < FRAGS; f += 2) {
         const int i = f * 16 + r16, row = c_row + r, col = c_col + c;
         f32x4 acc[NBW];
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k) {
+            const bool rows = KWP == 8 ? !SMALL || k < p.KH : k == 0 || 2 + g_row < p.KH, lo = rows && (!SMALL || lo_in), hi = rows && hi_in;
+            a[k] = u32x4{lo ? a[k].x : 0u, lo ? a[k].y : 0u, hi ? a[k].z : 0u, hi ? a[k].w : 0u};
+        }
 #pragma unroll
         for (int k = 0; k < NBLK; ++k)
 #pragma unroll
@@ -185,13 +195,13 @@ struct Tile { int h, w; };
 // Outputs per workgroup: the small tiles where the large ones would leave compute units without a workgroup.
 constexpr Tile PLAIN[2] = {{8, 16}, {4, 16}}, POOLED[2] = {{4, 8}, {4, 4}};
 
-template <typename T, int NBLK, int KWP, int NB, int S>
+template <typename T, int NBLK, int KWP, int NB, int S, bool SMALL = false>
 hipError_t launch(const StemDev &d, bool pool, bool small, unsigned grid, hipStream_t s)
 {
-    const void *k = pool ? small ? (const void *)stem_kernel<T, NBLK, KWP, NB, S, true, POOLED[1].h, POOLED[1].w>
-                                 : (const void *)stem_kernel<T, NBLK, KWP, NB, S, true, POOLED[0].h, POOLED[0].w>
-                         : small ? (const void *)stem_kernel<T, NBLK, KWP, NB, S, false, PLAIN[1].h, PLAIN[1].w>
-                                 : (const void *)stem_kernel<T, NBLK, KWP, NB, S, false, PLAIN[0].h, PLAIN[0].w>;
+    const void *k = pool ? small ? (const void *)stem_kernel<T, NBLK, KWP, NB, S, true, POOLED[1].h, POOLED[1].w, SMALL>
+                                 : (const void *)stem_kernel<T, NBLK, KWP, NB, S, true, POOLED[0].h, POOLED[0].w, SMALL>
+                         : small ? (const void *)stem_kernel<T, NBLK, KWP, NB, S, false, PLAIN[1].h, PLAIN[1].w, SMALL>
+                                 : (const void *)stem_kernel<T, NBLK, KWP, NB, S, false, PLAIN[0].h, PLAIN[0].w, SMALL>;
     StemDev arg = d;
     void *args[] = {&arg};
     return hipLaunchKernel(k, dim3(grid), dim3(256), args, 0, s);
@@ -200,6 +210,7 @@ template <typename T>
 hipError_t launch(const StemArgs &a, const StemDev &d, bool small, unsigned grid, hipStream_t s)
 {
     const bool wide = stem_window(a.KH, a.KW) == 8, many = a.N > 32;
+    if (wide && (a.KH < 7 || a.KW < 7)) return many ? launch<T, 7, 8, 4, 2, true>(d, a.pool, small, grid, s) : launch<T, 7, 8, 2, 2, true>(d, a.pool, small, grid, s);
     if (wide) return many ? launch<T, 7, 8, 4, 2>(d, a.pool, small, grid, s) : launch<T, 7, 8, 2, 2>(d, a.pool, small, grid, s);
     if (a.stride == 2) return many ? launch<T, 2, 4, 4, 2>(d, a.pool, small, grid, s) : launch<T, 2, 4, 2, 2>(d, a.pool, small, grid, s);
     return many ? launch<T, 2, 4, 4, 1>(d, a.pool, small, grid, s) : launch<T, 2, 4, 2, 1>(d, a.pool, small, grid, s);
@@ -229,7 +240,7 @@ hipError_t launch_stem(const StemArgs &a, int n_cu, hipStream_t s)
     d.x = (const uint16_t *)a.x; d.w = (const uint16_t *)a.w; d.bias = (const uint16_t *)a.bias; d.y = (uint16_t *)a.y;
     d.x_bytes = (unsigned)((size_t)a.B * a.C * a.H * a.W * 2);
     d.bias_bytes = a.bias ? (unsigned)a.N * 2u : 0u;
-    d.C = a.C; d.H = a.H; d.W = a.W; d.Ho = a.Ho; d.Wo = a.Wo; d.N = a.N; d.pad = a.pad; d.act = a.act;
+    d.C = a.C; d.H = a.H; d.W = a.W; d.KH = a.KH; d.KW = a.KW; d.Ho = a.Ho; d.Wo = a.Wo; d.N = a.N; d.pad = a.pad; d.act = a.act;
     d.Po = a.pool ? (a.Ho - 1) / 2 + 1 : a.Ho;
     d.Qo = a.pool ? (a.Wo - 1) / 2 + 1 : a.Wo;
     const Tile *of = a.pool ? POOLED : PLAIN;
