@@ -90,8 +90,10 @@ def _reach(bad, k, stride, pad):
 ])
 def test_values_that_are_not_finite_stay_in_their_windows(cin, cout, h, w, kh, kw, stride, pad, act, pool, dt):
     m = _model(dt, cin, cout, h, w, kh, kw, stride, pad, act, pool, keeps_nan=True)
-    # single pixels at all four parities
-    marks = [(np.inf, [(12, 12)]), (np.nan, [(13, 16)]), (-np.inf, [(16, 13)]), (np.inf, [(15, 11), (h - 2, w - 1)])]
+    # single pixels at all four parities, then blocks over opposite corners, where whole windows of the pool are NaN
+    corner = [(i, j) for i in range(11) for j in range(11)]
+    marks = [(np.inf, [(12, 12)]), (np.nan, [(13, 16)]), (-np.inf, [(16, 13)]), (np.inf, [(15, 11), (h - 2, w - 1)]),
+             (np.nan, corner + [(h - 1 - i, w - 1 - j) for i, j in corner])]
     clean = np.array(wl.make_input(m, len(marks)))
     x = clean.copy()
     hit = np.zeros((len(marks), h, w), bool)
