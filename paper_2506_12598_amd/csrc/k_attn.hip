@@ -498,8 +498,8 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(AttnDev p)
         for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sc[kb][r]);
     }
     mx = rows_max(mx);
-    // a wavefront whose keys are all padded adds nothing: exp2(-inf + 0), not exp2(-inf + inf)
-    const float c2 = p.scale * 1.4426950408889634f, off2 = key_base < p.S ? -mx * c2 : 0.0f;
+    // a wavefront whose keys are all padded, or all score -inf, adds nothing: exp2(-inf + 0), not exp2(-inf + inf)
+    const float c2 = p.scale * 1.4426950408889634f, off2 = mx > -INFINITY ? -mx * c2 : 0.0f;
     float sum = 0.0f;
     f32x4 o[D / 16];
 #pragma unroll

@@ -32,3 +32,25 @@ def test_shared_keys(seq, hidden, heads, batch, peaked, dt):
     # probabilities and values are rounded to 16 bits, float32 throughout otherwise: the bound of the other attention tests
     for got in (few, many):
         assert np.isfinite(got).all() and rel_to_range(got, exp) <= 6e-3
+
+
+@pytest.mark.parametrize("dt", [wl.DT_BF16, wl.DT_F16])
+@pytest.mark.parametrize("seq", [33, 64, 65, 97, 128, 129, 161, 225, 256])
+def test_a_share_of_keys_without_weight(seq, dt):
+    """All keys of one wavefront's share score -inf (an infinite element, as a projection that overflowed leaves it): they weigh nothing, whichever share it is."""
+    hidden, heads = 128, 2
+    m = wl.single_layer("attention", dt, seed=seq, seq=seq, hidden=hidden, heads=heads)
+    x0 = np.array(wl.make_input(m, 1))
+    x0[:, :, 0:hidden:64] = wl.round_to_dtype(np.abs(x0[:, :, 0:hidden:64]).astype(np.float32) + 0.25, dt)      # the element that meets the infinite one
+    g = GpuModel(m, max_batch=1)
+    try:
+        for first in range(0, seq, 32):
+            x = x0.copy()
+            x[:, first:first + 32, hidden:2 * hidden:64] = -np.inf
+            exp = orc.run_model(m, x)
+            assert np.isfinite(exp).all()
+            for table in (5, 1):                 # 256 CUs, 32 CUs
+                got = g.run(x, table=[table])
+                assert np.isfinite(got).all() and rel_to_range(got, exp) <= 6e-3, (first, table)
+    finally:
+        g.free()
