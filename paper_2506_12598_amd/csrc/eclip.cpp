@@ -758,14 +758,13 @@ static eclip_status plan_model(const eclip_model_desc *d, size_t weight_elems, e
         m->stem_direct = d->in_kind == ECLIP_IN_IMAGE && S.L.op == ECLIP_OP_CONV && (f32 ? S.L.groups <= 1 : d->in_c <= 4 && m->in_cp == 8 && S.gemm) &&
                          S.L.in0 == -1 && S.L.in1 != -1 && only_reader && d->n_layers > 1;
     }
-    // The stem kernel takes a max-pool along when nobody else reads the convolution (ResNet at 224 x 224, batch 1, 128 CUs: 5.8 us for both,
-    // 4.2 more for a pool of its own).  Maps of up to 16 x 16 keep the pool apart: requests on images that small go on launching what they did.
+    // The stem kernel takes a max-pool along when nobody else reads the convolution (ResNet at 224 x 224, batch 1, 128 CUs: 6.3 us for both,
+    // 4.2 more for a pool of its own; images of 9 x 9 to 64 x 64, batch 1 to 32, 32 to 256 CUs, 7 x 7 and 3 x 3: 1.4 to 4.5 us less than apart).
     if (m->stem_direct && d->n_layers > 2) {
         const LayerPlan &Q = m->layers[1];
         bool only_reader = d->group_of_layer[0] == d->group_of_layer[1];
         for (uint32_t j = 2; j < d->n_layers; ++j) only_reader &= m->layers[j].L.in0 != 0 && m->layers[j].L.in1 != 0;
-        m->stem_pool = only_reader && Q.L.op == ECLIP_OP_MAXPOOL && Q.L.in0 == 0 && Q.L.kh == 3 && Q.L.kw == 3 && Q.L.stride == 2 && Q.L.pad == 1 &&
-                       Q.out.h * Q.out.w > 256;
+        m->stem_pool = only_reader && Q.L.op == ECLIP_OP_MAXPOOL && Q.L.in0 == 0 && Q.L.kh == 3 && Q.L.kw == 3 && Q.L.stride == 2 && Q.L.pad == 1;
     }
     // Pool + classifier candidates: a GAP layer read only by the linear layer right after it, same group,
     // the linear layer taking no second operand.  Whether the fused kernel pays depends on batch and compute units (decided per request).

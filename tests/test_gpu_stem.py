@@ -34,6 +34,7 @@ def _model(dt, cin, cout, h, w, kh, kw, stride, pad, act, pool, keeps_nan=False)
     (3, 64, 224, 224, 7, 7, 2, 3, wl.ACT_RELU, 3, True),         # more large tiles than compute units
     (4, 40, 70, 66, 3, 4, 2, 1, wl.ACT_NONE, 1, True),           # negative values in the pool; 40 of 64 channels
     (1, 24, 133, 130, 3, 3, 2, 1, wl.ACT_RELU6, 1, True),        # one plane, 24 of 32 channels
+    (3, 64, 9, 12, 7, 7, 2, 3, wl.ACT_NONE, 3, True),            # a pooled map of 3 x 3, less than a tile
     (2, 8, 33, 35, 5, 6, 2, 0, wl.ACT_GELU, 3, False),           # 5 x 6 in the 7 x 8 form, no padding
     (3, 64, 37, 45, 3, 3, 1, 1, wl.ACT_RELU, 2, False),          # stride 1: pairs of pixels not aligned
     (3, 32, 9, 5, 4, 3, 1, 2, wl.ACT_NONE, 1, False),            # a map smaller than a tile
