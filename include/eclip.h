@@ -284,7 +284,8 @@ eclip_status eclip_wait(eclip_req *req, uint64_t timeout_ns, eclip_timing *opt_o
  * kernel of the group in execution order (host array).  A sample is the HIP-event time of 8
  * back-to-back launches of the kernel on that stream, divided by 8 (an event pair around one
  * microsecond-scale kernel would mostly time the events).  Runs one untimed forward pass on zero
- * input first so every buffer is initialised.  Must not overlap other requests of this model. */
+ * input first so every buffer is initialised.  Must not overlap other requests of this model.  Every layer is launched
+ * by itself, also where a request gives it a launch together with its neighbour. */
 eclip_status eclip_profile_group(eclip_model *model, uint32_t group, uint32_t mask_id, uint32_t batch,
                                  uint32_t iters, uint64_t *ns_per_kernel_out);
 
@@ -294,7 +295,10 @@ eclip_status eclip_profile_group(eclip_model *model, uint32_t group, uint32_t ma
  * and the way its operand is addressed: rows, or a window over whole or ragged runs of channels -- every candidate launch
  * plan is timed on pool entry `mask_id` (minimum over `iters` samples of 6 back-to-back launches) and the fastest is
  * remembered for streams of that CU count -- unless the cost model's own
- * choice is within 5 % of it, in which case that one stays.  Later eclip_submit / eclip_profile_* / kernel_info
+ * choice is within 5 % of it, in which case that one stays.  3 x 3 windows that the image-patch kernel takes are distinct by
+ * the image's height and width and the stride too.  Layers that requests of this batch on this pool entry run on another
+ * kernel are left out: a first layer that reads the caller's planes, and a pointwise layer in one launch with the
+ * depthwise layer before it.  Later eclip_submit / eclip_profile_* / kernel_info
  * calls use the remembered plans; problems or CU counts never tuned keep the cost model's plans.  Results stay
  * within the same tolerances (a different tile only reassociates the fp32 sums).  *n_tuned_out (optional) receives
  * the number of problems timed.  Same preconditions as eclip_profile_group. */
@@ -313,7 +317,8 @@ eclip_status eclip_profile_group_served(eclip_model *model, uint32_t group, uint
 eclip_status eclip_model_group_size(const eclip_model *model, uint32_t group, uint32_t *n_kernels);
 
 /* How layer `layer` would be launched for `batch` samples on pool entry `mask_id`: which kernel and
- * with what shape.  For reporting; nothing is launched. */
+ * with what shape.  A layer by itself, as eclip_profile_group times it: requests may give neighbouring layers one
+ * launch (see eclip_profile_group_served).  For reporting; nothing is launched. */
 typedef struct {
     char kernel[48];        /* kernel function name, e.g. "conv_wsk_kernel" */
     uint32_t launches;      /* kernels launched for this layer (2 when K is split over the grid) */

@@ -1037,10 +1037,10 @@ static void relayout_weights(eclip_model *m, const E *w, std::vector<char> &aren
     }
 }
 
-// GEMM view of a CONV / LINEAR layer
 // pixel pitch (in channels) a reader of layer idx must use, 0 when the tensor is contiguous
 static int pitch_of(const eclip_model *m, int idx) { return idx >= 0 ? m->layers[idx].ld : 0; }
 
+// GEMM view of a CONV / LINEAR layer
 struct GemmShape { int B, H, W, Cin, Ho, Wo, Cout, KH, KW, stride, pad, ldx; };
 static GemmShape gemm_shape(const eclip_model *m, const LayerPlan &P, int batch)
 {
@@ -1084,6 +1084,24 @@ static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, const CuShare 
         if (it != m->tuned.end()) return it->second;
     }
     return conv_gemm_plan(M, N, K, n_cu, m->ws_floats, traits_of(g, cu));
+}
+
+static const void *wptr(const eclip_model *m, size_t off) { return off == NONE ? nullptr : (const void *)(m->d_weights + off); }
+// The first layer runs on the stem kernel.
+static bool stem_takes(const eclip_model *m) { return m->stem_w != NONE && !getenv("ECLIP_GEMM_FORCE") && !getenv("ECLIP_NO_PAIRS"); }
+static StemArgs stem_args(const eclip_model *m, int batch, const void *d_in, void *y, bool pool)
+{
+    const LayerPlan &P = m->layers[0];
+    const GemmShape g = gemm_shape(m, P, batch);
+    return StemArgs{d_in, wptr(m, m->stem_w), wptr(m, P.b_dev), y, batch, m->in_c, g.H, g.W, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, P.L.act, m->dtype, pool};
+}
+// The depthwise layer i and the pointwise layer behind it run as one launch.
+static bool dwpw_takes(const eclip_model *m, uint32_t i, int batch, const CuShare &cu, DwPwPlan *pl)
+{
+    const LayerPlan &D = m->layers[i];
+    if (!D.dwpw_next || getenv("ECLIP_GEMM_FORCE") || getenv("ECLIP_NO_PAIRS")) return false;
+    const LayerPlan &Q = m->layers[i + 1];
+    return dwpw_plan((long)batch * Q.out.h * Q.out.w, D.L.c, Q.L.c, m->dtype, cu.even_cu(), pl);
 }
 
 extern "C" eclip_status eclip_model_load(eclip_pool *pool, const eclip_model_desc *desc, const void *weights,
@@ -1268,7 +1286,10 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
     case ECLIP_OP_LINEAR: {
         const GemmShape g = gemm_shape(model, P, (int)batch);
         out->m = (uint64_t)g.B * g.Ho * g.Wo; out->n = (uint64_t)g.Cout; out->k = (uint64_t)g.KH * g.KW * g.Cin;
-        if (P.gemm) {
+        if (layer == 0 && stem_takes(model)) {
+            name = "stem_kernel";
+            out->workgroups = stem_workgroups(stem_args(model, (int)batch, nullptr, nullptr, false), (int)model->pool->streams[mask_id].n_cu, &out->tile_m, &out->tile_n);
+        } else if (P.gemm) {
             const GemmPlan pl = plan_of(model, g, share_of(model->pool->streams[mask_id]));
             int bm, bn, bk;
             if (pl.kind == 2) {
@@ -1349,7 +1370,6 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
 // ------------------------------------------------------------------------------------------------
 // executor
 // ------------------------------------------------------------------------------------------------
-static const void *wptr(const eclip_model *m, size_t off) { return off == NONE ? nullptr : (const void *)(m->d_weights + off); }
 // where layer P's output lives: its own buffer, or its channel range of the buffer of a concatenation done in place
 static char *out_ptr(const eclip_model *m, const LayerPlan &P)
 {
@@ -1379,7 +1399,9 @@ static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_
     case ECLIP_OP_CONV:
     case ECLIP_OP_LINEAR: {
         const GemmShape g = gemm_shape(m, P, batch);
-        if (P.gemm) {
+        if (i == 0 && stem_takes(m)) {
+            e = launch_stem(stem_args(m, batch, d_in, y, false), n_cu, s);
+        } else if (P.gemm) {
             if (d_out32 && chan_last_out) y32 = d_out32;
             ConvGemmArgs a{src(L.in0), wptr(m, P.w_dev), wptr(m, P.b_dev), src(L.in1), y32 ? nullptr : y, y32, m->ws,
                            g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, L.act, dt};
@@ -1508,7 +1530,7 @@ static hipError_t launch_dwpw_pair(eclip_model *m, uint32_t i, int batch, hipStr
     *done = false;
     const LayerPlan &D = m->layers[i], &Q = m->layers[i + 1];
     DwPwPlan pl;
-    if (getenv("ECLIP_GEMM_FORCE") || getenv("ECLIP_NO_PAIRS") || !dwpw_plan((long)batch * Q.out.h * Q.out.w, D.L.c, Q.L.c, m->dtype, cu.even_cu(), &pl)) return hipSuccess;
+    if (!dwpw_takes(m, i, batch, cu, &pl)) return hipSuccess;
     *done = true;
     *n_launched += 1;
     const DwPwArgs a{out_ptr(m, m->layers[D.L.in0]), wptr(m, D.w_dev), wptr(m, D.b_dev), wptr(m, Q.w_dev), wptr(m, Q.b_dev),
@@ -1527,14 +1549,11 @@ static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, c
     const GemmShape g = gemm_shape(m, P, batch);
     // A launch, a re-layout or the gather of the NCHW form, and (stem_pool) a pool less.  First launches of requests, us, before and with it: ResNet at
     // batch 1 on 128 CUs 16.6, 5.8; at batch 8 on 112 45.9, 15.8; VGG-16 at batch 8 on 256 32.4, 17.3; MobileNetV2 at batch 3 on 192 12.4, 5.0.
-    if (m->stem_w != NONE && !getenv("ECLIP_GEMM_FORCE") && !getenv("ECLIP_NO_PAIRS")) {
-        StemArgs a{d_in, wptr(m, m->stem_w), wptr(m, P.b_dev), nullptr, batch, m->in_c, g.H, g.W, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad,
-                   P.L.act, m->dtype, m->stem_pool};
-        a.y = out_ptr(m, m->layers[a.pool ? 1 : 0]);
+    if (stem_takes(m)) {
         *done = true;
-        *consumed = a.pool ? 2 : 1;
+        *consumed = m->stem_pool ? 2 : 1;
         *n_launched += 1;
-        return launch_stem(a, cu.n_cu, s);
+        return launch_stem(stem_args(m, batch, d_in, out_ptr(m, m->layers[m->stem_pool ? 1 : 0]), m->stem_pool), cu.n_cu, s);
     }
     if (m->dtype == ECLIP_F32) {
         if (getenv("ECLIP_NO_PAIRS")) return hipSuccess;
@@ -1912,7 +1931,9 @@ extern "C" eclip_status eclip_model_tune(eclip_model *model, uint32_t mask_id, u
     const uint32_t REPS = 6;
     for (uint32_t i = 0; i < n_layers && st == ECLIP_OK; ++i) {
         const LayerPlan &P = model->layers[i];
-        if (!P.gemm) continue;
+        DwPwPlan fused;
+        // layers that another kernel takes have no plan that a request would read
+        if (!P.gemm || (i == 0 && stem_takes(model)) || (i > 0 && dwpw_takes(model, i - 1, (int)batch, share_of(ps), &fused))) continue;
         const eclip_layer &L = P.L;
         const GemmShape g = gemm_shape(model, P, (int)batch);
         const long M = (long)g.B * g.Ho * g.Wo, N = g.Cout, K = (long)g.KH * g.KW * g.Cin;

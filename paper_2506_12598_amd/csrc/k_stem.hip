@@ -188,9 +188,29 @@ __global__ __launch_bounds__(256) void stem_kernel(StemDev p)
     }
 }
 
+// window columns with their padding: 4 or 8; 0: too large
+int stem_window(int KH, int KW) { return KH <= 4 && KW <= 4 ? 4 : KH <= 7 && KW <= 8 ? 8 : 0; }
+
 struct Tile { int h, w; };
 // Outputs per workgroup: the small tiles where the large ones would leave compute units without a workgroup.
 constexpr Tile PLAIN[2] = {{8, 16}, {4, 16}}, POOLED[2] = {{4, 8}, {4, 4}};
+
+struct Cut { int Po, Qo; unsigned rows, cols, grid; bool small; Tile tile; };          // outputs, and the tiles they are cut into
+Cut cut_of(const StemArgs &a, int n_cu)
+{
+    Cut c;
+    c.Po = a.pool ? (a.Ho - 1) / 2 + 1 : a.Ho;
+    c.Qo = a.pool ? (a.Wo - 1) / 2 + 1 : a.Wo;
+    for (int k = 0; k < 2; ++k) {
+        c.small = k == 1;
+        c.tile = (a.pool ? POOLED : PLAIN)[k];
+        c.rows = (unsigned)((c.Po + c.tile.h - 1) / c.tile.h);
+        c.cols = (unsigned)((c.Qo + c.tile.w - 1) / c.tile.w);
+        c.grid = c.rows * c.cols * (unsigned)a.B;
+        if (c.grid >= (unsigned)n_cu) break;
+    }
+    return c;
+}
 
 template <typename T, int NBLK, int KWP, int NB, int S, bool SMALL = false>
 hipError_t launch(const StemDev &d, bool pool, bool small, unsigned grid, hipStream_t s)
@@ -215,7 +235,6 @@ hipError_t launch(const StemArgs &a, const StemDev &d, bool small, unsigned grid
 
 }  // namespace
 
-int stem_window(int KH, int KW) { return KH <= 4 && KW <= 4 ? 4 : KH <= 7 && KW <= 8 ? 8 : 0; }
 bool stem_supported(int C, int KH, int KW, int stride, int N)
 {
     const int w = stem_window(KH, KW);
@@ -231,6 +250,14 @@ long stem_weight_source(int KH, int KW, int N, int C, size_t at)
     return (((long)n * C + c) * KH + kh) * KW + kw;
 }
 
+unsigned stem_workgroups(const StemArgs &a, int n_cu, uint32_t *tile_m, uint32_t *tile_n)
+{
+    const Cut c = cut_of(a, n_cu);
+    *tile_m = (uint32_t)(c.tile.h * c.tile.w);
+    *tile_n = a.N > 32 ? 64u : 32u;
+    return c.grid;
+}
+
 hipError_t launch_stem(const StemArgs &a, int n_cu, hipStream_t s)
 {
     StemDev d{};
@@ -238,21 +265,11 @@ hipError_t launch_stem(const StemArgs &a, int n_cu, hipStream_t s)
     d.x_bytes = (unsigned)((size_t)a.B * a.C * a.H * a.W * 2);
     d.bias_bytes = a.bias ? (unsigned)a.N * 2u : 0u;
     d.C = a.C; d.H = a.H; d.W = a.W; d.KH = a.KH; d.KW = a.KW; d.Ho = a.Ho; d.Wo = a.Wo; d.N = a.N; d.pad = a.pad; d.act = a.act;
-    d.Po = a.pool ? (a.Ho - 1) / 2 + 1 : a.Ho;
-    d.Qo = a.pool ? (a.Wo - 1) / 2 + 1 : a.Wo;
-    const Tile *of = a.pool ? POOLED : PLAIN;
-    unsigned rows, cols;
-    auto grid_of = [&](const Tile &t) {
-        rows = (unsigned)((d.Po + t.h - 1) / t.h);
-        cols = (unsigned)((d.Qo + t.w - 1) / t.w);
-        return rows * cols * (unsigned)a.B;
-    };
-    unsigned grid = grid_of(of[0]);
-    const bool small = grid < (unsigned)n_cu;
-    if (small) grid = grid_of(of[1]);
-    d.tiles = magic_of(rows * cols); d.cols = magic_of(cols); d.chunks = magic_of((unsigned)a.N / 8);
-    if (a.dtype == DT_BF16) return launch<bf16_t>(a, d, small, grid, s);
-    if (a.dtype == DT_F16) return launch<f16_t>(a, d, small, grid, s);
+    const Cut c = cut_of(a, n_cu);
+    d.Po = c.Po; d.Qo = c.Qo;
+    d.tiles = magic_of(c.rows * c.cols); d.cols = magic_of(c.cols); d.chunks = magic_of((unsigned)a.N / 8);
+    if (a.dtype == DT_BF16) return launch<bf16_t>(a, d, c.small, c.grid, s);
+    if (a.dtype == DT_F16) return launch<f16_t>(a, d, c.small, c.grid, s);
     return hipErrorInvalidValue;
 }
 

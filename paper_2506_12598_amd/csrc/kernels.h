@@ -106,10 +106,10 @@ struct StemArgs {
     int B, C, H, W, Ho, Wo, N, KH, KW, stride, pad, act, dtype;
     bool pool;           // followed by a 3 x 3 max-pool of stride 2 and padding 1
 };
-int stem_window(int KH, int KW);             // window columns with their padding: 4 or 8; 0: too large
 bool stem_supported(int C, int KH, int KW, int stride, int N);
 size_t stem_weight_elems(int KH, int KW, int N);
 long stem_weight_source(int KH, int KW, int N, int C, size_t at);       // index into [N][C][KH][KW]
+unsigned stem_workgroups(const StemArgs &a, int n_cu, uint32_t *tile_m, uint32_t *tile_n);       // and a workgroup's outputs x channels
 hipError_t launch_stem(const StemArgs &a, int n_cu, hipStream_t s);
 
 // ---- float32 direct convolution / linear (plain FMA) -------------------------------------------

@@ -7,6 +7,7 @@ import pytest
 
 import paper_2506_12598_amd as ec
 import workloads as wl
+import workloads.graphs as graphs
 from gpu_util import shared_pool
 
 pytestmark = pytest.mark.gpu
@@ -42,3 +43,49 @@ def test_depthwise_workgroups():
     rows = {24: 9, 18: 12, 12: 17, 9: 23}
     assert i["kernel"] == "dwconv3_strip_kernel"
     assert i["workgroups"] in {(-(-2 * r * 101 * 8 // 256) + 7) // 8 * 8 for r in rows.values()}
+
+
+def _layers_behind_an_image():
+    b = graphs._Builder("first", wl.DT_BF16, 3, graphs.IN_IMAGE, 3, 64, 64)
+    x = b.conv(-1, 64, 7, 2, 3, act=wl.ACT_RELU)
+    b.eltwise(b.maxpool(x, 3, 2, 1))
+    return b.finish()
+
+
+def _depthwise_and_pointwise():
+    b = graphs._Builder("dwpw", wl.DT_BF16, 4, graphs.IN_IMAGE, 8, 20, 20)
+    x = b.conv(-1, 64, 1)
+    b.eltwise(b.conv(b.conv(x, 64, 3, 1, 1, groups=64), 32, 1))
+    return b.finish()
+
+
+@pytest.mark.parametrize("plain", [False, True])
+def test_a_first_layer_on_the_callers_planes_is_reported_timed_and_left_out_of_tuning(plain):
+    m = _layers_behind_an_image()
+    if plain:
+        os.environ["ECLIP_NO_PAIRS"] = "1"
+    h = ec.Model(shared_pool(), m, wl.to_storage(m.weights, m.dtype), max_batch=2)
+    try:
+        i = h.kernel_info(0, 5, 2)
+        if plain:
+            assert i["kernel"] != "stem_kernel"
+        else:
+            # 32 x 32 outputs in tiles of 4 x 16, since 16 of 8 x 16 would leave CUs without one
+            assert (i["kernel"], i["workgroups"], i["threads"], i["tile"], i["mnk"]) == ("stem_kernel", 32, 256, (64, 64), (2048, 64, 147 // 3 * 8))
+        assert len(h.profile_group(0, 5, 2, iters=3)) == 3
+        assert h.tune(5, batch=2, iters=1) == (1 if plain else 0)
+    finally:
+        h.free()
+        os.environ.pop("ECLIP_NO_PAIRS", None)
+
+
+@pytest.mark.parametrize("plan,tuned", [("2,2", 1), ("0,0", 2)])
+def test_a_pointwise_layer_in_one_launch_with_the_depthwise_is_left_out_of_tuning(plan, tuned):
+    m = _depthwise_and_pointwise()
+    os.environ["ECLIP_DWPW"] = plan
+    h = ec.Model(shared_pool(), m, wl.to_storage(m.weights, m.dtype), max_batch=1)
+    try:
+        assert h.tune(0, batch=1, iters=1) == tuned and h.tune(0, batch=1, iters=1) == 0
+    finally:
+        h.free()
+        os.environ.pop("ECLIP_DWPW", None)
