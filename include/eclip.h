@@ -323,8 +323,8 @@ typedef struct {
     char kernel[48];        /* kernel function name, e.g. "conv_wsk_kernel" */
     uint32_t launches;      /* kernels launched for this layer (2 when K is split over the grid) */
     uint32_t workgroups;    /* workgroups of the main kernel that are given work (a stream whose shader engines hold
-                             * different numbers of CUs launches more, which end at once); CONV, LINEAR, LAYERNORM and
-                             * SOFTMAX layers, else 0 */
+                             * different numbers of CUs launches more, which end at once); CONV, LINEAR, LAYERNORM,
+                             * SOFTMAX and ATTENTION layers, else 0 */
     uint32_t threads;       /* threads per workgroup of the main kernel (same layers) */
     uint32_t tile_m, tile_n;/* output tile of a matrix-core kernel, else 0 */
     uint32_t k_splits;      /* grid-level K slices (matrix-core LDS-tiled kernel), else 1 */

@@ -1350,7 +1350,10 @@ extern "C" eclip_status eclip_model_kernel_info(const eclip_model *model, uint32
         out->workgroups = (uint32_t)((rows + per_wg - 1) / per_wg);
         break;
     }
-    case ECLIP_OP_ATTENTION: name = (P.in.w + 31) / 32 * 32 > 256 ? "attention_chunk_kernel" : "attention_kernel"; break;   // see launch_attention
+    case ECLIP_OP_ATTENTION:
+        name = (P.in.w + 31) / 32 * 32 > 256 ? "attention_chunk_kernel" : "attention_kernel";   // see launch_attention
+        out->workgroups = attention_workgroups((int)batch, P.in.w, P.L.heads, (int)model->pool->streams[mask_id].n_cu, &out->threads);
+        break;
     case ECLIP_OP_EMBED: name = "embed_kernel"; break;
     case ECLIP_OP_ELTWISE: name = "eltwise_kernel"; break;
     case ECLIP_OP_CONCAT:

@@ -658,10 +658,20 @@ hipError_t attention_init()
 // 8.  Beyond, a workgroup of 64 queries that stages the values once does the same work in fewer instructions.  us, 12 heads, shared keys against 64
 // queries: 128 keys, batch 1 on 256 CUs (0.4 workgroups per CU) 4.0, 5.5 (one wavefront for 16 queries: 5.5); batch 4 on 128 CUs (3.0) 6.0, 6.7; on
 // 112 (3.4) 7.0, 6.7; 256 keys, batch 2 on 256 (1.5) 7.1, 9.0; batch 4 on 256 (3.0) 9.4, 9.1; 201 keys, batch 4 on 256 (2.4) 8.6, 8.3.
-bool attention_splits_keys(int B, int S, int heads, int n_cu)
+static bool attention_splits_keys(int B, int S, int heads, int n_cu)
 {
     const int Sp = round_up(S, 32);
     return Sp <= 256 && (long)B * heads * ((S + 15) / 16) <= (long)n_cu * (Sp <= 128 ? 3 : 2);
+}
+// More than 256 keys (staged in LDS chunk by chunk): 128 queries per workgroup when that still gives every other CU a workgroup, else 64.
+static bool attention_is_wide(int B, int S, int heads, int n_cu) { return round_up(S, 32) > 256 && 2L * B * heads * ((S + 127) / 128) >= n_cu; }
+
+unsigned attention_workgroups(int B, int S, int heads, int n_cu, uint32_t *threads)
+{
+    const bool split = attention_splits_keys(B, S, heads, n_cu), wide = attention_is_wide(B, S, heads, n_cu);
+    const int queries = split ? 16 : wide ? 128 : 64;
+    *threads = split ? (round_up(S, 32) <= 128 ? 256u : 512u) : (uint32_t)queries * 4u;
+    return (unsigned)(B * heads * ((S + queries - 1) / queries));
 }
 
 hipError_t launch_attention(const AttnArgs &a, const CuShare &cu, hipStream_t s)
@@ -677,11 +687,8 @@ hipError_t launch_attention(const AttnArgs &a, const CuShare &cu, hipStream_t s)
     const int D = a.Hd / a.heads;
     d.scale = 1.0f / sqrtf((float)D);
     const size_t lds = attention_lds_bytes(a.S, D);
-    // more than 256 keys (keys staged in LDS chunk by chunk): 128 queries per workgroup when that still gives every
-    // other CU a workgroup, else 64
-    const bool longseq = d.Sp > 256;
-    const bool wide = longseq && 2L * a.B * a.heads * ((a.S + 127) / 128) >= n_cu;
-    if (longseq) {
+    if (d.Sp > 256) {
+        const bool wide = attention_is_wide(a.B, a.S, a.heads, n_cu);
         d.ck = round_up(d.Sp / 2, 32);
         d.nchunks = (d.Sp + d.ck - 1) / d.ck;
         d.ldv = ldv_of(d.ck);

@@ -219,7 +219,7 @@ struct AttnArgs {
     int B, S, Hd, heads, dtype;
 };
 size_t attention_lds_bytes(int S, int d);
-bool attention_splits_keys(int B, int S, int heads, int n_cu);               // the form of attention_kernel whose wavefronts share the keys
+unsigned attention_workgroups(int B, int S, int heads, int n_cu, uint32_t *threads);
 hipError_t launch_attention(const AttnArgs &a, const CuShare &cu, hipStream_t s);
 hipError_t attention_init();   // raises the dynamic LDS limit once per process
 
