@@ -30,10 +30,17 @@
  * Environment variables (read by the library; for tuning and tests, never needed in service)
  *   ECLIP_GEMM_FORCE="kind,variant,n"  every matrix-core layer takes this plan instead of the planner's or the tuned
  *                         one: kind 0 = LDS-tiled kernel (variant = tile id, n = K slices), kind 1 = wave-split-K
- *                         kernel (variant = tile id, n = 4, 8 or 16 wavefronts); a tile id that does not exist
- *                         leaves the choice to the planner; also turns launch sharing off
- *   ECLIP_NO_PAIRS=1      independent layers never share a launch (pairs of convolutions, pool + classifier, first
- *                         convolution reading the caller's tensor)
+ *                         kernel (variant = tile id, n = 4, 8 or 16 wavefronts), kind 2 = image-patch kernel of 3 x 3
+ *                         windows (variant = tile id, n = 2, 4, 8 or 16 wavefronts); a tile id that does not exist, or
+ *                         a kernel that does not take the layer, leaves the choice to the planner; also turns launch
+ *                         sharing off, except that of pool and classifier
+ *   ECLIP_NO_PAIRS=1      layers never share a launch (pairs of convolutions, pool + classifier, depthwise + pointwise,
+ *                         first convolution reading the caller's tensor with the max-pool behind it)
+ *   ECLIP_DWPW="n,w"      depthwise + pointwise: one launch with columns of 16 n output channels (n = 1, 2 or 4) and w
+ *                         wavefronts sharing K (1, 2, 4 or 8) instead of the planner's choice; "0,0": two launches
+ *   ECLIP_GCONV3=n        grouped 3 x 3 convolutions on groups of 32 inputs: n blocks of 4 x 4 pixels per wavefront (1, 2
+ *                         or 4) instead of the planner's choice; 0: the wave-split-K kernel.  Other values of either leave the
+ *                         choice to the planner
  *   ECLIP_GCONV_DIRECT=1  read at eclip_model_load: grouped convolutions take the direct kernel, not the matrix cores
  *   ECLIP_CONCAT_COPY=1   read at eclip_model_load: every CONCAT layer copies its operands (no concatenation in place)
  *   ECLIP_SHUFFLE_KERNEL=1  read at eclip_model_load: every SHUFFLE layer runs its kernel (no folding into weights)

@@ -462,7 +462,10 @@ int gconv3_blocks(const GConvArgs &a, int S, int n_cu)
 {
     const int SI = S * (a.Cin / a.groups), SO = S * (a.Cout / a.groups), tn = SO % 32 ? 1 : 2, cols = SO / (16 * tn);
     if (SI != 32 || SO % 16 || (cols & (cols - 1)) || !conv3_takes(a.KH, a.KW, a.stride, a.pad, a.H, a.W, a.Cin, a.Cout, a.Cin)) return 0;
-    if (const char *f = getenv("ECLIP_GCONV3")) return atoi(f);       // blocks; 0: the wave-split-K kernel
+    if (const char *f = getenv("ECLIP_GCONV3")) {                    // blocks; 0: the wave-split-K kernel; no such number: the choice below
+        int blocks = -1;
+        if (sscanf(f, "%d", &blocks) == 1 && (blocks == 0 || blocks == 1 || blocks == 2 || blocks == 4)) return blocks;
+    }
     const double per_cu = (double)gconv3_workgroups(a, S, 1) / n_cu;
     return per_cu <= 1.75 ? 1 : per_cu <= 5.0 ? 2 : 4;
 }

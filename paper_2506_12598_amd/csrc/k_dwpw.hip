@@ -214,11 +214,15 @@ bool dwpw_plan(long M, int C, int N, int dtype, int n_cu, DwPwPlan *out)
             }
         }
     }
-    if (const char *f = getenv("ECLIP_DWPW")) {              // "channels / 16, wavefronts sharing K"; "0,0": apart
+    if (const char *f = getenv("ECLIP_DWPW")) {              // "channels / 16, wavefronts sharing K"; "0,0": apart; no such shape: the choice above
         int tn = 0, wk = 0;
-        if (sscanf(f, "%d,%d", &tn, &wk) != 2 || tn == 0) return false;
-        *out = DwPwPlan{tn, wk, wk >= 4 ? 1 : 4 / wk};
-        return true;
+        if (sscanf(f, "%d,%d", &tn, &wk) == 2) {
+            if (tn == 0) return false;
+            if ((tn == 1 || tn == 2 || tn == 4) && (wk == 1 || wk == 2 || wk == 4 || wk == 8)) {
+                *out = DwPwPlan{tn, wk, wk >= 4 ? 1 : 4 / wk};
+                return true;
+            }
+        }
     }
     const double apart = 7.06 + ((double)M * C * 4.47e-4 + (double)M * N * 1.37e-4 + (double)N * C * 1.26e-4) / n_cu + C * 5.1e-4;
     // The two prices meet 0.25 us apart: timed as served, 500 problems whose prices differ by less than 0.75 us, one launch against two, mean us: where
