@@ -131,7 +131,9 @@ __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const
     const int r16 = lane & 15, q = lane >> 4, pix0 = (r16 >> 2) * SD * PW + (r16 & 3) * SD;
     const char *const base = reinterpret_cast<const char *>(smem) + wave * region;
     auto at = [&](int k) { return pix0 * 64 + ((q ^ ((((pix0 + (k & 3)) >> 2) + (k >> 2)) & 3)) << 4); };
-    // The patch has arrived when no more than what was fetched behind it is on its way (accesses return in order).
+    // The patch has arrived when no more than what was fetched behind it is on its way (accesses return in order): six taps' weights, bias and
+    // residual.  That count has to be what the compiler issues: a fetch that it merged with another or dropped would let this wait end early.
+    // None can be: the addresses differ, or their conditions do.  (tests/test_counted_waits.py counts them in the compiled kernels.)
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"((9 - EARLY) * TN + 2 * SLOTS) : "memory");
     __builtin_amdgcn_sched_barrier(0);
     auto taps = [&](int s, bool more) {
@@ -264,7 +266,7 @@ __global__ __launch_bounds__(256) void gconv_mfma_kernel(const uint16_t *x, cons
     const int pix0 = (r16 >> 2) * SD * PW + (r16 & 3) * SD;
     const char *const base = smem + wave * (COPIES * 1024);
     auto at = [&](int k) { return pix0 * 64 + ((q ^ ((((pix0 + (k & 3)) >> 2) + (k >> 2)) & 3)) << 4); };
-    // as in conv3_kernel: the patch has arrived when no more than what was fetched behind it is on its way
+    // as in conv3_kernel: the patch has arrived when no more than what was fetched behind it is on its way, which has to be what the compiler issues
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"((9 - EARLY) * TN + TN + TM * TN) : "memory");
     __builtin_amdgcn_sched_barrier(0);
     static_for<9>([&](auto tc) {
