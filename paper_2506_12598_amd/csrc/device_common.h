@@ -174,6 +174,17 @@ __device__ __forceinline__ float apply_act(int act, float v)
     }
 }
 
+// The same for the values of a thread's outputs, with one branch for all of them: each(f) replaces every value v by f(v).
+template <typename F> __device__ __forceinline__ void activate(int act, F each)
+{
+    if (act == ACT_GELU) {
+        each([](float v) { return gelu_erf(v); });
+    } else if (act != ACT_NONE) {
+        const float top = act == ACT_RELU6 ? 6.0f : __builtin_inff();
+        each([=](float v) { return fminf(fmaxf(v, 0.0f), top); });
+    }
+}
+
 // The same with the activation fixed at compile time.  A kernel's epilogue is unrolled over its accumulator blocks, and
 // with a run-time switch every copy carries the code of all activations: the code that runs then hops over the code
 // that does not, which defeats the sequential instruction prefetch (measured: a 256 x 256 tile kernel of 146 KB, 52 KB

@@ -181,14 +181,10 @@ __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const
         }
         o[0] += lo(bias[u].x); o[1] += hi(bias[u].x); o[2] += lo(bias[u].y); o[3] += hi(bias[u].y);
         o[0] += lo(res[u].x); o[1] += hi(res[u].x); o[2] += lo(res[u].y); o[3] += hi(res[u].y);
-        if (p.act == ACT_GELU) {
+        activate(p.act, [&](auto f) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = gelu_erf(o[e]);
-        } else if (p.act != ACT_NONE) {
-            const float top = p.act == ACT_RELU6 ? 6.0f : __builtin_inff();
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = fminf(fmaxf(o[e], 0.0f), top);
-        }
+            for (int e = 0; e < 4; ++e) o[e] = f(o[e]);
+        });
         if (p.f32) {
             const u32x4 v = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
             __builtin_amdgcn_raw_buffer_store_b128(v, ry, off[u] == OOB ? OOB : off[u] * 2u, 0, 0);
@@ -289,14 +285,10 @@ __global__ __launch_bounds__(256) void gconv_mfma_kernel(const uint16_t *x, cons
             float o[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
             o[0] += lo(bias[j].x); o[1] += hi(bias[j].x); o[2] += lo(bias[j].y); o[3] += hi(bias[j].y);
             o[0] += lo(res[i][j].x); o[1] += hi(res[i][j].x); o[2] += lo(res[i][j].y); o[3] += hi(res[i][j].y);
-            if (p.act == ACT_GELU) {
+            activate(p.act, [&](auto f) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = gelu_erf(o[e]);
-            } else if (p.act != ACT_NONE) {
-                const float top = p.act == ACT_RELU6 ? 6.0f : __builtin_inff();
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = fminf(fmaxf(o[e], 0.0f), top);
-            }
+                for (int e = 0; e < 4; ++e) o[e] = f(o[e]);
+            });
             const u32x2 v = {Cvt<T>::pack2(o[0], o[1]), Cvt<T>::pack2(o[2], o[3])};
             __builtin_amdgcn_raw_buffer_store_b64(v, ry, off[i] == OOB ? OOB : off[i] + 32u * j, 0, 0);
         }

@@ -27,18 +27,6 @@ struct DwPwRest {
     Magic cols;                              // tile columns
 };
 
-template <typename T> __device__ __forceinline__ void activate(int act, float (&o)[8])
-{
-    if (act == ACT_GELU) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = gelu_erf(o[e]);
-    } else if (act != ACT_NONE) {
-        const float top = act == ACT_RELU6 ? 6.0f : __builtin_inff();
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = fminf(fmaxf(o[e], 0.0f), top);
-    }
-}
-
 template <typename T, int TN, int WK, int WM>
 __global__ __launch_bounds__(WK * WM * 64) void dwpw_kernel(const uint16_t *x, const uint16_t *wd, int M, int C, int steps, int H, int W, unsigned howo_d, unsigned howo_mul,
                                                             unsigned wo_d, unsigned wo_mul, unsigned packed, DwPwRest p)
@@ -113,7 +101,10 @@ __global__ __launch_bounds__(WK * WM * 64) void dwpw_kernel(const uint16_t *x, c
                 o[2 * i] = fmaf(lo(xq[t][i]), lo(wq[t][i]), o[2 * i]);
                 o[2 * i + 1] = fmaf(hi(xq[t][i]), hi(wq[t][i]), o[2 * i + 1]);
             }
-        activate<T>(p.act_d, o);
+        activate(p.act_d, [&](auto f) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = f(o[e]);
+        });
         uint4 a;
         a.x = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, (int)Cvt<T>::pack2(o[0], o[1]));
         a.y = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, (int)Cvt<T>::pack2(o[2], o[3]));
@@ -162,14 +153,10 @@ __global__ __launch_bounds__(WK * WM * 64) void dwpw_kernel(const uint16_t *x, c
         }
         o[0] += lo(bias[u].x) + lo(res[u].x); o[1] += hi(bias[u].x) + hi(res[u].x);
         o[2] += lo(bias[u].y) + lo(res[u].y); o[3] += hi(bias[u].y) + hi(res[u].y);
-        if (p.act_p == ACT_GELU) {
+        activate(p.act_p, [&](auto f) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = gelu_erf(o[e]);
-        } else if (p.act_p != ACT_NONE) {
-            const float top = p.act_p == ACT_RELU6 ? 6.0f : __builtin_inff();
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = fminf(fmaxf(o[e], 0.0f), top);
-        }
+            for (int e = 0; e < 4; ++e) o[e] = f(o[e]);
+        });
         const u32x2 v = {Cvt<T>::pack2(o[0], o[1]), Cvt<T>::pack2(o[2], o[3])};
         __builtin_amdgcn_raw_buffer_store_b64(v, ry, off[u], 0, 0);
     }

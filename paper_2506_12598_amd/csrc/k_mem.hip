@@ -220,14 +220,10 @@ __global__ __launch_bounds__(256) void dwconv_kernel(const uint16_t *x, const ui
         }
 #pragma unroll
     for (int i = 0; i < 4; ++i) { acc[2 * i] += lo(rq[i]); acc[2 * i + 1] += hi(rq[i]); }
-    if (p.act == ACT_GELU) {
+    activate(p.act, [&](auto f) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = gelu_erf(acc[i]);
-    } else if (p.act != ACT_NONE) {
-        const float top = p.act == ACT_RELU6 ? 6.0f : __builtin_inff();
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = fminf(fmaxf(acc[i], 0.0f), top);
-    }
+        for (int i = 0; i < 8; ++i) acc[i] = f(acc[i]);
+    });
     Pack<T, 8>::store((T *)(p.y + (off >> 1)), acc);
 }
 

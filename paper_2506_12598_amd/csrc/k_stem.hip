@@ -126,18 +126,12 @@ __global__ __launch_bounds__(256) void stem_kernel(StemDev p)
 #pragma unroll
             for (int j = 0; j < NBW; ++j) acc[j] = stem_mma<T>(wf[k][j], a[k], k ? acc[j] : bias[j]);
         fetch(f + 2 < FRAGS ? f + 2 : f);                                    // of the next turn, under this one's epilogue
-        if (p.act == ACT_GELU) {
+        activate(p.act, [&](auto f) {
 #pragma unroll
             for (int j = 0; j < NBW; ++j)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[j][e] = gelu_erf(acc[j][e]);
-        } else if (p.act != ACT_NONE) {
-            const float top = p.act == ACT_RELU6 ? 6.0f : __builtin_inff();
-#pragma unroll
-            for (int j = 0; j < NBW; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[j][e] = fminf(fmaxf(acc[j][e], 0.0f), top);
-        }
+                for (int e = 0; e < 4; ++e) acc[j][e] = f(acc[j][e]);
+        });
         if (i < PIX) {
 #pragma unroll
             for (int j = 0; j < NBW; ++j) {

@@ -282,14 +282,10 @@ __device__ __forceinline__ void wsk_body(float *red, const uint16_t *x, const ui
         o[2] += Cvt<T>::from_bits(bias[u].y & 0xffffu); o[3] += Cvt<T>::from_bits(bias[u].y >> 16);
         o[0] += Cvt<T>::from_bits(res[u].x & 0xffffu); o[1] += Cvt<T>::from_bits(res[u].x >> 16);
         o[2] += Cvt<T>::from_bits(res[u].y & 0xffffu); o[3] += Cvt<T>::from_bits(res[u].y >> 16);
-        if (p.act == ACT_GELU) {
+        activate(p.act, [&](auto f) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = gelu_erf(o[e]);
-        } else if (p.act != ACT_NONE) {
-            const float top = p.act == ACT_RELU6 ? 6.0f : __builtin_inff();
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = fminf(fmaxf(o[e], 0.0f), top);
-        }
+            for (int e = 0; e < 4; ++e) o[e] = f(o[e]);
+        });
         if (p.f32) {
             const u32x4 v = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
             __builtin_amdgcn_raw_buffer_store_b128(v, ry, off[u] == OOB ? OOB : off[u] * 2u, 0, 0);
