@@ -23,6 +23,7 @@ Prints ONE JSON line on stdout; progress goes to stderr.
 from __future__ import annotations
 
 import argparse
+import faulthandler
 import glob
 import json
 import os
@@ -1002,6 +1003,12 @@ def main():
     log(f"profiled in {time.perf_counter() - t0:.1f}s; switch cost {switch_cost_ns} ns; co-run slowdown {slowdown:.3f} -> "
         f"overlap slope {slope:.3f}; candidates " + "; ".join(f"{n}: {[_runs([configs[c] for c in w]) for w in a]}" for n, a, _ in cand))
 
+    if cfg == 3:
+        # Once, this mix printed nothing for three minutes here, between its profile and the end of the first candidate's trial, and was ended from
+        # outside; the same steps of the other mixes went through.  Whether the GPU, the runtime or the host waited is not known: reading the
+        # library and this file has not shown a cause.  Until one is shown the mix is profiled but not served.
+        raise SystemExit("the mix of --config 3 is not served: its first trial once did not return, and the cause is not known")
+
     # ---- serving pool: id 0 = shared unmasked stream (policy unpart_a); ids 1..n_w = one private unmasked stream per
     # worker (policy unpart_b); then only the masked streams the allocation uses, created back to back so that they
     # land on distinct pipes
@@ -1032,13 +1039,16 @@ def main():
     sampler = PowerSampler()
     prev_pool = prof_pool
     for name, a, sw in cand:
+        faulthandler.dump_traceback_later(120, exit=True)          # a trial takes about 5 s: one that does not return ends here, with every thread's place
         pool_c, table_c = serving_pool(a)
         for wk, t in zip(workers, table_c):
             wk.h.rebind(pool_c)
             wk.h.alloc_set(t)
+        log(f"trial, {name}: serving pool of {pool_c.n_masks} streams")
         prev_pool.destroy()
         prev_pool = pool_c
         run_closed_for(workers, n_cal, seconds=0.3)
+        log(f"trial, {name}: warm")
         sampler.start()
         time.sleep(0.05)
         t_a = time.perf_counter()
@@ -1046,6 +1056,7 @@ def main():
         torch.cuda.synchronize()
         t_b = time.perf_counter()
         sampler.stop()
+        faulthandler.cancel_dump_traceback_later()
         e = sampler.energy_j(t_a, t_b)
         rate = served / dt
         ipj = None if not e else rate * (t_b - t_a) / e          # the window holds a short lead-in at the same load
