@@ -1551,7 +1551,7 @@ static hipError_t launch_stem_direct(eclip_model *m, int batch, hipStream_t s, c
     const LayerPlan &P = m->layers[0];
     const GemmShape g = gemm_shape(m, P, batch);
     // A launch, a re-layout or the gather of the NCHW form, and (stem_pool) a pool less.  First launches of requests, us, before and with it: ResNet at
-    // batch 1 on 128 CUs 16.6, 5.8; at batch 8 on 112 45.9, 15.8; VGG-16 at batch 8 on 256 32.4, 17.3; MobileNetV2 at batch 3 on 192 12.4, 5.0.
+    // batch 1 on 128 CUs 16.6, 6.4; at batch 8 on 112 45.9, 15.8; VGG-16 at batch 8 on 256 32.4, 17.9; MobileNetV2 at batch 3 on 192 12.4, 5.1.
     if (stem_takes(m)) {
         *done = true;
         *consumed = m->stem_pool ? 2 : 1;
