@@ -8,6 +8,7 @@ thread per model on a pre-allocated pool of CU-masked streams (16..256 CUs in st
 streams.  The CU share of every group comes from the library's exact solver of the paper's allocation model
 (Sec. III-B), fed with latency-vs-CU tables profiled here.  `--config 1|2|3` run the smaller mixes (2 x ResNet-18
 batch 1; ResNet-50 + BERT-base; ResNet-50 + VGG-16 + MobileNetV2 + BERT-base with batch 1-8) through the same code.
+`--config 3` ends before its trials, with an error that says why.
 
 One step = one request on every co-located model.  The timed region is exactly `--steps` steps under the ECLIP
 policy with inputs resident in HBM; `value` is total inferences per second (a request of batch b counts b).
