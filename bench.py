@@ -516,7 +516,7 @@ def plans_mode(shapes, cus):
     import paper_2506_12598_amd as ec
     wsk = [(16, 64), (32, 64), (64, 64), (16, 16), (16, 32), (32, 32)]
     plans = [f"1,{v},{nw}" for v, (bm, bn) in enumerate(wsk) for nw in (4, 8, 16) if nw * bm * bn * 4 <= 131072]
-    plans += [f"0,{v},1" for v in (0, 1, 3, 5, 8, 13, 15, 16, *range(17, 29))]
+    plans += [f"0,{v},1" for v in (0, 1, 3, 5, 8, 13, 15, 16, *range(17, 32))]
     pool = ec.Pool([(ec.eclip_mask_layout(256, 16, 1, 0, c // 16), 0) for c in cus])
     print("M,N,K  CUs: planner's pick, us per layer | best plan (kind,variant,n), us | pick / best")
     ratios = []

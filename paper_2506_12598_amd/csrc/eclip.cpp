@@ -1041,13 +1041,13 @@ static void relayout_weights(eclip_model *m, const E *w, std::vector<char> &aren
 static int pitch_of(const eclip_model *m, int idx) { return idx >= 0 ? m->layers[idx].ld : 0; }
 
 // GEMM view of a CONV / LINEAR layer
-struct GemmShape { int B, H, W, Cin, Ho, Wo, Cout, KH, KW, stride, pad, ldx; };
+struct GemmShape { int B, H, W, Cin, Ho, Wo, Cout, KH, KW, stride, pad, ldx, act; };
 static GemmShape gemm_shape(const eclip_model *m, const LayerPlan &P, int batch)
 {
     const eclip_layer &L = P.L;
     GemmShape g;
     g.ldx = pitch_of(m, L.in0);
-    g.B = batch; g.Cin = P.in.c; g.Cout = L.c;
+    g.B = batch; g.Cin = P.in.c; g.Cout = L.c; g.act = L.act;
     if (P.flat) {
         g.Cin = P.in.c * P.in.h * P.in.w;
         g.H = 1; g.W = 1; g.Ho = 1; g.Wo = 1; g.KH = 1; g.KW = 1; g.stride = 1; g.pad = 0;
@@ -1067,13 +1067,13 @@ static int lean_form_of(const GemmShape &g) { return conv_wsk_lean_form(g.KH, g.
 static bool conv3_of(const GemmShape &g) { return conv3_takes(g.KH, g.KW, g.stride, g.pad, g.H, g.W, g.Cin, g.Cout, g.ldx ? g.ldx : g.Cin); }
 static GemmTraits traits_of(const GemmShape &g, const CuShare &cu)
 {
-    return GemmTraits{lean_form_of(g) >= 0, cu.even_cu(), conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout), conv3_of(g), g.B, g.Ho, g.Wo, g.Cin, g.stride};
+    return GemmTraits{lean_form_of(g) >= 0, cu.even_cu(), conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout), conv3_of(g), g.B, g.Ho, g.Wo, g.Cin, g.stride, g.act == ECLIP_ACT_GELU};
 }
 // Layers of one (M, N, K) can still be different work: which kernels take them in a fast form is part of what a measurement holds for.
 static long form_key(const GemmShape &g)
 {
     const long image = conv3_of(g) ? 16 * (((long)g.H << 12 | g.W) * 2 + g.stride) : 0;       // the patch kernel's tiles follow the image
-    return image + 2 * lean_form_of(g) + (conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout) ? 1 : 0);
+    return image + 2 * lean_form_of(g) + (conv_gemm_is_copied(g.KH, g.KW, g.Cin, g.Cout) ? 1 : 0) + (g.act == ECLIP_ACT_GELU ? 8 : 0);
 }
 static GemmPlan plan_of(const eclip_model *m, const GemmShape &g, const CuShare &cu)
 {

@@ -43,6 +43,7 @@ template <int VM, bool LGKM = true> __device__ __forceinline__ void wait_and_mee
 // Accumulators that leave no room for the rest in the 256 vector registers go to the accumulation registers (one wavefront
 // per SIMD has both files).  The matrix instruction is then written out: left to itself the compiler copies accumulators
 // between registers around every instruction.
+// (They have to fit there: accumulators that the compiler moves between the files next to such an instruction are read before they are written.)
 constexpr bool dma_acc_in_agprs(int bm, int bn, int waves) { return bm * bn / waves > 128 * 64; }
 template <typename T> __device__ __forceinline__ void mma_agpr(uint4 a, uint4 b, f32x4 &c)
 {
@@ -555,7 +556,7 @@ __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 
         return;
     }
     if constexpr (dma_acc_in_agprs(BM, BN, NW)) {
-        static_assert(4 * (TM * 8) * (TN * 16 + 4) * 4 <= ST * STAGE, "half the sub-tiles fit the ring");
+        static_assert(4 * (TM * 8) * (TN * 16 + 4) * 4 <= dma_lds_bytes(BM, BN, BK, ST), "half the sub-tiles fit");
         dma_epilogue_rest<T, BM, BN, WM, WN, TM, TN>(p, acc, smem, m_base, n_base, wm, wn, blockIdx.y);
     } else tile_epilogue<T, BM, BN, WM, WN, TM, TN>(p, acc, smem, m_base, n_base, blockIdx.y);
 }

@@ -622,16 +622,22 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p, SeDe
 
 // Ping-pong tiles (8 wavefronts) and copied tiles (4): X(variant id, BM, BN, BK, stages, K-loop schedule).  Each is compiled in a
 // translation unit of its own (k_gemm_pp.hip with ECLIP_PP_ID set), which exports launch_pp<ID> and init_pp<ID>.
-// Id 3 keeps both operands in LDS; 5..16 fetch the weights straight into registers; 17..28 copy both operands straight into LDS
-// (rs: stages of the ring).  Ids without a tile (2, 4, 6, 7, 9..12, 14) had one that the planner never picked and that measuring
+// Id 3 keeps both operands in LDS; 5..16 fetch the weights straight into registers; 17..31 copy both operands straight into LDS
+// (rs: stages of the ring).  29..31 are the largest of which two workgroups fit a compute unit (256 vector registers, 74 KB of LDS each): one's
+// epilogue and its way to the first operands pass under the other's K loop, where a 256 x 256 tile has nothing beside it.  Served as BERT-large's first
+// feed-forward layer (1536 x 4096 x 1024 with GELU) on 96 CUs: 17 32.9 us, 29 29.0; 1536 x 3072 x 768 with GELU on 128 CUs 23.1 (17), 19.4 (30);
+// a 3 x 3 window of 25088 x 256 x 2304 on 96 CUs 78.4 (18), 72.3 (31).  (192 x 192 tiles, whose accumulators exceed the 128 accumulation registers that
+// two wavefronts per SIMD leave each, gave wrong sums: the compiler moves accumulators between the register files next to matrix instructions
+// that it does not know.)  They exist in the fast address forms only: the general one would spill.  Ids without a tile (2, 4, 6, 7, 9..12, 14) had one that the planner never picked and that measuring
 // every candidate on 900 problems (9 networks, 64 to 256 compute units) found best by more than 1.2 % once, by 3.3 %.
 #define ECLIP_PP_TILES(X)                                                                                                   \
     X(3, 256, 256, 32, 2, LOOP_PINGPONG) X(5, 256, 256, 32, 2, LOOP_PP_BDIRECT) X(8, 192, 128, 64, 2, LOOP_PP_BDIRECT)      \
     X(13, 64, 128, 64, 2, LOOP_PP_BDIRECT) X(15, 96, 64, 64, 2, LOOP_PP_BDIRECT) X(16, 96, 192, 64, 2, LOOP_PP_BDIRECT)     \
-    X(17, 256, 256, 32, 5, LOOP_DMA) X(18, 256, 128, 64, 3, LOOP_DMA) X(19, 128, 256, 64, 3, LOOP_DMA)                      \
+    X(17, 256, 256, 32, 4, LOOP_DMA) X(18, 256, 128, 64, 3, LOOP_DMA) X(19, 128, 256, 64, 3, LOOP_DMA)                      \
     X(20, 128, 128, 64, 4, LOOP_DMA) X(21, 192, 128, 64, 3, LOOP_DMA) X(22, 128, 64, 64, 3, LOOP_DMA)                       \
     X(23, 64, 128, 64, 3, LOOP_DMA) X(24, 256, 192, 32, 5, LOOP_DMA) X(25, 192, 256, 32, 5, LOOP_DMA)                       \
-    X(26, 64, 64, 64, 4, LOOP_DMA) X(27, 128, 64, 32, 3, LOOP_DMA) X(28, 128, 128, 32, 3, LOOP_DMA)
+    X(26, 64, 64, 64, 4, LOOP_DMA) X(27, 128, 64, 32, 3, LOOP_DMA) X(28, 128, 128, 32, 3, LOOP_DMA)                         \
+    X(29, 128, 256, 32, 3, LOOP_DMA) X(30, 128, 192, 32, 3, LOOP_DMA) X(31, 192, 128, 32, 3, LOOP_DMA)
 
 struct PPTile { int id, bm, bn, bk, rs, loop; };
 constexpr PPTile kPPTiles[] = {
@@ -639,6 +645,7 @@ constexpr PPTile kPPTiles[] = {
     ECLIP_PP_TILES(X)
 #undef X
 };
+constexpr bool pp_fast_forms_only(int id) { return id >= 29; }
 constexpr PPTile pp_tile(int id)
 {
     for (const PPTile &t : kPPTiles)
@@ -654,11 +661,11 @@ constexpr size_t lds_bytes(int bm, int bn, int bk, int pad = 8, bool weights_in_
     const size_t stage = pad == 16 ? (size_t)8 * 32 * (bn / 4 + 4) * 4 : 0;
     return ring > stage ? ring : stage;
 }
-// the same for conv_gemm_dma_kernel with 4 wavefronts: its ring of `stages` K steps, or the staged epilogue
+// the same for conv_gemm_dma_kernel with 4 wavefronts: its ring of `stages` K steps, or the staged epilogue (of the largest tiles half the sub-tiles at once)
 constexpr bool dma_touches(int bm, int bn, int bk, int stages) { return (size_t)stages * (bm + bn) * bk * 2 + 256 <= 160 * 1024; }
 constexpr size_t dma_lds_bytes(int bm, int bn, int bk, int stages)
 {
-    const size_t ring = (size_t)stages * (bm + bn) * bk * 2 + (dma_touches(bm, bn, bk, stages) ? 256 : 0), stage = (size_t)4 * 32 * (bn / 2 + 4) * 4;
+    const size_t ring = (size_t)stages * (bm + bn) * bk * 2 + (dma_touches(bm, bn, bk, stages) ? 256 : 0), stage = (size_t)(bm * bn > 128 * 256 ? bm : 128) * (bn / 2 + 4) * 4;
     return ring > stage ? ring : stage;
 }
 

@@ -286,7 +286,7 @@ std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, siz
         }
     for (const PPTile &t : kPPTiles) {
         const int v = t.id, bm = t.bm, bn = t.bn, bk = t.bk;
-        if (bm > 2 * M + 32 || bn > 2 * N + 32) continue;
+        if (bm > 2 * M + 32 || bn > 2 * N + 32 || (pp_fast_forms_only(v) && !traits.copied)) continue;
         const long KT = cdiv(K, bk);
         for (long sp = 1; sp <= 4; sp *= 2) {
             if (sp > 1 && (K < 512 * sp || (size_t)(sp * M * N) > ws_floats)) continue;
@@ -324,7 +324,7 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     }
     if (f_kind == 2 && traits.conv3 && conv3_launchable(f_variant, f_n, traits, (int)N))
         return GemmPlan{2, f_variant, 1, (int)conv3_tiles(f_variant, traits.B, traits.Ho, traits.Wo, (int)N), f_n, 0};
-    if (f_kind == 0 && tile_of_id(f_variant).id >= 0) {
+    if (f_kind == 0 && tile_of_id(f_variant).id >= 0 && (traits.copied || !pp_fast_forms_only(f_variant))) {
         pl.variant = f_variant;
         pl.tiles = (int)tiles(pl.variant);
         int bm, bn, bk;
@@ -371,16 +371,29 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // 89.6 us on 3 and 14.0, 16.5, 21.3, 31.5, 46.7, 82.7 on 17, on 48 CUs 23.1, 28.1, 38.8, 60.2, 92.9, 168.8 and 24.3, 28.7, 38.7, 59.6, 87.5, 157.6;
     // in its general address form K = 264, 1032, 2056: 18.7, 38.6, 62.5 and 19.8, 38.7, 60.7.  With 4092 columns it is the faster one
     // at every K (256: 42.0 and 33.6), which the second row does not say.)
-    struct LdsTile { int variant; double step, fixed, more, two; };
+    // Layers that the copied tiles take in their fast form, of at least 512 rows and with sums of at least 768, have a table of their own, set by what gets
+    // picked: 441 problems (linear layers of 512 to 3072 rows with and without GELU, 3 x 3 convolutions of 1568 to 50176 pixels; 48 to 256 CUs) x 15
+    // tiles in chains with weights of their own.  Its picks take 2.3 % more than the best tile on the geometric mean and 56 % at worst, the other
+    // table's, which has no 29 to 31, 4.1 and 90 % (1536 x 4096 x 1024 with GELU on 96 CUs 32.2 us, now 29.2, on 64 49.0, now 42.1; 2048 x 2304 x 768 on
+    // 64 39.8, now 30.1; a 3 x 3 window of 50176 x 128 x 1152 on 96 49.2, now 45.5).  Shorter sums were not among them: with this table for all, three
+    // co-located CNNs and encoders on 32 to 80 CUs took 2.3 % longer.  Of 29 to 31 a compute unit runs two at a time, in `two` times one's steps, and an odd
+    // one alone.  `gelu`: what GELU adds per 1000 outputs that a compute unit computes.
+    struct LdsTile { int variant; double step, fixed, more, two, gelu; };
     static const LdsTile copied_256 = {17, 0.515, 9.7, 16.75, 0};
-    static const LdsTile lds[] = {
-                                  {0, 0.509, 4.049, 7.322, 1.373}, {3, 0.568, 8.784, 16.049, 0}, {5, 0.595, 8.271, 16.021, 0}, {8, 0.525, 5.267, 9.068, 0},
-                                  {13, 0.312, 2.898, 4.535, 1.656}, {15, 0.278, 3.194, 5.868, 1.418}, {16, 0.483, 4.611, 5.981, 0}, {17, 0.512, 10.9, 16.4, 0},
-                                  {18, 0.552, 6.313, 10.504, 0}, {19, 0.579, 6.094, 8.303, 0}, {20, 0.337, 4.272, 6.499, 0}, {21, 0.444, 5.202, 8.054, 0},
-                                  {22, 0.267, 3.021, 6.171, 1.444}, {23, 0.257, 3.012, 4.226, 1.544}, {24, 0.406, 8.399, 13.526, 0}, {25, 0.409, 8.333, 11.372, 0},
-                                  {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.222, 3.505, 5.135, 1.609}};
-    for (const LdsTile &row : lds) {
-        const LdsTile &c = row.variant == 17 && traits.copied ? copied_256 : row;
+    static const std::vector<LdsTile> any = {
+        {0, 0.509, 4.049, 7.322, 1.373}, {3, 0.568, 8.784, 16.049, 0}, {5, 0.595, 8.271, 16.021, 0}, {8, 0.525, 5.267, 9.068, 0},
+        {13, 0.312, 2.898, 4.535, 1.656}, {15, 0.278, 3.194, 5.868, 1.418}, {16, 0.483, 4.611, 5.981, 0}, {17, 0.512, 10.9, 16.4, 0},
+        {18, 0.552, 6.313, 10.504, 0}, {19, 0.579, 6.094, 8.303, 0}, {20, 0.337, 4.272, 6.499, 0}, {21, 0.444, 5.202, 8.054, 0},
+        {22, 0.267, 3.021, 6.171, 1.444}, {23, 0.257, 3.012, 4.226, 1.544}, {24, 0.406, 8.399, 13.526, 0}, {25, 0.409, 8.333, 11.372, 0},
+        {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.222, 3.505, 5.135, 1.609}};
+    static const std::vector<LdsTile> copied_long = {
+        {13, 0.312, 2.898, 4.535, 1.656}, {15, 0.278, 3.194, 5.868, 1.418}, {16, 0.483, 4.611, 5.981, 0, 0.055}, {17, 0.515, 9.7, 7.009, 0, 0.055},
+        {18, 0.558, 6.215, 5.632, 0, 0.053}, {19, 0.545, 6.852, 5.409, 0, 0.085}, {20, 0.337, 4.272, 4.836, 0, 0.071}, {21, 0.409, 5.709, 6.58, 0, 0.051},
+        {22, 0.267, 3.021, 6.171, 1.444}, {23, 0.257, 3.012, 4.226, 1.544}, {24, 0.372, 8.17, 8.751, 0, 0.048}, {25, 0.35, 9.163, 8.532, 0, 0.084},
+        {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.234, 4.367, 5.066, 1.549, 0.017}, {29, 0.3, 6.339, 4.349, 1.754, 0.045},
+        {30, 0.286, 4.895, 4.854, 1.539, 0.038}, {31, 0.291, 4.786, 5.235, 1.587, 0.024}};
+    for (const LdsTile &row : traits.copied && M >= 512 && K >= 768 ? copied_long : any) {
+        const LdsTile &c = &row == &any[7] && traits.copied ? copied_256 : row;
         if (c.fixed >= best) continue;                                   // planned anew for every launch: what cannot win is not worked out
         int bm, bn, bk;
         conv_gemm_tile(c.variant, &bm, &bn, &bk);
@@ -392,9 +405,12 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
             const int cus = dealt || wgs <= even_cu ? n_cu : even_cu;            // few tiles in many slices: not dealt
             const double load = wgs >= cus ? 1.0 : (double)wgs / cus;
             double rounds = (double)cdiv(wgs, cus);
-            if (c.two > 0.0 && rounds >= 2.0) rounds = c.two * ((double)wgs / cus > 2.0 ? (double)wgs / (2.0 * cus) : 1.0);
+            const double per_cu = rounds;
+            if (pp_fast_forms_only(c.variant)) rounds = (double)(cdiv(wgs, cus) / 2) * c.two + (double)(cdiv(wgs, cus) % 2);
+            else if (c.two > 0.0 && rounds >= 2.0) rounds = c.two * ((double)wgs / cus > 2.0 ? (double)wgs / (2.0 * cus) : 1.0);
             double cost = c.fixed + (rounds - 1.0) * c.more + rounds * (double)cdiv(KT, sp) * c.step * (1.0 + 0.15 * load * load);
             if (dealt && even_cu < n_cu) cost += wgs <= n_cu ? 1.1 : even_cu < 0.8 * n_cu ? 3.0 * (0.8 - (double)even_cu / n_cu) : 0.0;
+            if (traits.gelu && sp == 1) cost += per_cu * c.gelu * 1e-3 * bm * bn;
             if (sp > 1) cost += 15.48 + (double)M * N * (4.0 * sp + 2.0) / 4.243e6;
             if (cost < best) {
                 best = cost;

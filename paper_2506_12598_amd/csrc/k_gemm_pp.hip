@@ -46,7 +46,9 @@ hipError_t launch_mode(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStrea
     switch (gemm_amode(d, kTile.bk, kTile.loop)) {
     case A_MATRIX: return launch_one<T, A_MATRIX>(d, deal, grid, s);
     case A_UNIFORM: return launch_one<T, A_UNIFORM>(d, deal, grid, s);
-    default: return launch_one<T, A_GENERAL>(d, deal, grid, s);
+    default:
+        if constexpr (pp_fast_forms_only(ECLIP_PP_ID)) return hipErrorInvalidValue;          // the planner keeps such layers away (GemmTraits::copied)
+        else return launch_one<T, A_GENERAL>(d, deal, grid, s);
     }
 }
 
@@ -77,8 +79,9 @@ template <> hipError_t launch_pp<ECLIP_PP_ID>(const GemmDev &d, const SeDeal &de
 template <> hipError_t init_pp<ECLIP_PP_ID>()
 {
     hipError_t e;
-    if ((e = init_one<bf16_t, A_GENERAL>()) != hipSuccess || (e = init_one<bf16_t, A_UNIFORM>()) != hipSuccess ||
-        (e = init_one<bf16_t, A_MATRIX>()) != hipSuccess || (e = init_one<f16_t, A_GENERAL>()) != hipSuccess ||
+    if constexpr (!pp_fast_forms_only(ECLIP_PP_ID))
+        if ((e = init_one<bf16_t, A_GENERAL>()) != hipSuccess || (e = init_one<f16_t, A_GENERAL>()) != hipSuccess) return e;
+    if ((e = init_one<bf16_t, A_UNIFORM>()) != hipSuccess || (e = init_one<bf16_t, A_MATRIX>()) != hipSuccess ||
         (e = init_one<f16_t, A_UNIFORM>()) != hipSuccess || (e = init_one<f16_t, A_MATRIX>()) != hipSuccess)
         return e;
     return hipSuccess;

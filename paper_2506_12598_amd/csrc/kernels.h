@@ -44,9 +44,9 @@ struct GemmPlan {
 bool conv_gemm_plan_stem(long M, long N, long K, int n_cu, size_t ws_floats, double stage_us, GemmPlan *out, int even_cu = 0);   // ConvGemmArgs::nchw_c
 // Tile ids of the LDS-tiled kernels.  0, 1: 128x128x32, 64x64x64 (4 wavefronts); 3: 256x256x32 (8 wavefronts on the ping-pong
 // schedule, both operands in LDS); 5, 8, 13, 15, 16: ping-pong with the weights straight from memory: 256x256x32, 192x128x64, 64x128x64,
-// 96x64x64, 96x192x64; 17..28: both operands copied straight into LDS (4 wavefronts): 256x256x32, 256x128x64, 128x256x64, 128x128x64,
+// 96x64x64, 96x192x64; 17..31: both operands copied straight into LDS (4 wavefronts): 256x256x32, 256x128x64, 128x256x64, 128x128x64,
 // 192x128x64, 128x64x64, 64x128x64, 256x192x32, 192x256x32, 64x64x64; 27, 28: 128x64x32, 128x128x32 (small rings: three or four
-// workgroups per CU)
+// workgroups per CU); 29, 30, 31: 128x256x32, 128x192x32, 192x128x32 (two workgroups per CU; layers of GemmTraits::copied only)
 void conv_gemm_tile(int variant, int *bm, int *bn, int *bk);
 const char *conv_gemm_kernel_name(int variant);
 int conv_gemm_threads(int variant);
@@ -67,6 +67,7 @@ struct GemmTraits {
     bool copied = false; // the copied tiles take the layer in a fast address form and with their fast epilogue (conv_gemm_is_copied)
     bool conv3 = false;  // the patch kernel takes the layer (conv3_takes); then its geometry:
     int B = 0, Ho = 0, Wo = 0, Cin = 0, stride = 0;
+    bool gelu = false;   // the layer's activation is GELU: arithmetic that tiles with a compute unit to themselves pay after their K loop
 };
 bool conv_gemm_is_copied(int KH, int KW, int Cin, int Cout);
 // Chooses tile shape and K split for a stream restricted to n_cu compute units.
