@@ -76,12 +76,15 @@ __device__ __forceinline__ uint4 acc_agpr(const f32x4 &a)
     return v;
 }
 
-// Epilogue for outputs of the storage type, or (F32) float ones, with N a multiple of 8 (the rest goes through tile_epilogue).  One wavefront per SIMD
+// Forms of the kernel (conv_gemm_dma_kernel)
+enum { DMA_PLAIN, DMA_F32, DMA_POOL };
+
+// Epilogue for outputs of the storage type, or (DMA_F32) float ones, or (DMA_POOL) their maxima over windows, with N a multiple of 8 (the rest goes through tile_epilogue).  One wavefront per SIMD
 // has nobody to hide behind, so this one is kept short and straight: buffer stores that drop what lies beyond M or N instead
 // of a branch per store, accumulators taken block row by block row.
 // (256 x 192 tile: 5.5 us with
 // the general epilogue, 5.0 with this one.  Passing the accumulators through LDS to a short rolled loop was slower, 7 us.)
-template <typename T, int BM, int BN, int WM, int WN, int TM, int TN, int ACT, bool RES, bool EARLY, bool F32>
+template <typename T, int BM, int BN, int WM, int WN, int TM, int TN, int ACT, bool RES, bool EARLY, int FORM>
 __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][TN], const u32x4 (&bq)[TN / 2], int m_base, int n_base, int wm, int wn)
 {
     static_assert(TN % 2 == 0, "pairs of blocks");
@@ -89,14 +92,16 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
     const int lane = threadIdx.x & 63, q = lane >> 4;
     const int m0 = m_base + wm * (BM / WM) + (lane & 15), n0 = n_base + wn * (BN / WN) + 16 * (q & 1) + 8 * (q >> 1);   // see tile_epilogue_impl
     constexpr unsigned OOB = 0xffffffffu;
-    const unsigned bytes = (unsigned)(((size_t)(p.M - 1) * p.ldy + p.N) * 2);
+    constexpr bool F32 = FORM == DMA_F32;
+    constexpr int WIN = FORM == DMA_POOL ? 4 : 1;                      // rows of the tile per row of y
+    const unsigned bytes = (unsigned)(((size_t)(p.M / WIN - 1) * p.ldy + p.N) * 2);
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(F32 ? (void *)p.y32 : (void *)p.y, 0, (int)(F32 ? 2u * bytes : bytes), 0x00020000);
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void *)(RES ? p.res : p.y), 0, (int)bytes, 0x00020000);
     unsigned off[TN / 2];
     float bv[TN / 2][8];
     static_for<TN / 2>([&](auto jc) {
         constexpr int jp = decltype(jc)::value;
-        off[jp] = n0 + 32 * jp < p.N ? ((unsigned)m0 * (unsigned)p.ldy + (unsigned)(n0 + 32 * jp)) * 2u : OOB;
+        off[jp] = n0 + 32 * jp < p.N ? ((unsigned)(m0 / WIN) * (unsigned)p.ldy + (unsigned)(n0 + 32 * jp)) * 2u : OOB;
 #pragma unroll
         for (int e = 0; e < 8; ++e) bv[jp][e] = 0.f;
         if constexpr (EARLY) {
@@ -104,7 +109,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
             for (int e = 0; e < 4; ++e) { bv[jp][2 * e] = Cvt<T>::from_bits(bq[jp][e] & 0xffffu); bv[jp][2 * e + 1] = Cvt<T>::from_bits(bq[jp][e] >> 16); }
         } else if (p.bias && n0 + 32 * jp < p.N) Pack<T, 8>::load(reinterpret_cast<const T *>(p.bias) + n0 + 32 * jp, bv[jp]);
     });
-    const unsigned row16 = 32u * (unsigned)p.ldy;
+    const unsigned row16 = 32u / WIN * (unsigned)p.ldy;
     u32x4 rq[2][TN / 2];
     auto load_res = [&](auto ic) {
         constexpr int i = decltype(ic)::value;
@@ -141,10 +146,17 @@ __device__ __forceinline__ void dma_epilogue(const GemmDev &p, f32x4 (&acc)[TM][
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = apply_act_c<ACT>(o[e]);
+            if constexpr (FORM == DMA_POOL) {                          // lanes 4 w .. 4 w + 3 hold window w
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    o[e] = fmaxf(o[e], __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(o[e]), 0xb1, 0xf, 0xf, true)));        // quad_perm 1 0 3 2
+                    o[e] = fmaxf(o[e], __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(o[e]), 0x4e, 0xf, 0xf, true)));        // quad_perm 2 3 0 1
+                }
+            }
             // The row's offset goes into the vector offset here, not into the scalar one: with a scalar-register offset the compiler
             // leaves no gap between a 16-byte store and the next write of its data registers, and on this GPU the store then
             // now and then takes the new values (only with several workgroups on the CU).
-            const bool ok = m0 + 16 * i < p.M && n0 + 32 * jp < p.N;
+            const bool ok = m0 + 16 * i < p.M && n0 + 32 * jp < p.N && (WIN == 1 || (lane & 3) == 0);
             u32x4 v;
             if constexpr (F32) {
 #pragma unroll
@@ -246,12 +258,14 @@ template <> struct RingPos<unsigned> {
 // n bits (0 to 32) from bit `at` on
 __device__ __forceinline__ unsigned bits_run(int at, int n) { return (n >= 32 ? ~0u : (1u << n) - 1u) << (at & 31); }
 
-// F32: the form of the tiles whose accumulators fill the accumulation registers for layers that write floats (dma_writes_floats).  It is a kernel of
+// DMA_F32: the form of the tiles whose accumulators fill the accumulation registers for layers that write floats (dma_writes_floats).  It is a kernel of
 // its own: as one more branch its epilogues cost the launches that do not take them 0.5 % of the stress mix, with no instruction more
 // executed but the code further apart.  (Through dma_epilogue_rest, whose short loop waits for its bias on every turn, requests of one layer with
 // float outputs took: 3000 x 4096 x 1024 on 96 CUs 97 us, now 74, on 64 CUs 136, now 98; 1536 x 3000 x 1024 on 96 48, now 39; 1005 x 3072 x 768 on 64
 // 43, now 33.)
-template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE, bool F32 = false>
+// DMA_POOL (A_UNIFORM, ReLU): the rows of the tile are the pixels of 2 x 2 windows, window by window, so that four neighbouring lanes hold a window and its
+// maximum costs two lane exchanges: the pool's launch goes, and three quarters of the stores (GemmDev::pool).
+template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE, int FORM = DMA_PLAIN>
 __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 1024 ? 1 : 2) void conv_gemm_dma_kernel(const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int N, int K, int ldx, int kt_per, unsigned walk, unsigned tiles,
                           unsigned fast_d, unsigned fast_mul, GemmDev p, SeDeal deal)
 {
@@ -305,8 +319,13 @@ __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 
         if (AMODE == A_MATRIX && rows) {
             a_off[i] = (unsigned)mm * (unsigned)p.ldx * 2u;
         } else {
-            const int b = (int)div_by((unsigned)mm, p.howo), r = mm - b * (int)p.howo.d;
-            const int oh = (int)div_by((unsigned)r, p.wo), ow = r - oh * (int)p.wo.d;
+            const int win = FORM == DMA_POOL ? mm >> 2 : mm;
+            const int b = (int)div_by((unsigned)win, p.howo), r = win - b * (int)p.howo.d;
+            int oh = (int)div_by((unsigned)r, p.wo), ow = r - oh * (int)p.wo.d;
+            if constexpr (FORM == DMA_POOL) {
+                oh = 2 * oh + (mm >> 1 & 1);
+                ow = 2 * ow + (mm & 1);
+            }
             a_ih0[i] = oh * p.stride - p.pad;
             a_iw0[i] = ow * p.stride - p.pad;
             a_off[i] = (unsigned)((b * p.H + a_ih0[i]) * p.W + a_iw0[i]) * (unsigned)p.ldx * 2u;
@@ -541,16 +560,20 @@ __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 
     }
     asm volatile("s_nop 15");                                          // the compiler does not see the latency of mma_agpr
     wait_and_meet<0>();
-    if constexpr (F32) {
-#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY, true>(p, acc, bq, m_base, n_base, wm, wn) \
-                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY, true>(p, acc, bq, m_base, n_base, wm, wn)
+    if constexpr (FORM == DMA_POOL) {
+        dma_epilogue<T, BM, BN, WM, WN, TM, TN, ACT_RELU, false, EARLY, DMA_POOL>(p, acc, bq, m_base, n_base, wm, wn);
+        return;
+    }
+    if constexpr (FORM == DMA_F32) {
+#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY, DMA_F32>(p, acc, bq, m_base, n_base, wm, wn) \
+                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY, DMA_F32>(p, acc, bq, m_base, n_base, wm, wn)
         ECLIP_ACT_SWITCH(p.act, EPI)
 #undef EPI
         return;
     }
     if (p.splits == 1 && p.y && (p.N & 7) == 0) {
-#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY, false>(p, acc, bq, m_base, n_base, wm, wn) \
-                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY, false>(p, acc, bq, m_base, n_base, wm, wn)
+#define EPI(A) p.res ? dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, true, EARLY, DMA_PLAIN>(p, acc, bq, m_base, n_base, wm, wn) \
+                     : dma_epilogue<T, BM, BN, WM, WN, TM, TN, A, false, EARLY, DMA_PLAIN>(p, acc, bq, m_base, n_base, wm, wn)
         ECLIP_ACT_SWITCH(p.act, EPI)
 #undef EPI
         return;

@@ -35,6 +35,7 @@ struct Conv3Rest {
     void *y;
     unsigned bias_bytes, res_bytes, y_bytes;
     int ldy, act, Ho, Wo, f32;               // f32: y holds floats
+    int pool;                                // 1: y holds the maxima of 2 x 2 outputs (ConvGemmArgs::pool)
 };
 
 // packed: bits 0-1 GemmPlan::raster, 2-6, 7-11 and 12-16 the shifts of the divisions by inner_d, by the patches of an image and by those of a row of
@@ -117,7 +118,8 @@ __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const
         const int s = u * NW * 64 + tid, c4 = s % C4, r = s / C4, blk = r >> 4;
         const int oy = oy0 + 4 * (blk / TW) + (r >> 2 & 3), ox = ox0 + 4 * (blk % TW) + (r & 3), n = (int)tile_n * TN * 16 + c4 * 4;
         const bool in = sums && blk < TM && oy < p.Ho && ox < p.Wo;
-        off[u] = in ? (unsigned)((((int)b * p.Ho + oy) * p.Wo + ox) * p.ldy + n) * 2u : OOB;
+        const bool out = in && !(p.pool && (r & 5));                   // of a pooled window's four the upper left one is stored
+        off[u] = out ? (unsigned)((((int)b * (p.Ho >> p.pool) + (oy >> p.pool)) * (p.Wo >> p.pool) + (ox >> p.pool)) * p.ldy + n) * 2u : OOB;
         bias[u] = __builtin_amdgcn_raw_buffer_load_b64(rb, in ? n * 2 : OOB, 0, 0);
         res[u] = __builtin_amdgcn_raw_buffer_load_b64(rr, off[u], 0, 0);
     }
@@ -189,6 +191,16 @@ __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const
             const u32x4 v = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
             __builtin_amdgcn_raw_buffer_store_b128(v, ry, off[u] == OOB ? OOB : off[u] * 2u, 0, 0);
         } else {
+            if (p.pool)                          // pixels one to the right and one down lie C4 and 4 C4 lanes on; all lanes of the wavefront are here
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int v = __float_as_int(o[e]);
+                    o[e] = fmaxf(o[e], __int_as_float(TN == 2 ? __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, true)             // row_ror:8
+                                                              : __builtin_amdgcn_ds_swizzle(v, 4 << 10 | 0x1f)));              // lane ^ 4
+                    const unsigned m = __float_as_uint(o[e]);
+                    const u32x2 both = TN == 2 ? __builtin_amdgcn_permlane32_swap(m, m, false, false) : __builtin_amdgcn_permlane16_swap(m, m, false, false);
+                    o[e] = fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1]));
+                }
             const u32x2 v = {Cvt<T>::pack2(o[0], o[1]), Cvt<T>::pack2(o[2], o[3])};
             __builtin_amdgcn_raw_buffer_store_b64(v, ry, off[u], 0, 0);
         }
@@ -439,7 +451,8 @@ hipError_t launch_conv3(const ConvGemmArgs &a, int variant, int nw, hipStream_t 
     p.bias = (const uint16_t *)a.bias; p.res = (const uint16_t *)a.res; p.f32 = a.y32 != nullptr;
     p.y = p.f32 ? (void *)a.y32 : a.y;
     p.bias_bytes = a.bias ? (unsigned)a.Cout * 2u : 0u;
-    const unsigned elems = (unsigned)(a.B * a.Ho * a.Wo - 1) * (unsigned)ldy + (unsigned)a.Cout;
+    p.pool = a.pool;
+    const unsigned elems = (unsigned)((a.B * a.Ho * a.Wo >> 2 * p.pool) - 1) * (unsigned)ldy + (unsigned)a.Cout;
     p.y_bytes = elems * (p.f32 ? 4u : 2u);
     p.res_bytes = a.res ? elems * 2u : 0u;
     p.ldy = ldy; p.act = a.act; p.Ho = a.Ho; p.Wo = a.Wo;

@@ -519,14 +519,26 @@ static GemmDev make_dev(const ConvGemmArgs &a, const GemmPlan &pl)
     d.tiles_m = (d.M + bm - 1) / bm;
     d.tiles_n = (d.N + bn - 1) / bn;
     d.raster = pl.raster;
-    d.howo = magic_of((unsigned)(a.Ho * a.Wo));
-    d.wo = magic_of((unsigned)a.Wo);
+    d.pool = a.pool;
+    d.howo = magic_of((unsigned)(a.Ho * a.Wo >> 2 * d.pool));
+    d.wo = magic_of((unsigned)(a.Wo >> d.pool));
     d.fast = magic_of((unsigned)(pl.raster == 3 ? d.tiles_n : d.tiles_m));
     return d;
 }
 
+// The patch kernel (whole windows lie in its blocks of 4 x 4 pixels) and the copied tiles with K in one piece, whose pooling form is compiled for windows
+// over channels of whole K steps and for ReLU.
+bool conv_gemm_pools(const ConvGemmArgs &a, const GemmPlan &pl)
+{
+    if (a.res || a.y32 || a.nchw_c || a.Ho % 2 || a.Wo % 2 || a.act != ACT_RELU) return false;
+    if (pl.kind == 2) return true;
+    if (pl.kind != 0 || pl.splits != 1 || a.Cout % 8 || a.KH * a.KW == 1 || tile_of_id(pl.variant).loop != LOOP_DMA) return false;
+    return a.Cin % tile_of_id(pl.variant).bk == 0 && a.KH * a.KW <= 32;
+}
+
 hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &pl, const SeDeal &deal, hipStream_t s, uint32_t *n_launched)
 {
+    if (a.pool && !conv_gemm_pools(a, pl)) return hipErrorInvalidValue;
     if ((a.ldx && (a.ldx % 8 || a.ldx < a.Cin || a.nchw_c)) || (a.ldy && (a.ldy % 8 || a.ldy < a.Cout || a.res || a.y32 || ((uintptr_t)a.y & 15))))
         return hipErrorInvalidValue;
     if (n_launched) *n_launched += pl.splits > 1 ? 2 : 1;

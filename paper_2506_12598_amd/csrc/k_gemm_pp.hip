@@ -16,10 +16,10 @@ static_assert(kTile.id == ECLIP_PP_ID, "ECLIP_PP_ID is not in ECLIP_PP_TILES");
 
 constexpr bool kFloatForm = kTile.loop == LOOP_DMA && dma_acc_in_agprs(kTile.bm, kTile.bn, 4);
 
-template <typename T, int AMODE, bool F32>
+template <typename T, int AMODE, int FORM>
 void launch_dma(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream_t s)
 {
-    hipLaunchKernelGGL((conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, F32>), grid, dim3(256),
+    hipLaunchKernelGGL((conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, FORM>), grid, dim3(256),
                        dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs), s, d.x, d.w, d.x_bytes, d.M, d.N, d.K, d.ldx, d.kt_per,
                        dma_walk(d, deal), (unsigned)(d.tiles_m * d.tiles_n), d.fast.d, d.fast.mul, d, deal);
 }
@@ -30,10 +30,16 @@ hipError_t launch_one(const GemmDev &d, const SeDeal &deal, dim3 grid, hipStream
     if constexpr (kTile.loop == LOOP_DMA) {
         if constexpr (kFloatForm)
             if (dma_writes_floats(d)) {
-                launch_dma<T, AMODE, true>(d, deal, grid, s);
+                launch_dma<T, AMODE, DMA_F32>(d, deal, grid, s);
                 return hipGetLastError();
             }
-        launch_dma<T, AMODE, false>(d, deal, grid, s);
+        if constexpr (AMODE == A_UNIFORM)
+            if (d.pool) {
+                launch_dma<T, AMODE, DMA_POOL>(d, deal, grid, s);
+                return hipGetLastError();
+            }
+        if (d.pool) return hipErrorInvalidValue;
+        launch_dma<T, AMODE, DMA_PLAIN>(d, deal, grid, s);
     } else
         hipLaunchKernelGGL((conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>), grid, dim3(512),
                        lds_bytes(kTile.bm, kTile.bn, kTile.bk, 16, kTile.loop != LOOP_PP_BDIRECT), s, d, deal);
@@ -58,11 +64,16 @@ hipError_t init_one()
     if constexpr (kTile.loop == LOOP_DMA) {
         const int lds = (int)dma_lds_bytes(kTile.bm, kTile.bn, kTile.bk, kTile.rs);
         if constexpr (kFloatForm) {
-            const hipError_t e = hipFuncSetAttribute((const void *)conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, true>,
+            const hipError_t e = hipFuncSetAttribute((const void *)conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, DMA_F32>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return e;
         }
-        return hipFuncSetAttribute((const void *)conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, false>,
+        if constexpr (AMODE == A_UNIFORM) {
+            const hipError_t e = hipFuncSetAttribute((const void *)conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, DMA_POOL>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+        }
+        return hipFuncSetAttribute((const void *)conv_gemm_dma_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 2, kTile.rs, AMODE, DMA_PLAIN>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     } else
         return hipFuncSetAttribute((const void *)conv_gemm_kernel<T, kTile.bm, kTile.bn, kTile.bk, 2, 4, kTile.rs, kTile.loop, AMODE>,

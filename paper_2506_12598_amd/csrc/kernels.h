@@ -30,6 +30,8 @@ struct ConvGemmArgs {
     int ldx = 0;         // > 0: elements between consecutive pixels of x (x is the first Cin channels of a wider tensor); a multiple of 8
     int ldy = 0;         // > 0: elements between consecutive rows of y (y points at a channel range of a wider tensor); a multiple of 8,
                          // y 16-byte aligned, res and y32 null
+    bool pool = false;   // y is [B][Ho / 2][Wo / 2][Cout], the maxima of 2 x 2 outputs at stride 2 (conv_gemm_pools); Ho and Wo are even: a last row or
+                         // column that no window takes is not computed
 };
 struct GemmPlan {
     int kind;      // 0 = LDS-tiled kernel (large problems), 1 = wave-split-K kernel (few tiles, long K), 2 = 3 x 3 windows from a patch in LDS
@@ -78,6 +80,7 @@ double conv_wsk_cost_estimate(long M, long N, long K, int n_cu, int variant, int
 // the wave-split-K shape of the lowest estimate whose tile columns divide `columns` channels (0: any); n_cu: CuShare::even_cu
 GemmPlan conv_wsk_plan_columns(long M, long N, long K, int n_cu, int columns);
 // *n_launched (optional) is increased by the number of kernels launched (2 when K is split).
+bool conv_gemm_pools(const ConvGemmArgs &a, const GemmPlan &p);      // a plan's kernel can take the max-pool behind a layer along
 hipError_t launch_conv_gemm(const ConvGemmArgs &a, const GemmPlan &p, const SeDeal &deal, hipStream_t s, uint32_t *n_launched);
 // Two layers that do not depend on each other in one launch (wave-split-K kernel only).  conv_gemm_plan_pair takes
 // the layers' own plans and returns true, with a common plan for each, when sharing a launch is modelled to pay.
