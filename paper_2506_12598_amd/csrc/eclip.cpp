@@ -200,6 +200,7 @@ extern "C" eclip_status eclip_pool_create(int device, const eclip_mask *masks, u
     HIP_TRY(conv_gemm_init());
     HIP_TRY(conv_wsk_init());
     HIP_TRY(conv3_init());
+    HIP_TRY(expdw_init());
     TRACE("kernel attributes set");
     eclip_pool *p = new (std::nothrow) eclip_pool;
     if (!p) return fail(ECLIP_ENOMEM, "out of host memory");
@@ -461,6 +462,7 @@ struct LayerPlan {
     int perm_groups = 0;       // > 0: this layer's input arrives NOT shuffled; its weights are laid out for that order
     bool pair_next = false;    // this layer and the next are independent GEMM layers of one group: one launch may carry both
     bool dwpw_next = false;    // depthwise 3 x 3 whose only reader is the pointwise layer that follows: one launch may do both
+    bool expdw_next = false;   // pointwise expansion whose only reader is the depthwise layer of a pair (dwpw_next) behind it: one launch may do all three
     bool pool_next = false;    // convolution with ReLU whose only reader is the 2 x 2 max-pool that follows: one launch may do both
     bool gapfc_next = false;   // global average pool whose only reader is the linear layer that follows: one launch may do both
 };
@@ -905,6 +907,17 @@ static eclip_status plan_model(const eclip_model_desc *d, size_t weight_elems, e
         bool other_reader = d->group_of_layer[i] != d->group_of_layer[i + 1];
         for (uint32_t j = i + 2; j < d->n_layers; ++j) other_reader |= m->layers[j].L.in0 == (int)i || m->layers[j].L.in1 == (int)i;
         D.dwpw_next = !other_reader;
+    }
+    for (uint32_t i = 1; m->dtype != ECLIP_F32 && i + 3 < d->n_layers; ++i) {
+        LayerPlan &P = m->layers[i];
+        const LayerPlan &D = m->layers[i + 1];
+        if (!D.dwpw_next || D.L.in0 != (int)i || D.L.pad != 1 || D.perm_groups || P.L.op != ECLIP_OP_CONV || !P.gemm || P.ld || P.perm_groups) continue;
+        if (P.L.kh != 1 || P.L.kw != 1 || P.L.stride != 1 || P.L.pad != 0 || P.L.in0 < 0 || P.L.in1 != -2 || m->layers[P.L.in0].ld) continue;
+        // the kernel's offsets are bytes in 32 bits
+        if (((size_t)P.in.c * P.in.h * P.in.w + (size_t)m->layers[i + 2].out.c * m->layers[i + 2].out.h * m->layers[i + 2].out.w) * d->max_batch >= ((size_t)1 << 30)) continue;
+        bool other_reader = d->group_of_layer[i] != d->group_of_layer[i + 1];
+        for (uint32_t j = i + 2; j < d->n_layers; ++j) other_reader |= m->layers[j].L.in0 == (int)i || m->layers[j].L.in1 == (int)i;
+        P.expdw_next = !other_reader;
     }
     return ECLIP_OK;
 }
@@ -1553,6 +1566,22 @@ static hipError_t launch_dwpw_pair(eclip_model *m, uint32_t i, int batch, hipStr
     return launch_dwpw(a, pl, s);
 }
 
+// Launches the pointwise expansion i, the depthwise layer i + 1 and the pointwise layer i + 2 (expdw_next) as one kernel when that pays.
+static hipError_t launch_expdw_triple(eclip_model *m, uint32_t i, int batch, hipStream_t s, const CuShare &cu, uint32_t *n_launched, bool *done)
+{
+    *done = false;
+    const LayerPlan &P = m->layers[i], &D = m->layers[i + 1], &Q = m->layers[i + 2];
+    if (getenv("ECLIP_GEMM_FORCE") || getenv("ECLIP_NO_PAIRS") || getenv("ECLIP_DWPW")) return hipSuccess;
+    ExpDwPlan pl;
+    if (!expdw_plan(batch, Q.out.h, Q.out.w, P.in.c, P.L.c, Q.L.c, D.L.stride, cu.even_cu(), &pl)) return hipSuccess;
+    *done = true;
+    *n_launched += 1;
+    const ExpDwArgs a{out_ptr(m, m->layers[P.L.in0]), wptr(m, P.w_dev), wptr(m, P.b_dev), wptr(m, D.w_dev), wptr(m, D.b_dev), wptr(m, Q.w_dev), wptr(m, Q.b_dev),
+                      Q.L.in1 >= 0 ? (const void *)out_ptr(m, m->layers[Q.L.in1]) : nullptr, out_ptr(m, Q), batch, P.in.h, P.in.w, P.in.c, P.L.c, Q.out.h, Q.out.w,
+                      Q.L.c, D.L.stride, P.L.act, D.L.act, Q.L.act, m->dtype};
+    return launch_expdw(a, pl, s);
+}
+
 // Launches the convolution i and the 2 x 2 max-pool i + 1 (pool_next) as one kernel when the convolution's can take the pool along: always the faster way, since
 // a launch and three quarters of the stores go.  us for both, apart and now, on 256 CUs at batch 8: 224 x 224 x 64 56.1, 46.2; 112 x 112 x 128 45.1, 34.6;
 // 56 x 56 x 256 37.8, 31.3; 28 x 28 x 512 37.1, 32; 14 x 14 x 512 19.0, 16.
@@ -1633,6 +1662,11 @@ static hipError_t launch_unit(eclip_model *m, uint32_t i, int batch, hipStream_t
             if (stem_done) return hipSuccess;
         }
         if ((e = launch_input_stage(m, batch, d_in, s, n_launched)) != hipSuccess) return e;
+    }
+    if (m->layers[i].expdw_next) {
+        bool fused = false;
+        if ((e = launch_expdw_triple(m, i, batch, s, cu, n_launched, &fused)) != hipSuccess) return e;
+        if (fused) { *consumed = 3; return hipSuccess; }
     }
     if (m->layers[i].pair_next) {
         bool paired = false;

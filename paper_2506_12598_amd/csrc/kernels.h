@@ -154,6 +154,19 @@ struct DwPwPlan { int tn, wk, wm; };         // 16 tn output channels; wk wavefr
 bool dwpw_plan(long M, int C, int N, int dtype, int n_cu, DwPwPlan *out);      // false: better apart
 hipError_t launch_dwpw(const DwPwArgs &a, const DwPwPlan &p, hipStream_t s);
 
+// pointwise expansion, depthwise 3x3 (padding 1, stride 1 or 2) and pointwise layer in one launch (k_expdw.hip): 16-bit types, Cin and C multiples of 8, N of 4
+struct ExpDwArgs {
+    const void *x, *we, *bias_e;             // [B][H][W][Cin]; blocked GEMM layout of a C x Cin matrix; [C] or null
+    const void *wd, *bias_d;                 // [3][3][C]; [C] or null
+    const void *wp, *bias_p, *res;           // blocked GEMM layout of an N x C matrix; [N] or null; [B][Ho][Wo][N] or null
+    void *y;
+    int B, H, W, Cin, C, Ho, Wo, N, stride, act_e, act_d, act_p, dtype;
+};
+struct ExpDwPlan { int kmax, tn, nw; };      // steps of 32 input channels held; 16 tn output channels; wavefronts
+bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_cu, ExpDwPlan *out);      // false: better apart; n_cu: CuShare::even_cu
+hipError_t expdw_init();       // raises the dynamic LDS limit once per process
+hipError_t launch_expdw(const ExpDwArgs &a, const ExpDwPlan &p, hipStream_t s);
+
 // grouped convolution, 1 < groups < C: one thread per output element, weights [Cout][KH][KW][Cin/groups]
 struct GConvArgs {
     const void *x, *w, *bias, *res;
