@@ -14,12 +14,12 @@ SOURCES = ["eclip.cpp", "alloc_solver.cpp", "k_gemm.hip", "k_wsk.hip", "k_wsk_le
 
 
 def pp_tile_ids():
-    """Ids of the ping-pong tile shapes listed in gemm_tile.h; k_gemm_pp.hip is compiled once per id."""
+    """(id, is copied) of the tile shapes listed in gemm_tile.h; k_gemm_pp.hip is compiled once per id, copied tiles a second time for their pooling form."""
     import re
     text = open(os.path.join(CSRC, "gemm_tile.h")).read()
     body = text[text.index("#define ECLIP_PP_TILES(X)"):]
     body = body[:body.index("\n\n")]
-    return [int(v) for v in re.findall(r"X\((\d+),", body)]
+    return [(int(v), loop == "LOOP_DMA") for v, loop in re.findall(r"X\((\d+),[^)]*?(LOOP_\w+)\)", body)]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
@@ -54,7 +54,9 @@ def build(force: bool = False, verbose: bool = False) -> str:
         return obj
 
     # the slowest translation units first, so that the pool stays full to the end
-    jobs = [("k_gemm_pp.hip", [f"-DECLIP_PP_ID={i}"] + PRELOAD, f".{i}") for i in pp_tile_ids()] + [(src, MORE_FLAGS.get(src, []), "") for src in SOURCES]
+    jobs = [("k_gemm_pp.hip", [f"-DECLIP_PP_ID={i}"] + PRELOAD, f".{i}") for i, _ in pp_tile_ids()]
+    jobs += [("k_gemm_pp.hip", [f"-DECLIP_PP_ID={i}", "-DECLIP_PP_POOL"] + PRELOAD, f".{i}p") for i, copied in pp_tile_ids() if copied]
+    jobs += [(src, MORE_FLAGS.get(src, []), "") for src in SOURCES]
     with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(compile_one, jobs))
     if force or _needs(LIB, objs):

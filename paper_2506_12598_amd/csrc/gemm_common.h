@@ -16,13 +16,16 @@ struct GemmDev {
     int M, N, K, KT, kt_per, splits, tiles_m, tiles_n, raster;
     unsigned x_bytes, w_bytes;               // sizes of the x and w tensors (each below 4 GiB)
     int nchw_c;                              // > 0: x is the caller's [B][nchw_c][H][W] tensor (first layer), Cin == 8
-    int pool = 0;                            // 1: rows are the pixels of 2 x 2 windows, window by window, and y holds their maxima; howo, wo count windows
-    Magic howo, wo, fast;                    // output pixels per image and per row; tiles along the dimension that gemm_tile_of walks first
+    Magic howo, wo, fast;                    // output pixels (gemm_pools: windows) per image and per row; tiles along the dimension that gemm_tile_of walks first
     int n_groups = 0;                        // > 0 (wave-split-K, both forms): the output channels fall into this many groups, group g reads the Cin
                                              // channels from g Cin on of every pixel
     int ldx, ldy;                            // elements between consecutive pixels of x / rows of y (Cin and N unless the tensor is
                                              // a channel range of a wider buffer: concatenation in place); res is null when ldy != N
 };
+
+// The rows are the pixels of 2 x 2 windows, window by window, and y holds the windows' maxima (ConvGemmArgs::pool).  Told by the sizes, so that the launches
+// without a pool keep their arguments where they are.
+inline bool gemm_pools(const GemmDev &d) { return (unsigned)d.M != (unsigned)d.B * d.howo.d; }
 
 template <typename T> struct Mma;
 template <> struct Mma<bf16_t> {

@@ -264,7 +264,7 @@ __device__ __forceinline__ unsigned bits_run(int at, int n) { return (n >= 32 ? 
 // float outputs took: 3000 x 4096 x 1024 on 96 CUs 97 us, now 74, on 64 CUs 136, now 98; 1536 x 3000 x 1024 on 96 48, now 39; 1005 x 3072 x 768 on 64
 // 43, now 33.)
 // DMA_POOL (A_UNIFORM, ReLU): the rows of the tile are the pixels of 2 x 2 windows, window by window, so that four neighbouring lanes hold a window and its
-// maximum costs two lane exchanges: the pool's launch goes, and three quarters of the stores (GemmDev::pool).
+// maximum costs two lane exchanges: the pool's launch goes, and three quarters of the stores (gemm_pools).
 template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE, int FORM = DMA_PLAIN>
 __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 1024 ? 1 : 2) void conv_gemm_dma_kernel(const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int N, int K, int ldx, int kt_per, unsigned walk, unsigned tiles,
                           unsigned fast_d, unsigned fast_mul, GemmDev p, SeDeal deal)

@@ -680,5 +680,7 @@ inline int gemm_amode(const GemmDev &d, int bk, int loop)
 
 template <int ID> hipError_t launch_pp(const GemmDev &d, const SeDeal &deal, int dtype, dim3 grid, hipStream_t s);
 template <int ID> hipError_t init_pp();
+template <int ID> hipError_t launch_pp_pool(const GemmDev &d, const SeDeal &deal, int dtype, dim3 grid, hipStream_t s);      // gemm_pools; copied tiles only
+template <int ID> hipError_t init_pp_pool();
 
 }  // namespace eclip

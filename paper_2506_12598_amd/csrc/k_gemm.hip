@@ -78,7 +78,10 @@ hipError_t launch_t(const GemmDev &d, const GemmPlan &pl, SeDeal deal, hipStream
     case 0: hipLaunchKernelGGL((conv_gemm_kernel<T, 128, 128, 32, 2, 2, 2>), grid, dim3(256), lds_bytes(128, 128, 32), s, d, deal); break;
     case 1: hipLaunchKernelGGL((conv_gemm_kernel<T, 64, 64, 64, 2, 2, 4>), grid, dim3(256), lds_bytes(64, 64, 64), s, d, deal); break;
 #define X(ID, BM, BN, BK, RS, LP) \
-    case ID: return launch_pp_split<T>(d, pl, s, launch_pp<ID>(d, deal, std::is_same<T, bf16_t>::value ? DT_BF16 : DT_F16, grid, s));
+    case ID:                                                                                                                    \
+        if constexpr (LP == LOOP_DMA)                                                                                           \
+            if (gemm_pools(d)) return launch_pp_pool<ID>(d, deal, std::is_same<T, bf16_t>::value ? DT_BF16 : DT_F16, grid, s);  \
+        return launch_pp_split<T>(d, pl, s, launch_pp<ID>(d, deal, std::is_same<T, bf16_t>::value ? DT_BF16 : DT_F16, grid, s));
         ECLIP_PP_TILES(X)
 #undef X
     default: return hipErrorInvalidValue;
@@ -103,7 +106,9 @@ hipError_t conv_gemm_init()
 {
     hipError_t e;
 #define X(ID, BM, BN, BK, RS, LP) \
-    if ((e = init_pp<ID>()) != hipSuccess) return e;
+    if ((e = init_pp<ID>()) != hipSuccess) return e;                      \
+    if constexpr (LP == LOOP_DMA)                                         \
+        if ((e = init_pp_pool<ID>()) != hipSuccess) return e;
     ECLIP_PP_TILES(X)
 #undef X
     return hipSuccess;
@@ -519,9 +524,8 @@ static GemmDev make_dev(const ConvGemmArgs &a, const GemmPlan &pl)
     d.tiles_m = (d.M + bm - 1) / bm;
     d.tiles_n = (d.N + bn - 1) / bn;
     d.raster = pl.raster;
-    d.pool = a.pool;
-    d.howo = magic_of((unsigned)(a.Ho * a.Wo >> 2 * d.pool));
-    d.wo = magic_of((unsigned)(a.Wo >> d.pool));
+    d.howo = magic_of((unsigned)(a.Ho * a.Wo >> (a.pool ? 2 : 0)));
+    d.wo = magic_of((unsigned)(a.Wo >> (a.pool ? 1 : 0)));
     d.fast = magic_of((unsigned)(pl.raster == 3 ? d.tiles_n : d.tiles_m));
     return d;
 }
