@@ -33,11 +33,14 @@
  *                         kernel (variant = tile id, n = 4, 8 or 16 wavefronts), kind 2 = image-patch kernel of 3 x 3
  *                         windows (variant = tile id, n = 2, 4, 8 or 16 wavefronts); a tile id that does not exist, or
  *                         a kernel that does not take the layer, leaves the choice to the planner; also turns launch
- *                         sharing off, except that of pool and classifier
- *   ECLIP_NO_PAIRS=1      layers never share a launch (pairs of convolutions, pool + classifier, depthwise + pointwise,
- *                         first convolution reading the caller's tensor with the max-pool behind it)
+ *                         sharing off, except that of pool and classifier and of convolution and max-pool
+ *   ECLIP_NO_PAIRS=1      layers never share a launch (pairs of convolutions, pool + classifier, depthwise + pointwise with
+ *                         the expansion before them, convolution + 2 x 2 max-pool, first convolution reading the caller's tensor with the max-pool behind it)
  *   ECLIP_DWPW="n,w"      depthwise + pointwise: one launch with columns of 16 n output channels (n = 1, 2 or 4) and w
- *                         wavefronts sharing K (1, 2, 4 or 8) instead of the planner's choice; "0,0": two launches
+ *                         wavefronts sharing K (1, 2, 4 or 8) instead of the planner's choice; "0,0": two launches;
+ *                         set to anything, it keeps an expansion before them apart
+ *   ECLIP_EXPDW=n         expansion + depthwise + pointwise: 1 = one launch where the kernel takes them, 0 = apart, instead of
+ *                         the planner's choice
  *   ECLIP_GCONV3=n        grouped 3 x 3 convolutions on groups of 32 inputs: n blocks of 4 x 4 pixels per wavefront (1, 2
  *                         or 4) instead of the planner's choice; 0: the wave-split-K kernel.  Other values of either leave the
  *                         choice to the planner
@@ -305,15 +308,15 @@ eclip_status eclip_profile_group(eclip_model *model, uint32_t group, uint32_t ma
  * choice is within 5 % of it, in which case that one stays.  3 x 3 windows that the image-patch kernel takes are distinct by
  * the image's height and width and the stride too.  Layers that requests of this batch on this pool entry run on another
  * kernel are left out: a first layer that reads the caller's planes, and a pointwise layer in one launch with the
- * depthwise layer before it.  Later eclip_submit / eclip_profile_* / kernel_info
+ * depthwise layer before it; of an expansion in that launch too the plan is kept for requests that run it apart.  Later eclip_submit / eclip_profile_* / kernel_info
  * calls use the remembered plans; problems or CU counts never tuned keep the cost model's plans.  Results stay
  * within the same tolerances (a different tile only reassociates the fp32 sums).  *n_tuned_out (optional) receives
  * the number of problems timed.  Same preconditions as eclip_profile_group. */
 eclip_status eclip_model_tune(eclip_model *model, uint32_t mask_id, uint32_t batch, uint32_t iters, uint32_t *n_tuned_out);
 
 /* The group as eclip_submit serves it (Sec. III-B: the allocator's beta of a unit): all launches of `group` in
- * order on pool entry `mask_id` -- including the input re-layout in group 0, two independent layers sharing a
- * launch, pool + classifier in one launch -- timed as one interval; median over `iters` samples in integer
+ * order on pool entry `mask_id` -- including the input re-layout in group 0, layers that share a
+ * launch -- timed as one interval; median over `iters` samples in integer
  * nanoseconds to *group_ns_out, and the number of kernels launched per pass to *n_launches_out (optional; the
  * kernel count the allocator's CUAverage should weigh the unit with).  Same preconditions as
  * eclip_profile_group. */

@@ -252,10 +252,12 @@ hipError_t expdw_init()
 
 // One launch against two, us by HIP events, 11 bottlenecks of MobileNetV2 x images of 224, 128 and 64 x batch 1, 3 and 8 x 32 to 256 CUs (both types).  By
 // workgroups per compute unit: up to 32 input channels at stride 1 never slower (56 x 56 x 24 at batch 3 on 128 CUs 16.0 apart, 9.9; 1.02 times at worst of
-// 54), at stride 2, where the border is five times the tile, up to 4.6 (112 x 112 x 16 on 128 CUs 12.5, 11.6; at 5.3 per unit 5 % slower, at 49 40 %); 64 input
+// 54), at stride 2, where the border is five times the tile, up to 4
+// (112 x 112 x 16 at batch 1 on 64 CUs 1.25 times faster; at 4.6 1.1 times in this measurement and even as served, at 5.3 per unit 5 % slower, at 49 40 %); 64 input
 // and output channels up to the 4 that were measured (14 x 14 at batch 3 on 192 9.3, 7.1); more than 64 output channels, whose columns are wide, while every
 // workgroup has a unit to itself (14 x 14 x 64 -> 96 9.3, 8.0; at 1.3 5 % slower).  Three slices per wavefront pay only where the two launches have
-// several rounds, from 0.35 workgroups per unit on (14 x 14 x 96 at batch 8 on 128 CUs 13.0, 9.7; at 0.25 and less even or up to 20 % slower).  Four, in
+// several rounds, from 0.45 workgroups per unit on (14 x 14 x 96 at batch 8 on 128 CUs 13.0, 9.7; at 0.38 9.7, 9.4 and as served 8.9, 9.3; below up to 20 %
+// slower).  Four, in
 // kernels for up to 160 input channels, did not: 7 x 7 x 160 10.5 apart, 14.3.
 bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_cu, ExpDwPlan *out)
 {
@@ -269,9 +271,9 @@ bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_
     const int slices = ((C + 31) / 32 + nw - 1) / nw;
     const double per_cu = (double)B * ((Ho + 3) / 4) * ((Wo + 3) / 4) * ((N + 16 * tn - 1) / (16 * tn)) / n_cu;
     if (slices > 3) return false;
-    if (slices == 3 && per_cu < 0.35) return false;
+    if (slices == 3 && per_cu < 0.45) return false;
     if (slices == 3 || tn == 10) return per_cu <= 1.0;
-    return kmax == 3 ? per_cu <= 4.0 : stride == 1 || per_cu <= 4.6;
+    return kmax == 3 ? per_cu <= 4.0 : stride == 1 || per_cu <= 4.0;
 }
 
 hipError_t launch_expdw(const ExpDwArgs &a, const ExpDwPlan &pl, hipStream_t s)
