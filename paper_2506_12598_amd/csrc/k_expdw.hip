@@ -173,11 +173,13 @@ __global__ __launch_bounds__(NW * 64) void expdw_kernel(ExpDwDev p)
 #pragma unroll
             for (int c = 0; c < 8; ++c) o[c] = f(o[c]);
         });
+        // channels beyond C, whose weights are zeros, are zeros here: expanded from an infinite pixel they would be NaN
+        const bool some = 32 * ks + 8 * g < p.C;
         uint4 a;
-        a.x = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, (int)Cvt<T>::pack2(o[0], o[1]));
-        a.y = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, (int)Cvt<T>::pack2(o[2], o[3]));
-        a.z = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, (int)Cvt<T>::pack2(o[4], o[5]));
-        a.w = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, (int)Cvt<T>::pack2(o[6], o[7]));
+        a.x = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, some ? (int)Cvt<T>::pack2(o[0], o[1]) : 0);
+        a.y = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, some ? (int)Cvt<T>::pack2(o[2], o[3]) : 0);
+        a.z = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, some ? (int)Cvt<T>::pack2(o[4], o[5]) : 0);
+        a.w = (unsigned)__builtin_amdgcn_ds_bpermute(perm_src, some ? (int)Cvt<T>::pack2(o[6], o[7]) : 0);
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[j] = Mma<T>::run(make_uint4(cur.wf[j].x, cur.wf[j].y, cur.wf[j].z, cur.wf[j].w), a, acc[j]);
     }

@@ -88,3 +88,18 @@ def test_an_expansion_of_many_channels_stays_apart():
     x = wl.make_input(m, 2)
     got, ref = _both(m, x, fewer=1)
     assert rel_to_range(got, ref) <= 2.0 ** -10
+
+
+@pytest.mark.parametrize("dt,cin,c,n,stride", [(wl.DT_BF16, 16, 40, 16, 1), (wl.DT_F16, 32, 72, 24, 2), (wl.DT_BF16, 72, 264, 40, 1)])
+def test_infinities_stay_out_of_the_channels_that_fill_a_slice(dt, cin, c, n, stride):
+    # hidden channels that do not fill their last slice of 32: what stands there for the missing ones must not turn an infinity into a NaN.  All weights are
+    # positive, so that the windows that reach the infinite pixel sum to infinity and the others stay finite.
+    m = _model(dt, cin, c, n, 9, 8, stride, (NONE, NONE, NONE), False)
+    m.weights[:] = np.abs(m.weights)
+    x = np.abs(wl.make_input(m, 2))
+    x[1, 3, 4, 4] = np.inf
+    got, ref = _both(m, x)
+    assert np.isposinf(ref).any() and not np.isnan(ref).any() and np.isfinite(ref).any()
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and not np.isnan(got).any()
+    ok = np.isfinite(ref)
+    assert np.abs(got[ok] - ref[ok]).max() <= (2.0 ** -7 if dt == wl.DT_BF16 else 2.0 ** -10) * np.abs(ref[ok]).max()
