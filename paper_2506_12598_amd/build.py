@@ -56,6 +56,7 @@ def build(force: bool = False, verbose: bool = False) -> str:
     # the slowest translation units first, so that the pool stays full to the end
     jobs = [("k_gemm_pp.hip", [f"-DECLIP_PP_ID={i}"] + PRELOAD, f".{i}") for i, _ in pp_tile_ids()]
     jobs += [("k_gemm_pp.hip", [f"-DECLIP_PP_ID={i}", "-DECLIP_PP_POOL"] + PRELOAD, f".{i}p") for i, copied in pp_tile_ids() if copied]
+    jobs += [("k_conv3.hip", ["-DECLIP_CONV3_POOL"] + PRELOAD, ".p")]               # its kernels' pooling forms
     jobs += [(src, MORE_FLAGS.get(src, []), "") for src in SOURCES]
     with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(compile_one, jobs))

@@ -35,12 +35,14 @@ struct Conv3Rest {
     void *y;
     unsigned bias_bytes, res_bytes, y_bytes;
     int ldy, act, Ho, Wo, f32;               // f32: y holds floats
-    int pool;                                // 1: y holds the maxima of 2 x 2 outputs (ConvGemmArgs::pool)
 };
 
 // packed: bits 0-1 GemmPlan::raster, 2-6, 7-11 and 12-16 the shifts of the divisions by inner_d, by the patches of an image and by those of a row of
 // it; hw: H | W << 16; px_slices: bytes between pixels | slices of 32 channels << 16
-template <typename T, int TH, int TW, int TN, int NW, int SD, bool MULTI>
+// POOL: y holds the maxima of 2 x 2 outputs (ConvGemmArgs::pool).  A form of its own, compiled apart (ECLIP_CONV3_POOL): with the pool as an argument all
+// kernels were some 75 instructions longer, about a dozen of them on the way of launches without one.  (ResNet-18 next to itself, 13 of whose 18 launches
+// these are, 739 and 755 us with the argument and 725 and 771 without on two boxes: the difference drowns in the 2 % by which two runs of one side differ.)
+template <typename T, int TH, int TW, int TN, int NW, int SD, bool MULTI, bool POOL>
 __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const uint16_t *w, unsigned packed, int tiles, unsigned inner_d, unsigned inner_mul,
                                                         unsigned hw, unsigned px_slices, unsigned image_d, unsigned image_mul, unsigned row_d, unsigned row_mul,
                                                         Conv3Rest p)
@@ -118,8 +120,8 @@ __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const
         const int s = u * NW * 64 + tid, c4 = s % C4, r = s / C4, blk = r >> 4;
         const int oy = oy0 + 4 * (blk / TW) + (r >> 2 & 3), ox = ox0 + 4 * (blk % TW) + (r & 3), n = (int)tile_n * TN * 16 + c4 * 4;
         const bool in = sums && blk < TM && oy < p.Ho && ox < p.Wo;
-        const bool out = in && !(p.pool && (r & 5));                   // of a pooled window's four the upper left one is stored
-        off[u] = out ? (unsigned)((((int)b * (p.Ho >> p.pool) + (oy >> p.pool)) * (p.Wo >> p.pool) + (ox >> p.pool)) * p.ldy + n) * 2u : OOB;
+        if constexpr (POOL) off[u] = in && !(r & 5) ? (unsigned)((((int)b * (p.Ho >> 1) + (oy >> 1)) * (p.Wo >> 1) + (ox >> 1)) * p.ldy + n) * 2u : OOB;     // a window's upper left
+        else off[u] = in ? (unsigned)((((int)b * p.Ho + oy) * p.Wo + ox) * p.ldy + n) * 2u : OOB;
         bias[u] = __builtin_amdgcn_raw_buffer_load_b64(rb, in ? n * 2 : OOB, 0, 0);
         res[u] = __builtin_amdgcn_raw_buffer_load_b64(rr, off[u], 0, 0);
     }
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const
             const u32x4 v = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
             __builtin_amdgcn_raw_buffer_store_b128(v, ry, off[u] == OOB ? OOB : off[u] * 2u, 0, 0);
         } else {
-            if (p.pool)                          // pixels one to the right and one down lie C4 and 4 C4 lanes on; all lanes of the wavefront are here
+            if constexpr (POOL)                  // pixels one to the right and one down lie C4 and 4 C4 lanes on; all lanes of the wavefront are here
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int v = __float_as_int(o[e]);
@@ -207,6 +209,7 @@ __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const
     }
 }
 
+#ifndef ECLIP_CONV3_POOL
 // Grouped convolutions whose super-groups (k_gconv.hip) read 32 channels: nine steps of the matrix instruction are all there is to sum, so a wavefront
 // does a tile of 16 TN channels by itself and stores from its registers, without a barrier; the four of a workgroup take neighbouring channels of the
 // same pixels, whose cache lines they share.
@@ -317,6 +320,10 @@ template <typename T> const void *kernel_of(int tn, int sd, int blocks)
     return sd == 1 ? kernel_of<T, 1, 1>(blocks) : kernel_of<T, 1, 2>(blocks);
 }
 }  // namespace patch
+constexpr bool kPool = false;
+#else
+constexpr bool kPool = true;
+#endif
 
 struct Shape { int th, tw, tn; };
 constexpr Shape kShapes[CONV3_VARIANTS] = {{1, 1, 1}, {1, 1, 2}, {2, 1, 1}, {2, 1, 2}, {2, 2, 1}, {2, 2, 2}};
@@ -324,9 +331,9 @@ constexpr Shape kShapes[CONV3_VARIANTS] = {{1, 1, 1}, {1, 1, 2}, {2, 1, 1}, {2, 
 template <typename T, int V, int NW, int SD> const void *kernel_of(bool multi)
 {
     constexpr Shape s = kShapes[V];
-    if (!multi) return (const void *)conv3_kernel<T, s.th, s.tw, s.tn, NW, SD, false>;
+    if (!multi) return (const void *)conv3_kernel<T, s.th, s.tw, s.tn, NW, SD, false, kPool>;
     if constexpr (NW < 8 || (NW == 16 && V == 5)) return nullptr;
-    else return (const void *)conv3_kernel<T, s.th, s.tw, s.tn, NW, SD, true>;
+    else return (const void *)conv3_kernel<T, s.th, s.tw, s.tn, NW, SD, true, kPool>;
 }
 template <typename T, int V, int SD> const void *kernel_of(int nw, bool multi)
 {
@@ -351,8 +358,20 @@ template <typename T, int SD> const void *kernel_of(int v, int nw, bool multi)
     }
 }
 template <typename T> const void *kernel_of(int v, int nw, int sd, bool multi) { return sd == 1 ? kernel_of<T, 1>(v, nw, multi) : kernel_of<T, 2>(v, nw, multi); }
+const void *kernel_of(int dtype, int v, int nw, int sd, bool multi)
+{
+    return dtype == DT_BF16 ? kernel_of<bf16_t>(v, nw, sd, multi) : dtype == DT_F16 ? kernel_of<f16_t>(v, nw, sd, multi) : nullptr;
+}
 
 }  // namespace
+
+const void *conv3_pool_kernel(int dtype, int v, int nw, int sd, bool multi)
+#ifdef ECLIP_CONV3_POOL
+{
+    return kernel_of(dtype, v, nw, sd, multi);
+}
+#else
+    ;                                        // the pooling forms, compiled from this file a second time
 
 void conv3_tile(int variant, int *th, int *tw, int *bn)
 {
@@ -382,11 +401,12 @@ hipError_t conv3_init()
         for (int nw = 2; nw <= 16; nw *= 2)
             for (int sd = 1; sd <= 2; ++sd)
                 for (bool multi : {false, true})
-                    for (const void *k : {kernel_of<bf16_t>(v, nw, sd, multi), kernel_of<f16_t>(v, nw, sd, multi)}) {
-                        if (!k) continue;
-                        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, CONV3_MAX_LDS);
-                        if (e != hipSuccess) return e;
-                    }
+                    for (int dtype : {DT_BF16, DT_F16})
+                        for (const void *k : {kernel_of(dtype, v, nw, sd, multi), conv3_pool_kernel(dtype, v, nw, sd, multi)}) {
+                            if (!k) continue;
+                            const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, CONV3_MAX_LDS);
+                            if (e != hipSuccess) return e;
+                        }
     return hipSuccess;
 }
 
@@ -437,7 +457,7 @@ hipError_t launch_conv3(const ConvGemmArgs &a, int variant, int nw, hipStream_t 
     conv3_tile(variant, &th, &tw, &bn);
     const size_t lds = conv3_lds_bytes(variant, nw, a.stride, a.Cin);
     const bool multi = a.Cin / 32 > nw;
-    const void *k = a.dtype == DT_BF16 ? kernel_of<bf16_t>(variant, nw, a.stride, multi) : a.dtype == DT_F16 ? kernel_of<f16_t>(variant, nw, a.stride, multi) : nullptr;
+    const void *k = a.pool ? conv3_pool_kernel(a.dtype, variant, nw, a.stride, multi) : kernel_of(a.dtype, variant, nw, a.stride, multi);
     if (!k || a.Cout % bn || lds > CONV3_MAX_LDS) return hipErrorInvalidValue;
     const uint16_t *x = (const uint16_t *)a.x, *w = (const uint16_t *)a.w;
     const int tiles_x = (a.Wo + tw - 1) / tw, tiles_y = (a.Ho + th - 1) / th, tiles_n = a.Cout / bn, tiles_m = a.B * tiles_x * tiles_y;
@@ -451,8 +471,7 @@ hipError_t launch_conv3(const ConvGemmArgs &a, int variant, int nw, hipStream_t 
     p.bias = (const uint16_t *)a.bias; p.res = (const uint16_t *)a.res; p.f32 = a.y32 != nullptr;
     p.y = p.f32 ? (void *)a.y32 : a.y;
     p.bias_bytes = a.bias ? (unsigned)a.Cout * 2u : 0u;
-    p.pool = a.pool;
-    const unsigned elems = (unsigned)((a.B * a.Ho * a.Wo >> 2 * p.pool) - 1) * (unsigned)ldy + (unsigned)a.Cout;
+    const unsigned elems = (unsigned)((a.B * a.Ho * a.Wo >> (a.pool ? 2 : 0)) - 1) * (unsigned)ldy + (unsigned)a.Cout;
     p.y_bytes = elems * (p.f32 ? 4u : 2u);
     p.res_bytes = a.res ? elems * 2u : 0u;
     p.ldy = ldy; p.act = a.act; p.Ho = a.Ho; p.Wo = a.Wo;
@@ -502,5 +521,7 @@ hipError_t launch_gconv3(const GConvArgs &a, int S, int blocks, hipStream_t s)
     void *args[] = {&x, &w, &packed, &tiles, &cols.d, &cols.mul, &hw, &px, &image.d, &image.mul, &row.d, &row.mul, &p};
     return hipLaunchKernel(k, dim3((gconv3_workgroups(a, S, blocks) + 7u) & ~7u), dim3(256), args, 0, s);
 }
+
+#endif
 
 }  // namespace eclip
