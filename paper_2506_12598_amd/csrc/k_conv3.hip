@@ -41,7 +41,7 @@ struct Conv3Rest {
 // it; hw: H | W << 16; px_slices: bytes between pixels | slices of 32 channels << 16
 // POOL: y holds the maxima of 2 x 2 outputs (ConvGemmArgs::pool).  A form of its own, compiled apart (ECLIP_CONV3_POOL): with the pool as an argument all
 // kernels were some 75 instructions longer, about a dozen of them on the way of launches without one.  (ResNet-18 next to itself, 13 of whose 18 launches
-// these are, 739 and 755 us with the argument and 725 and 771 without on two boxes: the difference drowns in the 2 % by which two runs of one side differ.)
+// these are, timed in turn: 754 us with the argument and 771 without; 739 before there was a pool and 725 now.  Two runs of one side differ by 2 %.)
 template <typename T, int TH, int TW, int TN, int NW, int SD, bool MULTI, bool POOL>
 __global__ __launch_bounds__(NW * 64) void conv3_kernel(const uint16_t *x, const uint16_t *w, unsigned packed, int tiles, unsigned inner_d, unsigned inner_mul,
                                                         unsigned hw, unsigned px_slices, unsigned image_d, unsigned image_mul, unsigned row_d, unsigned row_mul,
