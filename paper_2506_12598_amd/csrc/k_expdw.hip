@@ -252,15 +252,22 @@ hipError_t expdw_init()
     return hipSuccess;
 }
 
-// One launch against two, us by HIP events, 11 bottlenecks of MobileNetV2 x images of 224, 128 and 64 x batch 1, 3 and 8 x 32 to 256 CUs (both types).  By
-// workgroups per compute unit: up to 32 input channels at stride 1 never slower (56 x 56 x 24 at batch 3 on 128 CUs 16.0 apart, 9.9; 1.02 times at worst of
-// 54), at stride 2, where the border is five times the tile, up to 4
-// (112 x 112 x 16 at batch 1 on 64 CUs 1.25 times faster; at 4.6 1.1 times in this measurement and even as served, at 5.3 per unit 5 % slower, at 49 40 %); 64 input
-// and output channels up to the 4 that were measured (14 x 14 at batch 3 on 192 9.3, 7.1); more than 64 output channels, whose columns are wide, while every
-// workgroup has a unit to itself (14 x 14 x 64 -> 96 9.3, 8.0; at 1.3 5 % slower).  Three slices per wavefront pay only where the two launches have
-// several rounds, from 0.45 workgroups per unit on (14 x 14 x 96 at batch 8 on 128 CUs 13.0, 9.7; at 0.38 9.7, 9.4 and as served 8.9, 9.3; below up to 20 %
-// slower).  Four, in
-// kernels for up to 160 input channels, did not: 7 x 7 x 160 10.5 apart, 14.3.
+// One launch against two, device time of six in a row as served from graphs: 71 bottlenecks (nine of MobileNetV2 at images of 224 and 112, and 53 of other
+// widths: 8 to 96 input, 32 to 576 hidden, 16 to 512 output channels, both strides) x batch 1, 3 and 8 x 32 to 256 CUs, both types.  Every tile column repeats
+// the expansion and the depthwise layer, every tile the border; against that stands a hidden tensor written and read back and a launch.  So the kernel pays
+// within bounds on its workgroups (columns counted) per compute unit, which stand where the timings cross.  What the rule takes is 1.16 times faster than
+// apart on the geometric mean, 0.97 at worst.  Times faster in one launch, and beyond the line:
+// - up to 32 input channels, one column, stride 1: 56 x 56 x 24 1.2 and more up to the 49 that were timed; with 64 hidden channels, which occupy half of the
+//   wavefronts, 1.0 to 1.2 up to 6.1 (0.98 at 12, 0.65 at 196).  Stride 2: 1.02 to 1.2 up to 6.1 (0.95 at 9.2); with two slices per wavefront and 64 output channels from 0.19 on
+//   (0.95 to 0.99 below).
+// - two columns: stride 1 1.05 at 6.1 (0.97 at 9.2), stride 2 1.02 at 3.1 (0.99 at 4.6, 0.5 at 98).  Three to eight: 1.02 to 1.2 at 3.0 (0.93 at 3.06, 0.83 at 4, 0.45
+//   at 196), stride 2 1.01 to 1.1 at 1.5 (0.82 at 2.25).  More were not timed.
+// - up to 96 input and 64 output channels: stride 1 1.1 at the 4 that were timed (64 to 256 hidden channels: 0.99 to 1.1 from 2.3 on), stride 2 1.03 to 1.2 at 2.0 (0.85 to 0.98
+//   at 4), with two slices from 0.19 on (0.93 to 0.99 below).
+// - more than 64 output channels: up to 1.0, where they gain 1.05 to 1.3 (0.75 to 0.95 at 1.5); with one slice from 0.25 on (0.98 to 0.99 below), with two from
+//   0.375 (0.99 to 1.1; 0.9 to 1.04 at 0.25), with three from 0.5 (1.09; 14 x 14 x 96 at 0.375 0.96) and in one column only (0.88 to 0.98 in two).
+// - three slices elsewhere from 0.375 on, 1.02 to 1.3 up to 12 at stride 1 and 4 at stride 2.  Four, in kernels for up to 160 input channels, did not pay: 7 x 7 x 160
+//   10.5 us apart, 14.3.
 bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_cu, ExpDwPlan *out)
 {
     if (Cin > 96 || (stride != 1 && stride != 2)) return false;
@@ -270,12 +277,24 @@ bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_
         int take = -1;
         if (sscanf(f, "%d", &take) == 1 && (take == 0 || take == 1)) return take == 1;
     }
-    const int slices = ((C + 31) / 32 + nw - 1) / nw;
-    const double per_cu = (double)B * ((Ho + 3) / 4) * ((Wo + 3) / 4) * ((N + 16 * tn - 1) / (16 * tn)) / n_cu;
-    if (slices > 3) return false;
-    if (slices == 3 && per_cu < 0.45) return false;
-    if (slices == 3 || tn == 10) return per_cu <= 1.0;
-    return kmax == 3 ? per_cu <= 4.0 : stride == 1 || per_cu <= 4.0;
+    const int slices = ((C + 31) / 32 + nw - 1) / nw, cols = (N + 16 * tn - 1) / (16 * tn);
+    const double per_cu = (double)B * ((Ho + 3) / 4) * ((Wo + 3) / 4) * cols / n_cu;
+    if (slices > 3 || cols > (tn == 10 ? 2 : 8) || (slices == 3 && cols > 1)) return false;
+    double least, most;
+    if (tn == 10) {
+        least = slices == 1 ? 0.25 : slices == 2 ? 0.37 : 0.45;
+        most = 1.0;
+    } else if (slices == 3) {
+        least = kmax == 3 ? 0.45 : 0.37;
+        most = kmax == 3 ? 1.0 : stride == 1 ? 12.5 : 4.0;
+    } else {
+        least = stride == 2 && slices == 2 && tn == 4 ? 0.18 : 0.0;
+        if (kmax == 3) most = stride == 1 ? 4.0 : 2.0;
+        else if (cols == 1) most = stride == 1 && C > 64 ? 50.0 : 6.5;
+        else if (cols == 2) most = stride == 1 ? 6.5 : 3.1;
+        else most = stride == 1 ? 3.0 : 1.5;
+    }
+    return per_cu >= least && per_cu <= most;
 }
 
 hipError_t launch_expdw(const ExpDwArgs &a, const ExpDwPlan &pl, hipStream_t s)
