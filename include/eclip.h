@@ -306,7 +306,8 @@ eclip_status eclip_profile_group(eclip_model *model, uint32_t group, uint32_t ma
  * plan is timed on pool entry `mask_id` (minimum over `iters` samples of 6 back-to-back launches) and the fastest is
  * remembered for streams of that CU count -- unless the cost model's own
  * choice is within 5 % of it, in which case that one stays.  3 x 3 windows that the image-patch kernel takes are distinct by
- * the image's height and width and the stride too.  Layers that requests of this batch on this pool entry run on another
+ * the image's height and width and the stride too.  A convolution that may take the 2 x 2 max-pool behind it along is a
+ * problem of its own besides: timed on every plan that takes the pool into its launch and as two launches.  Layers that requests of this batch on this pool entry run on another
  * kernel are left out: a first layer that reads the caller's planes, and a pointwise layer in one launch with the
  * depthwise layer before it; of an expansion in that launch too the plan is kept for requests that run it apart.  Later eclip_submit / eclip_profile_* / kernel_info
  * calls use the remembered plans; problems or CU counts never tuned keep the cost model's plans.  Results stay
