@@ -1946,11 +1946,10 @@ static eclip_status profile_prepare(eclip_model *model, uint32_t group, uint32_t
     const PoolStream &ps = pool->streams[mask_id];
     const uint32_t n_layers = (uint32_t)model->layers.size();
     uint32_t dummy = 0;
-    for (uint32_t i = 0; i < n_layers;) {
-        uint32_t consumed = 1;
-        HIP_TRY(launch_unit(model, i, (int)batch, ps.stream, share_of(ps), model->d_self_in, model->d_self_out, &dummy, &consumed));
-        i += consumed;
-    }
+    // every layer by itself: where requests give several of them one launch, what passes between these is in no buffer, but it is read where they are timed
+    HIP_TRY(launch_input_stage(model, (int)batch, model->d_self_in, ps.stream, &dummy));
+    for (uint32_t i = 0; i < n_layers; ++i)
+        HIP_TRY(launch_layer(model, i, (int)batch, ps.stream, share_of(ps), model->d_self_in, i + 1 == n_layers ? model->d_self_out : nullptr, &dummy));
     HIP_TRY(hipStreamSynchronize(ps.stream));
     return ECLIP_OK;
 }

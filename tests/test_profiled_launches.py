@@ -1,0 +1,39 @@
+"""What the profiler and eclip_model_tune launch, on a runtime that only writes down which kernels it is given."""
+import pytest
+
+import fake_runtime
+
+pytestmark = pytest.mark.skipif(not fake_runtime.HAVE, reason="needs hipcc")
+
+PROGRAM = """
+import paper_2506_12598_amd as ec
+import workloads as wl
+import workloads.graphs as graphs
+b = graphs._Builder("bottleneck", wl.DT_BF16, 1, graphs.IN_IMAGE, 8, 14, 14)
+x = b.conv(-1, 32, 1)
+y = b.conv(x, 96, 1, act=wl.ACT_RELU6)
+d = b.conv(y, 96, 3, 1, 1, wl.ACT_RELU6, groups=96)
+z = b.conv(d, 24, 1)
+b.maxpool(z, 1, 1, 0)
+m = b.finish()
+pool = ec.Pool([(None, -1)])
+h = ec.Model(pool, m, wl.to_storage(m.weights, m.dtype), 2)
+print(h.{call})
+"""
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    tmp = str(tmp_path_factory.mktemp("fake"))
+    lib = fake_runtime.build(tmp)
+    return lambda call, **env: fake_runtime.run(lib, tmp, PROGRAM.format(call=call), **env)
+
+
+@pytest.mark.parametrize("call", ["tune(0, batch=2, iters=1)", "profile_group(0, 0, 2, 1)", "profile_group_served(0, 0, 2, 1)"])
+def test_layers_that_share_a_launch_are_written_before_they_are_timed(launches, call):
+    # timed one by one, the pointwise layer reads what the depthwise layer left; in one launch with the expansion it leaves nothing
+    _, kernels = launches(call, ECLIP_EXPDW="1")
+    convs = [k for k in kernels if "conv" in k or "expdw" in k]
+    depthwise = [i for i, k in enumerate(convs) if "dwconv" in k]
+    assert depthwise and depthwise[0] <= 2, convs[:6]                 # behind the first convolution and the expansion
+    assert ("served" in call) == any("expdw" in k for k in convs)
