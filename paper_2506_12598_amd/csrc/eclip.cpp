@@ -1137,6 +1137,14 @@ static bool dwpw_takes(const eclip_model *m, uint32_t i, int batch, const CuShar
     const LayerPlan &Q = m->layers[i + 1];
     return dwpw_plan((long)batch * Q.out.h * Q.out.w, D.L.c, Q.L.c, m->dtype, cu.even_cu(), pl);
 }
+// The pointwise expansion i, the depthwise layer and the pointwise layer behind it run as one launch when a unit starts at i.
+static bool expdw_takes(const eclip_model *m, uint32_t i, int batch, const CuShare &cu, ExpDwPlan *pl)
+{
+    const LayerPlan &P = m->layers[i];
+    if (!P.expdw_next || getenv("ECLIP_GEMM_FORCE") || getenv("ECLIP_NO_PAIRS") || getenv("ECLIP_DWPW")) return false;
+    const LayerPlan &D = m->layers[i + 1], &Q = m->layers[i + 2];
+    return expdw_plan(batch, Q.out.h, Q.out.w, P.in.c, P.L.c, Q.L.c, D.L.stride, cu.even_cu(), pl);
+}
 
 extern "C" eclip_status eclip_model_load(eclip_pool *pool, const eclip_model_desc *desc, const void *weights,
                                          size_t weight_bytes, int weights_on_device, eclip_model **out)
@@ -1516,14 +1524,29 @@ static hipError_t launch_layer(eclip_model *m, uint32_t i, int batch, hipStream_
     return launch_to_f32(y, d_out32, rows * P.out.c, dt, s);
 }
 
+// The common plan of the layers i and i + 1 (pair_next), when the planner finds one
+static bool pair_takes(const eclip_model *m, uint32_t i, int batch, const CuShare &cu, GemmPlan pl[2])
+{
+    if (!m->layers[i].pair_next) return false;
+    GemmPlan own[2];
+    long mnk[2][3];
+    int form[2];
+    for (int k = 0; k < 2; ++k) {
+        const GemmShape g = gemm_shape(m, m->layers[i + k], batch);
+        mnk[k][0] = (long)g.B * g.Ho * g.Wo; mnk[k][1] = g.Cout; mnk[k][2] = (long)g.KH * g.KW * g.Cin;
+        own[k] = plan_of(m, g, cu);
+        form[k] = lean_form_of(g);
+    }
+    return conv_gemm_plan_pair(own[0], mnk[0][0], mnk[0][1], mnk[0][2], form[0], own[1], mnk[1][0], mnk[1][1], mnk[1][2], form[1], cu.even_cu(), &pl[0], &pl[1]);
+}
+
 // Launches layers i and i + 1 (pair_next) in one kernel when the planner finds a common plan; *done tells whether it did.
 static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t s, const CuShare &cu, const void *d_in, uint32_t *n_launched, bool *done)
 {
     *done = false;
     ConvGemmArgs a[2];
-    GemmPlan own[2], pl[2];
-    long mnk[2][3];
-    int form[2];
+    GemmPlan pl[2];
+    if (!pair_takes(m, i, batch, cu, pl)) return hipSuccess;
     for (int k = 0; k < 2; ++k) {
         const LayerPlan &P = m->layers[i + k];
         const eclip_layer &L = P.L;
@@ -1537,12 +1560,7 @@ static hipError_t launch_pair(eclip_model *m, uint32_t i, int batch, hipStream_t
                             g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.KH, g.KW, g.stride, g.pad, L.act, m->dtype};
         a[k].ldx = pitch_of(m, L.in0);
         a[k].ldy = P.ld;
-        mnk[k][0] = (long)g.B * g.Ho * g.Wo; mnk[k][1] = g.Cout; mnk[k][2] = (long)g.KH * g.KW * g.Cin;
-        own[k] = plan_of(m, g, cu);
-        form[k] = lean_form_of(g);
     }
-    if (!conv_gemm_plan_pair(own[0], mnk[0][0], mnk[0][1], mnk[0][2], form[0], own[1], mnk[1][0], mnk[1][1], mnk[1][2], form[1], cu.even_cu(), &pl[0], &pl[1]))
-        return hipSuccess;
     *done = true;
     return launch_conv_gemm_pair(a[0], pl[0], a[1], pl[1], s, n_launched);
 }
@@ -1581,9 +1599,8 @@ static hipError_t launch_expdw_triple(eclip_model *m, uint32_t i, int batch, hip
 {
     *done = false;
     const LayerPlan &P = m->layers[i], &D = m->layers[i + 1], &Q = m->layers[i + 2];
-    if (getenv("ECLIP_GEMM_FORCE") || getenv("ECLIP_NO_PAIRS") || getenv("ECLIP_DWPW")) return hipSuccess;
     ExpDwPlan pl;
-    if (!expdw_plan(batch, Q.out.h, Q.out.w, P.in.c, P.L.c, Q.L.c, D.L.stride, cu.even_cu(), &pl)) return hipSuccess;
+    if (!expdw_takes(m, i, batch, cu, &pl)) return hipSuccess;
     *done = true;
     *n_launched += 1;
     const ExpDwArgs a{out_ptr(m, m->layers[P.L.in0]), wptr(m, P.w_dev), wptr(m, P.b_dev), wptr(m, D.w_dev), wptr(m, D.b_dev), wptr(m, Q.w_dev), wptr(m, Q.b_dev),
@@ -2041,11 +2058,21 @@ extern "C" eclip_status eclip_model_tune(eclip_model *model, uint32_t mask_id, u
         }
         return ECLIP_OK;
     };
+    // pointwise layers in one launch with the expansion before them, found as launch_unit finds them: three layers start there, or were taken before
+    std::vector<bool> expanded(n_layers, false);
+    for (uint32_t i = 0, covers; i < n_layers; i += covers) {
+        ExpDwPlan ep;
+        DwPwPlan dp;
+        GemmPlan pp[2];
+        covers = expdw_takes(model, i, (int)batch, share_of(ps), &ep) ? 3
+               : pair_takes(model, i, (int)batch, share_of(ps), pp) || dwpw_takes(model, i, (int)batch, share_of(ps), &dp) ? 2 : 1;
+        if (covers == 3) expanded[i + 2] = true;
+    }
     for (uint32_t i = 0; i < n_layers && st == ECLIP_OK; ++i) {
         const LayerPlan &P = model->layers[i];
         DwPwPlan fused;
         // layers that another kernel takes have no plan that a request would read
-        if (!P.gemm || (i == 0 && stem_takes(model)) || (i > 0 && dwpw_takes(model, i - 1, (int)batch, share_of(ps), &fused))) continue;
+        if (!P.gemm || (i == 0 && stem_takes(model)) || expanded[i] || (i > 0 && dwpw_takes(model, i - 1, (int)batch, share_of(ps), &fused))) continue;
         const eclip_layer &L = P.L;
         const GemmShape g = gemm_shape(model, P, (int)batch);
         const long M = (long)g.B * g.Ho * g.Wo, N = g.Cout, K = (long)g.KH * g.KW * g.Cin;
