@@ -43,8 +43,14 @@ template <int VM, bool LGKM = true> __device__ __forceinline__ void wait_and_mee
 // Accumulators that leave no room for the rest in the 256 vector registers go to the accumulation registers (one wavefront
 // per SIMD has both files).  The matrix instruction is then written out: left to itself the compiler copies accumulators
 // between registers around every instruction.
-// (They have to fit there: accumulators that the compiler moves between the files next to such an instruction are read before they are written.)
+// They have to fit there (dma_acc_fit): accumulators that the compiler moves between the files next to such an instruction are read before they are written.
+// Two wavefronts on a SIMD have 128 accumulation registers each, which is less than any such tile needs; one has 256.
 constexpr bool dma_acc_in_agprs(int bm, int bn, int waves) { return bm * bn / waves > 128 * 64; }
+constexpr int dma_per_cu(int bm, int bn, int bk, int stages) { return dma_lds_bytes(bm, bn, bk, stages) > 80 * 1024 ? 1 : 2; }      // workgroups that the registers are for
+constexpr bool dma_acc_fit(int bm, int bn, int bk, int stages, int waves)
+{
+    return !dma_acc_in_agprs(bm, bn, waves) || (bm * bn / waves <= 256 * 64 && waves * dma_per_cu(bm, bn, bk, stages) <= 4);
+}
 template <typename T> __device__ __forceinline__ void mma_agpr(uint4 a, uint4 b, f32x4 &c)
 {
     const u32x4 va = {a.x, a.y, a.z, a.w}, vb = {b.x, b.y, b.z, b.w};
@@ -266,7 +272,7 @@ __device__ __forceinline__ unsigned bits_run(int at, int n) { return (n >= 32 ? 
 // DMA_POOL (A_UNIFORM, ReLU): the rows of the tile are the pixels of 2 x 2 windows, window by window, so that four neighbouring lanes hold a window and its
 // maximum costs two lane exchanges: the pool's launch goes, and three quarters of the stores (gemm_pools).
 template <typename T, int BM, int BN, int BK, int WM, int WN, int ST, int AMODE, int FORM = DMA_PLAIN>
-__global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 1024 ? 1 : 2) void conv_gemm_dma_kernel(const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int N, int K, int ldx, int kt_per, unsigned walk, unsigned tiles,
+__global__ __launch_bounds__(WM * WN * 64, dma_per_cu(BM, BN, BK, ST)) void conv_gemm_dma_kernel(const uint16_t *x, const uint16_t *w, unsigned x_bytes, int M, int N, int K, int ldx, int kt_per, unsigned walk, unsigned tiles,
                           unsigned fast_d, unsigned fast_mul, GemmDev p, SeDeal deal)
 {
     // What the first copies need comes as 14 words of separate arguments, which the hardware puts into scalar registers before the
@@ -280,6 +286,7 @@ __global__ __launch_bounds__(WM * WN * 64, dma_lds_bytes(BM, BN, BK, ST) > 80 * 
                      "+s"(p.howo.shift), "+s"(p.wo.d), "+s"(p.wo.mul), "+s"(p.wo.shift));
     constexpr int NW = WM * WN, KS = BK / 32;                           // KS: matrix instructions along K per step and block
     static_assert(KS == 1 || KS == 2, "K step of 32 or 64");
+    static_assert(dma_acc_fit(BM, BN, BK, ST, NW), "accumulators fit the accumulation registers");
     constexpr int TM = BM / WM / 16, TN = BN / WN / 16, NM = TM * TN;
     constexpr int RPC = 16 / KS, CPR = 4 * KS;                          // rows per 1 KB copy of the activations, 16-byte chunks per row
     constexpr int AI = BM / RPC / NW, BI = BN / 16 * KS / NW;           // 1 KB copies per wavefront and step

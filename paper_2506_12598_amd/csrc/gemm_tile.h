@@ -628,7 +628,7 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_gemm_kernel(GemmDev p, SeDe
 // feed-forward layer (1536 x 4096 x 1024 with GELU) on 96 CUs: 17 32.9 us, 29 29.0; 1536 x 3072 x 768 with GELU on 128 CUs 23.1 (17), 19.4 (30);
 // a 3 x 3 window of 25088 x 256 x 2304 on 96 CUs 78.4 (18), 72.3 (31).  (192 x 192 tiles, whose accumulators exceed the 128 accumulation registers that
 // two wavefronts per SIMD leave each, gave wrong sums: the compiler moves accumulators between the register files next to matrix instructions
-// that it does not know.)  They exist in the fast address forms only: the general one would spill.  Ids without a tile (2, 4, 6, 7, 9..12, 14) had one that the planner never picked and that measuring
+// that it does not know.  dma_acc_fit keeps such tiles from being compiled.)  They exist in the fast address forms only: the general one would spill.  Ids without a tile (2, 4, 6, 7, 9..12, 14) had one that the planner never picked and that measuring
 // every candidate on 900 problems (9 networks, 64 to 256 compute units) found best by more than 1.2 % once, by 3.3 %.
 #define ECLIP_PP_TILES(X)                                                                                                   \
     X(3, 256, 256, 32, 2, LOOP_PINGPONG) X(5, 256, 256, 32, 2, LOOP_PP_BDIRECT) X(8, 192, 128, 64, 2, LOOP_PP_BDIRECT)      \
