@@ -351,6 +351,8 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
             if (cost < best) { best = cost; pl = GemmPlan{1, v, 1, (int)wsk_tiles(v), nw, 0}; }
         }
     if (!lean) best = wsk_whole_cost(M, N, K, even_cu, pl.variant, pl.nw);
+    const bool long_sums = traits.copied && M >= 512 && K >= 768;        // copied_long, below
+    if (long_sums && traits.gelu) best += (pl.nw == 4 ? 0.3 + 1.4e-5 * M * N / even_cu : 6.2e-5 * M * N / even_cu);
     // LDS-tiled kernels, optionally with K cut into slices (second launch: its cost plus the traffic of the partial sums).
     // A tile costs `fixed` us once (fill of the pipeline, epilogue) and `step` us per K step of its own depth when it has a
     // compute unit to itself; every further round of workgroups on a compute unit pays the steps again and `more` us; where two
@@ -382,8 +384,16 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // table's, which has no 29 to 31, 4.1 and 90 % (1536 x 4096 x 1024 with GELU on 96 CUs 32.2 us, now 29.2, on 64 49.0, now 42.1; 2048 x 2304 x 768 on
     // 64 39.8, now 30.1; a 3 x 3 window of 50176 x 128 x 1152 on 96 49.2, now 45.5).  Shorter sums were not among them: with this table for all, three
     // co-located CNNs and encoders on 32 to 80 CUs took 2.3 % longer.  Of 29 to 31 a compute unit runs two at a time, in `two` times one's steps, and an odd
-    // one alone.  `gelu`: what GELU adds per 1000 outputs that a compute unit computes.
-    struct LdsTile { int variant; double step, fixed, more, two, gelu; };
+    // one alone.
+    // GELU is priced there too: per 1000 outputs of a tile, `gelu` for the first workgroup of a compute unit and `gelu_more` for each further one.
+    // It is 0.063 us per 1000 outputs wherever nothing runs beside a tile's epilogue; of workgroups that share a unit all but the first hide it under the others' K
+    // loops.  13, 15, 22, 23, 26 and 27 have what GELU adds to 16 linear layers (512 to 3072 rows, sums of 768 to 3072) on 48, 64, 96, 128 and 256 CUs, 0.2 to
+    // 0.4 us rms of 0.5 to 1.0 (it was nothing, which drew GELU layers to small tiles: 768 x 3072 x 768 on 256 CUs 12.5 us on 26, 10.6 on 20).  The rows with equal
+    // numbers are set by what gets picked, as the rest of their row: with the measured 0.055 to 0.065 and 0.00 to 0.09 there 128 layers x shares take 0.4 % longer.
+    // K in slices pays it in the launch that sums them (1.7 us on average over those layers), wave-split-K tiles by their wavefronts (0.3 to 2.8 us).
+    // With GELU the picks for the 16 layers on eight shares (160, 176 and 192 too) take 3.4 % more than the best tile and 66 % at worst, without it 2.3 and 78 %: one workgroup
+    // for every CU of an uneven share that sit two on a unit (1024 x 4096 x 1024 on 176 CUs: 30 31.2 us, 29 18.8).
+    struct LdsTile { int variant; double step, fixed, more, two, gelu, gelu_more; };
     static const LdsTile copied_256 = {17, 0.515, 9.7, 16.75, 0};
     static const std::vector<LdsTile> any = {
         {0, 0.509, 4.049, 7.322, 1.373}, {3, 0.568, 8.784, 16.049, 0}, {5, 0.595, 8.271, 16.021, 0}, {8, 0.525, 5.267, 9.068, 0},
@@ -392,12 +402,13 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
         {22, 0.267, 3.021, 6.171, 1.444}, {23, 0.257, 3.012, 4.226, 1.544}, {24, 0.406, 8.399, 13.526, 0}, {25, 0.409, 8.333, 11.372, 0},
         {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.222, 3.505, 5.135, 1.609}};
     static const std::vector<LdsTile> copied_long = {
-        {13, 0.312, 2.898, 4.535, 1.656}, {15, 0.278, 3.194, 5.868, 1.418}, {16, 0.483, 4.611, 5.981, 0, 0.055}, {17, 0.515, 9.7, 7.009, 0, 0.055},
-        {18, 0.558, 6.215, 5.632, 0, 0.053}, {19, 0.545, 6.852, 5.409, 0, 0.085}, {20, 0.337, 4.272, 4.836, 0, 0.071}, {21, 0.409, 5.709, 6.58, 0, 0.051},
-        {22, 0.267, 3.021, 6.171, 1.444}, {23, 0.257, 3.012, 4.226, 1.544}, {24, 0.372, 8.17, 8.751, 0, 0.048}, {25, 0.35, 9.163, 8.532, 0, 0.084},
-        {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.234, 4.367, 5.066, 1.549, 0.017}, {29, 0.3, 6.339, 4.349, 1.754, 0.045},
-        {30, 0.286, 4.895, 4.854, 1.539, 0.038}, {31, 0.291, 4.786, 5.235, 1.587, 0.024}};
-    for (const LdsTile &row : traits.copied && M >= 512 && K >= 768 ? copied_long : any) {
+        {13, 0.312, 2.898, 4.535, 1.656, 0.061, 0.000}, {15, 0.278, 3.194, 5.868, 1.418, 0.092, 0.002}, {16, 0.483, 4.611, 5.981, 0, 0.055, 0.055},
+        {17, 0.515, 9.7, 7.009, 0, 0.055, 0.055}, {18, 0.558, 6.215, 5.632, 0, 0.053, 0.053}, {19, 0.545, 6.852, 5.409, 0, 0.085, 0.085},
+        {20, 0.337, 4.272, 4.836, 0, 0.071, 0.071}, {21, 0.409, 5.709, 6.58, 0, 0.051, 0.051}, {22, 0.267, 3.021, 6.171, 1.444, 0.083, 0.010},
+        {23, 0.257, 3.012, 4.226, 1.544, 0.077, 0.008}, {24, 0.372, 8.17, 8.751, 0, 0.048, 0.048}, {25, 0.35, 9.163, 8.532, 0, 0.084, 0.084},
+        {26, 0.176, 2.682, 3.32, 1.565, 0.106, 0.007}, {27, 0.177, 2.781, 4.298, 1.491, 0.057, 0.000}, {28, 0.234, 4.367, 5.066, 1.549, 0.017, 0.017},
+        {29, 0.3, 6.339, 4.349, 1.754, 0.045, 0.045}, {30, 0.286, 4.895, 4.854, 1.539, 0.038, 0.038}, {31, 0.291, 4.786, 5.235, 1.587, 0.024, 0.024}};
+    for (const LdsTile &row : long_sums ? copied_long : any) {
         const LdsTile &c = &row == &any[7] && traits.copied ? copied_256 : row;
         if (c.fixed >= best) continue;                                   // planned anew for every launch: what cannot win is not worked out
         int bm, bn, bk;
@@ -415,8 +426,8 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
             else if (c.two > 0.0 && rounds >= 2.0) rounds = c.two * ((double)wgs / cus > 2.0 ? (double)wgs / (2.0 * cus) : 1.0);
             double cost = c.fixed + (rounds - 1.0) * c.more + rounds * (double)cdiv(KT, sp) * c.step * (1.0 + 0.15 * load * load);
             if (dealt && even_cu < n_cu) cost += wgs <= n_cu ? 1.1 : even_cu < 0.8 * n_cu ? 3.0 * (0.8 - (double)even_cu / n_cu) : 0.0;
-            if (traits.gelu && sp == 1) cost += per_cu * c.gelu * 1e-3 * bm * bn;
             if (sp > 1) cost += 15.48 + (double)M * N * (4.0 * sp + 2.0) / 4.243e6;
+            if (long_sums && traits.gelu) cost += sp > 1 ? 5.2e-5 * M * N / n_cu : (c.gelu + (per_cu - 1.0) * c.gelu_more) * 1e-3 * bm * bn;
             if (cost < best) {
                 best = cost;
                 pl = GemmPlan{0, c.variant, 1, (int)mn, 4, 0};
