@@ -409,7 +409,7 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
         {26, 0.176, 2.682, 3.32, 1.565, 0.106, 0.007}, {27, 0.177, 2.781, 4.298, 1.491, 0.057, 0.000}, {28, 0.234, 4.367, 5.066, 1.549, 0.017, 0.017},
         {29, 0.3, 6.339, 4.349, 1.754, 0.045, 0.045}, {30, 0.286, 4.895, 4.854, 1.539, 0.038, 0.038}, {31, 0.291, 4.786, 5.235, 1.587, 0.024, 0.024}};
     for (const LdsTile &row : long_sums ? copied_long : any) {
-        const LdsTile &c = &row == &any[7] && traits.copied ? copied_256 : row;
+        const LdsTile &c = row.variant == copied_256.variant && traits.copied && !long_sums ? copied_256 : row;
         if (c.fixed >= best) continue;                                   // planned anew for every launch: what cannot win is not worked out
         int bm, bn, bk;
         conv_gemm_tile(c.variant, &bm, &bn, &bk);
