@@ -1621,9 +1621,12 @@ static ConvGemmArgs pool_args(const eclip_model *m, uint32_t i, int batch, const
     return a;
 }
 
-// Launches the convolution i and the 2 x 2 max-pool i + 1 (pool_next) as one kernel when the convolution's can take the pool along: always the faster way, since
-// a launch and three quarters of the stores go.  us for both, apart and now, on 256 CUs at batch 8: 224 x 224 x 64 56.1, 46.2; 112 x 112 x 128 45.1, 34.6;
-// 56 x 56 x 256 37.8, 31.3; 28 x 28 x 512 37.1, 32; 14 x 14 x 512 19.0, 16.
+// Launches the convolution i and the 2 x 2 max-pool i + 1 (pool_next) as one kernel when the convolution's can take the pool along: a launch and three
+// quarters of the stores go.  us for both, apart and now, on 256 CUs at batch 8: 224 x 224 x 64 56.1, 46.2; 112 x 112 x 128 45.1, 34.6;
+// 56 x 56 x 256 37.8, 31.3; 28 x 28 x 512 37.1, 32; 14 x 14 x 512 19.0, 16.  Over 132 of them (eleven layers of 14 x 14 to 224 x 224 pixels and 64 to 512 channels x batch 1, 3
+// and 8 x 32, 64, 128 and 256 CUs) one launch is 1.34 times as fast on the geometric mean where it is the patch kernel's (76; 0.99 at worst, 1.9 at best) and
+// 1.13 times where it is a copied tile's (56; 1.01, 1.35): so no rule beyond the kernel's.  The plan is still the layer's own: 64 x 64 x 32 is planned
+// on the wave-split-K kernel and stays apart (batch 1 on 128 CUs 8.1; 5.5 on a tile with the pool, which eclip_model_tune finds).
 static hipError_t launch_pool_pair(eclip_model *m, uint32_t i, int batch, hipStream_t s, const CuShare &cu, const void *d_in, uint32_t *n_launched, bool *done)
 {
     *done = false;
