@@ -114,7 +114,7 @@ __global__ __launch_bounds__(NW * 64) void expdw_kernel(ExpDwDev p)
     for (int ks = wave; ks < p.steps; ks += NW) {
         Slice cur;
         fetch(cur, ks);
-        // ---- expansion of 32 channels over the patch
+        // ---- expansion of 32 channels over the patch; the steps are summed one by one, as the wavefronts of conv_wsk_kernel that have one each
         f32x4 e[PB][2];
 #pragma unroll
         for (int i = 0; i < PB; ++i) e[i][0] = e[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -124,7 +124,15 @@ __global__ __launch_bounds__(NW * 64) void expdw_kernel(ExpDwDev p)
             for (int i = 0; i < PB; ++i) {
                 const uint4 a = *reinterpret_cast<const uint4 *>(lds + (16 * i + r16) * PITCH + k * 64 + q * 16);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) e[i][j] = Mma<T>::run(make_uint4(cur.we[k][j].x, cur.we[k][j].y, cur.we[k][j].z, cur.we[k][j].w), a, e[i][j]);
+                for (int j = 0; j < 2; ++j) {
+                    const uint4 we = make_uint4(cur.we[k][j].x, cur.we[k][j].y, cur.we[k][j].z, cur.we[k][j].w);
+                    if constexpr (KMAX == 1) e[i][j] = Mma<T>::run(we, a, e[i][j]);
+                    else {
+                        const f32x4 v = Mma<T>::run(we, a, f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) e[i][j][c] += v[c];
+                    }
+                }
             }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -228,6 +236,11 @@ __global__ __launch_bounds__(NW * 64) void expdw_kernel(ExpDwDev p)
 
 // steps of 32 input channels that a workgroup holds, tile columns of 16 channels, wavefronts
 #define ECLIP_EXPDW(X) X(1, 2, 4) X(1, 4, 4) X(3, 4, 8) X(3, 10, 8)
+struct Form { int kmax, tn, nw; };
+constexpr Form form_of(int Cin, int N)
+{
+    return Cin <= 32 ? Form{1, N <= 32 ? 2 : 4, 4} : Form{3, N <= 64 ? 4 : 10, 8};
+}
 template <typename T> const void *kernel_of(int kmax, int tn, int nw, int sd)
 {
 #define X(K, N, W)                                                                                                          \
@@ -268,15 +281,18 @@ hipError_t expdw_init()
 //   0.375 (0.99 to 1.1; 0.9 to 1.04 at 0.25), with three from 0.5 (1.09; 14 x 14 x 96 at 0.375 0.96) and in one column only (0.88 to 0.98 in two).
 // - three slices elsewhere from 0.375 on, 1.02 to 1.3 up to 12 at stride 1 and 4 at stride 2.  Four, in kernels for up to 160 input channels, did not pay: 7 x 7 x 160
 //   10.5 us apart, 14.3.
-bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_cu, ExpDwPlan *out)
+// The timings set the lines alone; besides, the sums have to be those of the launches apart (expdw_sums_as_apart).  Of ten bottlenecks of MobileNetV2 at images of 224, 160
+// and 96 x batch 1, 3 and 8 x nine shares x both types that the lines take, 727 of 974 have them; MobileNetV2 at batch 3 on 192 CUs: 187 us apart, 174 with them.
+bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_cu, ExpDwPlan *out, bool same_sums)
 {
     if (Cin > 96 || (stride != 1 && stride != 2)) return false;
-    const int kmax = Cin <= 32 ? 1 : 3, tn = kmax == 1 ? (N <= 32 ? 2 : 4) : N <= 64 ? 4 : 10, nw = kmax == 1 ? 4 : 8;
+    const auto [kmax, tn, nw] = form_of(Cin, N);
     *out = ExpDwPlan{kmax, tn, nw};
     if (const char *f = getenv("ECLIP_EXPDW")) {             // 0: apart, 1: one launch; anything else: the choice below
         int take = -1;
         if (sscanf(f, "%d", &take) == 1 && (take == 0 || take == 1)) return take == 1;
     }
+    if (!same_sums) return false;
     const int slices = ((C + 31) / 32 + nw - 1) / nw, cols = (N + 16 * tn - 1) / (16 * tn);
     const double per_cu = (double)B * ((Ho + 3) / 4) * ((Wo + 3) / 4) * cols / n_cu;
     if (slices > 3 || cols > (tn == 10 ? 2 : 8) || (slices == 3 && cols > 1)) return false;
@@ -295,6 +311,19 @@ bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_
         else most = stride == 1 ? 3.0 : 1.5;
     }
     return per_cu >= least && per_cu <= most;
+}
+
+// Outputs are the same bits in one launch and apart where both sum in one order.  The pointwise layer: here and in dwpw_kernel wavefront w of W sums slices w,
+// w + W, ... and the wavefronts are added in their order, so W has to be the same, or large enough in both that none has two.  The expansion: one step of 32 input
+// channels has no order; up to three are added one by one as conv_wsk_kernel does with a step per wavefront, where the LDS tiles keep one running sum.
+// (Without this rule one launch took MobileNetV2's layers of 64 and 96 input channels too, and its outputs differed by 0.04 to 0.1 % of their range.)
+bool expdw_sums_as_apart(int Cin, int C, int N, const GemmPlan &expansion, bool lean, const DwPwPlan &dwpw)
+{
+    const Form f = form_of(Cin, N);
+    const int slices = (C + 31) / 32;
+    if (dwpw.wk != f.nw && (slices > dwpw.wk || slices > f.nw)) return false;
+    if (f.kmax == 1) return expansion.kind == 1 || (expansion.kind == 0 && expansion.splits == 1);
+    return expansion.kind == 1 && lean;
 }
 
 hipError_t launch_expdw(const ExpDwArgs &a, const ExpDwPlan &pl, hipStream_t s)

@@ -163,7 +163,10 @@ struct ExpDwArgs {
     int B, H, W, Cin, C, Ho, Wo, N, stride, act_e, act_d, act_p, dtype;
 };
 struct ExpDwPlan { int kmax, tn, nw; };      // steps of 32 input channels held; 16 tn output channels; wavefronts
-bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_cu, ExpDwPlan *out);      // false: better apart; n_cu: CuShare::even_cu
+// false: better apart, or (same_sums false) with other sums than apart; n_cu: CuShare::even_cu
+bool expdw_plan(int B, int Ho, int Wo, int Cin, int C, int N, int stride, int n_cu, ExpDwPlan *out, bool same_sums = true);
+// Whether its sums are those of the launches that the layers have apart: the expansion's plan and dwpw_plan's
+bool expdw_sums_as_apart(int Cin, int C, int N, const GemmPlan &expansion, bool lean, const DwPwPlan &dwpw);
 hipError_t expdw_init();       // raises the dynamic LDS limit once per process
 hipError_t launch_expdw(const ExpDwArgs &a, const ExpDwPlan &p, hipStream_t s);
 

@@ -41,9 +41,9 @@ def test_layers_that_share_a_launch_are_written_before_they_are_timed(launches, 
     assert ("served" in call) == any("expdw" in k for k in convs)
 
 
-@pytest.mark.parametrize("env,timed", [({}, 2), ({"ECLIP_EXPDW": "0"}, 3)])
+@pytest.mark.parametrize("env,timed", [({"ECLIP_EXPDW": "1"}, 2), ({}, 3), ({"ECLIP_EXPDW": "0"}, 3)])
 def test_a_pointwise_layer_in_one_launch_with_its_expansion_is_not_tuned(launches, env, timed):
-    # 56 x 56 pixels, 16 -> 144 -> 96 channels on 64 CUs: three layers in one launch, but no two of them.  The first convolution and the expansion have plans
-    # that requests may read, the last layer only where the three are apart.
+    # 56 x 56 pixels, 16 -> 144 -> 96 channels on 64 CUs: two of the layers do not share a launch, and three only when told to.  The first convolution and the
+    # expansion have plans that requests may read, the last layer only where the three are apart.
     out, _ = launches("tune(0, batch=1, iters=1)", (56, 16, 144, 96, 1, 64), **env)
     assert int(out) == timed
