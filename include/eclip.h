@@ -39,8 +39,8 @@
  *   ECLIP_DWPW="n,w"      depthwise + pointwise: one launch with columns of 16 n output channels (n = 1, 2 or 4) and w
  *                         wavefronts sharing K (1, 2, 4 or 8) instead of the planner's choice; "0,0": two launches;
  *                         set to anything, it keeps an expansion before them apart
- *   ECLIP_EXPDW=n         expansion + depthwise + pointwise: 1 = one launch where the kernel takes them, 0 = apart, instead of
- *                         the planner's choice
+ *   ECLIP_EXPDW=n         expansion + depthwise + pointwise: 1 = one launch where the kernel takes them (also where its sums
+ *                         associate otherwise than apart), 0 = apart, instead of the planner's choice
  *   ECLIP_GCONV3=n        grouped 3 x 3 convolutions on groups of 32 inputs: n blocks of 4 x 4 pixels per wavefront (1, 2
  *                         or 4) instead of the planner's choice; 0: the wave-split-K kernel.  Other values of either leave the
  *                         choice to the planner

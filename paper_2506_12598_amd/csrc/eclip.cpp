@@ -1683,7 +1683,7 @@ static hipError_t launch_input_stage(eclip_model *m, int batch, const void *d_in
 }
 
 // One launch unit of the served path, starting at layer i: the first layer together with the input re-layout it needs
-// (or reading the caller's tensor itself), two independent matrix-core layers in one launch, depthwise + pointwise, convolution + 2 x 2 max-pool or
+// (or reading the caller's tensor itself), two independent matrix-core layers in one launch, depthwise + pointwise (with the expansion before them), convolution + 2 x 2 max-pool or
 // pool + classifier in one launch, or a single layer.  *consumed receives the number of layers the unit covered.  eclip_submit and the profiler
 // both walk a model through this function, so what is profiled is what is served.
 static hipError_t launch_unit(eclip_model *m, uint32_t i, int batch, hipStream_t s, const CuShare &cu, const void *d_in, float *d_out,
