@@ -391,8 +391,10 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // 0.4 us rms of 0.5 to 1.0 (it was nothing, which drew GELU layers to small tiles: 768 x 3072 x 768 on 256 CUs 12.5 us on 26, 10.6 on 20).  The rows with equal
     // numbers are set by what gets picked, as the rest of their row: with the measured 0.055 to 0.065 and 0.00 to 0.09 there 128 layers x shares take 0.4 % longer.
     // K in slices pays it in the launch that sums them (1.7 us on average over those layers), wave-split-K tiles by their wavefronts (0.3 to 2.8 us).
-    // With GELU the picks for the 16 layers on eight shares (160, 176 and 192 too) take 3.4 % more than the best tile and 66 % at worst, without it 2.3 and 78 %: one workgroup
-    // for every CU of an uneven share that sit two on a unit (1024 x 4096 x 1024 on 176 CUs: 30 31.2 us, 29 18.8).
+    // With GELU the picks for the 16 layers on eight shares (160, 176 and 192 too) take 2.8 % more than the best tile, without it 1.8.  Over 56 layers (44 linear ones of 512
+    // to 3072 rows, 12 convolutions) x 8 or 13 shares without it the picks of this table take 2.8 % more than the best of 18 tiles, those of the other one 4.4; of the
+    // 88 that differ 62 are faster by more than 3 %, 13 slower: on 96 CUs 29 and 30 with three workgroups per unit and outputs of 14 to 19 MB
+    // (3072 x 3072 x 768 65.0 us, 41.5 on 25; on 80 and 128 CUs they are the better ones), the others by 3 to 8 %.
     struct LdsTile { int variant; double step, fixed, more, two, gelu, gelu_more; };
     static const LdsTile copied_256 = {17, 0.515, 9.7, 16.75, 0};
     static const std::vector<LdsTile> any = {
@@ -415,6 +417,11 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
         conv_gemm_tile(c.variant, &bm, &bn, &bk);
         const long KT = cdiv(K, bk), mn = cdiv(M, bm) * cdiv(N, bn);
         const bool dealt = mn > even_cu;
+        // Dealing brings a shader engine's workgroups and its surplus in one row, and with room for two on a compute unit two may sit on one next to an idle one: 29 to
+        // 31 take 0.9 to 1.8 times their price there, and which cannot be told from the sizes (160 tiles on 160 CUs 13.0 us, 176 on 176 29.8).  On 280 layers x
+        // shares of 144 to 224 CUs their picks took 1.29 times as long as the next best's (30 for 1024 x 4096 x 1024 on 176 29.8, 18 17.3; 29 for
+        // 3072 x 4096 x 1024 on 192 47.8, 17 30.4), by which the table was slower there than the other one, 3.4 % over the best tile instead of 2.7.
+        if (pp_fast_forms_only(c.variant) && dealt && even_cu < n_cu) continue;
         for (long sp = 1; sp <= 4; sp *= 2) {
             if (sp > 1 && (K < 512 * sp || (size_t)(sp * M * N) > ws_floats)) break;
             const long wgs = mn * sp;

@@ -14,10 +14,11 @@ PROGRAM = r"""
 using namespace eclip;
 int main()
 {
-    int v[6];
-    while (std::scanf("%d %d %d %d %d %d", v, v + 1, v + 2, v + 3, v + 4, v + 5) == 6) {
+    int v[7];
+    while (std::scanf("%d %d %d %d %d %d %d", v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6) == 7) {
         GemmTraits t;
         t.lean = true;
+        t.even_cu = v[6];
         t.copied = v[4] != 0;
         t.gelu = v[5] != 0;
         const GemmPlan p = conv_gemm_plan(v[0], v[1], v[2], v[3], (size_t)16 << 20, t);
@@ -40,8 +41,8 @@ def plan(tmp_path_factory):
     subprocess.run(["hipcc", obj, "-o", exe, os.path.join(pkg, "libeclip.so"), "-Wl,-rpath," + pkg], check=True, capture_output=True)
 
     def run(problems):
-        """[(M, N, K, CUs, copied form, GELU)] -> [((kind, variant, slices or wavefronts), us)]"""
-        text = "".join(" ".join(str(int(v)) for v in p) + "\n" for p in problems)
+        """[(M, N, K, CUs, copied form, GELU[, CUs an undealt launch can count on])] -> [((kind, variant, slices or wavefronts), us)]"""
+        text = "".join(" ".join(str(int(v)) for v in (*p, 0)[:7]) + "\n" for p in problems)
         lines = [s.split() for s in subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.splitlines()]
         return [(tuple(int(v) for v in f[:3]), float(f[3])) for f in lines]
     return run
@@ -77,3 +78,12 @@ def test_tiles_that_have_fast_forms_only(plan):
     small = [(m, n, k, c, 1, g) for m, n, k in ((511, 4096, 1024), (384, 4096, 1024), (1536, 4096, 736), (3072, 1024, 256)) for c in (48, 64, 96, 128) for g in (0, 1)]
     for problems in ([p[:4] + (0, p[5]) for p in wide], small):        # layers whose address form they lack; layers below the table
         assert not {v for (kind, v, _), _ in plan(problems) if kind == 0} & {29, 30, 31}
+
+
+@pytest.mark.parametrize("m,n,k,cus,even", [(1024, 4096, 1024, 176, 96), (3072, 4096, 1024, 192, 128), (3072, 4096, 1024, 208, 160)])      # us 29.8, 17.3; 47.8, 30.4; 46.9, 30.4
+def test_no_two_workgroups_on_a_unit_where_launches_are_dealt(plan, m, n, k, cus, even):
+    assert plan([(m, n, k, cus, 1, 0, even)])[0][0][1] not in (29, 30, 31)
+    dealt = [p[:3] + (c, 1, g, e) for p in GRID for c, e in ((144, 32), (160, 64), (176, 96), (192, 128), (208, 160), (224, 192)) for g in (0, 1)]
+    rows, cols = {29: 128, 30: 128, 31: 192}, {29: 256, 30: 192, 31: 128}
+    for p, ((kind, v, _), _) in zip(dealt, plan(dealt)):
+        assert kind != 0 or v not in rows or -(-p[0] // rows[v]) * -(-p[1] // cols[v]) <= p[6], p
