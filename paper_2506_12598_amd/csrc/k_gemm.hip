@@ -306,6 +306,19 @@ std::vector<GemmPlan> conv_gemm_candidates(long M, long N, long K, int n_cu, siz
     return out;
 }
 
+// Tiles of the XCD that the block raster (set_raster) gives the most: whole blocks of 8 x 4 are dealt out, 9 of them as 2 to one and 1 to seven
+static long heaviest_xcd(long tm, long tn)
+{
+    const long rows = cdiv(tm, 8), cols = cdiv(tn, 4), blocks = rows * cols;
+    long most = 0;
+    for (long x = 0; x < 8; ++x) {
+        long n = 0;
+        for (long b = x; b < blocks; b += 8) n += std::min(8l, tm - b % rows * 8) * std::min(4l, tn - b / rows * 4);
+        most = std::max(most, n);
+    }
+    return most;
+}
+
 // conv_gemm_plan; *cost receives the modelled time of the plan (us, without the launch)
 static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_floats, const GemmTraits &traits, double *cost_out)
 {
@@ -391,10 +404,9 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // 0.4 us rms of 0.5 to 1.0 (it was nothing, which drew GELU layers to small tiles: 768 x 3072 x 768 on 256 CUs 12.5 us on 26, 10.6 on 20).  The rows with equal
     // numbers are set by what gets picked, as the rest of their row: with the measured 0.055 to 0.065 and 0.00 to 0.09 there 128 layers x shares take 0.4 % longer.
     // K in slices pays it in the launch that sums them (1.7 us on average over those layers), wave-split-K tiles by their wavefronts (0.3 to 2.8 us).
-    // With GELU the picks for the 16 layers on eight shares (160, 176 and 192 too) take 2.8 % more than the best tile, without it 1.8.  Over 56 layers (44 linear ones of 512
-    // to 3072 rows, 12 convolutions) x 8 or 13 shares without it the picks of this table take 2.8 % more than the best of 18 tiles, those of the other one 4.4; of the
-    // 88 that differ 62 are faster by more than 3 %, 13 slower: on 96 CUs 29 and 30 with three workgroups per unit and outputs of 14 to 19 MB
-    // (3072 x 3072 x 768 65.0 us, 41.5 on 25; on 80 and 128 CUs they are the better ones), the others by 3 to 8 %.
+    // With GELU the picks for the 16 layers on eight shares (160, 176 and 192 too) take 2.3 % more than the best tile, without it 1.4.  Over 56 layers (44 linear ones of 512
+    // to 3072 rows, 12 convolutions) x 8 or 13 shares without it the picks of this table take 2.3 % more than the best of 18 tiles and 50 % at worst, those of the
+    // other one 4.4 and 84 %; of the 91 that differ 69 are faster by more than 3 %, 9 slower, by 8 % at worst (1536 x 4096 x 1024 on 160 CUs 23.7 us on 25, 25.8 on 24).
     struct LdsTile { int variant; double step, fixed, more, two, gelu, gelu_more; };
     static const LdsTile copied_256 = {17, 0.515, 9.7, 16.75, 0};
     static const std::vector<LdsTile> any = {
@@ -424,7 +436,9 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
         if (pp_fast_forms_only(c.variant) && dealt && even_cu < n_cu) continue;
         for (long sp = 1; sp <= 4; sp *= 2) {
             if (sp > 1 && (K < 512 * sp || (size_t)(sp * M * N) > ws_floats)) break;
-            const long wgs = mn * sp;
+            // the table for long sums counts a launch on the block raster as eight times its heaviest XCD: 24 x 12 tiles of 128 x 256 (9 blocks) on 96 CUs
+            // take 65.0 us, 24 x 9 (9 blocks as well, but 216 tiles, which are dealt in rows) 35.8
+            const long wgs = long_sums && sp == 1 && mn >= 256 && cdiv(N, bn) >= 4 ? 8 * heaviest_xcd(cdiv(M, bm), cdiv(N, bn)) : mn * sp;
             const int cus = dealt || wgs <= even_cu ? n_cu : even_cu;            // few tiles in many slices: not dealt
             const double load = wgs >= cus ? 1.0 : (double)wgs / cus;
             double rounds = (double)cdiv(wgs, cus);

@@ -87,3 +87,13 @@ def test_no_two_workgroups_on_a_unit_where_launches_are_dealt(plan, m, n, k, cus
     rows, cols = {29: 128, 30: 128, 31: 192}, {29: 256, 30: 192, 31: 128}
     for p, ((kind, v, _), _) in zip(dealt, plan(dealt)):
         assert kind != 0 or v not in rows or -(-p[0] // rows[v]) * -(-p[1] // cols[v]) <= p[6], p
+
+
+@pytest.mark.parametrize("m,n,k,cus,slow,best", [
+    # us on the tile that looks cheaper by its tiles per compute unit, us on the best one
+    (3072, 3072, 768, 96, 29, 25), (2720, 3072, 768, 96, 29, 25), (3072, 2304, 768, 96, 30, 29),       # 65.0, 41.5; 54.0, 37.8; 53.8, 35.8
+    (3072, 3072, 1536, 128, 30, 25),                                                                   # 67.5, 59.3
+])
+def test_blocks_that_one_xcd_has_more_of_are_priced(plan, m, n, k, cus, slow, best):
+    (kind, v, _), _ = plan([(m, n, k, cus, 1, 0)])[0]
+    assert kind == 0 and v != slow and v in (best, 24)                 # 24 is next to 25 in all of them
