@@ -400,11 +400,10 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // one alone.
     // GELU is priced there too: per 1000 outputs of a tile, `gelu` for the first workgroup of a compute unit and `gelu_more` for each further one.
     // It is 0.063 us per 1000 outputs wherever nothing runs beside a tile's epilogue; of workgroups that share a unit all but the first hide it under the others' K
-    // loops.  13, 15, 22, 23, 26 and 27 have what GELU adds to 16 linear layers (512 to 3072 rows, sums of 768 to 3072) on 48, 64, 96, 128 and 256 CUs, 0.2 to
-    // 0.4 us rms of 0.5 to 1.0 (it was nothing, which drew GELU layers to small tiles: 768 x 3072 x 768 on 256 CUs 12.5 us on 26, 10.6 on 20).  The rows with equal
-    // numbers are set by what gets picked, as the rest of their row: with the measured 0.055 to 0.065 and 0.00 to 0.09 there 128 layers x shares take 0.4 % longer.
+    // loops.  Fitted to what GELU adds to 16 linear layers (512 to 3072 rows, sums of 768 to 3072) on 48, 64, 96, 128 and 256 CUs, 0.2 to 1.1 us rms of 0.5 to
+    // 4.9.  (Six small tiles had paid nothing, which drew GELU layers to them: 768 x 3072 x 768 on 256 CUs 12.5 us on 26, 10.6 on 20.)
     // K in slices pays it in the launch that sums them (1.7 us on average over those layers), wave-split-K tiles by their wavefronts (0.3 to 2.8 us).
-    // With GELU the picks for the 16 layers on eight shares (160, 176 and 192 too) take 2.3 % more than the best tile, without it 1.4.  Over 56 layers (44 linear ones of 512
+    // With GELU the picks for the 16 layers on eight shares (160, 176 and 192 too) take 1.3 % more than the best tile, without it 1.4.  Over 56 layers (44 linear ones of 512
     // to 3072 rows, 12 convolutions) x 8 or 13 shares without it the picks of this table take 2.3 % more than the best of 18 tiles and 50 % at worst, those of the
     // other one 4.4 and 84 %; of the 91 that differ 69 are faster by more than 3 %, 9 slower, by 8 % at worst (1536 x 4096 x 1024 on 160 CUs 23.7 us on 25, 25.8 on 24).
     struct LdsTile { int variant; double step, fixed, more, two, gelu, gelu_more; };
@@ -416,12 +415,12 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
         {22, 0.267, 3.021, 6.171, 1.444}, {23, 0.257, 3.012, 4.226, 1.544}, {24, 0.406, 8.399, 13.526, 0}, {25, 0.409, 8.333, 11.372, 0},
         {26, 0.176, 2.682, 3.32, 1.565}, {27, 0.177, 2.781, 4.298, 1.491}, {28, 0.222, 3.505, 5.135, 1.609}};
     static const std::vector<LdsTile> copied_long = {
-        {13, 0.312, 2.898, 4.535, 1.656, 0.061, 0.000}, {15, 0.278, 3.194, 5.868, 1.418, 0.092, 0.002}, {16, 0.483, 4.611, 5.981, 0, 0.055, 0.055},
-        {17, 0.515, 9.7, 7.009, 0, 0.055, 0.055}, {18, 0.558, 6.215, 5.632, 0, 0.053, 0.053}, {19, 0.545, 6.852, 5.409, 0, 0.085, 0.085},
-        {20, 0.337, 4.272, 4.836, 0, 0.071, 0.071}, {21, 0.409, 5.709, 6.58, 0, 0.051, 0.051}, {22, 0.267, 3.021, 6.171, 1.444, 0.083, 0.010},
-        {23, 0.257, 3.012, 4.226, 1.544, 0.077, 0.008}, {24, 0.372, 8.17, 8.751, 0, 0.048, 0.048}, {25, 0.35, 9.163, 8.532, 0, 0.084, 0.084},
-        {26, 0.176, 2.682, 3.32, 1.565, 0.106, 0.007}, {27, 0.177, 2.781, 4.298, 1.491, 0.057, 0.000}, {28, 0.234, 4.367, 5.066, 1.549, 0.017, 0.017},
-        {29, 0.3, 6.339, 4.349, 1.754, 0.045, 0.045}, {30, 0.286, 4.895, 4.854, 1.539, 0.038, 0.038}, {31, 0.291, 4.786, 5.235, 1.587, 0.024, 0.024}};
+        {13, 0.312, 2.898, 4.535, 1.656, 0.061, 0.000}, {15, 0.278, 3.194, 5.868, 1.418, 0.092, 0.002}, {16, 0.483, 4.611, 5.981, 0, 0.094, 0.033},
+        {17, 0.515, 9.7, 7.009, 0, 0.065, 0.053}, {18, 0.558, 6.215, 5.632, 0, 0.056, 0.088}, {19, 0.545, 6.852, 5.409, 0, 0.056, 0.087},
+        {20, 0.337, 4.272, 4.836, 0, 0.053, 0.085}, {21, 0.409, 5.709, 6.58, 0, 0.057, 0.086}, {22, 0.267, 3.021, 6.171, 1.444, 0.083, 0.010},
+        {23, 0.257, 3.012, 4.226, 1.544, 0.077, 0.008}, {24, 0.372, 8.17, 8.751, 0, 0.064, 0.061}, {25, 0.35, 9.163, 8.532, 0, 0.061, 0.056},
+        {26, 0.176, 2.682, 3.32, 1.565, 0.106, 0.007}, {27, 0.177, 2.781, 4.298, 1.491, 0.057, 0.000}, {28, 0.234, 4.367, 5.066, 1.549, 0.055, 0.001},
+        {29, 0.3, 6.339, 4.349, 1.754, 0.059, 0.000}, {30, 0.286, 4.895, 4.854, 1.539, 0.058, 0.003}, {31, 0.291, 4.786, 5.235, 1.587, 0.057, 0.006}};
     for (const LdsTile &row : long_sums ? copied_long : any) {
         const LdsTile &c = row.variant == copied_256.variant && traits.copied && !long_sums ? copied_256 : row;
         if (c.fixed >= best) continue;                                   // planned anew for every launch: what cannot win is not worked out
