@@ -393,7 +393,7 @@ static GemmPlan plan_with_cost(long M, long N, long K, int n_cu, size_t ws_float
     // at every K (256: 42.0 and 33.6), which the second row does not say.)
     // Layers that the copied tiles take in their fast form, of at least 512 rows and with sums of at least 768, have a table of their own, set by what gets
     // picked: 441 problems (linear layers of 512 to 3072 rows with and without GELU, 3 x 3 convolutions of 1568 to 50176 pixels; 48 to 256 CUs) x 15
-    // tiles in chains with weights of their own.  Its picks take 2.3 % more than the best tile on the geometric mean and 56 % at worst, the other
+    // tiles in chains with weights of their own (13, 15, 22, 23, 26 and 27 kept their rows).  Its picks took 2.3 % more than the best tile on the geometric mean and 56 % at worst, the other
     // table's, which has no 29 to 31, 4.1 and 90 % (1536 x 4096 x 1024 with GELU on 96 CUs 32.2 us, now 29.2, on 64 49.0, now 42.1; 2048 x 2304 x 768 on
     // 64 39.8, now 30.1; a 3 x 3 window of 50176 x 128 x 1152 on 96 49.2, now 45.5).  Shorter sums were not among them: with this table for all, three
     // co-located CNNs and encoders on 32 to 80 CUs took 2.3 % longer.  Of 29 to 31 a compute unit runs two at a time, in `two` times one's steps, and an odd
