@@ -1143,10 +1143,11 @@ static bool expdw_takes(const eclip_model *m, uint32_t i, int batch, const CuSha
     const LayerPlan &P = m->layers[i];
     if (!P.expdw_next || getenv("ECLIP_GEMM_FORCE") || getenv("ECLIP_NO_PAIRS") || getenv("ECLIP_DWPW")) return false;
     const LayerPlan &D = m->layers[i + 1], &Q = m->layers[i + 2];
+    auto plan = [&](bool same_sums) { return expdw_plan(batch, Q.out.h, Q.out.w, P.in.c, P.L.c, Q.L.c, D.L.stride, cu.even_cu(), pl, same_sums); };
+    if (!plan(true)) return false;               // before the layers' own plans, which cost the host more
     const GemmShape g = gemm_shape(m, P, batch);
     DwPwPlan apart;
-    const bool same_sums = dwpw_takes(m, i + 1, batch, cu, &apart) && expdw_sums_as_apart(P.in.c, P.L.c, Q.L.c, plan_of(m, g, cu), lean_form_of(g) >= 0, apart);
-    return expdw_plan(batch, Q.out.h, Q.out.w, P.in.c, P.L.c, Q.L.c, D.L.stride, cu.even_cu(), pl, same_sums);
+    return plan(dwpw_takes(m, i + 1, batch, cu, &apart) && expdw_sums_as_apart(P.in.c, P.L.c, Q.L.c, plan_of(m, g, cu), lean_form_of(g) >= 0, apart));
 }
 
 extern "C" eclip_status eclip_model_load(eclip_pool *pool, const eclip_model_desc *desc, const void *weights,
