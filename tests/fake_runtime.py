@@ -86,6 +86,6 @@ def run(lib, tmp, program, **env):
     open(log, "w").close()
     kept = {k: v for k, v in os.environ.items() if not k.startswith("ECLIP_")}
     out = subprocess.run([sys.executable, "-c", program], cwd=ROOT, check=True, capture_output=True, text=True, timeout=100,
-                         env={**kept, "LD_PRELOAD": lib, "FAKE_RUNTIME_LOG": log, **env}).stdout
+                         env={**kept, "LD_PRELOAD": " ".join([lib] + kept.get("LD_PRELOAD", "").split()), "FAKE_RUNTIME_LOG": log, **env}).stdout
     with open(log) as f:
         return out, f.read().split()
