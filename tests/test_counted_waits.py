@@ -9,7 +9,6 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 OBJ = os.path.join(ROOT, "paper_2506_12598_amd", "_build", "k_conv3.hip.o")
-POOLING = os.path.join(ROOT, "paper_2506_12598_amd", "_build", "k_conv3.hip.p.o")
 OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
 pytestmark = pytest.mark.skipif(not (os.path.exists(OBJ) and os.path.exists(OBJDUMP)), reason="needs the object file of the build")
 
@@ -35,9 +34,9 @@ def test_what_is_counted():
     assert fetches_behind_the_copies(code) == (2, None) and fetches_behind_the_copies(code[1:]) is None
 
 
-def _kernels(path, tmp_path):
+def test_the_patch_kernels(tmp_path):
     obj = str(tmp_path / "k.o")
-    shutil.copy(path, obj)
+    shutil.copy(OBJ, obj)
     subprocess.run([OBJDUMP, "--offloading", obj], check=True, capture_output=True, cwd=tmp_path)
     device = [f for f in os.listdir(tmp_path) if f.endswith("gfx950")]
     assert len(device) == 1
@@ -50,25 +49,8 @@ def _kernels(path, tmp_path):
             kernels[name] = []
         elif name and line.startswith("\t"):
             kernels[name].append(line.strip())
-    return kernels
-
-
-def test_the_patch_kernels(tmp_path):
-    kernels = _kernels(OBJ, tmp_path)
     got = {n: fetches_behind_the_copies(code) for n, code in kernels.items() if "conv" in n}
     # 2 types x 2 strides x (6 shapes x (4 wavefront counts + 2 of several slices) - 1) and x 2 widths x 3 patches of the grouped form
     assert len(got) == 2 * 2 * (6 * 6 - 1) + 2 * 2 * 2 * 3
-    for n, v in got.items():
-        assert v and v[1] and v[0] >= v[1], (n, v)
-
-
-def test_the_pooling_forms_stand_apart(tmp_path):
-    # a launch without a pool runs no instruction of one: the exchange between the lanes of a window is in the pooling forms, all of them, and nowhere else
-    (tmp_path / "p").mkdir()
-    plain, pooling = _kernels(OBJ, tmp_path), _kernels(POOLING, tmp_path / "p")
-    swaps = {n: any(re.match(r"v_permlane(16|32)_swap", line) for line in code) for kernels in (plain, pooling) for n, code in kernels.items() if "conv" in n}
-    assert not any(swaps[n] for n in plain if "conv" in n) and all(swaps[n] for n in pooling if "conv" in n)
-    got = {n: fetches_behind_the_copies(code) for n, code in pooling.items() if "conv" in n}
-    assert len(got) == 2 * 2 * (6 * 6 - 1)
     for n, v in got.items():
         assert v and v[1] and v[0] >= v[1], (n, v)
